@@ -2,18 +2,19 @@
 // attention scores of the token sequence through dot products; every output
 // token independent).  qkv[b*T + t, :] = [q | k | v], each block head-major.
 //
-// Persistent workgroups, one per compute unit, each walking a list of (image,
-// head) pairs.  The keys and values of a pair stream through LDS in chunks of 96
+// Persistent workgroups, at most one per compute unit, each walking a list of units:
+// a unit is one (image, head) pair with all its queries, or with one group of them
+// where pairs are few (plan_attention).  The keys and values of a pair stream through LDS in chunks of 96
 // tokens, K and V both row-major as they lie in memory: two loader waves bring
 // chunk after chunk in with buffer_load ... lds (no register staging, no
 // transposing copy) into a ring of five chunk buffers, up to four chunks - more
 // than a whole pair at T = 257 - ahead of the query waves, so the memory latency
-// of a pair hides behind the arithmetic of the one before, and any number of
+// of a unit hides behind the arithmetic of the one before, and any number of
 // tokens passes through the same buffers.  One barrier per chunk both hands a
 // landed chunk to the query waves and returns the buffer they have finished to
 // the loaders.
 //
-// A query wave owns 32 queries (two 16-query blocks) and walks a chunk in three
+// A query wave owns 32 queries (two 16-query blocks; one where pairs are few) and walks a chunk in three
 // steps of 32 keys with v_mfma_f32_16x16x32_bf16:
 //   S^T = K . Q^T   (A = K fragment: 16 keys x 32 components, one ds_read_b128
 //                    per lane; B = Q fragment, held in registers for the pair):
@@ -39,8 +40,6 @@
 //                   rounded probabilities, i.e. of the weights actually applied).
 // The last 32-component step of a head width that is not a multiple of 32 (80)
 // reads past the row into the next row (finite data) against zeros in Q.
-// More than 320 tokens: the query tiles are taken in passes of ten waves, the
-// keys streaming through once per pass.
 #include "ep_kernels.h"
 #include "ep_device.h"
 #include "ep_launch.h"
@@ -57,7 +56,7 @@ constexpr int SUBS = CK / 32;                        // 32-key steps per chunk
 constexpr int NBUF = 5;                              // chunk buffers in the ring
 constexpr int DEPTH = NBUF - 1;                      // chunks in flight ahead of the one being consumed
 constexpr int NLOADER = 2;                           // loader waves
-constexpr int MAXQW = 10;                            // query waves (32 queries each)
+constexpr int MAXQW = 10;                            // query waves
 
 template <int DH>
 struct StreamShape {
@@ -90,9 +89,7 @@ __device__ inline float quarter_max(float v)
 
 // Q fragments of NQB 16-query blocks starting at query q0 of a pair (B operand: column = query l15 of the
 // block, 8 consecutive components at 32 ks + 8 g; components past the head width read as zeros: an offset
-// past the descriptor's end).  The loads are issued here and NOT waited for: they are written as assembly
-// so that the compiler neither tracks them nor sinks them to their use, a whole pair later.  Whoever
-// consumes qf first calls q_landed on it.
+// past the descriptor's end).  The empty assembly keeps the loads here, a whole unit ahead of their use.
 template <int DH, int NQB>
 __device__ __forceinline__ void issue_q(const uint16_t *__restrict__ qkv, int T, int D, int H, int pair, int q0,
                                         u32x4 (&qf)[NQB][StreamShape<DH>::KS])
@@ -102,12 +99,8 @@ __device__ __forceinline__ void issue_q(const uint16_t *__restrict__ qkv, int T,
     const int l15 = lane & 15, g = lane >> 4;
     const int row_bytes = 3 * D * 2;
     const int seg_bytes = (T - 1) * row_bytes + DH * 2;
-    const uint64_t base = reinterpret_cast<uint64_t>(qkv + (size_t)(pair / H) * T * 3 * D + (size_t)(pair % H) * DH);
-    u32x4 rs;                                                       // raw buffer descriptor: base, no stride, size, flags
-    rs[0] = __builtin_amdgcn_readfirstlane((uint32_t)base);
-    rs[1] = __builtin_amdgcn_readfirstlane((uint32_t)(base >> 32) & 0xFFFFu);
-    rs[2] = __builtin_amdgcn_readfirstlane((uint32_t)seg_bytes);
-    rs[3] = 0x00020000u;
+    const uint16_t *base = qkv + (size_t)(pair / H) * T * 3 * D + (size_t)(pair % H) * DH;
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(base), 0, seg_bytes, 0x00020000);
 #pragma unroll
     for (int qb = 0; qb < NQB; ++qb) {
         const int qrow = min(q0 + qb * 16 + l15, T - 1);
@@ -115,20 +108,10 @@ __device__ __forceinline__ void issue_q(const uint16_t *__restrict__ qkv, int T,
         for (int ks = 0; ks < KS; ++ks) {
             const bool in_row = ks * 32 + g * 8 < DH;
             const int voff = in_row ? qrow * row_bytes + ks * 64 + g * 16 : 0x7FFFFFF0;
-            asm volatile("buffer_load_dwordx4 %0, %1, %2, 0 offen" : "=v"(qf[qb][ks]) : "v"(voff), "s"(rs) : "memory");
+            qf[qb][ks] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, voff, 0, 0));
         }
     }
-}
-
-// every vector-memory operation this wave has issued has completed, the fragments of issue_q among them
-template <int NQB, int KS>
-__device__ __forceinline__ void q_landed(u32x4 (&qf)[NQB][KS])
-{
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-#pragma unroll
-    for (int qb = 0; qb < NQB; ++qb)
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(qf[qb][ks]));   // uses of qf stay below the wait
+    asm volatile("" ::: "memory");
 }
 
 // One pass of a query wave over the keys of a pair: NQB 16-query blocks starting at query q0 (the second
@@ -137,7 +120,7 @@ __device__ __forceinline__ void q_landed(u32x4 (&qf)[NQB][KS])
 // one): the place for the caller's fetch of the next pair's fragments, away from the burst of output stores
 // at the end of a pair.
 template <int DH, int NQB, class Mid>
-__device__ __forceinline__ void attn_pass(const u32x4 (&qf)[NQB][StreamShape<DH>::KS], char *lds, int T, int q0, int nch, int j0,
+__device__ __forceinline__ void attn_pass(const u32x4 (&qf)[NQB][StreamShape<DH>::KS], char *lds, int T, int nch, int j0,
                                           float scale_log2e, f32x4 (&acc_o)[StreamShape<DH>::EB][NQB], f32x4 (&acc_sum)[NQB],
                                           Mid mid)
 {
@@ -293,71 +276,85 @@ __device__ __forceinline__ void store_pass(const f32x4 (&acc_o)[StreamShape<DH>:
     }
 }
 
-// All the tiles of a query wave.  With one pass per pair (T <= 32 * query waves) the wave's tile is the
-// same 32 queries in every pair, and the Q fragments of the next pair are fetched before the current
-// pair is worked on, so their latency hides behind it; with several passes they are fetched per pass.
+// All the work of a query wave.  A unit is one pair's keys against one group of nqw query tiles (QW = 16 NQB
+// queries each; ng groups to a pair).  The Q fragments of the next unit are fetched before the current one is
+// worked on, so their latency hides behind it.  A wave whose tile lies past the last query of its unit's pair (the
+// last group may be short) only keeps the barrier count.
 template <int DH, int NQB>
-__device__ __forceinline__ void attn_wave_single_pass(const uint16_t *__restrict__ qkv, uint16_t *__restrict__ o, char *lds,
-                                                      int T, int D, int H, int pair, int pair_step, int my_pairs, int q0,
-                                                      int nch, float scale_log2e)
+__device__ __forceinline__ void attn_wave(const uint16_t *__restrict__ qkv, uint16_t *__restrict__ o, char *lds, int T, int D,
+                                          int H, int ng, int nqw, int wave, int unit, int unit_step, int my_units, int nch,
+                                          float scale_log2e)
 {
-    constexpr int KS = StreamShape<DH>::KS;
+    constexpr int KS = StreamShape<DH>::KS, QW = 16 * NQB;
     u32x4 qf[NQB][KS], qn[NQB][KS];
+    int pair = unit / ng, q0 = ((unit - pair * ng) * nqw + wave) * QW;
     issue_q<DH, NQB>(qkv, T, D, H, pair, q0, qf);
-    q_landed<NQB, KS>(qf);
-    for (int pi = 0; pi < my_pairs; ++pi, pair += pair_step) {
-        const bool more = pi + 1 < my_pairs;
-        f32x4 acc_o[StreamShape<DH>::EB][NQB], acc_sum[NQB];
-        attn_pass<DH, NQB>(qf, lds, T, q0, nch, pi * nch, scale_log2e, acc_o, acc_sum,
-                           [&]() { if (more) issue_q<DH, NQB>(qkv, T, D, H, pair + pair_step, q0, qn); });
-        if (more) q_landed<NQB, KS>(qn);    // issued a pair ago; ahead of the stores, so that it does not wait for them
-        store_pass<DH, NQB>(acc_o, acc_sum, o, T, D, H, pair, q0);
-        if (more) {
+    for (int ui = 0; ui < my_units; ++ui) {
+        const int o_pair = pair, o_q0 = q0;
+        const bool more = ui + 1 < my_units;
+        unit += unit_step;
+        pair = unit / ng;
+        q0 = ((unit - pair * ng) * nqw + wave) * QW;
+        // qf takes the next unit's fragments ahead of the output stores (a wait for them behind the stores would
+        // be a wait for the stores as well)
+        auto take_next = [&]() {
 #pragma unroll
             for (int qb = 0; qb < NQB; ++qb)
 #pragma unroll
                 for (int ks = 0; ks < KS; ++ks) qf[qb][ks] = qn[qb][ks];
+        };
+        if (o_q0 < T) {                                             // wave-uniform
+            f32x4 acc_o[StreamShape<DH>::EB][NQB], acc_sum[NQB];
+            attn_pass<DH, NQB>(qf, lds, T, nch, ui * nch, scale_log2e, acc_o, acc_sum,
+                               [&]() { if (more) issue_q<DH, NQB>(qkv, T, D, H, pair, q0, qn); });
+            if (more) take_next();
+            store_pass<DH, NQB>(acc_o, acc_sum, o, T, D, H, o_pair, o_q0);
+        } else {
+            for (int c = 0; c < nch; ++c) {
+                asm volatile("" ::: "memory");
+                __builtin_amdgcn_s_barrier();
+                asm volatile("" ::: "memory");
+            }
+            if (more) issue_q<DH, NQB>(qkv, T, D, H, pair, q0, qf);
         }
     }
 }
 
-template <int DH>
+// QW: queries of a query wave (32 or 16)
+template <int DH, int QW>
 __global__ __launch_bounds__((MAXQW + NLOADER) * 64) void attn_stream_kernel(const uint16_t *__restrict__ qkv,
                                                                              uint16_t *__restrict__ o, int T, int D, int H,
-                                                                             int n_pairs, float scale_log2e)
+                                                                             int n_units, int ng, float scale_log2e)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
     using S = StreamShape<DH>;
-    constexpr int ROWB = S::ROWB, PARTB = S::PARTB, BUFB = S::BUFB, LPW = S::LPW, KS = S::KS, EB = S::EB;
+    constexpr int ROWB = S::ROWB, PARTB = S::PARTB, BUFB = S::BUFB, LPW = S::LPW;
     extern __shared__ uint4 smem_raw[];
     char *lds = reinterpret_cast<char *>(smem_raw);
     typedef __attribute__((address_space(3))) void *lds_ptr;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int l15 = lane & 15, g = lane >> 4;
     const int nqw = (int)(blockDim.x >> 6) - NLOADER;              // query waves of this launch
     const bool loader = wave >= nqw;                               // wave-uniform
     const int row_bytes = 3 * D * 2;
     const int seg_bytes = (T - 1) * row_bytes + DH * 2;            // first to last byte of a head's q, k or v
-    const int nch = (T + CK - 1) / CK;                             // chunks per pass
-    const int nqt = (T + 31) / 32;                                 // query tiles
-    const int npass = (nqt + nqw - 1) / nqw;
+    const int nch = (T + CK - 1) / CK;                             // chunks per unit
 
     // Workgroup w sits on XCD w % 8 (round-robin dispatch).  Each XCD gets a contiguous range of
-    // (image, head) pairs, as long as its share of the workgroups, so that the heads of an image, which
+    // units, as long as its share of the workgroups, so that the heads of an image, which
     // share cache lines of the qkv rows, meet in one L2; the workgroups of an XCD stride through it.
-    int pair, pair_end, pair_step;
+    int unit, unit_end, unit_step;
     {
         const int x = blockIdx.x % 8, g8 = gridDim.x / 8, r8 = gridDim.x % 8;
         const int before = x * g8 + min(x, r8);                    // workgroups on the XCDs in front of this one
-        pair_step = g8 + (x < r8 ? 1 : 0);                         // workgroups on this one
-        pair = (int)((int64_t)n_pairs * before / gridDim.x) + blockIdx.x / 8;
-        pair_end = (int)((int64_t)n_pairs * (before + pair_step) / gridDim.x);
+        unit_step = g8 + (x < r8 ? 1 : 0);                         // workgroups on this one
+        unit = (int)((int64_t)n_units * before / gridDim.x) + blockIdx.x / 8;
+        unit_end = (int)((int64_t)n_units * (before + unit_step) / gridDim.x);
     }
-    if (pair >= pair_end) return;                                  // whole workgroup
-    const int my_pairs = (pair_end - pair + pair_step - 1) / pair_step;
-    const int total = my_pairs * npass * nch;                      // chunk steps = barriers, the same for every wave
+    if (unit >= unit_end) return;                                  // whole workgroup
+    const int my_units = (unit_end - unit + unit_step - 1) / unit_step;
+    const int total = my_units * nch;                              // chunk steps = barriers, the same for every wave
 
     if (loader) {
         // ---- loader waves: loader 0 brings the K part of every chunk, loader 1 the V part, LPW loads of
@@ -372,7 +369,7 @@ __global__ __launch_bounds__((MAXQW + NLOADER) * 64) void attn_stream_kernel(con
             const int lin = s * 1024 + lane * 16;
             goff[s] = (lin / ROWB) * row_bytes + lin % ROWB;
         }
-        int pf_pair = pair, pf_pass = 0, pf_chunk = 0;               // the next chunk to fetch
+        int pf_unit = unit, pf_pair = unit / ng, pf_chunk = 0;       // the next chunk to fetch
         auto issue = [&](int buf) {
             const uint16_t *part = qkv + (size_t)(pf_pair / H) * T * 3 * D + (size_t)(pf_pair % H) * DH + (size_t)(1 + lw) * D;
             const __amdgpu_buffer_rsrc_t rs =
@@ -384,7 +381,8 @@ __global__ __launch_bounds__((MAXQW + NLOADER) * 64) void attn_stream_kernel(con
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr)(dst + s * 1024), 16, base + goff[s], 0, 0, 0);
             if (++pf_chunk == nch) {
                 pf_chunk = 0;
-                if (++pf_pass == npass) { pf_pass = 0; pf_pair += pair_step; }
+                pf_unit += unit_step;
+                pf_pair = pf_unit / ng;
             }
         };
         // Chunk 0 and its successor go out first, alone (everyone waits for them); from then on the loader
@@ -408,67 +406,70 @@ __global__ __launch_bounds__((MAXQW + NLOADER) * 64) void attn_stream_kernel(con
         return;
     }
 
-    // ---- query waves
-    auto idle_pass = [&]() {                                        // no tile in this pass: keep the barrier count
-        for (int c = 0; c < nch; ++c) {
-            asm volatile("" ::: "memory");
-            __builtin_amdgcn_s_barrier();
-            asm volatile("" ::: "memory");
-        }
-    };
-    if (npass == 1) {
-        const int q0 = wave * 32;                                   // < T: the launch has no more query waves than tiles
-        if (q0 + 16 < T)
-            attn_wave_single_pass<DH, 2>(qkv, o, lds, T, D, H, pair, pair_step, my_pairs, q0, nch, scale_log2e);
-        else
-            attn_wave_single_pass<DH, 1>(qkv, o, lds, T, D, H, pair, pair_step, my_pairs, q0, nch, scale_log2e);
-        return;
-    }
-    int j = 0;                                                      // chunk step
-    for (int pi = 0; pi < my_pairs; ++pi, pair += pair_step) {
-        for (int pass = 0; pass < npass; ++pass, j += nch) {
-            const int q0 = (pass * nqw + wave) * 32;
-            // wave-uniform: the tile's 16-query blocks with a query in them pick the code path once per pass
-            if (q0 + 16 < T) {
-                u32x4 qf[2][KS];
-                issue_q<DH, 2>(qkv, T, D, H, pair, q0, qf);
-                q_landed<2, KS>(qf);
-                f32x4 acc_o[EB][2], acc_sum[2];
-                attn_pass<DH, 2>(qf, lds, T, q0, nch, j, scale_log2e, acc_o, acc_sum, []() {});
-                store_pass<DH, 2>(acc_o, acc_sum, o, T, D, H, pair, q0);
-            } else if (q0 < T) {
-                u32x4 qf[1][KS];
-                issue_q<DH, 1>(qkv, T, D, H, pair, q0, qf);
-                q_landed<1, KS>(qf);
-                f32x4 acc_o[EB][1], acc_sum[1];
-                attn_pass<DH, 1>(qf, lds, T, q0, nch, j, scale_log2e, acc_o, acc_sum, []() {});
-                store_pass<DH, 1>(acc_o, acc_sum, o, T, D, H, pair, q0);
-            } else {
-                idle_pass();
-            }
-        }
-    }
+    // ---- query waves.  With one group to a pair a wave's tile is the same in every unit, and the wave that holds the
+    // ragged end of T leaves out a second 16-query block with no query in it.
+    if (QW == 32 && (ng > 1 || wave * 32 + 16 < T))
+        attn_wave<DH, 2>(qkv, o, lds, T, D, H, ng, nqw, wave, unit, unit_step, my_units, nch, scale_log2e);
+    else if (QW == 16 || ng == 1)
+        attn_wave<DH, 1>(qkv, o, lds, T, D, H, ng, QW == 16 ? nqw : 0, QW == 16 ? wave : 2 * wave, unit, unit_step, my_units, nch, scale_log2e);
 #endif
 }
 
-template <int DH>
-hipError_t launch_stream(const uint16_t *qkv, uint16_t *o, int B, int T, int D, int H, hipStream_t s)
+// How the queries of a pair are dealt: tiles of qw queries, ng groups of tiles, one workgroup per (pair, group).
+// A unit takes as long as its keys take to stream through and its busiest SIMD to work on them, so while pairs are
+// fewer than compute units the queries of a pair are spread over as many of them as there are to a pair
+// (microseconds per launch, before -> after, T = 197, d_head 64: 16 pairs 8.5 -> 5.5, 80 pairs 8.8 -> 6.7, 128
+// pairs 8.9 -> 7.4; T = 577: 24 pairs 35.1 -> 10.9, 96 pairs 36.3 -> 22.0; T = 257, d_head 80: 16 pairs
+// 10.9 -> 6.0); a second round of units would cost more than it saves (160 pairs at T = 197: 9.4 us with one group,
+// 12.0 with two).  Tiles of 16 queries where they leave the busiest SIMD with fewer 16-query blocks than tiles of
+// 32 (96 pairs at T = 257: 9.5 against 10.3 us), up to nine waves: every wave reads all keys and values from LDS
+// (60 pairs at T = 577: ten waves of 16 queries take 16.7 us, five of 32 15.8).  More than 320 queries to a group
+// do not fit the query waves of a workgroup.
+struct AttnPlan { int qw, ng; };
+
+AttnPlan plan_attention(int64_t pairs, int T, int n_cu)
+{
+    const int t32 = (T + 31) / 32, t16 = (T + 15) / 16;
+    const int most = (int)(n_cu / pairs);                           // groups to a pair that fit one round
+    const int ng_min = (t32 + MAXQW - 1) / MAXQW;
+    if (most <= ng_min) return {32, ng_min};
+    const int ng = most < t16 ? most : t16;
+    const int w32 = (t32 + ng - 1) / ng, w16 = (t16 + ng - 1) / ng;
+    if (w16 <= 9 && (w16 + 3) / 4 < 2 * ((w32 + 3) / 4)) return {16, ng};
+    return {32, ng < t32 ? ng : t32};
+}
+
+template <int DH, int QW>
+hipError_t launch_stream(const uint16_t *qkv, uint16_t *o, int B, int T, int D, int H, int ng, int n_cu, hipStream_t s)
 {
     using S = StreamShape<DH>;
-    auto kern = attn_stream_kernel<DH>;
+    auto kern = attn_stream_kernel<DH, QW>;
     static EpSmemLimit smem_limit;
-    hipError_t e = smem_limit.ensure(reinterpret_cast<const void *>(kern), (int)S::smem);
+    const hipError_t e = smem_limit.ensure(reinterpret_cast<const void *>(kern), (int)S::smem);
     if (e != hipSuccess) return e;
-    const int nqt = (T + 31) / 32;
-    const int nqw = nqt < MAXQW ? nqt : MAXQW;
+    const int tiles = (T + QW - 1) / QW, nqw = (tiles + ng - 1) / ng;
+    if (nqw > MAXQW) return hipErrorInvalidValue;
     const float scale_log2e = 1.4426950408889634f / sqrtf((float)DH);
-    int n_cu = 0;
-    if ((e = ep_device_cu_count(&n_cu)) != hipSuccess) return e;
-    const int n_pairs = B * H;
-    const int grid = n_pairs < n_cu ? n_pairs : n_cu;      // one workgroup per compute unit, or per pair if there are fewer
-    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3((nqw + NLOADER) * 64), S::smem, s, qkv, o, T, D, H, n_pairs,
+    const int64_t n_units = (int64_t)B * H * ng;
+    if (n_units > 0x7FFFFFFF) return hipErrorInvalidValue;
+    // at most one workgroup per compute unit, and no more than the rounds of units need: 272 units on 136 workgroups
+    // of two take 15.3 us where 256 workgroups, 16 of them with a second unit, take 16.2
+    const int64_t rounds = (n_units + n_cu - 1) / n_cu;
+    const int grid = (int)((n_units + rounds - 1) / rounds);
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3((nqw + NLOADER) * 64), S::smem, s, qkv, o, T, D, H, (int)n_units, ng,
                        scale_log2e);
     return hipGetLastError();
+}
+
+template <int DH>
+hipError_t launch_attention(const uint16_t *qkv, uint16_t *o, int B, int T, int D, int H, hipStream_t s)
+{
+    int n_cu = 0;
+    const hipError_t e = ep_device_cu_count(&n_cu);
+    if (e != hipSuccess) return e;
+    const AttnPlan p = plan_attention((int64_t)B * H, T, n_cu);
+    return p.qw == 32 ? launch_stream<DH, 32>(qkv, o, B, T, D, H, p.ng, n_cu, s)
+                      : launch_stream<DH, 16>(qkv, o, B, T, D, H, p.ng, n_cu, s);
 }
 
 }  // namespace
@@ -484,8 +485,8 @@ hipError_t ep_bf16_attention(const uint16_t *qkv, uint16_t *o, int B, int T, int
     if (H <= 0 || D % H != 0 || !ep_bf16_attention_supported(T, D / H)) return hipErrorInvalidValue;
     if ((int64_t)B * H > 0x7FFFFFFF || (int64_t)T * 3 * D * 2 >= 0x7FFFFFF0ll) return hipErrorInvalidValue;
     switch (D / H) {
-    case 64: return launch_stream<64>(qkv, o, B, T, D, H, s);
-    case 80: return launch_stream<80>(qkv, o, B, T, D, H, s);
+    case 64: return launch_attention<64>(qkv, o, B, T, D, H, s);
+    case 80: return launch_attention<80>(qkv, o, B, T, D, H, s);
     }
     return hipErrorInvalidValue;
 }
