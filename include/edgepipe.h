@@ -191,7 +191,8 @@ typedef enum {
 } ep_kernel_id;
 
 /*
- * Start timing one kernel of the layer: until ep_stage_trace_end, every launch
+ * Start timing one kernel of the layer (on the fp32 path a LayerNorm may run inside the
+ * dense layer behind it; its own bracket is then empty): until ep_stage_trace_end, every launch
  * of `kernel` made by ep_stage_forward on this stage is bracketed by a pair of
  * events recorded on the forward's stream (at most max_launches pairs, created
  * here; later launches run untimed).  Tracing one kernel at a time keeps the

@@ -1,8 +1,15 @@
-// fp32 path of a ViT encoder layer (paper section 2.1): plain-ALU kernels used
-// for small fp32 configurations where exactness matters more than speed.
-// LayerNorm: one wavefront per row.  GEMM: 64x64 LDS tiles, 4x4 outputs per
-// thread, the next K step's elements fetched while this one is multiplied.  Attention: one workgroup per (image, head, query), scores in LDS.
+// fp32 path of a ViT encoder layer (paper section 2.1) for configurations where
+// exactness matters more than speed: fp32 operands, products and sums everywhere.
+// The matrix products run on v_mfma_f32_16x16x4_f32 (fp32 in, fp32 accumulation,
+// twice the vector ALU's unpacked rate):
+//   dense layers   few tiles: 16 x 16 or 32 x 32 outputs per workgroup, K dealt to its four waves, operands straight
+//                  from memory into fragments, LayerNorm of the input rows done on the way where it comes first;
+//                  many tiles: 64 x 64 outputs, K panels through LDS;
+//   attention      16 or 32 queries per workgroup, keys dealt to its four waves, online softmax, merged at the end.
+// Plain vector-ALU kernels stand in where rows are not made of whole, aligned 16-byte pieces (K, D or d_head not
+// a multiple of 4, d_head above 128).
 #include "ep_kernels.h"
+#include "ep_launch.h"
 
 namespace {
 
@@ -47,7 +54,368 @@ __global__ __launch_bounds__(256) void ln_f32_kernel(const float *__restrict__ x
     for (int d = lane; d < D; d += WAVE) yr[d] = (xr[d] - mean) * inv * g[d] + b[d];
 }
 
-// --------------------------------------------------------------------- GEMM
+// The same for rows of whole 16-byte pieces, the row in registers: one pass over memory.  NV float4 per lane.
+template <int NV>
+__global__ __launch_bounds__(256) void ln_f32_vec_kernel(const float *__restrict__ x, const float *__restrict__ g,
+                                                         const float *__restrict__ b, float eps, float *__restrict__ y,
+                                                         int64_t rows, int D)
+{
+    const int lane = threadIdx.x & (WAVE - 1);
+    const int64_t row = (int64_t)blockIdx.x * (blockDim.x / WAVE) + (threadIdx.x / WAVE);
+    if (row >= rows) return;
+    const float4 *xr = reinterpret_cast<const float4 *>(x + row * D);
+    const float4 *g4 = reinterpret_cast<const float4 *>(g), *b4 = reinterpret_cast<const float4 *>(b);
+    const int nvec = D >> 2;
+    float4 v[NV], gg[NV], bb[NV];
+    float s = 0.f;
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+        const int c = lane + i * WAVE;
+        const bool in = c < nvec;
+        v[i] = in ? xr[c] : make_float4(0.f, 0.f, 0.f, 0.f);
+        gg[i] = in ? g4[c] : v[i];
+        bb[i] = in ? b4[c] : v[i];
+        s += (v[i].x + v[i].y) + (v[i].z + v[i].w);
+    }
+    const float mean = wave_sum(s) / (float)D;
+    float q = 0.f;
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+        if (lane + i * WAVE < nvec) {
+            v[i].x -= mean; v[i].y -= mean; v[i].z -= mean; v[i].w -= mean;
+            q += (v[i].x * v[i].x + v[i].y * v[i].y) + (v[i].z * v[i].z + v[i].w * v[i].w);
+        }
+    }
+    const float inv = 1.0f / sqrtf(wave_sum(q) / (float)D + eps);
+    float4 *yr = reinterpret_cast<float4 *>(y + row * D);
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+        const int c = lane + i * WAVE;
+        if (c < nvec)
+            yr[c] = make_float4(v[i].x * inv * gg[i].x + bb[i].x, v[i].y * inv * gg[i].y + bb[i].y,
+                                v[i].z * inv * gg[i].z + bb[i].z, v[i].w * inv * gg[i].w + bb[i].w);
+    }
+}
+
+// ------------------------------------------------------------- dense layers on the matrix cores
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float frag4 __attribute__((ext_vector_type(4)));   // one 16-byte piece of a row: four k, one per MFMA
+
+// v_mfma_f32_16x16x4_f32, four of them: slot g = lane / 16 of step j holds k = 4 g + j of a 16-wide slice (any
+// assignment does, as long as both operands share it), so one 16-byte piece per lane feeds four steps
+__device__ inline f32x4 mfma_slice(frag4 a, frag4 b, f32x4 c)
+{
+#pragma unroll
+    for (int j = 0; j < 4; ++j) c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[j], b[j], c, 0, 0, 0);
+    return c;
+}
+
+constexpr int F32_OOB = 0x7FFFFFF0;
+
+#if defined(__HIP_DEVICE_COMPILE__)   // buffer-resource builtins exist only in the device pass
+__device__ inline __amdgpu_buffer_rsrc_t make_rsrc(const float *p, int bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p), 0, bytes, 0x00020000);
+}
+__device__ inline frag4 load_piece(__amdgpu_buffer_rsrc_t rs, int byte)
+{
+    return __builtin_bit_cast(frag4, __builtin_amdgcn_raw_buffer_load_b128(rs, byte, 0, 0));
+}
+#endif
+
+// bias, GELU or residual, store of four consecutive columns n .. n+3 of row m; `vec`: N % 4 == 0 and 16-byte
+// aligned resid and C
+template <int EPI>
+__device__ inline void store_four(const float (&v)[4], const float *bias, const float *resid, float *C, int64_t m, int n, int N,
+                                  bool vec)
+{
+    const int64_t off = m * N + n;
+    if (vec) {
+        const float4 bb = *reinterpret_cast<const float4 *>(bias + n);
+        float4 r = make_float4(v[0] + bb.x, v[1] + bb.y, v[2] + bb.z, v[3] + bb.w);
+        if (EPI == EPI_BIAS_GELU) { r.x = gelu_erf(r.x); r.y = gelu_erf(r.y); r.z = gelu_erf(r.z); r.w = gelu_erf(r.w); }
+        if (EPI == EPI_BIAS_RESID) {
+            const float4 x = *reinterpret_cast<const float4 *>(resid + off);
+            r.x += x.x; r.y += x.y; r.z += x.z; r.w += x.w;
+        }
+        *reinterpret_cast<float4 *>(C + off) = r;
+    } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (n + i >= N) break;
+            float r = v[i] + bias[n + i];
+            if (EPI == EPI_BIAS_GELU) r = gelu_erf(r);
+            if (EPI == EPI_BIAS_RESID) r += resid[off + i];
+            C[off + i] = r;
+        }
+    }
+}
+
+// Workgroup -> tile, columns fastest: workgroup w runs on XCD w % 8 (round-robin dispatch), and each XCD takes a
+// contiguous run of tiles, so that the tiles of a row panel meet in one L2.  False: past the last tile.
+__device__ inline bool f32_tile_of(int tiles_n, int tiles, int *tm, int *tn)
+{
+    const int per = (tiles + 7) / 8, id = (int)(blockIdx.x % 8) * per + (int)(blockIdx.x / 8);
+    *tm = id / tiles_n;
+    *tn = id - *tm * tiles_n;
+    return blockIdx.x / 8 < (unsigned)per && id < tiles;
+}
+inline dim3 f32_tile_grid(int64_t tiles) { return dim3((unsigned)((tiles + 7) / 8 * 8)); }
+
+// Few tiles: one 16 MI x 16 MI tile per workgroup.  Such a launch is a chain of latencies (a 65-row layer has 60 to
+// 240 tiles of 16 x 16), so no wave waits for another on the way in: the 16-wide K slices are dealt to the four waves
+// and each brings its own from memory into its own part of LDS (buffer_load ... lds, R slices ahead, four lanes to
+// a 64-byte row piece; fragments loaded straight into registers would have every lane of a quarter wave on a row of its
+// own, four times the cache lines per load: 17.2 against 10.9 us at 1576 x 192 x 768), and the four sums are added
+// in wave order at the end.  Two layers on one 65 x 192 image: 229 us on the vector ALU, 64 x 64 tiles, before; 42 now.
+// LN > 0: A is the residual stream and its rows are normalised first (all K in LDS at once: LN slices per wave,
+// K <= 64 LN); every workgroup does that for its own rows, which costs two small exchanges through LDS and saves
+// the launch of LayerNorm and a trip through memory.
+// LDS rows are 64 bytes, four rows to all the banks: piece c of row r sits at slot c ^ (r >> 2 & 3), so that the
+// 16-byte reads of 16 rows meet no bank twice.
+template <int MI, int LN>
+struct F32Direct {
+    static constexpr int T = 16 * MI, R = LN ? LN : (MI == 1 ? 6 : 4), LP = T + 4;
+    static constexpr int SLICE = 2 * T * 4;                         // 16-byte pieces of a slice: A rows, then W rows
+    static constexpr size_t ring = (size_t)4 * R * SLICE * 16, sums = (size_t)4 * T * LP * 4;
+    static constexpr size_t smem = ring > sums ? ring : sums;       // the sums reuse the ring
+};
+
+template <int MI, int EPI, int LN>
+__global__ __launch_bounds__(256) void gemm_f32_direct_kernel(const float *__restrict__ A, const float *__restrict__ ln_g,
+                                                              const float *__restrict__ ln_b, float eps,
+                                                              const float *__restrict__ W, const float *__restrict__ bias,
+                                                              const float *resid, float *C, int64_t M, int N, int K, int tiles_n,
+                                                              int tiles, int vec)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    using S = F32Direct<MI, LN>;
+    constexpr int T = S::T, R = S::R;
+    extern __shared__ uint4 lds_raw[];
+    __shared__ float stat[2][4][T];
+    typedef __attribute__((address_space(3))) void *lds_ptr;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l15 = lane & 15, g = lane >> 4;
+    int tm, tn;
+    if (!f32_tile_of(tiles_n, tiles, &tm, &tn)) return;
+    const int64_t m0 = (int64_t)tm * T;
+    const int n0 = tn * T;
+    const int nsl = (K + 15) / 16, my = (nsl - wave + 3) / 4;       // slices of all, of this wave (wave, wave + 4, ...)
+    // rows past M or N lie past the end of the panel's descriptor, pieces past K get such an offset: both read as zeros
+    const int am = (int)(M - m0 < T ? M - m0 : T), wn = N - n0 < T ? N - n0 : T;
+    const __amdgpu_buffer_rsrc_t a_rs = make_rsrc(A + m0 * K, am * K * 4), w_rs = make_rsrc(W + (int64_t)n0 * K, wn * K * 4);
+    uint4 *ring = lds_raw + wave * R * S::SLICE;
+    const int lrow = lane >> 2, lk = ((lane & 3) ^ ((lrow >> 2) & 3)) * 4;
+    auto issue = [&](int t) {                                       // slice t of this wave
+        uint4 *dst = ring + (t % R) * S::SLICE;
+        const int k = (wave + 4 * t) * 16 + lk;
+#pragma unroll
+        for (int i = 0; i < MI; ++i) {
+            const int off = k < K ? ((i * 16 + lrow) * K + k) * 4 : F32_OOB;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rs, (lds_ptr)(dst + i * 64), 16, off, 0, 0, 0);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(w_rs, (lds_ptr)(dst + T * 4 + i * 64), 16, off, 0, 0, 0);
+        }
+    };
+    const int rd = l15 * 4 + (g ^ ((l15 >> 2) & 3));
+    auto frag = [&](int t, int part, int i) {                       // part 0: A rows, 1: W rows
+        return reinterpret_cast<const frag4 *>(ring + (t % R) * S::SLICE)[part * T * 4 + i * 64 + rd];
+    };
+
+    f32x4 acc[MI][MI];
+#pragma unroll
+    for (int ni = 0; ni < MI; ++ni)
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi) acc[ni][mi] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int t = 0; t < R; ++t) issue(t);
+
+    if (LN) {
+        frag4 fa[R][MI], gg[R], bb[R];
+        const __amdgpu_buffer_rsrc_t g_rs = make_rsrc(ln_g, K * 4), b_rs = make_rsrc(ln_b, K * 4);
+        auto col = [&](int t) { return (wave + 4 * t) * 16 + 4 * g; };          // first k of this lane in slice t
+#pragma unroll
+        for (int t = 0; t < R; ++t) {
+            gg[t] = load_piece(g_rs, col(t) < K ? col(t) * 4 : F32_OOB);
+            bb[t] = load_piece(b_rs, col(t) < K ? col(t) * 4 : F32_OOB);
+        }
+        __builtin_amdgcn_s_waitcnt(0 | (0x7 << 4) | (0xF << 8));
+#pragma unroll
+        for (int t = 0; t < R; ++t)
+#pragma unroll
+            for (int i = 0; i < MI; ++i) fa[t][i] = frag(t, 0, i);
+        float mean[MI], inv[MI];
+#pragma unroll
+        for (int pass = 0; pass < 2; ++pass) {
+#pragma unroll
+            for (int i = 0; i < MI; ++i) {
+                float s = 0.f;
+#pragma unroll
+                for (int t = 0; t < R; ++t) {
+                    if (pass == 1) {                                // K % 4 == 0: a piece is inside or outside as a whole
+                        const float in = col(t) < K ? 1.f : 0.f;
+                        fa[t][i] = (fa[t][i] - mean[i]) * in;
+                        s += (fa[t][i][0] * fa[t][i][0] + fa[t][i][1] * fa[t][i][1]) + (fa[t][i][2] * fa[t][i][2] + fa[t][i][3] * fa[t][i][3]);
+                    } else {
+                        s += (fa[t][i][0] + fa[t][i][1]) + (fa[t][i][2] + fa[t][i][3]);
+                    }
+                }
+                s += __shfl_xor(s, 16, WAVE);
+                s += __shfl_xor(s, 32, WAVE);
+                if (g == 0) stat[pass][wave][i * 16 + l15] = s;
+            }
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < MI; ++i) {
+                const int r = i * 16 + l15;
+                const float s = ((stat[pass][0][r] + stat[pass][1][r]) + (stat[pass][2][r] + stat[pass][3][r])) / (float)K;
+                if (pass == 0) mean[i] = s;
+                else inv[i] = 1.0f / sqrtf(s + eps);
+            }
+        }
+#pragma unroll
+        for (int t = 0; t < R; ++t) {
+            frag4 fw[MI];
+#pragma unroll
+            for (int i = 0; i < MI; ++i) {
+                fw[i] = frag(t, 1, i);
+                fa[t][i] = fa[t][i] * inv[i] * gg[t] + bb[t];       // zero beyond K: gain and shift are
+            }
+#pragma unroll
+            for (int ni = 0; ni < MI; ++ni)
+#pragma unroll
+                for (int mi = 0; mi < MI; ++mi) acc[ni][mi] = mfma_slice(fw[ni], fa[t][mi], acc[ni][mi]);
+        }
+    } else {
+        for (int t = 0; t < my; ++t) {
+            // slice t has landed once at most the loads of the R - 1 slices after it are in flight
+            constexpr int V = (R - 1) * 2 * MI;
+            __builtin_amdgcn_s_waitcnt((V & 0xF) | (V >> 4 << 14) | (0x7 << 4) | (0xF << 8));
+            asm volatile("" ::: "memory");
+            frag4 fa[MI], fw[MI];
+#pragma unroll
+            for (int i = 0; i < MI; ++i) { fa[i] = frag(t, 0, i); fw[i] = frag(t, 1, i); }
+#pragma unroll
+            for (int ni = 0; ni < MI; ++ni)
+#pragma unroll
+                for (int mi = 0; mi < MI; ++mi) acc[ni][mi] = mfma_slice(fw[ni], fa[mi], acc[ni][mi]);
+            __builtin_amdgcn_s_waitcnt(0xF | (0x3 << 14) | (0x7 << 4) | (0x0 << 8));       // lgkmcnt: the slice has been read
+            asm volatile("" ::: "memory");
+            issue(t + R);                                           // past the last slice: zeros, to keep the count
+        }
+        __builtin_amdgcn_s_waitcnt(0 | (0x7 << 4) | (0xF << 8));
+    }
+
+    // acc[ni][mi][i] <-> column ni*16 + 4 g + i, row mi*16 + l15
+    __syncthreads();
+    float (*part)[T][S::LP] = reinterpret_cast<float (*)[T][S::LP]>(lds_raw);
+#pragma unroll
+    for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+        for (int ni = 0; ni < MI; ++ni)
+            *reinterpret_cast<float4 *>(&part[wave][mi * 16 + l15][ni * 16 + g * 4]) =
+                make_float4(acc[ni][mi][0], acc[ni][mi][1], acc[ni][mi][2], acc[ni][mi][3]);
+    __syncthreads();
+    for (int id = tid; id < T * T / 4; id += 256) {
+        const int r = id / (T / 4), c = id % (T / 4) * 4;
+        float v[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = (part[0][r][c + i] + part[1][r][c + i]) + (part[2][r][c + i] + part[3][r][c + i]);
+        if (m0 + r < M && n0 + c < N) store_four<EPI>(v, bias, resid, C, m0 + r, n0 + c, N, vec);
+    }
+#endif
+}
+
+// Many tiles: 64 x 32 outputs, four waves of 32 x 16, K in steps of 32 (rows of 128 bytes) that go from memory
+// straight into LDS (buffer_load ... lds), FS - 1 steps ahead; up to six workgroups per compute unit, whose number
+// hides what two stages do not (four stages and two workgroups: 257 against 228 us per layer of 256 tiny images;
+// tiles of 64 columns no faster there, and 189 against 172 us with 17 deit_small images, 318 tiles of 64 on 256
+// compute units).  72 to 90 TFLOP/s at K = 192 to 1536, 30 with the vector-ALU kernel it replaced.  LDS rows are
+// eight 16-byte chunks, chunk c of row r at slot c ^ (r & 7) ^ (r >> 3 & 1), the chunks of a 16-wide slice dealt
+// 0, 2, 1, 3 to the quarters of a wave: the bf16 kernels' layout, free of bank conflicts.
+constexpr int FT = 64, FN = 32, FK = 32, FCH = FK / 4, FS = 2;
+template <int EPI>
+__global__ __launch_bounds__(256, 4) void gemm_f32_tile_kernel(const float *__restrict__ A, const float *__restrict__ W,
+                                                               const float *__restrict__ bias, const float *resid, float *C,
+                                                               int64_t M, int N, int K, int tiles_n, int tiles, int vec)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    extern __shared__ uint4 lds_raw[];                              // [FS][A panel | W panel], FT rows of FCH chunks each
+    typedef __attribute__((address_space(3))) void *lds_ptr;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l15 = lane & 15, g = lane >> 4;
+    int tm, tn;
+    if (!f32_tile_of(tiles_n, tiles, &tm, &tn)) return;
+    const int64_t m0 = (int64_t)tm * FT;
+    const int n0 = tn * FN;
+    constexpr int NI = FN / 32, STAGE = (FT + FN) * FCH;
+    const int wm0 = (wave >> 1) * 32, wn0 = (wave & 1) * (FN / 2);
+    auto swz = [](int r) { return (r & 7) ^ ((r >> 3) & 1); };
+    const int am = (int)(M - m0 < FT ? M - m0 : FT), wn = N - n0 < FN ? N - n0 : FN;
+    const __amdgpu_buffer_rsrc_t a_rs = make_rsrc(A + m0 * K, am * K * 4);
+    const __amdgpu_buffer_rsrc_t w_rs = make_rsrc(W + (int64_t)n0 * K, wn * K * 4);
+    // load i of a wave fills panel rows (4 i + wave) * 8 .. + 7; lane l lands at row l / 8, slot l % 8
+    int roff[2], kc[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int r = (i * 4 + wave) * 8 + (lane >> 3);
+        kc[i] = ((lane & 7) ^ swz(r)) * 4;
+        roff[i] = r * K * 4;                                        // rows past the panel's end lie past the descriptor's
+    }
+    const int KT = (K + FK - 1) / FK;
+    auto issue = [&](int kt) {
+        uint4 *dst = lds_raw + (kt % FS) * STAGE;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int k = kt * FK + kc[i];
+            const int off = k < K ? roff[i] + k * 4 : F32_OOB;          // past K: zeros
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rs, (lds_ptr)(dst + (i * 4 + wave) * 64), 16, off, 0, 0, 0);
+            if (i < NI)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(w_rs, (lds_ptr)(dst + FT * FCH + (i * 4 + wave) * 64), 16, off, 0, 0, 0);
+        }
+    };
+    f32x4 acc[NI][2];
+#pragma unroll
+    for (int a = 0; a < NI; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int kc4 = ((g & 1) << 1) | (g >> 1);
+#pragma unroll
+    for (int st = 0; st < FS - 1; ++st) issue(st);
+    for (int kt = 0; kt < KT; ++kt) {
+        __builtin_amdgcn_s_waitcnt(((FS - 2) * (2 + NI)) | (0x7 << 4) | (0xF << 8));       // vmcnt: step kt has landed
+        __builtin_amdgcn_s_barrier();
+        issue(kt + FS - 1);
+        const frag4 *Ab = reinterpret_cast<const frag4 *>(lds_raw + (kt % FS) * STAGE), *Wb = Ab + FT * FCH;
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk) {
+            const int c = (kk * 4 + kc4) ^ swz(l15);
+            frag4 fa[2], fw[NI];
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                fa[i] = Ab[(wm0 + i * 16 + l15) * FCH + c];
+                if (i < NI) fw[i] = Wb[(wn0 + i * 16 + l15) * FCH + c];
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+                    for (int mi = 0; mi < 2; ++mi)
+                        acc[ni][mi] = __builtin_amdgcn_mfma_f32_16x16x4f32(fw[ni][j], fa[mi][j], acc[ni][mi], 0, 0, 0);
+        }
+    }
+    __builtin_amdgcn_s_waitcnt(0 | (0x7 << 4) | (0xF << 8));        // the loads past the last step, before LDS goes away
+#pragma unroll
+    for (int mi = 0; mi < 2; ++mi)
+#pragma unroll
+        for (int ni = 0; ni < NI; ++ni) {
+            const int64_t m = m0 + wm0 + mi * 16 + l15;
+            const int n = n0 + wn0 + ni * 16 + g * 4;
+            const float v[4] = {acc[ni][mi][0], acc[ni][mi][1], acc[ni][mi][2], acc[ni][mi][3]};
+            if (m < M && n < N) store_four<EPI>(v, bias, resid, C, m, n, N, vec);
+        }
+#endif
+}
+
+// ---------------------------------------------- dense layers on the vector ALU: any K, any alignment
 constexpr int GT = 64;  // tile edge
 constexpr int GK = 64;  // k step: few, long steps (each one costs a trip to memory on the small problems this path serves)
 
@@ -120,7 +488,153 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float *__restrict__
 }
 
 // ---------------------------------------------------------------- attention
-// One workgroup (128 threads) per (image, head, query token).
+// A wave works on 16 queries of one (image, head), 16 keys at a time.  SPLIT: the four waves of a workgroup share the
+// queries, the key blocks are dealt to them, each with its own running maximum, sum and output, merged through LDS at
+// the end (few queries in all: latency counts); otherwise every wave has queries of its own and meets all keys.
+// Keys and values arrive a block ahead.  A value piece goes straight into registers (16 lanes to a row); key fragments
+// would put every lane of a quarter wave on a row of its own, so keys pass through LDS, each wave's through its own
+// part (piece c of row r at slot c ^ r: the 16-byte reads of 16 rows meet no bank twice).
+//   S^T = K . Q^T    lane: query l % 16, keys 4 (l/16) + i
+//   O^T += V^T . P^T step i multiplies key 4 g + i of every quarter g: the probabilities are the B operand as they
+//                    stand, and V's 16-byte piece 4 (l%16) .. + 3 of that key's row feeds four 16-component blocks,
+//                    block j holding components 4 r + j, r = 0 .. 15 (of each 64; NT of them).
+// d_head % 4 == 0, d_head <= 64 NT; pieces past it are zeros.
+template <int NT, bool SPLIT>
+__global__ __launch_bounds__(256) void attn_f32_mfma_kernel(const float *__restrict__ qkv, float *__restrict__ o, int T, int D,
+                                                            int H, int groups)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    constexpr int LP = 64 * NT + 4, CPR = 16 * NT;                  // padded output row; 16-byte pieces of a key row
+    __shared__ __align__(16) float Os[SPLIT ? 4 : 1][16][LP];
+    __shared__ float ms[4][16], ls[4][16];
+    __shared__ uint4 Ks[4][2][16 * CPR];
+    typedef __attribute__((address_space(3))) void *lds_ptr;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l15 = lane & 15, g = lane >> 4;
+    const int dh = D / H, grp = (int)(blockIdx.x % groups), q0 = (SPLIT ? grp : grp * 4 + wave) * 16;
+    if (q0 >= T) return;                                            // without SPLIT: a wave with no queries
+    const int64_t pair = blockIdx.x / groups, b = pair / H;
+    const int h = (int)(pair % H);
+    const float *base = qkv + b * T * 3 * D + h * dh;
+    const float scale = 1.0f / sqrtf((float)dh);
+    const __amdgpu_buffer_rsrc_t rs = make_rsrc(base, ((T - 1) * 3 * D + 2 * D + dh) * 4);
+    auto piece = [&](int t, int which, int e) -> frag4 {            // components e .. e+3 of q, k or v of token t
+        return load_piece(rs, t < T && e < dh ? (t * 3 * D + which * D + e) * 4 : F32_OOB);
+    };
+    const int w = __builtin_amdgcn_readfirstlane(wave);
+    frag4 qf[4 * NT], vf[4][NT], vn[4][NT];
+#pragma unroll
+    for (int s = 0; s < 4 * NT; ++s) qf[s] = piece(q0 + l15, 0, s * 16 + g * 4);
+    auto fetch = [&](int kb, int buf, frag4 (&v)[4][NT]) {          // a block past the last one: zeros, no traffic
+#pragma unroll
+        for (int i = 0; i < 4 * NT; ++i) {
+            const int p = i * 64 + lane, row = p / CPR, e = ((p % CPR) ^ row) * 4, t = kb * 16 + row;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr)(&Ks[w][buf][i * 64]), 16,
+                                                     t < T && e < dh ? (t * 3 * D + D + e) * 4 : F32_OOB, 0, 0, 0);
+        }
+        asm volatile("" ::: "memory");
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int t = 0; t < NT; ++t) v[i][t] = piece(kb * 16 + g * 4 + i, 2, t * 64 + l15 * 4);
+        asm volatile("" ::: "memory");
+    };
+    f32x4 acc[NT][4];
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[t][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float mx = -INFINITY, sum = 0.f;
+    const int nkb = (T + 15) / 16, step = SPLIT ? 4 : 1;
+    int kb = SPLIT ? wave : 0;
+    fetch(kb, 0, vf);
+    for (int buf = 0; kb < nkb; kb += step, buf ^= 1) {
+        fetch(kb + step, buf ^ 1, vn);
+        // this block's keys have landed: younger are its 4 NT value pieces and the next block's loads
+        __builtin_amdgcn_s_waitcnt((12 * NT & 0xF) | (12 * NT >> 4 << 14) | (0x7 << 4) | (0xF << 8));
+        asm volatile("" ::: "memory");
+        f32x4 s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int c = 0; c < 4 * NT; ++c)
+            s = mfma_slice(reinterpret_cast<const frag4 *>(Ks[w][buf])[l15 * CPR + ((c * 4 + g) ^ l15)], qf[c], s);
+        float p[4], m = -INFINITY;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            p[i] = kb * 16 + g * 4 + i < T ? s[i] * scale : -INFINITY;
+            m = fmaxf(m, p[i]);
+        }
+        m = fmaxf(m, __shfl_xor(m, 16, WAVE));
+        m = fmaxf(m, __shfl_xor(m, 32, WAVE));
+        m = fmaxf(m, mx);                                           // finite: a block has a key < T
+        const float alpha = expf(mx - m);
+        mx = m;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) p[i] = expf(p[i] - m);
+        sum = sum * alpha + ((p[0] + p[1]) + (p[2] + p[3]));        // this lane's keys
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) acc[t][j] *= alpha;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    acc[t][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[i][t][j], p[i], acc[t][j], 0, 0, 0);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int t = 0; t < NT; ++t) vf[i][t] = vn[i][t];
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                // nothing on its way to LDS when the wave ends
+    sum += __shfl_xor(sum, 16, WAVE);
+    sum += __shfl_xor(sum, 32, WAVE);
+    float *orow = o + (b * T + q0) * D + h * dh;                    // first query's output
+    // acc[t][j][i] <-> query l15, component 64 t + 16 g + 4 i + j
+    if (!SPLIT) {
+        const float inv = 1.0f / sum;
+        if (q0 + l15 < T) {
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int e = 64 * t + 16 * g + 4 * i;
+                    if (e < dh)
+                        *reinterpret_cast<float4 *>(orow + (int64_t)l15 * D + e) =
+                            make_float4(acc[t][0][i] * inv, acc[t][1][i] * inv, acc[t][2][i] * inv, acc[t][3][i] * inv);
+                }
+        }
+        return;
+    }
+    if (g == 0) { ms[wave][l15] = mx; ls[wave][l15] = sum; }
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            *reinterpret_cast<float4 *>(&Os[SPLIT ? wave : 0][l15][64 * t + 16 * g + 4 * i]) =
+                make_float4(acc[t][0][i], acc[t][1][i], acc[t][2][i], acc[t][3][i]);
+    __syncthreads();
+    const int d4 = dh / 4;
+    for (int id = tid; id < 16 * d4; id += 256) {
+        const int q = id / d4, e = id % d4 * 4;
+        if (q0 + q >= T) continue;
+        const float m = fmaxf(fmaxf(ms[0][q], ms[1][q]), fmaxf(ms[2][q], ms[3][q]));
+        float l = 0.f;
+        float4 r = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            const float f = expf(ms[w][q] - m);                     // 0 for a wave without keys
+            const float4 x = *reinterpret_cast<const float4 *>(&Os[SPLIT ? w : 0][q][e]);
+            l += f * ls[w][q];
+            r.x += f * x.x; r.y += f * x.y; r.z += f * x.z; r.w += f * x.w;
+        }
+        const float inv = 1.0f / l;
+        *reinterpret_cast<float4 *>(orow + (int64_t)q * D + e) = make_float4(r.x * inv, r.y * inv, r.z * inv, r.w * inv);
+    }
+#endif
+}
+
+// Any d_head: one workgroup (128 threads) per (image, head, query token).
 __global__ __launch_bounds__(128) void attn_f32_kernel(const float *__restrict__ qkv,
                                                        float *__restrict__ o, int T, int D, int H)
 {
@@ -179,42 +693,156 @@ __global__ void fill_pattern_kernel(float *x, int64_t n)
 
 }  // namespace
 
+static bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
+
 hipError_t ep_f32_layernorm(const float *x, const float *g, const float *b, float eps, float *y,
                             int64_t rows, int D, hipStream_t s)
 {
     if (rows <= 0) return hipSuccess;
     const int rows_per_block = 256 / WAVE;
-    const unsigned grid = (unsigned)((rows + rows_per_block - 1) / rows_per_block);
-    hipLaunchKernelGGL(ln_f32_kernel, dim3(grid), dim3(256), 0, s, x, g, b, eps, y, rows, D);
+    const dim3 grid((unsigned)((rows + rows_per_block - 1) / rows_per_block));
+    if (D % 4 == 0 && D <= 4 * 256 && aligned16(x) && aligned16(y)) {
+        switch ((D + 255) / 256) {
+        case 1: hipLaunchKernelGGL(ln_f32_vec_kernel<1>, grid, dim3(256), 0, s, x, g, b, eps, y, rows, D); break;
+        case 2: hipLaunchKernelGGL(ln_f32_vec_kernel<2>, grid, dim3(256), 0, s, x, g, b, eps, y, rows, D); break;
+        case 3: hipLaunchKernelGGL(ln_f32_vec_kernel<3>, grid, dim3(256), 0, s, x, g, b, eps, y, rows, D); break;
+        default: hipLaunchKernelGGL(ln_f32_vec_kernel<4>, grid, dim3(256), 0, s, x, g, b, eps, y, rows, D); break;
+        }
+    } else {
+        hipLaunchKernelGGL(ln_f32_kernel, grid, dim3(256), 0, s, x, g, b, eps, y, rows, D);
+    }
     return hipGetLastError();
 }
+
+namespace {
+
+// tiles of t x t outputs
+int64_t square_tiles(int64_t M, int N, int t) { return ((M + t - 1) / t) * ((N + t - 1) / t); }
+
+template <int MI, int EPI, int LN>
+hipError_t launch_f32_direct(const float *A, const float *g, const float *b, float eps, const float *W, const float *bias,
+                             const float *resid, float *C, int64_t M, int N, int K, int vec, hipStream_t s)
+{
+    using S = F32Direct<MI, LN>;
+    auto kern = gemm_f32_direct_kernel<MI, EPI, LN>;
+    static EpSmemLimit smem_limit;
+    const hipError_t e = smem_limit.ensure(reinterpret_cast<const void *>(kern), (int)S::smem);
+    if (e != hipSuccess) return e;
+    const int64_t tiles = square_tiles(M, N, S::T);
+    hipLaunchKernelGGL(kern, f32_tile_grid(tiles), dim3(256), S::smem, s, A, g, b, eps, W, bias, resid, C, M, N, K,
+                       (N + S::T - 1) / S::T, (int)tiles, vec);
+    return hipGetLastError();
+}
+
+template <int EPI>
+hipError_t launch_f32_gemm(const float *A, const float *W, const float *bias, const float *resid, float *C, int64_t M,
+                           int N, int K, hipStream_t s)
+{
+    if (K % 4 == 0 && aligned16(A) && aligned16(W) && square_tiles(M, N, 32) < (1 << 24) && K < (1 << 23)) {    // 2^32 threads to a grid, 32-bit offsets in a panel
+        int cus = 0;
+        const hipError_t e = ep_device_cu_count(&cus);
+        if (e != hipSuccess) return e;
+        const int vec = N % 4 == 0 && aligned16(bias) && aligned16(C) && (EPI != EPI_BIAS_RESID || aligned16(resid));
+        const int64_t t16 = square_tiles(M, N, 16), t32 = square_tiles(M, N, 32);
+        // The smallest tiles up to two to a compute unit (more of them: 16 tiny images 42.6 against 39.2 us per layer,
+        // one deit_small image 45.4 against 44.5), tiles of 32 up to three (four deit_small images 70.9 us per layer
+        // against 89.2 with twice as many, whose K panels every workgroup brings in on its own), then the LDS tiles.
+        if (t16 <= 2 * cus) {
+            return launch_f32_direct<1, EPI, 0>(A, nullptr, nullptr, 0.f, W, bias, resid, C, M, N, K, vec, s);
+        } else if (t32 <= 3 * cus) {
+            return launch_f32_direct<2, EPI, 0>(A, nullptr, nullptr, 0.f, W, bias, resid, C, M, N, K, vec, s);
+        } else {
+            const int tiles_n = (N + FN - 1) / FN, tiles = (int)((M + FT - 1) / FT) * tiles_n;
+            hipLaunchKernelGGL(gemm_f32_tile_kernel<EPI>, f32_tile_grid(tiles), dim3(256), FS * (FT + FN) * FK * sizeof(float), s, A, W,
+                               bias, resid, C, M, N, K, tiles_n, tiles, vec);
+        }
+        return hipGetLastError();
+    }
+    const dim3 grid((unsigned)((N + GT - 1) / GT), (unsigned)((M + GT - 1) / GT));
+    if (grid.y > 65535u) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(gemm_f32_kernel<EPI>, grid, dim3(256), 0, s, A, W, bias, resid, C, M, N, K);
+    return hipGetLastError();
+}
+
+}  // namespace
 
 hipError_t ep_f32_gemm(const float *A, const float *W, const float *bias, const float *resid,
                        float *C, int64_t M, int N, int K, int epi, hipStream_t s)
 {
     if (M <= 0 || N <= 0) return hipSuccess;
-    const dim3 grid((unsigned)((N + GT - 1) / GT), (unsigned)((M + GT - 1) / GT));
-    if (grid.y > 65535u) return hipErrorInvalidValue;
     switch (epi) {
-    case EPI_BIAS:
-        hipLaunchKernelGGL(gemm_f32_kernel<EPI_BIAS>, grid, dim3(256), 0, s, A, W, bias, resid, C, M, N, K);
-        break;
-    case EPI_BIAS_GELU:
-        hipLaunchKernelGGL(gemm_f32_kernel<EPI_BIAS_GELU>, grid, dim3(256), 0, s, A, W, bias, resid, C, M, N, K);
-        break;
-    case EPI_BIAS_RESID:
-        hipLaunchKernelGGL(gemm_f32_kernel<EPI_BIAS_RESID>, grid, dim3(256), 0, s, A, W, bias, resid, C, M, N, K);
-        break;
-    default: return hipErrorInvalidValue;
+    case EPI_BIAS: return launch_f32_gemm<EPI_BIAS>(A, W, bias, resid, C, M, N, K, s);
+    case EPI_BIAS_GELU: return launch_f32_gemm<EPI_BIAS_GELU>(A, W, bias, resid, C, M, N, K, s);
+    case EPI_BIAS_RESID: return launch_f32_gemm<EPI_BIAS_RESID>(A, W, bias, resid, C, M, N, K, s);
     }
-    return hipGetLastError();
+    return hipErrorInvalidValue;
+}
+
+namespace {
+
+template <int EPI>
+hipError_t launch_f32_ln_gemm(const float *x, const float *g, const float *b, float eps, const float *W, const float *bias,
+                              float *C, int64_t M, int N, int K, hipStream_t s)
+{
+    int cus = 0;
+    const hipError_t e = ep_device_cu_count(&cus);
+    if (e != hipSuccess) return e;
+    const int vec = N % 4 == 0 && aligned16(bias) && aligned16(C);
+    const int64_t t16 = square_tiles(M, N, 16);
+    if (t16 <= 2 * cus)
+        return K <= 192 ? launch_f32_direct<1, EPI, 3>(x, g, b, eps, W, bias, nullptr, C, M, N, K, vec, s)
+                        : launch_f32_direct<1, EPI, 6>(x, g, b, eps, W, bias, nullptr, C, M, N, K, vec, s);
+    return K <= 192 ? launch_f32_direct<2, EPI, 3>(x, g, b, eps, W, bias, nullptr, C, M, N, K, vec, s)
+                    : launch_f32_direct<2, EPI, 6>(x, g, b, eps, W, bias, nullptr, C, M, N, K, vec, s);
+}
+
+}  // namespace
+
+bool ep_f32_ln_gemm_supported(const float *x, const float *W, int64_t M, int N, int K)
+{
+    int cus = 0;
+    if (ep_device_cu_count(&cus) != hipSuccess) return false;
+    // where tiles of 32 serve the dense layer anyway (4 tiny images 28.1 us per layer against 33.0 with LayerNorm on its
+    // own; four deit_small images, past this line, 95 against 87)
+    return K % 4 == 0 && K <= 384 && M > 0 && N > 0 && aligned16(x) && aligned16(W) && square_tiles(M, N, 32) <= 3 * cus;
+}
+
+hipError_t ep_f32_ln_gemm(const float *x, const float *g, const float *b, float eps, const float *W, const float *bias, float *C,
+                          int64_t M, int N, int K, int epi, hipStream_t s)
+{
+    if (!ep_f32_ln_gemm_supported(x, W, M, N, K) || !aligned16(g) || !aligned16(b)) return hipErrorInvalidValue;
+    switch (epi) {
+    case EPI_BIAS: return launch_f32_ln_gemm<EPI_BIAS>(x, g, b, eps, W, bias, C, M, N, K, s);
+    case EPI_BIAS_GELU: return launch_f32_ln_gemm<EPI_BIAS_GELU>(x, g, b, eps, W, bias, C, M, N, K, s);
+    }
+    return hipErrorInvalidValue;
 }
 
 hipError_t ep_f32_attention(const float *qkv, float *o, int B, int T, int D, int H, hipStream_t s)
 {
     if (B <= 0) return hipSuccess;
     if (H > 65535 || B > 65535) return hipErrorInvalidValue;
-    const size_t smem = sizeof(float) * (size_t)(T + D / H + 2);
+    const int dh = D / H;
+    if (D % 4 == 0 && dh % 4 == 0 && dh <= 128 && aligned16(qkv) && aligned16(o) &&
+        (int64_t)B * H * ((T + 15) / 16) < (1 << 24) && (int64_t)T * 3 * D * 4 < F32_OOB) {
+        int cus = 0;
+        const hipError_t e = ep_device_cu_count(&cus);
+        if (e != hipSuccess) return e;
+        const int64_t pairs = (int64_t)B * H;
+        const int t16 = (T + 15) / 16;
+        // up to a wave and a half per SIMD the keys are split (24 deit_tiny images, 936 waves: 95.6 us per layer against
+        // 103.0; 768 tiny ones, 3840 waves: 222 against 219)
+        const bool split = pairs * t16 <= 6 * cus;
+        const int groups = split ? t16 : (t16 + 3) / 4;
+        const dim3 grid((unsigned)(pairs * groups));
+#define EP_LAUNCH(NT, SPLIT) \
+    hipLaunchKernelGGL((attn_f32_mfma_kernel<NT, SPLIT>), grid, dim3(256), 0, s, qkv, o, T, D, H, groups)
+        if (dh <= 64) { if (split) EP_LAUNCH(1, true); else EP_LAUNCH(1, false); }
+        else { if (split) EP_LAUNCH(2, true); else EP_LAUNCH(2, false); }
+#undef EP_LAUNCH
+        return hipGetLastError();
+    }
+    const size_t smem = sizeof(float) * (size_t)(T + dh + 2);
     if (smem > 64 * 1024) return hipErrorInvalidValue;
     hipLaunchKernelGGL(attn_f32_kernel, dim3(T, H, B), dim3(128), smem, s, qkv, o, T, D, H);
     return hipGetLastError();

@@ -225,12 +225,17 @@ ep_status run_layer(ep_stage *st, const Workspace &w, const LayerDev &L, const f
         }
     } else {
         float *a = (float *)w.a, *big = (float *)w.big;
-        EP_TRACED(EP_K_LN1, ep_f32_layernorm(xin, L.ln1_g, L.ln1_b, c.ln_eps, a, R, D, s));
-        EP_TRACED(EP_K_QKV, ep_f32_gemm(a, (const float *)L.w_qkv, L.b_qkv, nullptr, big, R, 3 * D, D, EPI_BIAS, s));
+        // a LayerNorm done inside the dense layer behind it leaves its own bracket empty
+        const bool fuse1 = ep_f32_ln_gemm_supported(xin, (const float *)L.w_qkv, R, 3 * D, D);
+        const bool fuse2 = ep_f32_ln_gemm_supported(w.x, (const float *)L.w_fc1, R, M, D);
+        EP_TRACED(EP_K_LN1, fuse1 ? hipSuccess : ep_f32_layernorm(xin, L.ln1_g, L.ln1_b, c.ln_eps, a, R, D, s));
+        EP_TRACED(EP_K_QKV, fuse1 ? ep_f32_ln_gemm(xin, L.ln1_g, L.ln1_b, c.ln_eps, (const float *)L.w_qkv, L.b_qkv, big, R, 3 * D, D, EPI_BIAS, s)
+                                  : ep_f32_gemm(a, (const float *)L.w_qkv, L.b_qkv, nullptr, big, R, 3 * D, D, EPI_BIAS, s));
         EP_TRACED(EP_K_ATTN, ep_f32_attention(big, a, B, T, D, H, s));
         EP_TRACED(EP_K_PROJ, ep_f32_gemm(a, (const float *)L.w_o, L.b_o, xin, w.x, R, D, D, EPI_BIAS_RESID, s));
-        EP_TRACED(EP_K_LN2, ep_f32_layernorm(w.x, L.ln2_g, L.ln2_b, c.ln_eps, a, R, D, s));
-        EP_TRACED(EP_K_FC1, ep_f32_gemm(a, (const float *)L.w_fc1, L.b_fc1, nullptr, big, R, M, D, EPI_BIAS_GELU, s));
+        EP_TRACED(EP_K_LN2, fuse2 ? hipSuccess : ep_f32_layernorm(w.x, L.ln2_g, L.ln2_b, c.ln_eps, a, R, D, s));
+        EP_TRACED(EP_K_FC1, fuse2 ? ep_f32_ln_gemm(w.x, L.ln2_g, L.ln2_b, c.ln_eps, (const float *)L.w_fc1, L.b_fc1, big, R, M, D, EPI_BIAS_GELU, s)
+                                  : ep_f32_gemm(a, (const float *)L.w_fc1, L.b_fc1, nullptr, big, R, M, D, EPI_BIAS_GELU, s));
         EP_TRACED(EP_K_FC2, ep_f32_gemm(big, (const float *)L.w_fc2, L.b_fc2, w.x, xout, R, D, M, EPI_BIAS_RESID, s));
     }
     return EP_OK;

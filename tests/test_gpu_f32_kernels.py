@@ -1,0 +1,66 @@
+"""GPU parity of the fp32 path at the edges of its kernels: the matrix-core dense layers (16- and 32-wide tiles with
+and without LayerNorm inside, 64 x 32 tiles), attention with the keys split over waves and not, head widths up to 128,
+and the vector-ALU kernels where rows are not whole 16-byte pieces.  fp32 tolerance throughout."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2110_14895_amd import binding, synth
+from tests import harness as H
+
+pytestmark = pytest.mark.gpu
+
+
+def run(T, D, Hh, M, B, offset=0):
+    import torch
+    sh = synth.custom_shape(f"f32k_{T}_{D}", 2, D, Hh, M, T)
+    layers = [synth.layer_params(sh, l, randomize_affine=True, w_std=0.1) for l in range(2)]
+    x = synth.activations(sh, B)
+    st = H.make_stage(sh, layers, 0, 2, B, bf16=False)
+    n = x.size
+    xin = torch.empty(n + 4, dtype=torch.float32, device="cuda")[offset:offset + n]
+    xin.copy_(torch.from_numpy(x).reshape(-1))
+    out = torch.full((n + 8,), float("nan"), dtype=torch.float32, device="cuda")
+    st.forward(xin, B, out[offset:offset + n], torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    got = out.cpu().numpy()
+    assert np.isnan(got[:offset]).all() and np.isnan(got[offset + n:]).all()        # nothing beside the output
+    got = got[offset:offset + n].reshape(x.shape)
+    pick = sorted({0, B // 2, B - 1})
+    ref = oracle.stage_forward(H.oracle_cfg(sh), layers, x[pick])
+    assert H.rel_err(got[pick], ref) <= H.TOL_F32
+
+
+@pytest.mark.parametrize("T,D,Hh,M,B", [
+    (65, 320, 4, 900, 1),      # 16-wide tiles, LayerNorm inside with K > 192, d_head 80
+    (50, 192, 2, 768, 9),      # 32-wide tiles, LayerNorm inside, d_head 96
+    (50, 320, 5, 640, 9),      # ... with K > 192
+    (33, 132, 3, 520, 180),    # 64 x 32 tiles with ragged K; attention with queries to every wave, d_head 44
+    (197, 256, 2, 260, 17),    # d_head 128, keys split
+    (40, 256, 2, 128, 300),    # d_head 128, queries to every wave, 12000 rows
+    (1, 64, 1, 64, 1),         # one row, one key
+    (17, 400, 8, 64, 2),       # K > 384: LayerNorm on its own, d_head 50 on the vector ALU
+    (19, 18, 3, 30, 4),        # K and N not multiples of 4
+    (19, 20, 2, 30, 4),        # only N is not
+    (21, 36, 6, 40, 3),        # d_head 6
+    (9, 288, 2, 64, 2),        # d_head 144
+])
+def test_f32_shapes(T, D, Hh, M, B):
+    run(T, D, Hh, M, B)
+
+
+@pytest.mark.parametrize("T,D,Hh,M,B", [(65, 192, 3, 768, 1), (33, 132, 3, 520, 60)])
+def test_f32_buffers_off_16_byte_alignment(T, D, Hh, M, B):
+    run(T, D, Hh, M, B, offset=1)
+
+
+def test_f32_trace_of_a_layernorm_inside_a_dense_layer():
+    sh = synth.SHAPES["tiny"]
+    st = H.make_stage(sh, [synth.layer_params(sh, l) for l in range(2)], 0, 2, 1, bf16=False)
+    x = synth.activations(sh, 1)
+    want = H.run_stage(st, x)
+    for kid in range(len(binding.KERNEL_NAMES)):
+        st.trace_begin(kid, 2)
+        np.testing.assert_array_equal(H.run_stage(st, x), want)
+        n, sec = st.trace_end()
+        assert n == 2 and sec >= 0
