@@ -7,19 +7,24 @@
 // A: bf16 activations, W: bf16 weights [out, in], both K-contiguous, fp32
 // accumulation on the matrix cores (v_mfma_f32_16x16x32_bf16).
 //
-// This file holds the one-tile-per-workgroup kernel used for problems too small
-// for the persistent kernel (ep_gemm_bf16_persist.hip) and the dispatcher
-// ep_bf16_gemm.
+// This file holds the one-tile-per-workgroup kernel used wherever the persistent kernel
+// (ep_gemm_bf16_persist.hip) is not the faster one, and the dispatcher ep_bf16_gemm.
 //
-// Tiling.  A workgroup owns a BM x BN tile of C and walks K in steps of BK (128,
-// 64 or 32).  Each K step's A and W panels live in LDS as rows of 16-byte chunks;
-// chunk c of row r is stored at slot c ^ f(r) (f below), which makes the MFMA
-// fragment reads bank-conflict free without padding.  The panels go from global
-// memory straight into LDS (buffer_load ... lds), STAGES - 1 steps ahead of the
-// MFMAs, with explicit s_waitcnt counts and one bare s_barrier per step.
-// Waves are laid out WM x WN; each wave keeps (BN/WN/16) x (BM/WM/16)
-// accumulators of 16x16 (the 16x16x32 form of the instruction draws less power
-// per flop than 32x32x16, and power is what limits the clock in these loops).
+// Tiling.  A workgroup owns a BM x BN tile of C and walks K in steps of 64 (rows of 128 bytes,
+// whole cache lines).  Each step's A and W panels live in LDS as rows of 16-byte chunks;
+// chunk c of row r is stored at slot c ^ swz(r), which makes the MFMA fragment reads
+// bank-conflict free without padding.  The panels go from global memory straight into LDS
+// (buffer_load ... lds), up to STAGES steps ahead of the MFMAs, with explicit s_waitcnt counts.
+// Waves are laid out WM x WN; each wave keeps (BN/WN/16) x (BM/WM/16) accumulators of 16x16 (the
+// 16x16x32 form of the instruction draws less power per flop than 32x32x16, and power is what
+// limits the clock in these loops).
+//
+// What bounds it: the chain of K steps.  With fragments read, multiplied and refilled one after the
+// other a step of a 128 x 128 tile took 0.60 us (32 KB into LDS, 96 KB of fragment reads, 0.24 us of
+// matrix instructions).  Reads of the next 32-wide slice and loads of a later step now go out between
+// the matrix instructions of this one, with one barrier per step: 0.43 us, where the loads alone are
+// 0.26 at the 56 bytes per clock a compute unit gets from its L2 (256 x 256: 1.04 us, 0.98 of matrix
+// instructions).  The second MLP layer of ViT-Large at 3152 rows, 200 tiles of 128 x 128: 39.5 -> 34.4 us.
 //
 // Operand roles are swapped with respect to C: the MFMA "A" operand is the W
 // fragment (rows = output columns n) and the "B" operand is the activation
@@ -33,12 +38,10 @@
 //
 // Ragged edges: rows beyond M and columns beyond N are read as zeros (per-lane
 // buffer offsets past the end of the buffer) and never stored.  K % 64 == 0 and
-// N % 8 == 0 required.
+// N % 8 == 0 (bf16 output) or N % 4 == 0 (fp32 output) required.
 //
-// Dispatcher: when 256-row tiles fill the chip the persistent kernel takes the
-// problem, its tile walk stopping up to two tile rows short of M when that saves
-// a round of tiles (the remaining rows are computed by the tail phase of the same
-// launch); everything else runs here.
+// Dispatcher: one cost model over the tile shapes of this kernel and the two of the
+// persistent one.
 #include <cstdint>
 #include "ep_kernels.h"
 #include "ep_device.h"
@@ -48,9 +51,11 @@ namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int NUM_XCD = 8;
 constexpr int GROUP_M = 4;
+constexpr int BK = 64;                               // K step
 
 
 #if defined(__HIP_DEVICE_COMPILE__)   // buffer-resource builtins exist only in the device pass
@@ -65,20 +70,16 @@ __device__ inline __amdgpu_buffer_rsrc_t make_rsrc(const void *p, uint32_t bytes
 // s_waitcnt with only the vector-memory counter constrained (gfx9 encoding)
 #define EP_WAIT_VMCNT(n) __builtin_amdgcn_s_waitcnt(((n) & 0xF) | (((n) >> 4) << 14) | (0x7 << 4) | (0xF << 8))
 
-// Row-dependent XOR applied to the 16-byte chunk index inside an LDS row, for
-// rows of 16 chunks (BK = 128), 8 chunks (BK = 64) or 4 chunks (BK = 32).  Chosen
-// so that the MFMA fragment reads (16 consecutive rows, same logical chunk) spread
-// over all banks whether the LDS serves 8 or 16 lanes of a 128-bit read per cycle.
-template <int BK_>
-__device__ inline int swz(int row)
-{
-    if (BK_ == 128) return row & 15;          // a row is 256 bytes, all the banks: 16 rows take 16 different chunks
-    if (BK_ == 64) return (row & 7) ^ ((row >> 3) & 1);
-    return ((row >> 1) & 3) ^ ((row >> 3) & 1);
-}
+#define EP_WAIT_LGKMCNT0() __builtin_amdgcn_s_waitcnt(0xF | (0x3 << 14) | (0x7 << 4) | (0x0 << 8))
+#define EP_SCHED_FENCE() __builtin_amdgcn_sched_barrier(0)
 
-template <int BM, int BN, int BK_, int STAGES, int WM, int WN, int EPI>
-__global__ __launch_bounds__(WM *WN * 64, (WM * WN <= 4 && STAGES * (BM + BN) * BK_ * 2 <= 80 * 1024) ? 2 : 1) void gemm_bf16_kernel(
+// Row-dependent XOR applied to the 16-byte chunk index inside an LDS row of 8 chunks.  Chosen so that the MFMA
+// fragment reads (16 consecutive rows, same logical chunk) spread over all banks whether the LDS serves 8 or 16
+// lanes of a 128-bit read per cycle.
+__device__ inline int swz(int row) { return (row & 7) ^ ((row >> 3) & 1); }
+
+template <int BM, int BN, int STAGES, int WM, int WN, int EPI>
+__global__ __launch_bounds__(WM *WN * 64, (WM * WN <= 4 && STAGES * (BM + BN) * BK * 2 <= 80 * 1024) ? 2 : 1) void gemm_bf16_kernel(
     const uint16_t *__restrict__ A, const uint16_t *__restrict__ W, const float *__restrict__ bias,
     const float *resid, void *Cout, int M, int N, int K, int k_len, int tiles_m, int tiles_n)
 {
@@ -86,11 +87,14 @@ __global__ __launch_bounds__(WM *WN * 64, (WM * WN <= 4 && STAGES * (BM + BN) * 
     constexpr int NW = WM * WN;                       // waves
     constexpr int WTM = BM / WM, WTN = BN / WN;       // wave tile
     constexpr int MI = WTM / 16, NI = WTN / 16;       // 16x16 accumulators per wave
-    constexpr int CPR = BK_ / 8;                      // 16-byte chunks per LDS row
+    constexpr int CPR = BK / 8;                      // 16-byte chunks per LDS row
     constexpr int RPI = 64 / CPR;                     // rows covered by one wave-wide 16-byte load
     constexpr int A_LD = BM / RPI / NW, W_LD = BN / RPI / NW;   // load instructions per wave per tile
     static_assert(BM % (RPI * NW) == 0 && BN % (RPI * NW) == 0, "panel must split evenly over waves");
-    static_assert(BK_ % 32 == 0 && WTM % 16 == 0 && WTN % 16 == 0, "16 x 16 x 32 fragments");
+    constexpr bool PAIRED = (EPI == EPI_BIAS || EPI == EPI_BIAS_GELU) && NI % 2 == 0;
+    constexpr int NS = BK / 32;                      // 32-wide slices per step
+    static_assert(NS % 2 == 0 && STAGES >= 2, "fragment registers alternate from slice to slice");
+    static_assert(WTM % 16 == 0 && WTN % 16 == 0, "16 x 16 x 32 fragments");
     constexpr int A_STAGE = BM * CPR, W_STAGE = BN * CPR;       // uint4 per stage
 
     extern __shared__ uint4 lds[];                    // [STAGES][A_STAGE] then [STAGES][W_STAGE]
@@ -129,34 +133,37 @@ __global__ __launch_bounds__(WM *WN * 64, (WM * WN <= 4 && STAGES * (BM + BN) * 
 #pragma unroll
     for (int i = 0; i < A_LD; ++i) {
         const int r = (i * NW + wave) * RPI + lane / CPR;
-        const int c = (lane % CPR) ^ swz<BK_>(r);
+        const int c = (lane % CPR) ^ swz(r);
         const int gr = m0 + r;
         a_off[i] = gr < M ? (gr * K + k0 + c * 8) * 2 : 0x7FFFFFF0;     // beyond the buffer -> zeros
     }
 #pragma unroll
     for (int i = 0; i < W_LD; ++i) {
         const int r = (i * NW + wave) * RPI + lane / CPR;
-        const int c = (lane % CPR) ^ swz<BK_>(r);
-        const int gr = n0 + r;
+        const int c = (lane % CPR) ^ swz(r);
+        // bf16 outputs: rows of a 32-column block are dealt so that a lane's accumulators of two neighbouring
+        // fragments are eight consecutive columns (one 16-byte store): fragment f, row 4 g + i <-> column 8 g + 4 f + i
+        const int gr = n0 + (PAIRED ? (r & ~31) + ((r >> 2) & 3) * 8 + ((r >> 4) & 1) * 4 + (r & 3) : r);
         w_off[i] = gr < N ? (gr * K + k0 + c * 8) * 2 : 0x7FFFFFF0;
     }
-    const int KT = k_len / BK_;
-    auto issue = [&](int kt) {
-        const int stage = kt % STAGES;
-        // past the last K step the per-lane offset points beyond the buffer: zeros, no traffic (the
-        // load is still issued so that the count of loads in flight stays fixed)
+    const int KT = k_len / BK;
+    constexpr int LD = A_LD + W_LD;
+    // load `which` of tile kt: A panel first.  Past the last K step the per-lane offset points beyond the buffer:
+    // zeros, no traffic (the load is still issued so that the count of loads in flight stays fixed)
+    auto issue_one = [&](int kt, int stage, int which) {
         const bool live = kt < KT;
-        const int koff = live ? kt * BK_ * 2 : 0;
+        const int koff = live ? kt * BK * 2 : 0;
         typedef __attribute__((address_space(3))) void *lds_ptr;
-#pragma unroll
-        for (int i = 0; i < A_LD; ++i)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rs, (lds_ptr)(As + stage * A_STAGE + (i * NW + wave) * 64), 16,
-                                                     live ? a_off[i] : 0x7FFFFFF0, koff, 0, 0);
-#pragma unroll
-        for (int i = 0; i < W_LD; ++i)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(w_rs, (lds_ptr)(Ws + stage * W_STAGE + (i * NW + wave) * 64), 16,
-                                                     live ? w_off[i] : 0x7FFFFFF0, koff, 0, 0);
+        if (which < A_LD)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rs, (lds_ptr)(As + stage * A_STAGE + (which * NW + wave) * 64), 16,
+                                                     live ? a_off[which] : 0x7FFFFFF0, koff, 0, 0);
+        else
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(w_rs, (lds_ptr)(Ws + stage * W_STAGE + ((which - A_LD) * NW + wave) * 64),
+                                                     16, live ? w_off[which - A_LD] : 0x7FFFFFF0, koff, 0, 0);
     };
+
+    // first of the four columns a lane's accumulators of fragment ni belong to
+    auto col = [&](int ni) { return n0 + wn0 + (PAIRED ? (ni >> 1) * 32 + g4 * 8 + (ni & 1) * 4 : ni * 16 + g4 * 4); };
 
     f32x4 acc[NI][MI];
 #pragma unroll
@@ -170,109 +177,145 @@ __global__ __launch_bounds__(WM *WN * 64, (WM * WN <= 4 && STAGES * (BM + BN) * 
     // fragment is 16 rows by 32 of K: lane l reads row l % 16 and one 8-element K chunk per quarter
     // l / 16 of the wave, the chunks dealt 0, 2, 1, 3 (both operands alike), which keeps the 16-byte reads
     // of the four quarters off each other's banks.
-    const int fsw = swz<BK_>(l15);
+    const int fsw = swz(l15);
     const int kc4 = ((g4 & 1) << 1) | (g4 >> 1);
-    int a_rd[BK_ / 32], w_rd[BK_ / 32];
+    int a_rd[BK / 32], w_rd[BK / 32];
 #pragma unroll
-    for (int kk = 0; kk < BK_ / 32; ++kk) {
+    for (int kk = 0; kk < BK / 32; ++kk) {
         a_rd[kk] = (wm0 + l15) * CPR + ((kk * 4 + kc4) ^ fsw);
         w_rd[kk] = (wn0 + l15) * CPR + ((kk * 4 + kc4) ^ fsw);
     }
 
-    // What the epilogue adds is fetched now, ahead of the first panel loads (loads return in order, so every
-    // counted wait below covers it): a small launch is a handful of K steps long and would otherwise end with
-    // one more trip to memory.  The residual only where it is a few registers (tiles of at most 64 rows).
-    constexpr bool PRE_RES = EPI == EPI_BIAS_RESID && MI * NI <= 8;
+    // ---- K loop, software-pipelined: while a 32-wide slice is multiplied the fragments of the next one are read
+    // and, in the last slice of a step, the loads of the step STAGES ahead go out, one at a time between the
+    // matrix instructions.  One barrier per step, before its last slice: by then every wave has read the
+    // stage for the last time (so it can be refilled) and the next step has landed.
+    bf16x8 wf[2][NI], af[2][MI];
+    constexpr int Q = NI * MI;                        // matrix instructions per slice
+    constexpr int RPM = (NI + MI + Q - 1) / Q;        // fragment reads per matrix instruction, from the first on
+    constexpr bool PRE_RES = EPI == EPI_BIAS_RESID && Q <= 8;
+    static_assert((STAGES - 1) * LD <= 63, "vmcnt is six bits");
+    auto read_frag = [&](int buf, const uint4 *Ab, const uint4 *Wb, int kk, int j) {
+        if (j < NI)
+            wf[buf][j] = __builtin_bit_cast(bf16x8, Wb[w_rd[kk] + j * 16 * CPR]);
+        else
+            af[buf][j - NI] = __builtin_bit_cast(bf16x8, Ab[a_rd[kk] + (j - NI) * 16 * CPR]);
+    };
+    // What the epilogue adds is fetched now: a small launch is a handful of K steps long and would otherwise end
+    // with one more trip to memory.  Loads return in order, so nothing here makes a counted wait below too short.
+    // The bias goes ahead of the first panel loads, the residual (where a few registers hold it) behind them:
+    // 0.3 us less per launch than ahead of them; with 16 accumulators a wave it cost 1 to 1.5 us instead.
     float4 bias_r[NI], res_r[PRE_RES ? NI : 1][PRE_RES ? MI : 1];
     if (EPI != EPI_PARTIAL) {
 #pragma unroll
         for (int ni = 0; ni < NI; ++ni) {
-            const int n = n0 + wn0 + ni * 16 + g4 * 4;
+            const int n = col(ni);
             bias_r[ni] = n < N ? *reinterpret_cast<const float4 *>(bias + n) : make_float4(0.f, 0.f, 0.f, 0.f);
-            if (PRE_RES) {
-#pragma unroll
-                for (int mi = 0; mi < MI; ++mi) {
-                    const int m = m0 + wm0 + mi * 16 + l15;
-                    res_r[ni][mi] = (m < M && n < N) ? *reinterpret_cast<const float4 *>(resid + (size_t)m * N + n)
-                                                     : make_float4(0.f, 0.f, 0.f, 0.f);
-                }
-            }
         }
     }
-
 #pragma unroll
-    for (int st = 0; st < STAGES - 1; ++st) issue(st);
+    for (int st = 0; st < STAGES; ++st)
+#pragma unroll
+        for (int j = 0; j < LD; ++j) issue_one(st, st, j);
+    if (PRE_RES) {
+#pragma unroll
+        for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+            for (int mi = 0; mi < MI; ++mi) {
+                const int n = col(ni), m = m0 + wm0 + mi * 16 + l15;
+                res_r[ni][mi] = (m < M && n < N) ? *reinterpret_cast<const float4 *>(resid + (size_t)m * N + n)
+                                                 : make_float4(0.f, 0.f, 0.f, 0.f);
+            }
+    }
+    EP_WAIT_VMCNT((STAGES - 1) * LD);
+    __builtin_amdgcn_s_barrier();
+#pragma unroll
+    for (int j = 0; j < NI + MI; ++j) read_frag(0, As, Ws, 0, j);
 
+    int stage = 0;
     for (int kt = 0; kt < KT; ++kt) {
-        // tile kt has landed once at most the loads of the STAGES-2 younger tiles are in flight
-        EP_WAIT_VMCNT((STAGES - 2) * (A_LD + W_LD));
-        __builtin_amdgcn_s_barrier();          // everyone's part of tile kt has landed; stage of tile kt-1 is free
-        issue(kt + STAGES - 1);
-        const uint4 *Ab = As + (kt % STAGES) * A_STAGE;
-        const uint4 *Wb = Ws + (kt % STAGES) * W_STAGE;
+        const int next = stage + 1 == STAGES ? 0 : stage + 1;
+        const uint4 *Ab = As + stage * A_STAGE, *Wb = Ws + stage * W_STAGE;
+        const uint4 *An = As + next * A_STAGE, *Wn = Ws + next * W_STAGE;
 #pragma unroll
-        for (int kk = 0; kk < BK_ / 32; ++kk) {
-            bf16x8 wf[NI], af[MI];
+        for (int kk = 0; kk < NS; ++kk) {
+            const bool last = kk == NS - 1;
+            const int cur = kk & 1;
+            if (last) {
+                EP_WAIT_LGKMCNT0();                    // my reads of this stage are done
+                EP_WAIT_VMCNT((STAGES - 2) * LD);      // my part of the next step has landed
+                __builtin_amdgcn_s_barrier();
+            }
 #pragma unroll
-            for (int ni = 0; ni < NI; ++ni) wf[ni] = __builtin_bit_cast(bf16x8, Wb[w_rd[kk] + ni * 16 * CPR]);
+            for (int q = 0; q < Q; ++q) {
+                const int ni = q / MI, mi = (ni & 1) ? MI - 1 - q % MI : q % MI;
+                acc[ni][mi] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[cur][ni], af[cur][mi], acc[ni][mi], 0, 0, 0);
+                if (q == 0) EP_SCHED_FENCE();
 #pragma unroll
-            for (int mi = 0; mi < MI; ++mi) af[mi] = __builtin_bit_cast(bf16x8, Ab[a_rd[kk] + mi * 16 * CPR]);
+                for (int j = q * RPM; j < (q + 1) * RPM && j < NI + MI; ++j)
+                    read_frag(cur ^ 1, last ? An : Ab, last ? Wn : Wb, last ? 0 : kk + 1, j);
+                if (last) {
 #pragma unroll
-            for (int ni = 0; ni < NI; ++ni)
-#pragma unroll
-                for (int mi = 0; mi < MI; ++mi)
-                    acc[ni][mi] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[ni], af[mi], acc[ni][mi], 0, 0, 0);
+                    for (int j = 0; j < LD; ++j)
+                        if (j * Q / LD == q) issue_one(kt + STAGES, stage, j);
+                }
+                EP_SCHED_FENCE();
+            }
         }
+        stage = next;
     }
     EP_WAIT_VMCNT(0);                          // drain the (empty) tail loads before LDS goes away
 
-    // ---- epilogue.  acc[ni][mi][i]: n = ni*16 + 4*(lane/16) + i, m = mi*16 + lane%16
+    // ---- epilogue.  acc[ni][mi][i]: n = col(ni) + i, m = mi*16 + lane%16.  (Stores that bypass the caches
+    // shorten a launch by 0.3 to 1.3 us and cost its reader more: ViT-Large at 6304 rows 1318 -> 1344 us a stage.)
 #pragma unroll
     for (int mi = 0; mi < MI; ++mi) {
         const int m = m0 + wm0 + mi * 16 + l15;
         if (m >= M) continue;
+        uint2 even;                                    // PAIRED: the first four of a lane's eight columns
 #pragma unroll
         for (int ni = 0; ni < NI; ++ni) {
-            {
-                const int n = n0 + wn0 + ni * 16 + g4 * 4;
-                if (n >= N) continue;
-                if (EPI == EPI_PARTIAL) {          // the bare sum over this K range, fp32, range-major
-                    const float4 o = make_float4(acc[ni][mi][0], acc[ni][mi][1], acc[ni][mi][2], acc[ni][mi][3]);
-                    *reinterpret_cast<float4 *>(reinterpret_cast<float *>(Cout) + ((size_t)split * M + m) * N + n) = o;
-                    continue;
-                }
-                const float4 bb = bias_r[ni];
-                float v0 = acc[ni][mi][0] + bb.x;
-                float v1 = acc[ni][mi][1] + bb.y;
-                float v2 = acc[ni][mi][2] + bb.z;
-                float v3 = acc[ni][mi][3] + bb.w;
-                const size_t off = (size_t)m * N + n;
-                if (EPI == EPI_BIAS_RESID) {
-                    const float4 r = PRE_RES ? res_r[PRE_RES ? ni : 0][PRE_RES ? mi : 0]
-                                             : *reinterpret_cast<const float4 *>(resid + off);
-                    float4 o = make_float4(v0 + r.x, v1 + r.y, v2 + r.z, v3 + r.w);
-                    *reinterpret_cast<float4 *>(reinterpret_cast<float *>(Cout) + off) = o;
-                } else {
-                    if (EPI == EPI_BIAS_GELU) {
-                        v0 = gelu_erf(v0); v1 = gelu_erf(v1); v2 = gelu_erf(v2); v3 = gelu_erf(v3);
-                    }
-                    uint2 o;
-                    o.x = pack_bf16x2(v0, v1);
-                    o.y = pack_bf16x2(v2, v3);
-                    *reinterpret_cast<uint2 *>(reinterpret_cast<uint16_t *>(Cout) + off) = o;
-                }
+            const int n = col(ni);
+            if (n >= N) continue;
+            const f32x4 c = acc[ni][mi];
+            if (EPI == EPI_PARTIAL) {                  // the bare sum over this K range, fp32, range-major
+                float *o = reinterpret_cast<float *>(Cout) + ((size_t)split * M + m) * N + n;
+                *reinterpret_cast<f32x4 *>(o) = c;
+                continue;
+            }
+            const float4 bb = bias_r[ni];
+            float v0 = c[0] + bb.x, v1 = c[1] + bb.y, v2 = c[2] + bb.z, v3 = c[3] + bb.w;
+            const size_t off = (size_t)m * N + n;
+            if (EPI == EPI_BIAS_RESID) {
+                const float4 r = PRE_RES ? res_r[PRE_RES ? ni : 0][PRE_RES ? mi : 0]
+                                         : *reinterpret_cast<const float4 *>(resid + off);
+                const f32x4 o = {v0 + r.x, v1 + r.y, v2 + r.z, v3 + r.w};
+                *reinterpret_cast<f32x4 *>(reinterpret_cast<float *>(Cout) + off) = o;
+                continue;
+            }
+            if (EPI == EPI_BIAS_GELU) {
+                v0 = gelu_erf(v0); v1 = gelu_erf(v1); v2 = gelu_erf(v2); v3 = gelu_erf(v3);
+            }
+            const uint2 o = make_uint2(pack_bf16x2(v0, v1), pack_bf16x2(v2, v3));
+            if (!PAIRED) {
+                *reinterpret_cast<uint2 *>(reinterpret_cast<uint16_t *>(Cout) + off) = o;
+            } else if ((ni & 1) == 0) {
+                even = o;
+            } else {
+                const u32x4 w = {even.x, even.y, o.x, o.y};
+                *reinterpret_cast<u32x4 *>(reinterpret_cast<uint16_t *>(Cout) + off - 4) = w;
             }
         }
     }
 #endif   // __HIP_DEVICE_COMPILE__
 }
 
-template <int BM, int BN, int BK_, int STAGES, int WM, int WN, int EPI>
+template <int BM, int BN, int STAGES, int WM, int WN, int EPI>
 hipError_t launch_cfg(const uint16_t *A, const uint16_t *W, const float *bias, const float *resid,
                       void *C, int M, int N, int K, int splits, hipStream_t s)
 {
-    auto kern = gemm_bf16_kernel<BM, BN, BK_, STAGES, WM, WN, EPI>;
-    constexpr size_t smem = (size_t)STAGES * (BM + BN) * (BK_ / 8) * sizeof(uint4);
+    auto kern = gemm_bf16_kernel<BM, BN, STAGES, WM, WN, EPI>;
+    constexpr size_t smem = (size_t)STAGES * (BM + BN) * (BK / 8) * sizeof(uint4);
     static EpSmemLimit smem_limit;
     const hipError_t e = smem_limit.ensure(reinterpret_cast<const void *>(kern), (int)smem);
     if (e != hipSuccess) return e;
@@ -284,159 +327,165 @@ hipError_t launch_cfg(const uint16_t *A, const uint16_t *W, const float *bias, c
     return hipGetLastError();
 }
 
-template <int BM, int BN, int BK_, int STAGES, int WM, int WN>
+template <int BM, int BN, int STAGES, int WM, int WN>
 hipError_t launch_epi(const uint16_t *A, const uint16_t *W, const float *bias, const float *resid,
-                      void *C, int M, int N, int K, int epi, hipStream_t s)
+                      void *C, int M, int N, int K, int splits, int epi, hipStream_t s)
 {
     switch (epi) {
-    case EPI_BIAS: return launch_cfg<BM, BN, BK_, STAGES, WM, WN, EPI_BIAS>(A, W, bias, resid, C, M, N, K, 1, s);
-    case EPI_BIAS_GELU: return launch_cfg<BM, BN, BK_, STAGES, WM, WN, EPI_BIAS_GELU>(A, W, bias, resid, C, M, N, K, 1, s);
-    case EPI_BIAS_RESID: return launch_cfg<BM, BN, BK_, STAGES, WM, WN, EPI_BIAS_RESID>(A, W, bias, resid, C, M, N, K, 1, s);
+    case EPI_BIAS: return launch_cfg<BM, BN, STAGES, WM, WN, EPI_BIAS>(A, W, bias, resid, C, M, N, K, 1, s);
+    case EPI_BIAS_GELU: return launch_cfg<BM, BN, STAGES, WM, WN, EPI_BIAS_GELU>(A, W, bias, resid, C, M, N, K, 1, s);
+    case EPI_BIAS_RESID: return launch_cfg<BM, BN, STAGES, WM, WN, EPI_BIAS_RESID>(A, W, bias, resid, C, M, N, K, 1, s);
+    case EPI_PARTIAL: return launch_cfg<BM, BN, STAGES, WM, WN, EPI_PARTIAL>(A, W, bias, resid, C, M, N, K, splits, s);
     }
     return hipErrorInvalidValue;
 }
 
-}  // namespace
+// The tile shapes of the one-tile-per-workgroup kernel, and what a launch costs in microseconds: `base` once,
+// `round` per workgroup one after the other on a compute unit (prologue and epilogue), `step` per 64-deep K step of
+// a workgroup that has a compute unit to itself, `step2` of two that share one (shapes whose LDS lets two fit), and
+// US_PER_MB for what the epilogue moves.  A least-squares fit to about 4000 launches (D = 192 to 1280, K = 192 to
+// 5120, 197 to 16448 rows, all epilogues, cut and uncut) on one MI355X: 3 to 8 % off a launch, and over the 390
+// uncut problems of the sweep the shape with the least modelled cost is within 0.5 % of the fastest one on average.
+//   Small tiles win while they leave no unit without work and the chain of K steps is the launch (a 64-deep step of
+// 64 x 64 costs 0.23 us, of 256 x 256 1.1 us); large ones once L2 -> LDS bandwidth is the bound (bytes per flop
+// fall with the tile's edge).  In a stage, against the
+// 64 x 64, 64 x 128 and 128 x 128 tiles of four waves and the persistent kernel alone: second MLP layer of
+// ViT-Large at 6304 rows 67.5 -> 62 us, q|k|v of ViT-Large at 3152 rows 32.1 -> 25.2, first MLP layer of ViT-Base
+// at 1576 rows 17.3 -> 14.3.
+struct TileShape { int bm, bn, per_cu; double base, round, step, step2; };
+constexpr TileShape TILES[] = {
+    {64, 64, 2, 2.2, 0.50, 0.23, 0.365},
+    {64, 128, 2, 2.7, 0.50, 0.315, 0.56},
+    {128, 128, 1, 1.8, 1.95, 0.42, 0.0},
+    {192, 128, 1, 1.7, 2.7, 0.54, 0.0},
+    {256, 128, 1, 1.5, 3.6, 0.65, 0.0},
+    {192, 256, 1, 1.5, 4.3, 0.96, 0.0},
+    {256, 192, 1, 1.7, 4.2, 0.94, 0.0},
+    {256, 256, 1, 1.0, 6.5, 1.11, 0.0},
+    {128, 128, 2, 2.6, 0.55, 0.60, 0.80},      // two stages, four waves: for more tiles than units
+};
+constexpr int N_TILES = sizeof(TILES) / sizeof(TILES[0]);
+constexpr double US_PER_MB = 0.16;
 
-// The small-problem kernel, one tile per workgroup, 4 waves, K step 64, in four shapes.  A launch that
-// cannot fill the chip is bound by the latency of its loads, one K step after the other, so where 64 x 64
-// tiles still give every compute unit at most one workgroup they are used with all of the unit's LDS in
-// flight: four stages of K steps of 128 (half the barriers of a step of 64: ViT-Large at micro-batch 1
-// 53.8 -> 50.2 us per layer), or eight stages of 64 when K is not a multiple of 128; ViT-Large at
-// micro-batch 1, 107 -> 65 us per layer against 128 x 128 tiles only.  Up to two such
-// workgroups per compute unit: four stages each.  Past that, 64 x 128 tiles with three stages while they
-// fit two per compute unit (128 x 128 tiles would leave a third of the units idle there: ViT-Large at
-// micro-batch 4, 80 -> 74 us per layer).  Everything else runs 128 x 128 tiles with two stages, two
-// workgroups per compute unit (four stages and one workgroup per unit were slower there: the second
-// workgroup hides more than the deeper prefetch).
-hipError_t ep_bf16_gemm_small(const uint16_t *A, const uint16_t *W, const float *bias, const float *resid,
-                              void *C, int64_t M, int N, int K, int epi, hipStream_t s)
+hipError_t launch_tile(int tile, const uint16_t *A, const uint16_t *W, const float *bias, const float *resid, void *C,
+                       int M, int N, int K, int splits, int epi, hipStream_t s)
 {
-    if (M <= 0 || N <= 0) return hipSuccess;
-    if (K <= 0 || K % 64 != 0 || N % 4 != 0) return hipErrorInvalidValue;
-    // byte offsets inside the kernel are 32-bit
-    if (M * (int64_t)K * 2 >= 0x7FFFFFF0ll || (int64_t)N * K * 2 >= 0x7FFFFFF0ll || M * (int64_t)N >= (1ll << 31))
-        return hipErrorInvalidValue;
-    if (epi == EPI_BIAS_RESID && !resid) return hipErrorInvalidValue;
-    int cus = 0;
-    const hipError_t e = ep_device_cu_count(&cus);
-    if (e != hipSuccess) return e;
-    const int64_t t64 = ((M + 63) / 64) * ((N + 63) / 64);
-    if (t64 <= cus && K % 128 == 0) return launch_epi<64, 64, 128, 4, 2, 2>(A, W, bias, resid, C, (int)M, N, K, epi, s);
-    if (t64 <= cus) return launch_epi<64, 64, 64, 8, 2, 2>(A, W, bias, resid, C, (int)M, N, K, epi, s);
-    if (t64 <= 2 * cus) return launch_epi<64, 64, 64, 4, 2, 2>(A, W, bias, resid, C, (int)M, N, K, epi, s);
-    const int64_t t64x128 = ((M + 63) / 64) * ((N + 127) / 128);
-    if (t64x128 <= 2 * cus) return launch_epi<64, 128, 64, 3, 2, 2>(A, W, bias, resid, C, (int)M, N, K, epi, s);
-    return launch_epi<128, 128, 64, 2, 2, 2>(A, W, bias, resid, C, (int)M, N, K, epi, s);
+    switch (tile) {
+    case 0: return launch_epi<64, 64, 4, 2, 2>(A, W, bias, resid, C, M, N, K, splits, epi, s);
+    case 1: return launch_epi<64, 128, 3, 2, 2>(A, W, bias, resid, C, M, N, K, splits, epi, s);
+    case 2: return launch_epi<128, 128, 3, 2, 4>(A, W, bias, resid, C, M, N, K, splits, epi, s);
+    case 3: return launch_epi<192, 128, 3, 4, 2>(A, W, bias, resid, C, M, N, K, splits, epi, s);
+    case 4: return launch_epi<256, 128, 3, 4, 2>(A, W, bias, resid, C, M, N, K, splits, epi, s);
+    case 5: return launch_epi<192, 256, 2, 2, 4>(A, W, bias, resid, C, M, N, K, splits, epi, s);
+    case 6: return launch_epi<256, 192, 2, 4, 2>(A, W, bias, resid, C, M, N, K, splits, epi, s);
+    case 7: return launch_epi<256, 256, 2, 2, 4>(A, W, bias, resid, C, M, N, K, splits, epi, s);
+    case 8: return launch_epi<128, 128, 2, 2, 2>(A, W, bias, resid, C, M, N, K, splits, epi, s);
+    }
+    return hipErrorInvalidValue;
 }
 
-// The same kernel with K cut into `splits` ranges, one workgroup per (range, tile): part[r][m][n] is the
-// bare fp32 sum over range r.  For dense layers with few tiles and a long K (the second MLP layer at small
-// micro-batches: ViT-Large at micro-batch 1 is 64 tiles of 64 K steps), where the chain of K steps of a
-// single workgroup is the whole launch time.  Whoever consumes `part` adds the ranges in index order, so
-// the result does not depend on which workgroup finishes first.
-hipError_t ep_bf16_gemm_partial(const uint16_t *A, const uint16_t *W, float *part, int64_t M, int N, int K,
-                                int splits, hipStream_t s)
+// modelled time of a launch over `splits` ranges of K, without what its epilogue moves
+double tile_us(const TileShape &t, int64_t M, int N, int K, int splits, int cus)
 {
-    if (M <= 0 || N <= 0) return hipSuccess;
-    if (splits < 1 || K <= 0 || K % (64 * splits) != 0 || N % 4 != 0) return hipErrorInvalidValue;
-    if (M * (int64_t)K * 2 >= 0x7FFFFFF0ll || (int64_t)N * K * 2 >= 0x7FFFFFF0ll || M * (int64_t)N >= (1ll << 31))
-        return hipErrorInvalidValue;
-    int cus = 0;
-    const hipError_t e = ep_device_cu_count(&cus);
-    if (e != hipSuccess) return e;
-    const int64_t w64 = ((M + 63) / 64) * ((N + 63) / 64) * splits;
-    if (w64 <= cus && K % (128 * splits) == 0)
-        return launch_cfg<64, 64, 128, 4, 2, 2, EPI_PARTIAL>(A, W, nullptr, nullptr, part, (int)M, N, K, splits, s);
-    if (w64 <= cus)
-        return launch_cfg<64, 64, 64, 8, 2, 2, EPI_PARTIAL>(A, W, nullptr, nullptr, part, (int)M, N, K, splits, s);
-    if (w64 <= 2 * cus)
-        return launch_cfg<64, 64, 64, 4, 2, 2, EPI_PARTIAL>(A, W, nullptr, nullptr, part, (int)M, N, K, splits, s);
-    return launch_cfg<128, 128, 64, 2, 2, 2, EPI_PARTIAL>(A, W, nullptr, nullptr, part, (int)M, N, K, splits, s);
+    const int64_t wgs = ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn) * splits;
+    const int steps = K / splits / BK;
+    const int64_t slots = (int64_t)cus * t.per_cu;
+    int64_t shared = t.per_cu == 2 ? wgs / slots : 0;               // rounds with two workgroups on a unit
+    int64_t alone = t.per_cu == 2 ? 0 : (wgs + slots - 1) / slots;  // rounds with one
+    if (t.per_cu == 2 && wgs % slots) (wgs % slots > cus ? shared : alone) += 1;
+    return t.base + (double)(alone + 2 * shared) * t.round + steps * ((double)alone * t.step + (double)shared * t.step2);
 }
 
-namespace {
+struct TileChoice { int tile; double us; };
 
-// How ep_bf16_gemm cuts the problem: the persistent kernel with tile width bn walks the tiles
-// of rows [0, m_main) and computes rows [m_main, M) in its tail phase (bn = 0: the
-// one-tile-per-workgroup kernel takes all rows).  Either way a dense layer is one launch.
-struct GemmPlan { int64_t m_main; int bn; };
-
-// Cost of the tail phase in the units of ep_bf16_gemm_persistent_cost (a round of 256 x bn tiles
-// costs bn): a round of 64 x 32 tiles over the compute units takes about a tenth of a round of
-// 256 x 320 tiles of the same K (3-4 us against 36 us at K = 1280).
-int64_t tail_cost(int64_t tail_rows, int N)
+TileChoice best_tile(int64_t M, int N, int K, int splits, int cus)
 {
-    const int64_t units = ((tail_rows + 63) / 64) * ((N + 31) / 32);
-    return (units + 255) / 256 * 32;
+    TileChoice best = {0, 0.0};
+    for (int i = 0; i < N_TILES; ++i) {
+        const double us = tile_us(TILES[i], M, N, K, splits, cus);
+        if (i == 0 || us < best.us) best = {i, us};
+    }
+    return best;
+}
+
+// what the kernels of this file index with 32 bits, and the shapes they take
+bool tiles_supported(int64_t M, int N, int K, int splits, bool bf16_out)
+{
+    return splits >= 1 && K > 0 && K % (BK * splits) == 0 && N % (bf16_out ? 8 : 4) == 0 &&
+           M * (int64_t)K * 2 < 0x7FFFFFF0ll && (int64_t)N * K * 2 < 0x7FFFFFF0ll && M * (int64_t)N < (1ll << 31);
+}
+
+// How ep_bf16_gemm cuts the problem: bn > 0, the persistent kernel with tile width bn walks the tiles of rows
+// [0, m_main) and computes rows [m_main, M) in its tail phase; bn = 0, the one-tile-per-workgroup kernel with
+// TILES[tile] takes all rows.  Either way a dense layer is one launch.
+struct GemmPlan { int64_t m_main; int bn; int tile; double us; };
+
+// The same model for the persistent kernel (256-row tiles, one workgroup per compute unit, no prologue between
+// tiles, so the whole cost of a round is its K steps).  A round of the tail phase's 64 x 32 tiles: 0.6 us and 0.035
+// per 64 of K.
+double persistent_us(int64_t m_main, int64_t M, int N, int K, int bn, int cus)
+{
+    const int64_t tiles = ((m_main + 255) / 256) * ((N + bn - 1) / bn);
+    const int steps = K / BK;
+    const int64_t tail_units = M > m_main ? ((M - m_main + 63) / 64) * ((N + 31) / 32) : 0;
+    return (bn == 320 ? 10.1 : 8.3) + (double)((tiles + cus - 1) / cus) * steps * (bn == 320 ? 1.49 : 1.30) +
+           (double)((tail_units + cus - 1) / cus) * (0.6 + 0.035 * steps);
 }
 
 GemmPlan plan_gemm(int64_t M, int N, int K)
 {
-    // The persistent kernel (256-row tiles, one workgroup per compute unit) when its tiles fill most of
-    // the chip, or already from about a hundred tiles on when the alternative, 128x128 tiles at two
-    // workgroups per compute unit, would need a second round (a launch of the persistent kernel takes
-    // about as long for 128 tiles as for 256, and that is less than two rounds of the small tiles:
-    // 130 against 153 us for the second MLP layer at 8224 rows).  The tile walk covers all rows, or stops
-    // one or two tile rows short of M and leaves the rest (at most 511 rows) to the tail phase of the
-    // same launch when that saves a round of tiles: a round of the narrow tail tiles is an order of
-    // magnitude cheaper.  Otherwise the 128x128 tiles, which quantise better on small micro-batches.
-    if (ep_bf16_gemm_persistent_supported(M, N, K)) {
-        const int64_t small_tiles = ((M + 127) / 128) * ((N + 127) / 128);
-        const int64_t min_tiles = small_tiles <= 2 * (int64_t)ep_bf16_gemm_persistent_workgroups() ? 192 : 96;
-        int bn_all = 0;
-        const int64_t cost_all = ep_bf16_gemm_persistent_cost(M, N, &bn_all);
-        const int64_t tiles_all = ((M + 255) / 256) * ((N + bn_all - 1) / bn_all);
-        GemmPlan best = {M, tiles_all >= min_tiles ? bn_all : 0};
-        int64_t best_cost = tiles_all >= min_tiles ? cost_all : INT64_MAX;
+    // The persistent kernel's tile walk covers all rows, or stops one or two tile rows short of M and leaves the
+    // rest (at most 511 rows) to the tail phase of the same launch when that saves a round of tiles: a round of
+    // the narrow tail tiles is an order of magnitude cheaper.
+    const int cus = ep_bf16_gemm_persistent_workgroups();
+    const TileChoice t = best_tile(M, N, K, 1, cus);
+    GemmPlan best = {M, 0, t.tile, t.us};
+    if (!ep_bf16_gemm_persistent_supported(M, N, K)) return best;
+    for (int bn : {320, 256}) {
+        const double all = persistent_us(M, M, N, K, bn, cus);
+        if (all < best.us) best = {M, bn, 0, all};
         for (int64_t m_main = M / 256 * 256; m_main > 0 && M - m_main < 512; m_main -= 256) {
-            const int64_t tail = M - m_main;
-            if (tail == 0 || !ep_bf16_gemm_skinny_supported(tail, N, K)) continue;
-            int bn_main = 0;
-            const int64_t cost = ep_bf16_gemm_persistent_cost(m_main, N, &bn_main) + tail_cost(tail, N);
-            const int64_t tiles_main = (m_main / 256) * ((N + bn_main - 1) / bn_main);
-            if (tiles_main >= min_tiles && cost < best_cost) { best = {m_main, bn_main}; best_cost = cost; }
+            if (m_main == M || !ep_bf16_gemm_skinny_supported(M - m_main, N, K)) continue;
+            const double us = persistent_us(m_main, M, N, K, bn, cus);
+            if (us < best.us) best = {m_main, bn, 0, us};
         }
-        if (best.bn) return best;
     }
-    return {M, 0};
+    return best;
 }
 
 }  // namespace
 
-// Into how many K ranges a dense layer with fp32 output is cut (1: not at all).  Only problems that the
-// one-tile-per-workgroup kernel runs.  Such a launch is a chain of K steps per workgroup, and what a step costs
-// depends on the shape class the launch falls into (measured on ViT-Base/Large/Huge second MLP layers at
-// micro-batches 1 to 16, microseconds per 64-deep step): 64 x 64 tiles with one workgroup per compute unit 0.28,
-// with two 0.40; 128 x 128 tiles 0.7 while they leave compute units idle, 1.0 when they double up.  Cutting K
-// into sp ranges divides the chain by sp, may move the launch to a dearer class, and makes the consumer of the
-// sums read sp x M x N floats more (priced at 3 TB/s: they are spread over a few hundred waves).  The cheapest
-// sp of 1, 2, 4, 8 wins; every range keeps at least eight K steps and the workgroups at most two per compute unit.
+// K cut into `splits` ranges, one workgroup per (range, tile): part[r][m][n] is the bare fp32 sum over range r.
+// For dense layers with few tiles and a long K (the second MLP layer at small micro-batches: ViT-Large at
+// micro-batch 1 is 64 tiles of 64 K steps), where the chain of K steps of a single workgroup is the whole launch
+// time.  Whoever consumes `part` adds the ranges in index order, so the result does not depend on which workgroup
+// finishes first.
+hipError_t ep_bf16_gemm_partial(const uint16_t *A, const uint16_t *W, float *part, int64_t M, int N, int K,
+                                int splits, hipStream_t s)
+{
+    if (M <= 0 || N <= 0) return hipSuccess;
+    if (!tiles_supported(M, N, K, splits, false)) return hipErrorInvalidValue;
+    const TileChoice t = best_tile(M, N, K, splits, ep_bf16_gemm_persistent_workgroups());
+    return launch_tile(t.tile, A, W, nullptr, nullptr, part, (int)M, N, K, splits, EPI_PARTIAL, s);
+}
+
+// Into how many K ranges a dense layer with fp32 output is cut (1: not at all): the least modelled cost, the
+// consumer of the sums included, which reads splits x M x N floats more and writes M x N back (1 us and 5.5 TB/s:
+// first LayerNorm of ViT-Large at 3152 rows 5.4 -> 10.5 us with two ranges).  Every range keeps at least eight K
+// steps.  (Three ranges would be chosen for ViT-Base at 1576 rows and gain nothing: 201.5 us a stage of three layers
+// either way, and the sum after a stage's last layer is one launch more.)
 int ep_bf16_gemm_splits(int64_t M, int N, int K)
 {
-    if (M <= 0 || N <= 0 || K <= 0 || K % 64 != 0) return 1;
-    if (plan_gemm(M, N, K).bn) return 1;
-    int cus = 0;
-    if (ep_device_cu_count(&cus) != hipSuccess) return 1;
-    const int64_t t64 = ((M + 63) / 64) * ((N + 63) / 64), t128 = ((M + 127) / 128) * ((N + 127) / 128);
-    const int steps = K / 64;
-    auto cost_us = [&](int sp) -> double {
-        double step;
-        if (t64 * sp <= cus) step = 0.28;
-        else if (t64 * sp <= 2 * cus) step = 0.40;
-        else if (t128 * sp <= cus) step = 0.7;
-        else if (t128 * sp <= 2 * cus) step = 1.0;
-        else step = 1.0 * (double)((t128 * sp + 2 * cus - 1) / (2 * cus));      // rounds of workgroups (sp == 1 only)
-        const double sums = sp > 1 ? (double)sp * (double)M * N * 4.0 / 3.0e6 : 0.0;
-        return (double)(steps / sp) * step + sums;
-    };
+    if (M <= 0 || N <= 0 || K <= 0 || K % BK != 0) return 1;
+    const GemmPlan whole = plan_gemm(M, N, K);
+    const int cus = ep_bf16_gemm_persistent_workgroups();
+    const double mb = (double)M * N * 4e-6;
     int best = 1;
-    double best_cost = cost_us(1);
-    for (int sp = 2; sp <= 8; sp *= 2) {
-        if (steps % sp != 0 || steps / sp < 8) break;
-        if ((t64 * sp <= 2 * cus ? t64 : t128) * sp > 2 * cus) break;
-        const double c = cost_us(sp);
-        if (c < best_cost - 1.0) { best = sp; best_cost = c; }      // a microsecond is within the noise of the model
+    double best_us = whole.us + US_PER_MB * 2 * mb - 0.5;         // half a microsecond is within the noise of the model
+    for (int sp : {2, 4, 8}) {
+        if (K % (BK * sp) != 0 || K / BK / sp < 8) continue;
+        const double us = best_tile(M, N, K, sp, cus).us + US_PER_MB * sp * mb + 1.0 + (sp + 1) * mb / 5.5;
+        if (us < best_us) { best = sp; best_us = us; }
     }
     return best;
 }
@@ -450,9 +499,12 @@ int64_t ep_bf16_gemm_main_rows(int64_t M, int N, int K)
 hipError_t ep_bf16_gemm(const uint16_t *A, const uint16_t *W, const float *bias, const float *resid,
                         void *C, int64_t M, int N, int K, int epi, hipEvent_t after_main, hipStream_t s)
 {
+    if (M <= 0 || N <= 0) return hipSuccess;
+    if (!tiles_supported(M, N, K, 1, epi != EPI_BIAS_RESID)) return hipErrorInvalidValue;
+    if (epi == EPI_BIAS_RESID && !resid) return hipErrorInvalidValue;
     const GemmPlan p = plan_gemm(M, N, K);
     hipError_t e = p.bn ? ep_bf16_gemm_persistent(A, W, bias, resid, C, M, p.m_main, N, K, epi, p.bn, true, s)
-                        : ep_bf16_gemm_small(A, W, bias, resid, C, M, N, K, epi, s);
+                        : launch_tile(p.tile, A, W, bias, resid, C, (int)M, N, K, 1, epi, s);
     if (e != hipSuccess) return e;
     if (after_main) e = hipEventRecord(after_main, s);
     return e;

@@ -4,8 +4,8 @@
 //   C[M, N] = A[M, K] . W[N, K]^T + bias[N]   (+ erf GELU | + fp32 residual)
 //
 // One workgroup per compute unit stays resident and walks a static list of
-// 256 x BN output tiles (BN = 256 or 320, chosen per problem so that the tile
-// count is a multiple of the number of compute units where possible); the K
+// 256 x BN output tiles (BN = 256 or 320, chosen per problem by the dispatcher's
+// cost model); the K
 // loop of consecutive tiles forms one continuous software pipeline, so the
 // first K step of the next tile is already in LDS when a tile is stored.
 //
@@ -531,14 +531,6 @@ hipError_t launch_tile(const uint16_t *A, const uint16_t *W, const float *bias, 
     return hipErrorInvalidValue;
 }
 
-// Rounds of tiles over `cus` compute units, weighted by the tile width: the cost of a tile
-// shape for this problem.
-int64_t tile_cost(int64_t rows, int N, int bn, int cus)
-{
-    const int64_t tiles = ((rows + BM - 1) / BM) * ((N + bn - 1) / bn);
-    return (tiles + cus - 1) / cus * bn;
-}
-
 }  // namespace
 
 hipError_t ep_bf16_gemm_persistent_clock(double *shader_mhz, double *seconds)
@@ -565,15 +557,7 @@ int ep_bf16_gemm_persistent_workgroups()
     return resident_grid(&g) == hipSuccess ? g : 256;
 }
 
-int64_t ep_bf16_gemm_persistent_cost(int64_t rows, int N, int *tile_bn)
-{
-    const int cus = ep_bf16_gemm_persistent_workgroups();
-    const int64_t c256 = tile_cost(rows, N, 256, cus), c320 = tile_cost(rows, N, 320, cus);
-    if (tile_bn) *tile_bn = c320 <= c256 ? 320 : 256;      // a tie goes to the wider tile (fewer bytes loaded per flop)
-    return c320 <= c256 ? c320 : c256;
-}
-
-// tile_bn: 0 = choose, else 256 or 320.  m_rows <= M: the tile walk covers rows [0, m_rows);
+// tile_bn: 256 or 320.  m_rows <= M: the tile walk covers rows [0, m_rows);
 // fuse_tail: rows [m_rows, M) are computed by the same launch as 64 x 32 tiles.
 hipError_t ep_bf16_gemm_persistent(const uint16_t *A, const uint16_t *W, const float *bias, const float *resid,
                                    void *C, int64_t M, int64_t m_rows, int N, int K, int epi, int tile_bn,
@@ -583,7 +567,6 @@ hipError_t ep_bf16_gemm_persistent(const uint16_t *A, const uint16_t *W, const f
     if (epi == EPI_BIAS_RESID && !resid) return hipErrorInvalidValue;
     if (m_rows == 0) return hipSuccess;
     const int tail = fuse_tail ? (int)(M - m_rows) : 0;
-    if (tile_bn == 0) (void)ep_bf16_gemm_persistent_cost(m_rows, N, &tile_bn);
     if (tile_bn == 320) return launch_tile<Tile320>(A, W, bias, resid, C, (int)M, (int)m_rows, N, K, epi, tail, s);
     if (tile_bn == 256) return launch_tile<Tile256>(A, W, bias, resid, C, (int)M, (int)m_rows, N, K, epi, tail, s);
     return hipErrorInvalidValue;

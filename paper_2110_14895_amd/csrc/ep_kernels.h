@@ -56,12 +56,7 @@ bool ep_bf16_attention_supported(int T, int d_head);
 // deterministic fill used by the profiler (values in [-1, 1])
 hipError_t ep_fill_pattern(float *x, int64_t n, hipStream_t s);
 
-// one tile per workgroup (64 x 64, 64 x 128 or 128 x 128 by the size of the problem): what is too small for the
-// persistent kernel
-hipError_t ep_bf16_gemm_small(const uint16_t *A, const uint16_t *W, const float *bias, const float *resid,
-                              void *C, int64_t M, int N, int K, int epi, hipStream_t s);
-
-// the same kernel with K cut into `splits` ranges: part[r] = A[:, range r] . W[:, range r]^T, fp32 [splits, M, N];
+// the one-tile-per-workgroup kernel with K cut into `splits` ranges: part[r] = A[:, range r] . W[:, range r]^T, fp32 [splits, M, N];
 // K % (64 * splits) == 0
 hipError_t ep_bf16_gemm_partial(const uint16_t *A, const uint16_t *W, float *part, int64_t M, int N, int K,
                                 int splits, hipStream_t s);
@@ -69,12 +64,9 @@ hipError_t ep_bf16_gemm_partial(const uint16_t *A, const uint16_t *W, float *par
 int ep_bf16_gemm_splits(int64_t M, int N, int K);
 
 // persistent kernel for large problems (ep_gemm_bf16_persist.hip): 256 x BN tiles, BN = tile_bn
-// (256 or 320; 0 = pick the one with fewer weighted rounds).  The tile walk covers rows
+// (256 or 320).  The tile walk covers rows
 // [0, m_rows); with fuse_tail the same launch also computes rows [m_rows, M) as 64 x 32 tiles.
 bool ep_bf16_gemm_persistent_supported(int64_t M, int N, int K);
-// rounds of tiles over the compute units times the tile width (lower is better); writes the
-// tile width it would pick
-int64_t ep_bf16_gemm_persistent_cost(int64_t rows, int N, int *tile_bn);
 // resident workgroups of a launch on the current device: one per compute unit (256 if the device cannot be asked)
 int ep_bf16_gemm_persistent_workgroups();
 hipError_t ep_bf16_gemm_persistent(const uint16_t *A, const uint16_t *W, const float *bias,
