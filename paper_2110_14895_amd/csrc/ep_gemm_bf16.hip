@@ -56,6 +56,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 constexpr int NUM_XCD = 8;
 constexpr int GROUP_M = 4;
 constexpr int BK = 64;                               // K step
+constexpr int PAST_END = 0x40000000;                 // at least the bytes of a tile's rows of C: 256 rows, N < 2^20
 
 
 #if defined(__HIP_DEVICE_COMPILE__)   // buffer-resource builtins exist only in the device pass
@@ -165,6 +166,21 @@ __global__ __launch_bounds__(WM *WN * 64, (WM * WN <= 4 && STAGES * (BM + BN) * 
     // first of the four columns a lane's accumulators of fragment ni belong to
     auto col = [&](int ni) { return n0 + wn0 + (PAIRED ? (ni >> 1) * 32 + g4 * 8 + (ni & 1) * 4 : ni * 16 + g4 * 4); };
 
+    // The tile's rows of C, and of the residual, are a buffer that ends behind row M - 1: rows past it and columns past
+    // N (an offset past any end) are not stored and read as zeros, without a branch (a branch per access had the
+    // compiler wait for all earlier stores at each of them).
+    constexpr int ESZ = EPI == EPI_BIAS_RESID || EPI == EPI_PARTIAL ? 4 : 2;
+    const uint32_t tile_bytes = (uint32_t)(min(BM, M - m0) * N * ESZ);
+    const __amdgpu_buffer_rsrc_t c_rs =
+        make_rsrc(reinterpret_cast<const char *>(Cout) + ((size_t)split * M + m0) * N * ESZ, tile_bytes);
+    const __amdgpu_buffer_rsrc_t r_rs = EPI == EPI_BIAS_RESID ? make_rsrc(resid + (size_t)m0 * N, tile_bytes) : c_rs;
+    auto offset = [&](int ni, int mi) {                // bytes from the tile's first row; a column past N: beyond any end
+        const int n = col(ni);
+        int past = n < N ? 0 : PAST_END;
+        asm volatile("" : "+v"(past));                 // a value, not a reason to branch
+        return ((wm0 + mi * 16 + l15) * N + n) * ESZ + past;
+    };
+
     f32x4 acc[NI][MI];
 #pragma unroll
     for (int ni = 0; ni < NI; ++ni)
@@ -205,13 +221,12 @@ __global__ __launch_bounds__(WM *WN * 64, (WM * WN <= 4 && STAGES * (BM + BN) * 
     // with one more trip to memory.  Loads return in order, so nothing here makes a counted wait below too short.
     // The bias goes ahead of the first panel loads, the residual (where a few registers hold it) behind them:
     // 0.3 us less per launch than ahead of them; with 16 accumulators a wave it cost 1 to 1.5 us instead.
-    float4 bias_r[NI], res_r[PRE_RES ? NI : 1][PRE_RES ? MI : 1];
+    f32x4 bias_r[NI], res_r[PRE_RES ? NI : 1][PRE_RES ? MI : 1];
     if (EPI != EPI_PARTIAL) {
+        const __amdgpu_buffer_rsrc_t b_rs = make_rsrc(bias, (uint32_t)N * 4);
 #pragma unroll
-        for (int ni = 0; ni < NI; ++ni) {
-            const int n = col(ni);
-            bias_r[ni] = n < N ? *reinterpret_cast<const float4 *>(bias + n) : make_float4(0.f, 0.f, 0.f, 0.f);
-        }
+        for (int ni = 0; ni < NI; ++ni)
+            bias_r[ni] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(b_rs, col(ni) * 4, 0, 0));
     }
 #pragma unroll
     for (int st = 0; st < STAGES; ++st)
@@ -221,11 +236,8 @@ __global__ __launch_bounds__(WM *WN * 64, (WM * WN <= 4 && STAGES * (BM + BN) * 
 #pragma unroll
         for (int ni = 0; ni < NI; ++ni)
 #pragma unroll
-            for (int mi = 0; mi < MI; ++mi) {
-                const int n = col(ni), m = m0 + wm0 + mi * 16 + l15;
-                res_r[ni][mi] = (m < M && n < N) ? *reinterpret_cast<const float4 *>(resid + (size_t)m * N + n)
-                                                 : make_float4(0.f, 0.f, 0.f, 0.f);
-            }
+            for (int mi = 0; mi < MI; ++mi)
+                res_r[ni][mi] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r_rs, offset(ni, mi), 0, 0));
     }
     EP_WAIT_VMCNT((STAGES - 1) * LD);
     __builtin_amdgcn_s_barrier();
@@ -266,46 +278,54 @@ __global__ __launch_bounds__(WM *WN * 64, (WM * WN <= 4 && STAGES * (BM + BN) * 
     }
     EP_WAIT_VMCNT(0);                          // drain the (empty) tail loads before LDS goes away
 
-    // ---- epilogue.  acc[ni][mi][i]: n = col(ni) + i, m = mi*16 + lane%16.  (Stores that bypass the caches
-    // shorten a launch by 0.3 to 1.3 us and cost its reader more: ViT-Large at 6304 rows 1318 -> 1344 us a stage.)
+    // ---- epilogue.  acc[ni][mi][i]: n = col(ni) + i, m = mi*16 + lane%16.  (Stores that bypass the caches shorten a
+    // launch by 0.3 to 1.3 us and cost its reader more: ViT-Large at 6304 rows 1318 -> 1344 us a stage.)
+    // a residual that was not fetched ahead: half of the wave's rows at once, the next ones as rows are stored (six
+    // ViT-Large layers on 32 images, whose two residual layers run 256 x 128 tiles: 1279 -> 1264 us against one
+    // 16-byte piece at a time, each behind the store of the one before)
+    constexpr bool LATE_RES = EPI == EPI_BIAS_RESID && !PRE_RES;
+    constexpr int PF = (MI + 1) / 2;
+    f32x4 late[LATE_RES ? PF : 1][LATE_RES ? NI : 1];
+    auto fetch_row = [&](int mi) {
+#pragma unroll
+        for (int ni = 0; ni < NI; ++ni)
+            late[LATE_RES ? mi % PF : 0][LATE_RES ? ni : 0] =
+                __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r_rs, offset(ni, mi), 0, 0));
+    };
+    if (LATE_RES) {
+#pragma unroll
+        for (int mi = 0; mi < PF; ++mi) fetch_row(mi);
+        EP_SCHED_FENCE();
+    }
 #pragma unroll
     for (int mi = 0; mi < MI; ++mi) {
-        const int m = m0 + wm0 + mi * 16 + l15;
-        if (m >= M) continue;
         uint2 even;                                    // PAIRED: the first four of a lane's eight columns
 #pragma unroll
         for (int ni = 0; ni < NI; ++ni) {
-            const int n = col(ni);
-            if (n >= N) continue;
-            const f32x4 c = acc[ni][mi];
+            f32x4 c = acc[ni][mi];
             if (EPI == EPI_PARTIAL) {                  // the bare sum over this K range, fp32, range-major
-                float *o = reinterpret_cast<float *>(Cout) + ((size_t)split * M + m) * N + n;
-                *reinterpret_cast<f32x4 *>(o) = c;
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, c), c_rs, offset(ni, mi), 0, 0);
                 continue;
             }
-            const float4 bb = bias_r[ni];
-            float v0 = c[0] + bb.x, v1 = c[1] + bb.y, v2 = c[2] + bb.z, v3 = c[3] + bb.w;
-            const size_t off = (size_t)m * N + n;
+            c += bias_r[ni];
             if (EPI == EPI_BIAS_RESID) {
-                const float4 r = PRE_RES ? res_r[PRE_RES ? ni : 0][PRE_RES ? mi : 0]
-                                         : *reinterpret_cast<const float4 *>(resid + off);
-                const f32x4 o = {v0 + r.x, v1 + r.y, v2 + r.z, v3 + r.w};
-                *reinterpret_cast<f32x4 *>(reinterpret_cast<float *>(Cout) + off) = o;
+                c += LATE_RES ? late[LATE_RES ? mi % PF : 0][LATE_RES ? ni : 0] : res_r[PRE_RES ? ni : 0][PRE_RES ? mi : 0];
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, c), c_rs, offset(ni, mi), 0, 0);
                 continue;
             }
             if (EPI == EPI_BIAS_GELU) {
-                v0 = gelu_erf(v0); v1 = gelu_erf(v1); v2 = gelu_erf(v2); v3 = gelu_erf(v3);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) c[i] = gelu_erf(c[i]);
             }
-            const uint2 o = make_uint2(pack_bf16x2(v0, v1), pack_bf16x2(v2, v3));
-            if (!PAIRED) {
-                *reinterpret_cast<uint2 *>(reinterpret_cast<uint16_t *>(Cout) + off) = o;
-            } else if ((ni & 1) == 0) {
+            const uint2 o = make_uint2(pack_bf16x2(c[0], c[1]), pack_bf16x2(c[2], c[3]));
+            static_assert(PAIRED || ESZ == 4, "bf16 outputs leave in pairs of fragments");
+            if ((ni & 1) == 0)
                 even = o;
-            } else {
-                const u32x4 w = {even.x, even.y, o.x, o.y};
-                *reinterpret_cast<u32x4 *>(reinterpret_cast<uint16_t *>(Cout) + off - 4) = w;
-            }
+            else
+                __builtin_amdgcn_raw_buffer_store_b128(u32x4{even.x, even.y, o.x, o.y}, c_rs, offset(ni - 1, mi), 0, 0);
         }
+        if (LATE_RES && mi + PF < MI) fetch_row(mi + PF);
+        if (LATE_RES) EP_SCHED_FENCE();
     }
 #endif   // __HIP_DEVICE_COMPILE__
 }
@@ -411,7 +431,7 @@ TileChoice best_tile(int64_t M, int N, int K, int splits, int cus)
 // what the kernels of this file index with 32 bits, and the shapes they take
 bool tiles_supported(int64_t M, int N, int K, int splits, bool bf16_out)
 {
-    return splits >= 1 && K > 0 && K % (BK * splits) == 0 && N % (bf16_out ? 8 : 4) == 0 &&
+    return splits >= 1 && K > 0 && K % (BK * splits) == 0 && N % (bf16_out ? 8 : 4) == 0 && N < (1 << 20) &&
            M * (int64_t)K * 2 < 0x7FFFFFF0ll && (int64_t)N * K * 2 < 0x7FFFFFF0ll && M * (int64_t)N < (1ll << 31);
 }
 
