@@ -35,11 +35,13 @@ hipError_t ep_bf16_layernorm(const float *x, const float *g, const float *b, flo
 // part is [splits, rows, D] fp32; splits 2, 4 or 8.
 hipError_t ep_bf16_layernorm_sum(float *x, const float *part, int splits, const float *bias, const float *g,
                                  const float *b, float eps, uint16_t *y, int64_t rows, int D, hipStream_t s);
-// Only the sum: out = ((part[0] + ... + part[splits-1]) + bias) + resid, n = rows * D elements, D % 4 == 0
-// (out may alias resid).
-hipError_t ep_f32_residual_sum(const float *resid, const float *part, int splits, const float *bias, float *out,
-                               int64_t rows, int D, hipStream_t s);
-hipError_t ep_bf16_to_f32(const uint16_t *in, float *out, int64_t n, hipStream_t s);
+// The same for the first layer of a stage that takes bf16: x = in, widened, then as above.
+hipError_t ep_bf16_layernorm_widen(const uint16_t *in, float *x, const float *g, const float *b, float eps, uint16_t *y,
+                                   int64_t rows, int D, hipStream_t s);
+// Only the sum: out = ((part[0] + ... + part[splits-1]) + bias) + resid, n = rows * D elements, D % 4 == 0, as fp32
+// (then out may alias resid) or rounded to bf16.
+hipError_t ep_f32_residual_sum(const float *resid, const float *part, int splits, const float *bias, void *out,
+                               bool out_bf16, int64_t rows, int D, hipStream_t s);
 hipError_t ep_f32_to_bf16(const float *in, uint16_t *out, int64_t n, hipStream_t s);
 // A bf16 [M, K], W bf16 [N, K]; out bf16 (EPI_BIAS, EPI_BIAS_GELU) or fp32 (EPI_BIAS_RESID).
 // after_main: if non-null, recorded on s right after the launch (it covers the rows

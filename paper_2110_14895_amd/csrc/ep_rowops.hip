@@ -1,6 +1,7 @@
 // HBM-bound row kernels of the bf16 path: LayerNorm over the fp32 residual
 // stream producing the bf16 GEMM operand (paper section 2.1: the two layer
-// normalisations of a layer), and dtype conversion at the stage boundary.
+// normalisations of a layer), with the widening of a stage's bf16 input on the
+// way, and narrowing at the stage's end.
 //
 // LayerNorm: one wavefront per row, the whole row held in registers (float4
 // loads, D <= 64*4*MAXV), mean then centred variance (two passes over
@@ -37,10 +38,22 @@ __device__ inline float4 ranges_bias_resid(const float4 *part, size_t range_stri
     return make_float4(a.x + resid.x, a.y + resid.y, a.z + resid.z, a.w + resid.w);
 }
 
+// SUM: the rows come from bf16 `src` [rows, D] and are left in x as fp32 (the first layer of a stage)
+constexpr int WIDEN = -1;
+
+__device__ inline float4 widen4(uint2 p)
+{
+    return make_float4(__uint_as_float(p.x << 16), __uint_as_float(p.x & 0xFFFF0000u), __uint_as_float(p.y << 16),
+                       __uint_as_float(p.y & 0xFFFF0000u));
+}
+
 // NV = number of float4 per lane (D = 256 * NV exactly, or ragged when GUARD).  SUM > 0: x is first brought up to
-// date in place from the SUM K ranges of the dense layer before it (part [SUM, rows, D], bias), then normalised.
+// date in place from the SUM K ranges of the dense layer before it (src: fp32 [SUM, rows, D], bias), then normalised.
+// Bound by memory from a few thousand rows on (4.4 to 6 TB/s), by its launch below; so what else a row needs while it
+// passes is done here.  Widening a stage's bf16 input in a launch of its own cost 2 us a stage on 197 rows of 1024
+// and 4 us on 6304.
 template <int NV, bool GUARD, int SUM>
-__global__ __launch_bounds__(256) void ln_bf16_kernel(float *__restrict__ x, const float *__restrict__ part,
+__global__ __launch_bounds__(256) void ln_bf16_kernel(float *__restrict__ x, const void *__restrict__ src,
                                                       const float *__restrict__ bias,
                                                       const float *__restrict__ g,
                                                       const float *__restrict__ b, float eps,
@@ -57,10 +70,15 @@ __global__ __launch_bounds__(256) void ln_bf16_kernel(float *__restrict__ x, con
     for (int i = 0; i < NV; ++i) {
         const int c = lane + i * WAVE;
         if (!GUARD || c < nvec) {
-            v[i] = xr[c];
+            if (SUM == WIDEN) {
+                v[i] = widen4(reinterpret_cast<const uint2 *>(static_cast<const uint16_t *>(src) + row * D)[c]);
+                xr[c] = v[i];
+            } else {
+                v[i] = xr[c];
+            }
             if (SUM > 0) {
-                v[i] = ranges_bias_resid<SUM ? SUM : 1>(reinterpret_cast<const float4 *>(part + row * D) + c,
-                                                       (size_t)rows * D / 4, reinterpret_cast<const float4 *>(bias)[c], v[i]);
+                v[i] = ranges_bias_resid<SUM >= 1 ? SUM : 1>(reinterpret_cast<const float4 *>(static_cast<const float *>(src) + row * D) + c,
+                                                            (size_t)rows * D / 4, reinterpret_cast<const float4 *>(bias)[c], v[i]);
                 xr[c] = v[i];
             }
             s += (v[i].x + v[i].y) + (v[i].z + v[i].w);
@@ -95,30 +113,21 @@ __global__ __launch_bounds__(256) void ln_bf16_kernel(float *__restrict__ x, con
     }
 }
 
-template <int S>
+// OUT16: the sum leaves as bf16 (a stage's last layer handing over to the next stage)
+template <int S, bool OUT16>
 __global__ __launch_bounds__(256) void residual_sum_kernel(const float *resid, const float *__restrict__ part,
-                                                           const float *__restrict__ bias, float *out,
+                                                           const float *__restrict__ bias, void *out,
                                                            int64_t n4, int d4)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n4) return;
-    reinterpret_cast<float4 *>(out)[i] =
+    const float4 v =
         ranges_bias_resid<S>(reinterpret_cast<const float4 *>(part) + i, (size_t)n4,
                              reinterpret_cast<const float4 *>(bias)[i % d4], reinterpret_cast<const float4 *>(resid)[i]);
-}
-
-__global__ __launch_bounds__(256) void bf16_to_f32_kernel(const uint16_t *__restrict__ in,
-                                                          float *__restrict__ out, int64_t n4)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n4) return;
-    const uint2 p = reinterpret_cast<const uint2 *>(in)[i];
-    float4 o;
-    o.x = __uint_as_float(p.x << 16);
-    o.y = __uint_as_float(p.x & 0xFFFF0000u);
-    o.z = __uint_as_float(p.y << 16);
-    o.w = __uint_as_float(p.y & 0xFFFF0000u);
-    reinterpret_cast<float4 *>(out)[i] = o;
+    if (OUT16)
+        static_cast<uint2 *>(out)[i] = make_uint2(pack_bf16x2(v.x, v.y), pack_bf16x2(v.z, v.w));
+    else
+        static_cast<float4 *>(out)[i] = v;
 }
 
 __global__ __launch_bounds__(256) void f32_to_bf16_kernel(const float *__restrict__ in,
@@ -135,15 +144,16 @@ __global__ __launch_bounds__(256) void f32_to_bf16_kernel(const float *__restric
 
 // part == nullptr: plain LayerNorm of x (which is then only read)
 template <int NV>
-hipError_t launch_ln(float *x, const float *part, int splits, const float *bias, const float *g, const float *b,
+hipError_t launch_ln(float *x, const void *src, int mode, const float *bias, const float *g, const float *b,
                      float eps, uint16_t *y, int64_t rows, int D, hipStream_t s)
 {
     const unsigned grid = (unsigned)((rows + 3) / 4);
     const bool ragged = D != NV * 256;
 #define EP_LN_LAUNCH(GUARD, SUM) \
-    hipLaunchKernelGGL((ln_bf16_kernel<NV, GUARD, SUM>), dim3(grid), dim3(256), 0, s, x, part, bias, g, b, eps, y, rows, D)
+    hipLaunchKernelGGL((ln_bf16_kernel<NV, GUARD, SUM>), dim3(grid), dim3(256), 0, s, x, src, bias, g, b, eps, y, rows, D)
 #define EP_LN_LAUNCH_SUM(SUM) do { if (ragged) EP_LN_LAUNCH(true, SUM); else EP_LN_LAUNCH(false, SUM); } while (0)
-    switch (part ? splits : 0) {
+    switch (mode) {
+    case WIDEN: EP_LN_LAUNCH_SUM(WIDEN); break;
     case 0: EP_LN_LAUNCH_SUM(0); break;
     case 2: EP_LN_LAUNCH_SUM(2); break;
     case 4: EP_LN_LAUNCH_SUM(4); break;
@@ -155,21 +165,22 @@ hipError_t launch_ln(float *x, const float *part, int splits, const float *bias,
     return hipGetLastError();
 }
 
-hipError_t layernorm_any(float *x, const float *part, int splits, const float *bias, const float *g, const float *b,
+// mode: 0, WIDEN or the number of K ranges
+hipError_t layernorm_any(float *x, const void *src, int mode, const float *bias, const float *g, const float *b,
                          float eps, uint16_t *y, int64_t rows, int D, hipStream_t s)
 {
     if (rows <= 0) return hipSuccess;
     if (D % 4 != 0 || D <= 0 || D > 8 * 256) return hipErrorInvalidValue;
     const int nv = (D + 255) / 256;
     switch (nv) {
-    case 1: return launch_ln<1>(x, part, splits, bias, g, b, eps, y, rows, D, s);
-    case 2: return launch_ln<2>(x, part, splits, bias, g, b, eps, y, rows, D, s);
-    case 3: return launch_ln<3>(x, part, splits, bias, g, b, eps, y, rows, D, s);
-    case 4: return launch_ln<4>(x, part, splits, bias, g, b, eps, y, rows, D, s);
-    case 5: return launch_ln<5>(x, part, splits, bias, g, b, eps, y, rows, D, s);
-    case 6: return launch_ln<6>(x, part, splits, bias, g, b, eps, y, rows, D, s);
-    case 7: return launch_ln<7>(x, part, splits, bias, g, b, eps, y, rows, D, s);
-    default: return launch_ln<8>(x, part, splits, bias, g, b, eps, y, rows, D, s);
+    case 1: return launch_ln<1>(x, src, mode, bias, g, b, eps, y, rows, D, s);
+    case 2: return launch_ln<2>(x, src, mode, bias, g, b, eps, y, rows, D, s);
+    case 3: return launch_ln<3>(x, src, mode, bias, g, b, eps, y, rows, D, s);
+    case 4: return launch_ln<4>(x, src, mode, bias, g, b, eps, y, rows, D, s);
+    case 5: return launch_ln<5>(x, src, mode, bias, g, b, eps, y, rows, D, s);
+    case 6: return launch_ln<6>(x, src, mode, bias, g, b, eps, y, rows, D, s);
+    case 7: return launch_ln<7>(x, src, mode, bias, g, b, eps, y, rows, D, s);
+    default: return launch_ln<8>(x, src, mode, bias, g, b, eps, y, rows, D, s);
     }
 }
 
@@ -189,28 +200,31 @@ hipError_t ep_bf16_layernorm_sum(float *x, const float *part, int splits, const 
     return layernorm_any(x, part, splits, bias, g, b, eps, y, rows, D, s);
 }
 
-hipError_t ep_f32_residual_sum(const float *resid, const float *part, int splits, const float *bias, float *out,
-                               int64_t rows, int D, hipStream_t s)
+hipError_t ep_bf16_layernorm_widen(const uint16_t *in, float *x, const float *g, const float *b, float eps, uint16_t *y,
+                                   int64_t rows, int D, hipStream_t s)
+{
+    if (!in) return hipErrorInvalidValue;
+    return layernorm_any(x, in, WIDEN, nullptr, g, b, eps, y, rows, D, s);
+}
+
+hipError_t ep_f32_residual_sum(const float *resid, const float *part, int splits, const float *bias, void *out,
+                               bool out_bf16, int64_t rows, int D, hipStream_t s)
 {
     if (rows <= 0) return hipSuccess;
     if (!part || !bias || D <= 0 || D % 4 != 0) return hipErrorInvalidValue;
     const int64_t n4 = rows * D / 4;
     const dim3 grid((unsigned)((n4 + 255) / 256));
+#define EP_SUM_LAUNCH(S) do { if (out_bf16) EP_SUM_LAUNCH_AS(S, true); else EP_SUM_LAUNCH_AS(S, false); } while (0)
+#define EP_SUM_LAUNCH_AS(S, OUT16) \
+    hipLaunchKernelGGL((residual_sum_kernel<S, OUT16>), grid, dim3(256), 0, s, resid, part, bias, out, n4, D / 4)
     switch (splits) {
-    case 2: hipLaunchKernelGGL(residual_sum_kernel<2>, grid, dim3(256), 0, s, resid, part, bias, out, n4, D / 4); break;
-    case 4: hipLaunchKernelGGL(residual_sum_kernel<4>, grid, dim3(256), 0, s, resid, part, bias, out, n4, D / 4); break;
-    case 8: hipLaunchKernelGGL(residual_sum_kernel<8>, grid, dim3(256), 0, s, resid, part, bias, out, n4, D / 4); break;
+    case 2: EP_SUM_LAUNCH(2); break;
+    case 4: EP_SUM_LAUNCH(4); break;
+    case 8: EP_SUM_LAUNCH(8); break;
     default: return hipErrorInvalidValue;
     }
-    return hipGetLastError();
-}
-
-hipError_t ep_bf16_to_f32(const uint16_t *in, float *out, int64_t n, hipStream_t s)
-{
-    if (n <= 0) return hipSuccess;
-    if (n % 4) return hipErrorInvalidValue;
-    const int64_t n4 = n / 4;
-    hipLaunchKernelGGL(bf16_to_f32_kernel, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, s, in, out, n4);
+#undef EP_SUM_LAUNCH_AS
+#undef EP_SUM_LAUNCH
     return hipGetLastError();
 }
 

@@ -181,8 +181,11 @@ struct PendingSum { int splits; const float *bias; };
 // `before`: the layer in front left its sums over K ranges in w.part (xin is w.x then); this layer's first
 // LayerNorm adds them.  `after`: if non-null the layer may leave its own in the same way (then xout must be
 // w.x, and *after says so with splits > 1); if null it finishes its output itself.
+// `xin16`: the stage's bf16 input in place of xin (which is w.x then and gets it as fp32).  `xout16`: where the layer
+// may leave its output as bf16 in place of xout; it says so in *narrowed.
 ep_status run_layer(ep_stage *st, const Workspace &w, const LayerDev &L, const float *xin, float *xout, int B,
-                    hipStream_t s, const PendingSum *before, PendingSum *after)
+                    hipStream_t s, const PendingSum *before, PendingSum *after, const uint16_t *xin16 = nullptr,
+                    uint16_t *xout16 = nullptr, bool *narrowed = nullptr)
 {
     const ep_vit_config &c = st->cfg;
     const int T = c.n_tokens, D = c.d_model, M = c.d_mlp, H = c.n_heads;
@@ -190,7 +193,9 @@ ep_status run_layer(ep_stage *st, const Workspace &w, const LayerDev &L, const f
     if (after) *after = {1, nullptr};
     if (st->bf16) {
         uint16_t *a = (uint16_t *)w.a, *big = (uint16_t *)w.big;
-        if (before && before->splits > 1)
+        if (xin16)
+            EP_TRACED(EP_K_LN1, ep_bf16_layernorm_widen(xin16, w.x, L.ln1_g, L.ln1_b, c.ln_eps, a, R, D, s));
+        else if (before && before->splits > 1)
             EP_TRACED(EP_K_LN1, ep_bf16_layernorm_sum(w.x, w.part, before->splits, before->bias, L.ln1_g, L.ln1_b,
                                                       c.ln_eps, a, R, D, s));
         else
@@ -214,10 +219,13 @@ ep_status run_layer(ep_stage *st, const Workspace &w, const LayerDev &L, const f
             TraceScope ts_(st, EP_K_FC2, EP_K_FC2_MAIN, s);
             EP_HIP(ep_bf16_gemm_partial(big, (const uint16_t *)L.w_fc2, w.part, R, D, M, sp, s));
             if (ts_.after_main()) EP_HIP(hipEventRecord(ts_.after_main(), s));
-            if (after && xout == w.x)
+            if (after && xout == w.x) {
                 *after = {sp, L.b_fc2};
-            else
-                EP_HIP(ep_f32_residual_sum(w.x, w.part, sp, L.b_fc2, xout, R, D, s));
+            } else {
+                EP_HIP(ep_f32_residual_sum(w.x, w.part, sp, L.b_fc2, xout16 ? (void *)xout16 : (void *)xout, xout16 != nullptr,
+                                           R, D, s));
+                if (xout16) *narrowed = true;
+            }
         } else {
             EP_TRACED_GEMM(EP_K_FC2, EP_K_FC2_MAIN,
                            ep_bf16_gemm(big, (const uint16_t *)L.w_fc2, L.b_fc2, w.x, xout, R, D, M, EPI_BIAS_RESID,
@@ -404,23 +412,22 @@ ep_status forward_on(ep_stage *st, const Workspace &w, const void *x_in, int32_t
     const int64_t n = (int64_t)B * c.n_tokens * c.d_model;
     const int nl = st->end - st->begin;
 
-    const float *cur;
-    if (c.in_dtype == EP_BF16) {
-        EP_HIP(ep_bf16_to_f32((const uint16_t *)x_in, w.x, n, s));
-        cur = w.x;
-    } else {
-        cur = (const float *)x_in;     // first layer reads the caller's buffer directly
-    }
+    // the first layer reads the caller's buffer directly, or widens it into w.x
+    const uint16_t *in16 = c.in_dtype == EP_BF16 ? (const uint16_t *)x_in : nullptr;
+    const float *cur = in16 ? w.x : (const float *)x_in;
+    uint16_t *out16 = c.out_dtype == EP_BF16 ? (uint16_t *)x_out : nullptr;
+    bool narrowed = false;
     PendingSum pending = {1, nullptr};
     for (int l = 0; l < nl; ++l) {
         const bool last = l + 1 == nl;
         float *dst = (last && c.out_dtype == EP_F32) ? (float *)x_out : w.x;
         const PendingSum before = pending;
-        ep_status rc = run_layer(st, w, st->layers[l], cur, dst, B, s, &before, last ? nullptr : &pending);
+        ep_status rc = run_layer(st, w, st->layers[l], cur, dst, B, s, &before, last ? nullptr : &pending,
+                                 l == 0 ? in16 : nullptr, last ? out16 : nullptr, &narrowed);
         if (rc != EP_OK) return rc;
         cur = dst;
     }
-    if (c.out_dtype == EP_BF16) EP_HIP(ep_f32_to_bf16(w.x, (uint16_t *)x_out, n, s));
+    if (out16 && !narrowed) EP_HIP(ep_f32_to_bf16(w.x, out16, n, s));
     return EP_OK;
 }
 
