@@ -32,7 +32,7 @@ __device__ inline float wave_max(float v)
 __device__ inline float gelu_erf(float u) { return 0.5f * u * (1.0f + erff(u * 0.70710678118654752440f)); }
 
 // ---------------------------------------------------------------- LayerNorm
-__global__ __launch_bounds__(256) void ln_f32_kernel(const float *__restrict__ x,
+__global__ __launch_bounds__(256) void ln_f32_kernel(const float *__restrict__ x, int64_t ldx,
                                                      const float *__restrict__ g,
                                                      const float *__restrict__ b, float eps,
                                                      float *__restrict__ y, int64_t rows, int D)
@@ -40,7 +40,7 @@ __global__ __launch_bounds__(256) void ln_f32_kernel(const float *__restrict__ x
     const int lane = threadIdx.x & (WAVE - 1);
     const int64_t row = (int64_t)blockIdx.x * (blockDim.x / WAVE) + (threadIdx.x / WAVE);
     if (row >= rows) return;
-    const float *xr = x + row * D;
+    const float *xr = x + row * ldx;
     float s = 0.f;
     for (int d = lane; d < D; d += WAVE) s += xr[d];
     const float mean = wave_sum(s) / (float)D;
@@ -56,14 +56,14 @@ __global__ __launch_bounds__(256) void ln_f32_kernel(const float *__restrict__ x
 
 // The same for rows of whole 16-byte pieces, the row in registers: one pass over memory.  NV float4 per lane.
 template <int NV>
-__global__ __launch_bounds__(256) void ln_f32_vec_kernel(const float *__restrict__ x, const float *__restrict__ g,
+__global__ __launch_bounds__(256) void ln_f32_vec_kernel(const float *__restrict__ x, int64_t ldx, const float *__restrict__ g,
                                                          const float *__restrict__ b, float eps, float *__restrict__ y,
                                                          int64_t rows, int D)
 {
     const int lane = threadIdx.x & (WAVE - 1);
     const int64_t row = (int64_t)blockIdx.x * (blockDim.x / WAVE) + (threadIdx.x / WAVE);
     if (row >= rows) return;
-    const float4 *xr = reinterpret_cast<const float4 *>(x + row * D);
+    const float4 *xr = reinterpret_cast<const float4 *>(x + row * ldx);
     const float4 *g4 = reinterpret_cast<const float4 *>(g), *b4 = reinterpret_cast<const float4 *>(b);
     const int nvec = D >> 2;
     float4 v[NV], gg[NV], bb[NV];
@@ -695,21 +695,21 @@ __global__ void fill_pattern_kernel(float *x, int64_t n)
 
 static bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
-hipError_t ep_f32_layernorm(const float *x, const float *g, const float *b, float eps, float *y,
+hipError_t ep_f32_layernorm(const float *x, int64_t ldx, const float *g, const float *b, float eps, float *y,
                             int64_t rows, int D, hipStream_t s)
 {
     if (rows <= 0) return hipSuccess;
     const int rows_per_block = 256 / WAVE;
     const dim3 grid((unsigned)((rows + rows_per_block - 1) / rows_per_block));
-    if (D % 4 == 0 && D <= 4 * 256 && aligned16(x) && aligned16(y)) {
+    if (D % 4 == 0 && ldx % 4 == 0 && D <= 4 * 256 && aligned16(x) && aligned16(y)) {
         switch ((D + 255) / 256) {
-        case 1: hipLaunchKernelGGL(ln_f32_vec_kernel<1>, grid, dim3(256), 0, s, x, g, b, eps, y, rows, D); break;
-        case 2: hipLaunchKernelGGL(ln_f32_vec_kernel<2>, grid, dim3(256), 0, s, x, g, b, eps, y, rows, D); break;
-        case 3: hipLaunchKernelGGL(ln_f32_vec_kernel<3>, grid, dim3(256), 0, s, x, g, b, eps, y, rows, D); break;
-        default: hipLaunchKernelGGL(ln_f32_vec_kernel<4>, grid, dim3(256), 0, s, x, g, b, eps, y, rows, D); break;
+        case 1: hipLaunchKernelGGL(ln_f32_vec_kernel<1>, grid, dim3(256), 0, s, x, ldx, g, b, eps, y, rows, D); break;
+        case 2: hipLaunchKernelGGL(ln_f32_vec_kernel<2>, grid, dim3(256), 0, s, x, ldx, g, b, eps, y, rows, D); break;
+        case 3: hipLaunchKernelGGL(ln_f32_vec_kernel<3>, grid, dim3(256), 0, s, x, ldx, g, b, eps, y, rows, D); break;
+        default: hipLaunchKernelGGL(ln_f32_vec_kernel<4>, grid, dim3(256), 0, s, x, ldx, g, b, eps, y, rows, D); break;
         }
     } else {
-        hipLaunchKernelGGL(ln_f32_kernel, grid, dim3(256), 0, s, x, g, b, eps, y, rows, D);
+        hipLaunchKernelGGL(ln_f32_kernel, grid, dim3(256), 0, s, x, ldx, g, b, eps, y, rows, D);
     }
     return hipGetLastError();
 }

@@ -16,7 +16,8 @@ enum EpEpilogue {
 };
 
 // ---- fp32 path -------------------------------------------------------------
-hipError_t ep_f32_layernorm(const float *x, const float *g, const float *b, float eps, float *y,
+// row r of x starts at x + r * ldx
+hipError_t ep_f32_layernorm(const float *x, int64_t ldx, const float *g, const float *b, float eps, float *y,
                             int64_t rows, int D, hipStream_t s);
 hipError_t ep_f32_gemm(const float *A, const float *W, const float *bias, const float *resid,
                        float *C, int64_t M, int N, int K, int epi, hipStream_t s);
@@ -27,8 +28,8 @@ hipError_t ep_f32_ln_gemm(const float *x, const float *g, const float *b, float 
 hipError_t ep_f32_attention(const float *qkv, float *o, int B, int T, int D, int H, hipStream_t s);
 
 // ---- bf16 path -------------------------------------------------------------
-// x fp32 [rows, D] -> y bf16, fp32 statistics
-hipError_t ep_bf16_layernorm(const float *x, const float *g, const float *b, float eps,
+// x fp32 (row r at x + r * ldx, on 16 bytes) -> y bf16 [rows, D], fp32 statistics
+hipError_t ep_bf16_layernorm(const float *x, int64_t ldx, const float *g, const float *b, float eps,
                              uint16_t *y, int64_t rows, int D, hipStream_t s);
 // The same after a dense layer whose K was cut into ranges (ep_bf16_gemm_partial): first
 // x[r, :] = ((part[0] + part[1] + ... + part[splits-1]) + bias) + x[r, :] in place, in that order, then as above.

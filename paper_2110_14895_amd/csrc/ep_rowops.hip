@@ -53,7 +53,7 @@ __device__ inline float4 widen4(uint2 p)
 // passes is done here.  Widening a stage's bf16 input in a launch of its own cost 2 us a stage on 197 rows of 1024
 // and 4 us on 6304.
 template <int NV, bool GUARD, int SUM>
-__global__ __launch_bounds__(256) void ln_bf16_kernel(float *__restrict__ x, const void *__restrict__ src,
+__global__ __launch_bounds__(256) void ln_bf16_kernel(float *__restrict__ x, int64_t ldx, const void *__restrict__ src,
                                                       const float *__restrict__ bias,
                                                       const float *__restrict__ g,
                                                       const float *__restrict__ b, float eps,
@@ -62,7 +62,7 @@ __global__ __launch_bounds__(256) void ln_bf16_kernel(float *__restrict__ x, con
     const int lane = threadIdx.x & (WAVE - 1);
     const int64_t row = (int64_t)blockIdx.x * (blockDim.x / WAVE) + (threadIdx.x / WAVE);
     if (row >= rows) return;
-    float4 *xr = reinterpret_cast<float4 *>(x + row * D);
+    float4 *xr = reinterpret_cast<float4 *>(x + row * ldx);
     const int nvec = D >> 2;
     float4 v[NV];
     float s = 0.f;
@@ -144,13 +144,13 @@ __global__ __launch_bounds__(256) void f32_to_bf16_kernel(const float *__restric
 
 // part == nullptr: plain LayerNorm of x (which is then only read)
 template <int NV>
-hipError_t launch_ln(float *x, const void *src, int mode, const float *bias, const float *g, const float *b,
+hipError_t launch_ln(float *x, int64_t ldx, const void *src, int mode, const float *bias, const float *g, const float *b,
                      float eps, uint16_t *y, int64_t rows, int D, hipStream_t s)
 {
     const unsigned grid = (unsigned)((rows + 3) / 4);
     const bool ragged = D != NV * 256;
 #define EP_LN_LAUNCH(GUARD, SUM) \
-    hipLaunchKernelGGL((ln_bf16_kernel<NV, GUARD, SUM>), dim3(grid), dim3(256), 0, s, x, src, bias, g, b, eps, y, rows, D)
+    hipLaunchKernelGGL((ln_bf16_kernel<NV, GUARD, SUM>), dim3(grid), dim3(256), 0, s, x, ldx, src, bias, g, b, eps, y, rows, D)
 #define EP_LN_LAUNCH_SUM(SUM) do { if (ragged) EP_LN_LAUNCH(true, SUM); else EP_LN_LAUNCH(false, SUM); } while (0)
     switch (mode) {
     case WIDEN: EP_LN_LAUNCH_SUM(WIDEN); break;
@@ -166,45 +166,45 @@ hipError_t launch_ln(float *x, const void *src, int mode, const float *bias, con
 }
 
 // mode: 0, WIDEN or the number of K ranges
-hipError_t layernorm_any(float *x, const void *src, int mode, const float *bias, const float *g, const float *b,
+hipError_t layernorm_any(float *x, int64_t ldx, const void *src, int mode, const float *bias, const float *g, const float *b,
                          float eps, uint16_t *y, int64_t rows, int D, hipStream_t s)
 {
     if (rows <= 0) return hipSuccess;
-    if (D % 4 != 0 || D <= 0 || D > 8 * 256) return hipErrorInvalidValue;
+    if (D % 4 != 0 || ldx % 4 != 0 || D <= 0 || D > 8 * 256) return hipErrorInvalidValue;
     const int nv = (D + 255) / 256;
     switch (nv) {
-    case 1: return launch_ln<1>(x, src, mode, bias, g, b, eps, y, rows, D, s);
-    case 2: return launch_ln<2>(x, src, mode, bias, g, b, eps, y, rows, D, s);
-    case 3: return launch_ln<3>(x, src, mode, bias, g, b, eps, y, rows, D, s);
-    case 4: return launch_ln<4>(x, src, mode, bias, g, b, eps, y, rows, D, s);
-    case 5: return launch_ln<5>(x, src, mode, bias, g, b, eps, y, rows, D, s);
-    case 6: return launch_ln<6>(x, src, mode, bias, g, b, eps, y, rows, D, s);
-    case 7: return launch_ln<7>(x, src, mode, bias, g, b, eps, y, rows, D, s);
-    default: return launch_ln<8>(x, src, mode, bias, g, b, eps, y, rows, D, s);
+    case 1: return launch_ln<1>(x, ldx, src, mode, bias, g, b, eps, y, rows, D, s);
+    case 2: return launch_ln<2>(x, ldx, src, mode, bias, g, b, eps, y, rows, D, s);
+    case 3: return launch_ln<3>(x, ldx, src, mode, bias, g, b, eps, y, rows, D, s);
+    case 4: return launch_ln<4>(x, ldx, src, mode, bias, g, b, eps, y, rows, D, s);
+    case 5: return launch_ln<5>(x, ldx, src, mode, bias, g, b, eps, y, rows, D, s);
+    case 6: return launch_ln<6>(x, ldx, src, mode, bias, g, b, eps, y, rows, D, s);
+    case 7: return launch_ln<7>(x, ldx, src, mode, bias, g, b, eps, y, rows, D, s);
+    default: return launch_ln<8>(x, ldx, src, mode, bias, g, b, eps, y, rows, D, s);
     }
 }
 
 }  // namespace
 
-hipError_t ep_bf16_layernorm(const float *x, const float *g, const float *b, float eps,
+hipError_t ep_bf16_layernorm(const float *x, int64_t ldx, const float *g, const float *b, float eps,
                              uint16_t *y, int64_t rows, int D, hipStream_t s)
 {
     // without ranges to add the kernel only reads x
-    return layernorm_any(const_cast<float *>(x), nullptr, 0, nullptr, g, b, eps, y, rows, D, s);
+    return layernorm_any(const_cast<float *>(x), ldx, nullptr, 0, nullptr, g, b, eps, y, rows, D, s);
 }
 
 hipError_t ep_bf16_layernorm_sum(float *x, const float *part, int splits, const float *bias, const float *g,
                                  const float *b, float eps, uint16_t *y, int64_t rows, int D, hipStream_t s)
 {
     if (!part || !bias || (splits != 2 && splits != 4 && splits != 8)) return hipErrorInvalidValue;
-    return layernorm_any(x, part, splits, bias, g, b, eps, y, rows, D, s);
+    return layernorm_any(x, D, part, splits, bias, g, b, eps, y, rows, D, s);
 }
 
 hipError_t ep_bf16_layernorm_widen(const uint16_t *in, float *x, const float *g, const float *b, float eps, uint16_t *y,
                                    int64_t rows, int D, hipStream_t s)
 {
     if (!in) return hipErrorInvalidValue;
-    return layernorm_any(x, in, WIDEN, nullptr, g, b, eps, y, rows, D, s);
+    return layernorm_any(x, D, in, WIDEN, nullptr, g, b, eps, y, rows, D, s);
 }
 
 hipError_t ep_f32_residual_sum(const float *resid, const float *part, int splits, const float *bias, void *out,

@@ -199,7 +199,7 @@ ep_status run_layer(ep_stage *st, const Workspace &w, const LayerDev &L, const f
             EP_TRACED(EP_K_LN1, ep_bf16_layernorm_sum(w.x, w.part, before->splits, before->bias, L.ln1_g, L.ln1_b,
                                                       c.ln_eps, a, R, D, s));
         else
-            EP_TRACED(EP_K_LN1, ep_bf16_layernorm(xin, L.ln1_g, L.ln1_b, c.ln_eps, a, R, D, s));
+            EP_TRACED(EP_K_LN1, ep_bf16_layernorm(xin, D, L.ln1_g, L.ln1_b, c.ln_eps, a, R, D, s));
         EP_TRACED_GEMM(EP_K_QKV, EP_K_QKV_MAIN,
                        ep_bf16_gemm(a, (const uint16_t *)L.w_qkv, L.b_qkv, nullptr, big, R, 3 * D, D, EPI_BIAS,
                                     ts_.after_main(), s));
@@ -207,7 +207,7 @@ ep_status run_layer(ep_stage *st, const Workspace &w, const LayerDev &L, const f
         EP_TRACED_GEMM(EP_K_PROJ, EP_K_PROJ_MAIN,
                        ep_bf16_gemm(a, (const uint16_t *)L.w_o, L.b_o, xin, w.x, R, D, D, EPI_BIAS_RESID,
                                     ts_.after_main(), s));
-        EP_TRACED(EP_K_LN2, ep_bf16_layernorm(w.x, L.ln2_g, L.ln2_b, c.ln_eps, a, R, D, s));
+        EP_TRACED(EP_K_LN2, ep_bf16_layernorm(w.x, D, L.ln2_g, L.ln2_b, c.ln_eps, a, R, D, s));
         EP_TRACED_GEMM(EP_K_FC1, EP_K_FC1_MAIN,
                        ep_bf16_gemm(a, (const uint16_t *)L.w_fc1, L.b_fc1, nullptr, big, R, M, D, EPI_BIAS_GELU,
                                     ts_.after_main(), s));
@@ -236,12 +236,12 @@ ep_status run_layer(ep_stage *st, const Workspace &w, const LayerDev &L, const f
         // a LayerNorm done inside the dense layer behind it leaves its own bracket empty
         const bool fuse1 = ep_f32_ln_gemm_supported(xin, (const float *)L.w_qkv, R, 3 * D, D);
         const bool fuse2 = ep_f32_ln_gemm_supported(w.x, (const float *)L.w_fc1, R, M, D);
-        EP_TRACED(EP_K_LN1, fuse1 ? hipSuccess : ep_f32_layernorm(xin, L.ln1_g, L.ln1_b, c.ln_eps, a, R, D, s));
+        EP_TRACED(EP_K_LN1, fuse1 ? hipSuccess : ep_f32_layernorm(xin, D, L.ln1_g, L.ln1_b, c.ln_eps, a, R, D, s));
         EP_TRACED(EP_K_QKV, fuse1 ? ep_f32_ln_gemm(xin, L.ln1_g, L.ln1_b, c.ln_eps, (const float *)L.w_qkv, L.b_qkv, big, R, 3 * D, D, EPI_BIAS, s)
                                   : ep_f32_gemm(a, (const float *)L.w_qkv, L.b_qkv, nullptr, big, R, 3 * D, D, EPI_BIAS, s));
         EP_TRACED(EP_K_ATTN, ep_f32_attention(big, a, B, T, D, H, s));
         EP_TRACED(EP_K_PROJ, ep_f32_gemm(a, (const float *)L.w_o, L.b_o, xin, w.x, R, D, D, EPI_BIAS_RESID, s));
-        EP_TRACED(EP_K_LN2, fuse2 ? hipSuccess : ep_f32_layernorm(w.x, L.ln2_g, L.ln2_b, c.ln_eps, a, R, D, s));
+        EP_TRACED(EP_K_LN2, fuse2 ? hipSuccess : ep_f32_layernorm(w.x, D, L.ln2_g, L.ln2_b, c.ln_eps, a, R, D, s));
         EP_TRACED(EP_K_FC1, fuse2 ? ep_f32_ln_gemm(w.x, L.ln2_g, L.ln2_b, c.ln_eps, (const float *)L.w_fc1, L.b_fc1, big, R, M, D, EPI_BIAS_GELU, s)
                                   : ep_f32_gemm(a, (const float *)L.w_fc1, L.b_fc1, nullptr, big, R, M, D, EPI_BIAS_GELU, s));
         EP_TRACED(EP_K_FC2, ep_f32_gemm(big, (const float *)L.w_fc2, L.b_fc2, w.x, xout, R, D, M, EPI_BIAS_RESID, s));

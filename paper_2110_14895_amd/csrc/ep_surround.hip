@@ -13,8 +13,8 @@
 // residual epilogue (the position rows are laid out once, at create time, as a
 // [max_batch * patches, D] matrix); a second small kernel moves the result to
 // the [B, T, D] token layout, inserts the class-token row and rounds once to
-// the output dtype.  Head: gather of the class-token rows, LayerNorm, and the
-// short-M GEMM with an fp32 store.
+// the output dtype.  Head: LayerNorm of the class-token rows where they lie, and
+// the short-M GEMM with an fp32 store.
 #include <hip/hip_runtime.h>
 
 #include <cstring>
@@ -50,28 +50,54 @@ void widen(const void *src, size_t n, int32_t dtype, std::vector<float> &dst)
     }
 }
 
-// patches as GEMM rows: out[(b*NP + p), k], k = (c, iy, ix) < K, zeros for K <= k < Kp
-template <typename OutT>
-__global__ __launch_bounds__(256) void embed_gather_kernel(const float *__restrict__ img, OutT *__restrict__ out,
-                                                           int64_t total, int C, int HW, int P, int G, int K, int Kp)
+// V elements at a time, narrowed to OutT
+template <typename OutT, int V>
+__device__ inline void store_run(OutT *dst, const float (&v)[V])
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= total) return;
-    const int k = (int)(i % Kp);
-    const int64_t row = i / Kp;
-    const int p = (int)(row % ((int64_t)G * G));
-    const int64_t b = row / ((int64_t)G * G);
-    float v = 0.f;
-    if (k < K) {
-        const int c = k / (P * P), iy = (k / P) % P, ix = k % P;
-        const int y = (p / G) * P + iy, x = (p % G) * P + ix;
-        v = img[((b * C + c) * HW + y) * HW + x];
-    }
-    if (sizeof(OutT) == 2) {
-        const __bf16 h = (__bf16)v;
-        reinterpret_cast<uint16_t *>(out)[i] = __builtin_bit_cast(uint16_t, h);
+    if constexpr (sizeof(OutT) == 2) {
+        if constexpr (V == 4) *reinterpret_cast<uint2 *>(dst) = make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
+        else if constexpr (V == 2) *reinterpret_cast<uint32_t *>(dst) = pack_bf16x2(v[0], v[1]);
+        else *dst = __builtin_bit_cast(uint16_t, (__bf16)v[0]);
     } else {
-        reinterpret_cast<float *>(out)[i] = v;
+        if constexpr (V == 4) *reinterpret_cast<float4 *>(dst) = make_float4(v[0], v[1], v[2], v[3]);
+        else if constexpr (V == 2) *reinterpret_cast<float2 *>(dst) = make_float2(v[0], v[1]);
+        else *dst = v[0];
+    }
+}
+
+template <int V>
+__device__ inline void load_run(const float *src, float (&v)[V])
+{
+    if constexpr (V == 4) {
+        const float4 q = *reinterpret_cast<const float4 *>(src);
+        v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
+    } else if constexpr (V == 2) {
+        const float2 q = *reinterpret_cast<const float2 *>(src);
+        v[0] = q.x; v[1] = q.y;
+    } else {
+        v[0] = *src;
+    }
+}
+
+// patches as GEMM rows: out[(b*NP + p), k], k = (c, iy, ix) < K, zeros for K <= k < Kp.  A workgroup takes a patch at a
+// time (what depends on the patch is scalar), a thread V pixels of a patch row: memory-bound at 32 images of
+// 224 x 224 (21.5 -> 8.3 us), where one pixel a thread was bound by the integer divisions around it.
+template <typename OutT, int V>
+__global__ __launch_bounds__(256) void embed_gather_kernel(const float *__restrict__ img, OutT *__restrict__ out,
+                                                           uint32_t rows, int C, int HW, int P, int G, int K, int Kp)
+{
+    const uint32_t np = (uint32_t)G * G, pp = (uint32_t)P * P;
+    for (uint32_t row = blockIdx.x; row < rows; row += gridDim.x) {
+        const uint32_t b = row / np, p = row % np;
+        const float *patch = img + (size_t)b * C * HW * HW + (size_t)(p / G) * P * HW + (p % G) * P;
+        for (uint32_t k = threadIdx.x * V; k < (uint32_t)Kp; k += blockDim.x * V) {
+            float v[V] = {};
+            if (k < (uint32_t)K) {
+                const uint32_t c = k / pp, iy = k % pp / P, ix = k % P;
+                load_run<V>(patch + ((size_t)c * HW + iy) * HW + ix, v);
+            }
+            store_run<OutT, V>(out + (size_t)row * Kp + k, v);
+        }
     }
 }
 
@@ -86,23 +112,25 @@ __global__ __launch_bounds__(256) void embed_pos_rows_kernel(const float *__rest
     posb[i] = pos[(size_t)(1 + p) * D + d];
 }
 
-// tmp [B*NP, D] fp32 -> x [B, 1 + NP, D] (row 0 = cls + pos[0]), rounded once to OutT
-template <typename OutT>
+// tmp [B*NP, D] fp32 -> x [B, 1 + NP, D] (row 0 = cls + pos[0]), rounded once to OutT.  A workgroup takes a token at
+// a time, a thread V elements of it.
+template <typename OutT, int V>
 __global__ __launch_bounds__(256) void embed_assemble_kernel(const float *__restrict__ tmp, const float *__restrict__ cls,
                                                              const float *__restrict__ pos, OutT *__restrict__ x,
-                                                             int64_t total, int NP, int D)
+                                                             uint32_t rows, int NP, int D)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= total) return;
-    const int d = (int)(i % D);
-    const int t = (int)((i / D) % (NP + 1));
-    const int64_t b = i / ((int64_t)D * (NP + 1));
-    const float v = t == 0 ? cls[d] + pos[d] : tmp[((size_t)b * NP + (t - 1)) * D + d];
-    if (sizeof(OutT) == 2) {
-        const __bf16 h = (__bf16)v;
-        reinterpret_cast<uint16_t *>(x)[i] = __builtin_bit_cast(uint16_t, h);
-    } else {
-        reinterpret_cast<float *>(x)[i] = v;
+    for (uint32_t row = blockIdx.x; row < rows; row += gridDim.x) {
+        const uint32_t b = row / (NP + 1), t = row % (NP + 1);
+        for (int d = threadIdx.x * V; d < D; d += blockDim.x * V) {
+            float v[V];
+            if (t == 0) {
+#pragma unroll
+                for (int i = 0; i < V; ++i) v[i] = cls[d + i] + pos[d + i];
+            } else {
+                load_run<V>(tmp + ((size_t)b * NP + (t - 1)) * D + d, v);
+            }
+            store_run<OutT, V>(x + (size_t)row * D + d, v);
+        }
     }
 }
 
@@ -116,6 +144,37 @@ __global__ __launch_bounds__(256) void head_gather_kernel(const float *__restric
 }
 
 inline unsigned blocks_for(int64_t total) { return (unsigned)((total + 255) / 256); }
+
+// one row of n units to a workgroup: threads for a row, workgroups for `rows` of them
+inline unsigned row_threads(int n) { return n >= 256 ? 256u : (unsigned)((n + 63) / 64 * 64); }
+inline unsigned row_blocks(int64_t rows) { return (unsigned)(rows < 65536 ? rows : 65536); }
+
+inline bool aligned(const void *p, size_t a) { return (reinterpret_cast<uintptr_t>(p) & (a - 1)) == 0; }
+
+template <typename OutT>
+void launch_gather(const float *img, OutT *out, int64_t rows, const ep_embed_config &c, int G, int K, int Kp, hipStream_t s)
+{
+    // runs of V pixels lie inside a patch row and on V * 4 bytes where patch and image are whole numbers of them
+    const int P = c.patch, HW = c.image_size;
+#define EP_GATHER(V) \
+    hipLaunchKernelGGL((embed_gather_kernel<OutT, V>), dim3(row_blocks(rows)), dim3(row_threads(Kp / V)), 0, s, img, out, \
+                       (uint32_t)rows, c.channels, HW, P, G, K, Kp)
+    if (P % 4 == 0 && HW % 4 == 0 && aligned(img, 16)) EP_GATHER(4);
+    else if (P % 2 == 0 && HW % 2 == 0 && aligned(img, 8)) EP_GATHER(2);
+    else EP_GATHER(1);
+#undef EP_GATHER
+}
+
+template <typename OutT>
+void launch_assemble(const float *tmp, const float *cls, const float *pos, OutT *x, int64_t rows, int NP, int D, hipStream_t s)
+{
+    if (D % 4 == 0 && aligned(x, 4 * sizeof(OutT)))
+        hipLaunchKernelGGL((embed_assemble_kernel<OutT, 4>), dim3(row_blocks(rows)), dim3(row_threads(D / 4)), 0, s, tmp, cls, pos, x,
+                           (uint32_t)rows, NP, D);
+    else
+        hipLaunchKernelGGL((embed_assemble_kernel<OutT, 1>), dim3(row_blocks(rows)), dim3(row_threads(D)), 0, s, tmp, cls, pos, x,
+                           (uint32_t)rows, NP, D);
+}
 
 }  // namespace
 
@@ -242,26 +301,20 @@ extern "C" ep_status ep_embed_forward(ep_embed_t *e, const void *images, int32_t
     const ep_embed_config &c = e->cfg;
     const int D = c.d_model;
     const int64_t R = (int64_t)B * e->NP;
-    const int64_t n_rows = R * e->Kp;
     if (e->bf16) {
-        hipLaunchKernelGGL(embed_gather_kernel<uint16_t>, dim3(blocks_for(n_rows)), dim3(256), 0, s, (const float *)images,
-                           (uint16_t *)e->rows, n_rows, c.channels, c.image_size, c.patch, e->G, e->K, e->Kp);
+        launch_gather((const float *)images, (uint16_t *)e->rows, R, c, e->G, e->K, e->Kp, s);
         EP_HIP(hipGetLastError());
         EP_HIP(ep_bf16_gemm((const uint16_t *)e->rows, (const uint16_t *)e->w, e->b, e->posb, e->tmp, R, D, e->Kp,
                             EPI_BIAS_RESID, nullptr, s));
     } else {
-        hipLaunchKernelGGL(embed_gather_kernel<float>, dim3(blocks_for(n_rows)), dim3(256), 0, s, (const float *)images,
-                           (float *)e->rows, n_rows, c.channels, c.image_size, c.patch, e->G, e->K, e->Kp);
+        launch_gather((const float *)images, (float *)e->rows, R, c, e->G, e->K, e->Kp, s);
         EP_HIP(hipGetLastError());
         EP_HIP(ep_f32_gemm((const float *)e->rows, (const float *)e->w, e->b, e->posb, e->tmp, R, D, e->Kp, EPI_BIAS_RESID, s));
     }
-    const int64_t n_out = (int64_t)B * e->T * D;
     if (c.out_dtype == EP_BF16)
-        hipLaunchKernelGGL(embed_assemble_kernel<uint16_t>, dim3(blocks_for(n_out)), dim3(256), 0, s, e->tmp, e->cls, e->pos,
-                           (uint16_t *)x_out, n_out, e->NP, D);
+        launch_assemble(e->tmp, e->cls, e->pos, (uint16_t *)x_out, (int64_t)B * e->T, e->NP, D, s);
     else
-        hipLaunchKernelGGL(embed_assemble_kernel<float>, dim3(blocks_for(n_out)), dim3(256), 0, s, e->tmp, e->cls, e->pos,
-                           (float *)x_out, n_out, e->NP, D);
+        launch_assemble(e->tmp, e->cls, e->pos, (float *)x_out, (int64_t)B * e->T, e->NP, D, s);
     EP_HIP(hipGetLastError());
     return EP_OK;
 }
@@ -356,15 +409,24 @@ extern "C" ep_status ep_head_forward(ep_head_t *h, const void *x, int32_t B, voi
     hipStream_t s = (hipStream_t)stream;
     const ep_head_config &c = h->cfg;
     const int D = c.d_model, NC = c.n_classes;
-    const int64_t n = (int64_t)B * D;
-    hipLaunchKernelGGL(head_gather_kernel, dim3(blocks_for(n)), dim3(256), 0, s, (const float *)x, h->rows, n, c.n_tokens, D);
-    EP_HIP(hipGetLastError());
+    // LayerNorm picks the class-token rows out of the tokens; on the bf16 path it reads 16-byte pieces, and tokens that
+    // do not lie on such are gathered first
+    const int64_t stride = (int64_t)c.n_tokens * D;
+    const float *rows = (const float *)x;
+    int64_t ld = stride;
+    if (h->bf16 && !aligned(x, 16)) {
+        const int64_t n = (int64_t)B * D;
+        hipLaunchKernelGGL(head_gather_kernel, dim3(blocks_for(n)), dim3(256), 0, s, rows, h->rows, n, c.n_tokens, D);
+        EP_HIP(hipGetLastError());
+        rows = h->rows;
+        ld = D;
+    }
     if (h->bf16) {
-        EP_HIP(ep_bf16_layernorm(h->rows, h->g, h->beta, c.ln_eps, (uint16_t *)h->z, B, D, s));
+        EP_HIP(ep_bf16_layernorm(rows, ld, h->g, h->beta, c.ln_eps, (uint16_t *)h->z, B, D, s));
         EP_HIP(ep_bf16_gemm_skinny((const uint16_t *)h->z, (const uint16_t *)h->w, h->b, nullptr, logits, B, NC, D,
                                    EPI_BIAS_F32, s));
     } else {
-        EP_HIP(ep_f32_layernorm(h->rows, h->g, h->beta, c.ln_eps, (float *)h->z, B, D, s));
+        EP_HIP(ep_f32_layernorm(rows, ld, h->g, h->beta, c.ln_eps, (float *)h->z, B, D, s));
         EP_HIP(ep_f32_gemm((const float *)h->z, (const float *)h->w, h->b, nullptr, (float *)logits, B, NC, D, EPI_BIAS, s));
     }
     return EP_OK;

@@ -1,0 +1,54 @@
+"""GPU parity of the embedding and the head where pixels, tokens or buffers are not whole 16-byte pieces: patch rows
+of 2 and 7 pixels, images and tokens that start 4 bytes past such a piece, an fp32 width that is not a multiple of
+four.  Against the checker; tolerances of the paths."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2110_14895_amd import binding, synth
+from tests import harness as H
+
+pytestmark = pytest.mark.gpu
+
+
+def shifted(a, shift):
+    """`a` on the device, `shift` floats past a fresh allocation."""
+    import torch
+    flat = torch.empty(a.size + shift, dtype=torch.float32, device="cuda")
+    flat[shift:] = torch.from_numpy(a).cuda().reshape(-1)
+    return flat[shift:].view(a.shape)
+
+
+# patch runs of 2 (K = 12 of 64), 1 (K = 49 of 64) and 4 pixels, the last from an unaligned image
+@pytest.mark.parametrize("size,patch,channels,d,bf16,shift", [
+    (6, 2, 3, 64, True, 0), (21, 7, 1, 64, True, 0), (16, 4, 3, 128, True, 1), (16, 4, 3, 128, False, 1), (6, 2, 3, 30, False, 0),
+])
+def test_embedding_runs(size, patch, channels, d, bf16, shift):
+    import torch
+    T, B = 1 + (size // patch) ** 2, 3
+    sh = synth.custom_shape(f"run{size}_{patch}", 1, d, 1, 4 * d, T)
+    prm = synth.surround_params(sh, patch, channels, 8, 5, bf16=bf16)
+    dt = binding.EP_BF16 if bf16 else binding.EP_F32
+    emb = binding.Embed(size, patch, channels, d, dt, binding.EP_F32, synth.as_param_dtype(prm, bf16), B)
+    img = synth.images(B, channels, size, seed=2)
+    out = shifted(np.full((B, T, d), np.nan, np.float32), shift)
+    emb.forward(shifted(img, shift), B, out, torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    ref = oracle.embed_forward(img, prm["w_patch"], prm["b_patch"], prm["cls"], prm["pos"], patch)
+    assert H.rel_err(out.cpu().numpy(), ref) <= (H.TOL_BF16 if bf16 else H.TOL_F32)
+
+
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_head_takes_tokens_where_they_lie(bf16, shift):
+    import torch
+    d, T, nc, B = 192, 65, 16, 7
+    sh = synth.custom_shape("headrow", 1, d, 3, 4 * d, T)
+    prm = synth.surround_params(sh, 2, 1, nc, 5, bf16=bf16)
+    head = binding.Head(d, T, nc, sh.ln_eps, binding.EP_BF16 if bf16 else binding.EP_F32, synth.as_param_dtype(prm, bf16), B)
+    x = (2.0 * synth.normal("head/rows", B * T * d, 1)).reshape(B, T, d).astype(np.float32)
+    logits = torch.full((B, nc), float("nan"), dtype=torch.float32, device="cuda")
+    head.forward(shifted(x, shift), B, logits, torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    ref = oracle.head_forward(x, prm["ln_g"], prm["ln_b"], sh.ln_eps, prm["w_head"], prm["b_head"])
+    assert H.rel_err(logits.cpu().numpy(), ref) <= (H.TOL_BF16 if bf16 else H.TOL_F32)
