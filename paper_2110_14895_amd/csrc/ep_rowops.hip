@@ -3,8 +3,8 @@
 // normalisations of a layer), with the widening of a stage's bf16 input on the
 // way, and narrowing at the stage's end.
 //
-// LayerNorm: one wavefront per row, the whole row held in registers (float4
-// loads, D <= 64*4*MAXV), mean then centred variance (two passes over
+// LayerNorm: one wavefront (of narrow rows half or a quarter) per row, the whole
+// row held in registers (float4 loads), mean then centred variance (two passes over
 // registers, one pass over memory), fp32 statistics, round-to-nearest-even
 // narrowing.  Algorithmic traffic per row: 4*D bytes read, 2*D written.
 #include "ep_kernels.h"
@@ -14,10 +14,12 @@ namespace {
 
 constexpr int WAVE = 64;
 
-__device__ inline float wave_sum(float v)
+// sum over the LPR lanes of a row
+template <int LPR>
+__device__ inline float row_sum(float v)
 {
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, WAVE);
+    for (int off = LPR / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, WAVE);
     return v;
 }
 
@@ -47,20 +49,22 @@ __device__ inline float4 widen4(uint2 p)
                        __uint_as_float(p.y & 0xFFFF0000u));
 }
 
-// NV = number of float4 per lane (D = 256 * NV exactly, or ragged when GUARD).  SUM > 0: x is first brought up to
+// LPR = lanes to a row, NV = number of float4 per lane (D = 4 * LPR * NV exactly, or ragged when GUARD).  Rows of up to
+// 512 elements share a wave: 384 are three float4 to each of 32 lanes, where a wave to a row had half its lanes idle
+// in the second of two (DeiT-Small, images to logits on 32: 1021 -> 998 us).  SUM > 0: x is first brought up to
 // date in place from the SUM K ranges of the dense layer before it (src: fp32 [SUM, rows, D], bias), then normalised.
 // Bound by memory from a few thousand rows on (4.4 to 6 TB/s), by its launch below; so what else a row needs while it
 // passes is done here.  Widening a stage's bf16 input in a launch of its own cost 2 us a stage on 197 rows of 1024
 // and 4 us on 6304.
-template <int NV, bool GUARD, int SUM>
+template <int LPR, int NV, bool GUARD, int SUM>
 __global__ __launch_bounds__(256) void ln_bf16_kernel(float *__restrict__ x, int64_t ldx, const void *__restrict__ src,
                                                       const float *__restrict__ bias,
                                                       const float *__restrict__ g,
                                                       const float *__restrict__ b, float eps,
                                                       uint16_t *__restrict__ y, int64_t rows, int D)
 {
-    const int lane = threadIdx.x & (WAVE - 1);
-    const int64_t row = (int64_t)blockIdx.x * (blockDim.x / WAVE) + (threadIdx.x / WAVE);
+    const int lane = threadIdx.x & (LPR - 1);
+    const int64_t row = (int64_t)blockIdx.x * (256 / LPR) + threadIdx.x / LPR;
     if (row >= rows) return;
     float4 *xr = reinterpret_cast<float4 *>(x + row * ldx);
     const int nvec = D >> 2;
@@ -68,7 +72,7 @@ __global__ __launch_bounds__(256) void ln_bf16_kernel(float *__restrict__ x, int
     float s = 0.f;
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
-        const int c = lane + i * WAVE;
+        const int c = lane + i * LPR;
         if (!GUARD || c < nvec) {
             if (SUM == WIDEN) {
                 v[i] = widen4(reinterpret_cast<const uint2 *>(static_cast<const uint16_t *>(src) + row * D)[c]);
@@ -86,23 +90,23 @@ __global__ __launch_bounds__(256) void ln_bf16_kernel(float *__restrict__ x, int
             v[i] = make_float4(0.f, 0.f, 0.f, 0.f);
         }
     }
-    const float mean = wave_sum(s) / (float)D;
+    const float mean = row_sum<LPR>(s) / (float)D;
     float q = 0.f;
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
-        const int c = lane + i * WAVE;
+        const int c = lane + i * LPR;
         if (!GUARD || c < nvec) {
             v[i].x -= mean; v[i].y -= mean; v[i].z -= mean; v[i].w -= mean;
             q += (v[i].x * v[i].x + v[i].y * v[i].y) + (v[i].z * v[i].z + v[i].w * v[i].w);
         }
     }
-    const float inv = 1.0f / sqrtf(wave_sum(q) / (float)D + eps);
+    const float inv = 1.0f / sqrtf(row_sum<LPR>(q) / (float)D + eps);
     const float4 *g4 = reinterpret_cast<const float4 *>(g);
     const float4 *b4 = reinterpret_cast<const float4 *>(b);
     uint2 *yr = reinterpret_cast<uint2 *>(y + row * D);
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
-        const int c = lane + i * WAVE;
+        const int c = lane + i * LPR;
         if (!GUARD || c < nvec) {
             const float4 gg = g4[c], bb = b4[c];
             uint2 o;
@@ -143,14 +147,15 @@ __global__ __launch_bounds__(256) void f32_to_bf16_kernel(const float *__restric
 }
 
 // part == nullptr: plain LayerNorm of x (which is then only read)
-template <int NV>
+template <int LPR, int NV>
 hipError_t launch_ln(float *x, int64_t ldx, const void *src, int mode, const float *bias, const float *g, const float *b,
                      float eps, uint16_t *y, int64_t rows, int D, hipStream_t s)
 {
-    const unsigned grid = (unsigned)((rows + 3) / 4);
-    const bool ragged = D != NV * 256;
+    constexpr int RPB = 256 / LPR;                     // rows per workgroup
+    const unsigned grid = (unsigned)((rows + RPB - 1) / RPB);
+    const bool ragged = D != 4 * LPR * NV;
 #define EP_LN_LAUNCH(GUARD, SUM) \
-    hipLaunchKernelGGL((ln_bf16_kernel<NV, GUARD, SUM>), dim3(grid), dim3(256), 0, s, x, ldx, src, bias, g, b, eps, y, rows, D)
+    hipLaunchKernelGGL((ln_bf16_kernel<LPR, NV, GUARD, SUM>), dim3(grid), dim3(256), 0, s, x, ldx, src, bias, g, b, eps, y, rows, D)
 #define EP_LN_LAUNCH_SUM(SUM) do { if (ragged) EP_LN_LAUNCH(true, SUM); else EP_LN_LAUNCH(false, SUM); } while (0)
     switch (mode) {
     case WIDEN: EP_LN_LAUNCH_SUM(WIDEN); break;
@@ -171,17 +176,29 @@ hipError_t layernorm_any(float *x, int64_t ldx, const void *src, int mode, const
 {
     if (rows <= 0) return hipSuccess;
     if (D % 4 != 0 || ldx % 4 != 0 || D <= 0 || D > 8 * 256) return hipErrorInvalidValue;
-    const int nv = (D + 255) / 256;
-    switch (nv) {
-    case 1: return launch_ln<1>(x, ldx, src, mode, bias, g, b, eps, y, rows, D, s);
-    case 2: return launch_ln<2>(x, ldx, src, mode, bias, g, b, eps, y, rows, D, s);
-    case 3: return launch_ln<3>(x, ldx, src, mode, bias, g, b, eps, y, rows, D, s);
-    case 4: return launch_ln<4>(x, ldx, src, mode, bias, g, b, eps, y, rows, D, s);
-    case 5: return launch_ln<5>(x, ldx, src, mode, bias, g, b, eps, y, rows, D, s);
-    case 6: return launch_ln<6>(x, ldx, src, mode, bias, g, b, eps, y, rows, D, s);
-    case 7: return launch_ln<7>(x, ldx, src, mode, bias, g, b, eps, y, rows, D, s);
-    default: return launch_ln<8>(x, ldx, src, mode, bias, g, b, eps, y, rows, D, s);
+    // the fewest lanes to a row that keep it to four float4 a lane
+#define EP_LN(LPR, NV) return launch_ln<LPR, NV>(x, ldx, src, mode, bias, g, b, eps, y, rows, D, s)
+    if (D <= 256) {
+        switch ((D + 63) / 64) {
+        case 1: EP_LN(16, 1);
+        case 2: EP_LN(16, 2);
+        case 3: EP_LN(16, 3);
+        default: EP_LN(16, 4);
+        }
     }
+    if (D <= 512) {
+        if (D <= 384) EP_LN(32, 3);
+        EP_LN(32, 4);
+    }
+    switch ((D + 255) / 256) {
+    case 3: EP_LN(64, 3);
+    case 4: EP_LN(64, 4);
+    case 5: EP_LN(64, 5);
+    case 6: EP_LN(64, 6);
+    case 7: EP_LN(64, 7);
+    default: EP_LN(64, 8);
+    }
+#undef EP_LN
 }
 
 }  // namespace
