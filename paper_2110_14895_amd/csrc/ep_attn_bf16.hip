@@ -152,12 +152,9 @@ __device__ __forceinline__ void attn_pass(const u32x4 (&qf)[NQB][StreamShape<DH>
         const char *Kb = lds + ((j0 + c) % NBUF) * BUFB;
         const char *Vb = Kb + PARTB;
         if (c == (nch > 1 ? 1 : 0)) mid();
-#pragma unroll
-        for (int sub = 0; sub < SUBS; ++sub) {
-            const int key0 = c * CK + sub * 32;
-            if (key0 >= T) break;                           // wave-uniform: nothing but padding from here on
-            // ---- S^T = K . Q^T: s[kb][qb][i] <-> key key0 + kb*16 + 4g + i, query q0 + qb*16 + l15
-            f32x4 s[2][NQB];
+        const int nsub = min(SUBS, (T - c * CK + 31) / 32); // 32-key steps that hold a key (wave-uniform)
+        // S^T = K . Q^T: s[kb][qb][i] <-> key key0 + kb*16 + 4g + i, query q0 + qb*16 + l15
+        auto scores = [&](int sub, f32x4 (&s)[2][NQB]) {
 #pragma unroll
             for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
@@ -172,6 +169,23 @@ __device__ __forceinline__ void attn_pass(const u32x4 (&qf)[NQB][StreamShape<DH>
                     for (int qb = 0; qb < NQB; ++qb)
                         s[kb][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, __builtin_bit_cast(bf16x8, qf[qb][ks]), s[kb][qb], 0, 0, 0);
                 }
+        };
+        // With one query block a wave is alone on its SIMD and one step after the other is a chain: there the next
+        // step's scores are on the matrix pipe while this step's go through the vector ALU (577 tokens, 24 pairs:
+        // twelve layers 774 -> 764 us).  With two blocks and two or three waves to a SIMD it gains nothing, and at
+        // d_head 80 the registers run out (three layers of 256 images 7945 -> 7971).
+        constexpr bool AHEAD = NQB == 1;
+        f32x4 sc[AHEAD ? 2 : 1][2][NQB];
+        if (AHEAD) scores(0, sc[0]);
+#pragma unroll
+        for (int sub = 0; sub < SUBS; ++sub) {
+            if (sub >= nsub) break;                         // nothing but padding from here on
+            if (!AHEAD)
+                scores(sub, sc[0]);
+            else if (sub + 1 < SUBS && sub + 1 < nsub)
+                scores(sub + 1, sc[AHEAD ? (sub + 1) & 1 : 0]);
+            f32x4 (&s)[2][NQB] = sc[AHEAD ? sub & 1 : 0];
+            const int key0 = c * CK + sub * 32;
             if (key0 + 32 > T) {                            // wave-uniform: keys to mask in the last step only
                 const int lim = T - key0 - 4 * g;
 #pragma unroll
