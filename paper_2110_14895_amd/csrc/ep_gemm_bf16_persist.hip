@@ -22,7 +22,9 @@
 //   - LDS rows are 8 chunks of 16 bytes; chunk c of row r sits at slot
 //     c ^ f(r), f(r) = (r & 7) ^ ((r >> 3) & 1): the 16-byte fragment reads of 16
 //     consecutive rows are conflict-free on the 64-bank LDS (with the K chunks
-//     dealt to the quarters of a wave in the order 0, 2, 1, 3).
+//     dealt to the quarters of a wave in the order 0, 2, 1, 3).  The W panel holds
+//     the fragments that the weights are stored in (ep_gemm_bf16_tile.h), 1 KB to a
+//     load, and is read lane by lane.
 //   - The matrix instruction is v_mfma_f32_16x16x32_bf16: at the power limit
 //     the chip runs the same flops about 15 % faster in this form than as
 //     32 x 32 x 16.  A 32-wide slice of the wave tile is multiplied in four
@@ -46,7 +48,7 @@
 // workgroups of an XCD take 32 consecutive tiles of an order that walks groups
 // of 4 tile rows column by column, so that they share A and W panels in L2.
 //
-// Requirements: K % 64 == 0, K >= 128, N % 8 == 0; M*K*2, N*K*2 < 2^31.  Rows
+// Requirements: K % 64 == 0, K >= 128, N % 16 == 0; M*K*2, N*K*2 < 2^31.  Rows
 // past M and columns past N are read as zeros (per-lane buffer offsets beyond
 // the end of the buffer) and never stored.  `m_rows` <= M limits the rows the
 // tile walk computes.  The remaining rows are left to the caller, or, with
@@ -191,11 +193,11 @@ __global__ __launch_bounds__(NW * 64, 1) void gemm_bf16_persistent_kernel(
             const bool ok = which * NW * 8 + row_lane < a_rows;
             const int vo = ok ? lane_off + a_tile + which * istride : OOB;
             __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rs, (lds_ptr)(dst + (which * NW + wave) * 64), 16, vo, koff, 0, 0);
-        } else {
-            const int i = which - LDA;
-            const bool ok = i * NW * 8 + row_lane < w_rows;
-            const int vo = ok ? lane_off + w_tile + i * istride : OOB;
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(w_rs, (lds_ptr)(dst + A_STAGE + (i * NW + wave) * 64), 16, vo, koff, 0, 0);
+        } else {                                     // weight fragment i * NW + wave of the panel, [BN / 16][slice]
+            const int f = (which - LDA) * NW + wave;
+            const bool ok = (f >> 1) * 16 < w_rows;  // wave-uniform
+            const int vo = ok ? lane * 16 + w_tile + (f >> 1) * K * 32 + (f & 1) * 1024 : OOB;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(w_rs, (lds_ptr)(dst + A_STAGE + f * 64), 16, vo, ld_kt * 2048, 0, 0);
         }
     };
     auto advance_load = [&]() {
@@ -230,12 +232,11 @@ __global__ __launch_bounds__(NW * 64, 1) void gemm_bf16_persistent_kernel(
         asm volatile("" : "+v"(le));
         const int l15 = le & 15, g4 = le >> 4;
         const int fsw = swz(l15), kc4 = ((g4 & 1) << 1) | (g4 >> 1);
-        const int p_row = P_ACT ? (wm0 + l15) * CPR : A_STAGE + (wn0 + l15) * CPR;
-        const int h_row = P_ACT ? A_STAGE + (wn0 + l15) * CPR : (wm0 + l15) * CPR;
 #pragma unroll
         for (int sl = 0; sl < 2; ++sl) {
-            p_off[sl] = p_row + ((sl * 4 + kc4) ^ fsw);
-            h_off[sl] = h_row + ((sl * 4 + kc4) ^ fsw);
+            const int act = (wm0 + l15) * CPR + ((sl * 4 + kc4) ^ fsw), wei = A_STAGE + wn0 * CPR + sl * 64 + le;
+            p_off[sl] = P_ACT ? act : wei;
+            h_off[sl] = P_ACT ? wei : act;
         }
     };
     derive_read_offsets();
@@ -389,9 +390,9 @@ __global__ __launch_bounds__(NW * 64, 1) void gemm_bf16_persistent_kernel(
         for (int u = G - 1 - first_id; u < units; u += G) {
             const int tm0 = m_rows + (u / tn) * tail_tm, tn0 = (u % tn) * ep_skinny::TN;
             if (tail_tm == 64)
-                ep_skinny::tile<EPI, 64>(A, W, bias, resid, Cout, m_rows + tail_rows, N, K, tm0, tn0, scratch);
+                ep_skinny::tile<EPI, 64, true>(A, W, bias, resid, Cout, m_rows + tail_rows, N, K, tm0, tn0, scratch);
             else if (tail_tm == 32)
-                ep_skinny::tile<EPI, 32>(A, W, bias, resid, Cout, m_rows + tail_rows, N, K, tm0, tn0, scratch);
+                ep_skinny::tile<EPI, 32, true>(A, W, bias, resid, Cout, m_rows + tail_rows, N, K, tm0, tn0, scratch);
             else
                 ep_skinny::tile16<EPI>(A, W, bias, resid, Cout, m_rows + tail_rows, N, K, tm0, tn0, scratch);
             __syncthreads();
@@ -554,7 +555,7 @@ hipError_t ep_bf16_gemm_persistent_clock(double *shader_mhz, double *seconds)
 
 bool ep_bf16_gemm_persistent_supported(int64_t M, int N, int K)
 {
-    return M > 0 && N > 0 && K >= 2 * BK && K % BK == 0 && N % 8 == 0 &&
+    return M > 0 && N > 0 && K >= 2 * BK && K % BK == 0 && N % 16 == 0 &&
            M * (int64_t)K * 2 < 0x7FFFFFF0ll && (int64_t)N * K * 2 < 0x7FFFFFF0ll && M * (int64_t)N < (1ll << 31);
 }
 

@@ -30,20 +30,20 @@ using ep_skinny::NW;
 using ep_skinny::SMEM;
 
 // grid: x = column tiles, y = row tiles
-template <int EPI>
+template <int EPI, bool PACKED>
 __global__ __launch_bounds__(NW * 64) void gemm_bf16_skinny_kernel(
     const uint16_t *__restrict__ A, const uint16_t *__restrict__ W, const float *__restrict__ bias,
     const float *resid, void *Cout, int M, int N, int K)
 {
     extern __shared__ float part_raw[];              // [NW][TM][TN] fp32 = 64 KB
-    ep_skinny::tile<EPI>(A, W, bias, resid, Cout, M, N, K, blockIdx.y * TM, blockIdx.x * TN, part_raw);
+    ep_skinny::tile<EPI, TM, PACKED>(A, W, bias, resid, Cout, M, N, K, blockIdx.y * TM, blockIdx.x * TN, part_raw);
 }
 
-template <int EPI>
+template <int EPI, bool PACKED>
 hipError_t launch_skinny(const uint16_t *A, const uint16_t *W, const float *bias, const float *resid, void *C,
                          int M, int N, int K, hipStream_t s)
 {
-    auto kern = gemm_bf16_skinny_kernel<EPI>;
+    auto kern = gemm_bf16_skinny_kernel<EPI, PACKED>;
     static EpSmemLimit smem_limit;
     const hipError_t e = smem_limit.ensure(reinterpret_cast<const void *>(kern), (int)SMEM);
     if (e != hipSuccess) return e;
@@ -60,16 +60,14 @@ bool ep_bf16_gemm_skinny_supported(int64_t M, int N, int K)
            M * (int64_t)K * 2 < 0x7FFFFFF0ll && (int64_t)N * K * 2 < 0x7FFFFFF0ll;
 }
 
-hipError_t ep_bf16_gemm_skinny(const uint16_t *A, const uint16_t *W, const float *bias, const float *resid,
+hipError_t ep_bf16_gemm_skinny(const uint16_t *A, const uint16_t *W, bool packed, const float *bias, const float *resid,
                                void *C, int64_t M, int N, int K, int epi, hipStream_t s)
 {
-    if (!ep_bf16_gemm_skinny_supported(M, N, K)) return hipErrorInvalidValue;
+    if (!ep_bf16_gemm_skinny_supported(M, N, K) || (packed && (K % 64 || N % 16))) return hipErrorInvalidValue;
     if (epi == EPI_BIAS_RESID && !resid) return hipErrorInvalidValue;
-    switch (epi) {
-    case EPI_BIAS: return launch_skinny<EPI_BIAS>(A, W, bias, resid, C, (int)M, N, K, s);
-    case EPI_BIAS_GELU: return launch_skinny<EPI_BIAS_GELU>(A, W, bias, resid, C, (int)M, N, K, s);
-    case EPI_BIAS_RESID: return launch_skinny<EPI_BIAS_RESID>(A, W, bias, resid, C, (int)M, N, K, s);
-    case EPI_BIAS_F32: return launch_skinny<EPI_BIAS_F32>(A, W, bias, resid, C, (int)M, N, K, s);
+    switch (epi) {                                   // the classifier's weights lie row by row, an embedding's in fragment order
+    case EPI_BIAS_RESID: return packed ? launch_skinny<EPI_BIAS_RESID, true>(A, W, bias, resid, C, (int)M, N, K, s) : hipErrorInvalidValue;
+    case EPI_BIAS_F32: return packed ? hipErrorInvalidValue : launch_skinny<EPI_BIAS_F32, false>(A, W, bias, resid, C, (int)M, N, K, s);
     }
     return hipErrorInvalidValue;
 }

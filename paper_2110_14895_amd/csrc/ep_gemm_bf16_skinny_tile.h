@@ -48,7 +48,8 @@ __device__ inline void store_epilogue(float v[4], const float *bias, const float
 
 // All 512 threads of the workgroup call this together.  TMU = 64 or 32: rows of the tile (two or one
 // 32x32x16 MFMA blocks).  lds: SMEM bytes, free on entry; the caller synchronises before it reuses them.
-template <int EPI, int TMU = TM>
+// PACKED: W in fragment order (ep_gemm_bf16_tile.h), K % 64 == 0; otherwise row by row.
+template <int EPI, int TMU, bool PACKED>
 __device__ inline void tile(const uint16_t *__restrict__ A, const uint16_t *__restrict__ W,
                             const float *__restrict__ bias, const float *resid, void *Cout, int M, int N, int K,
                             int m0, int n0, float *lds)
@@ -75,7 +76,13 @@ __device__ inline void tile(const uint16_t *__restrict__ A, const uint16_t *__re
         const int am = m0 + f * 32 + l31;
         a_off[f] = am < M ? (am * K + wave * 16 + g * 8) * 2 : OOB;
     }
-    w_off = n0 + l31 < N ? ((n0 + l31) * K + wave * 16 + g * 8) * 2 : OOB;
+    // in fragment order K chunk kc of a 32-wide block sits with the lanes of quarter kchunk(kc); a wave's slices are four
+    // blocks apart
+    const int kc = (wave & 1) * 2 + g, quarter = ((kc & 1) << 1) | (kc >> 1);
+    const int w_lane = PACKED ? (n0 + l31) / 16 * K * 32 + (wave >> 1) * 1024 + (quarter * 16 + (l31 & 15)) * 16
+                              : ((n0 + l31) * K + wave * 16 + g * 8) * 2;
+    constexpr int W_STEP = PACKED ? NW / 2 * 1024 : NW * 32;
+    w_off = n0 + l31 < N ? w_lane : OOB;
 
     f32x16 acc[MI];
 #pragma unroll
@@ -90,7 +97,7 @@ __device__ inline void tile(const uint16_t *__restrict__ A, const uint16_t *__re
         for (int u = 0; u < U; ++u) {
             const bool live = s0 + u < my_nsl;       // wave-uniform
             const int ko = (s0 + u) * NW * 32;       // bytes: my slices are NW * 16 elements apart
-            fw[u] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(w_rs, live ? w_off + ko : OOB, 0, 0));
+            fw[u] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(w_rs, live ? w_off + (s0 + u) * W_STEP : OOB, 0, 0));
 #pragma unroll
             for (int f = 0; f < MI; ++f)
                 fa[u][f] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(a_rs, live ? a_off[f] + ko : OOB, 0, 0));
@@ -128,7 +135,7 @@ __device__ inline void tile(const uint16_t *__restrict__ A, const uint16_t *__re
 }
 
 // The same for a 16-row tile (16 x 32 outputs, two 16x16x32 MFMA blocks side by side): for long K and
-// few columns, where only narrow tiles give every compute unit one.  K is dealt in 32-wide slices.
+// few columns, where only narrow tiles give every compute unit one.  K is dealt in 32-wide slices; W in fragment order.
 template <int EPI>
 __device__ inline void tile16(const uint16_t *__restrict__ A, const uint16_t *__restrict__ W,
                               const float *__restrict__ bias, const float *resid, void *Cout, int M, int N, int K,
@@ -153,8 +160,7 @@ __device__ inline void tile16(const uint16_t *__restrict__ A, const uint16_t *__
     int w_off[2];
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
-        const int wn = n0 + j * 16 + l15;
-        w_off[j] = wn < N ? (wn * K + wave * 32 + g * 8) * 2 : OOB;
+        w_off[j] = n0 + j * 16 < N ? (n0 + j * 16) * K * 2 + wave * 1024 + ((((g & 1) << 1) | (g >> 1)) * 16 + l15) * 16 : OOB;
     }
 
     f32x4 acc[2];
@@ -173,7 +179,7 @@ __device__ inline void tile16(const uint16_t *__restrict__ A, const uint16_t *__
             fa[u] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(a_rs, live ? a_off + ko : OOB, 0, 0));
 #pragma unroll
             for (int j = 0; j < 2; ++j)
-                fw[u][j] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(w_rs, live ? w_off[j] + ko : OOB, 0, 0));
+                fw[u][j] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(w_rs, live ? w_off[j] + (s0 + u) * NW * 1024 : OOB, 0, 0));
         }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll

@@ -44,7 +44,11 @@ hipError_t ep_bf16_layernorm_widen(const uint16_t *in, float *x, const float *g,
 hipError_t ep_f32_residual_sum(const float *resid, const float *part, int splits, const float *bias, void *out,
                                bool out_bf16, int64_t rows, int D, hipStream_t s);
 hipError_t ep_f32_to_bf16(const float *in, uint16_t *out, int64_t n, hipStream_t s);
-// A bf16 [M, K], W bf16 [N, K]; out bf16 (EPI_BIAS, EPI_BIAS_GELU) or fp32 (EPI_BIAS_RESID).
+// W bf16 [N, K] row by row -> p, the same bytes in the fragment order of ep_gemm_bf16_tile.h, in which every dense layer
+// below but the classifier takes its weights; N % 16 == 0, K % 32 == 0
+hipError_t ep_bf16_pack_weights(const uint16_t *w, uint16_t *p, int N, int K, hipStream_t s);
+// A bf16 [M, K], W bf16 [N, K] in fragment order; out bf16 (EPI_BIAS, EPI_BIAS_GELU) or fp32 (EPI_BIAS_RESID).
+// K % 64 == 0, N % 16 == 0.
 // after_main: if non-null, recorded on s right after the launch (it covers the rows
 // ep_bf16_gemm_main_rows reports: all of them).
 hipError_t ep_bf16_gemm(const uint16_t *A, const uint16_t *W, const float *bias,
@@ -92,8 +96,13 @@ hipError_t ep_bf16_gemm_persistent(const uint16_t *A, const uint16_t *W, const f
 // current device (hipErrorNotReady if none has); copies four counters from the device, so it synchronises.
 hipError_t ep_bf16_gemm_persistent_clock(double *shader_mhz, double *seconds);
 
+// dense layers of small and middling batches (ep_gemm_bf16_stream.hip) with the dispatcher's bm x bn tiles, bn <= 128
+hipError_t ep_bf16_gemm_stream(int bm, int bn, const uint16_t *A, const uint16_t *W, const float *bias, const float *resid,
+                               void *C, int64_t M, int N, int K, int splits, int epi, hipStream_t s);
+
 // short-M kernel (ep_gemm_bf16_skinny.hip): 64 x 32 tiles, K dealt to the 8 waves of a workgroup
 bool ep_bf16_gemm_skinny_supported(int64_t M, int N, int K);
-hipError_t ep_bf16_gemm_skinny(const uint16_t *A, const uint16_t *W, const float *bias,
+// packed: W in fragment order (EPI_BIAS_RESID), otherwise row by row (EPI_BIAS_F32)
+hipError_t ep_bf16_gemm_skinny(const uint16_t *A, const uint16_t *W, bool packed, const float *bias,
                                const float *resid, void *C, int64_t M, int N, int K, int epi,
                                hipStream_t s);

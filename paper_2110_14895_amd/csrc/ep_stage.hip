@@ -373,6 +373,18 @@ extern "C" ep_status ep_stage_create(const ep_vit_config *cfg, int32_t layer_beg
         return fail(ep_fail(EP_ERR_OOM, "ep_stage_create: host staging allocation failed"));
     }
     st->layers.resize(nl);
+    // Layers of the bf16 path arrive, dense weights row by row, in a block of their own and are put in fragment order from
+    // there: in the workspace where that holds a layer (allocating and freeing a block cost 3 ms a stage of six
+    // ViT-Large layers)
+    struct Arrival { char *p = nullptr; bool mine = false; ~Arrival() { if (mine) (void)hipFree(p); } } rows;
+    if (st->bf16 && st->ws_bytes >= layer_bytes) {
+        rows.p = st->ws;
+    } else if (st->bf16) {
+        if ((e = hipMalloc((void **)&rows.p, layer_bytes)) != hipSuccess)
+            return fail(ep_fail(EP_ERR_OOM, "hipMalloc of %zu bytes for a layer's weights failed: %s", layer_bytes, hipGetErrorString(e)));
+        rows.mine = true;
+    }
+    const int dim_n[4] = {(int)(3 * D), (int)D, (int)M, (int)D}, dim_k[4] = {(int)D, (int)D, (int)D, (int)M};
     for (int l = 0; l < nl; ++l) {
         const ep_layer_weights &w = layers[l];
         const void *src_w[4] = {w.w_qkv, w.w_o, w.w_fc1, w.w_fc2};
@@ -389,7 +401,16 @@ extern "C" ep_status ep_stage_create(const ep_vit_config *cfg, int32_t layer_beg
             }
         }
         char *base = st->params + (size_t)l * layer_bytes;
-        e = hipMemcpy(base, stage_buf.data(), layer_bytes, hipMemcpyHostToDevice);
+        if (st->bf16) {
+            // in order on the null stream: each upload behind what still reads the block for the layer before
+            e = hipMemcpy(rows.p, stage_buf.data(), layer_bytes, hipMemcpyHostToDevice);
+            for (int i = 0; i < 4 && e == hipSuccess; ++i)
+                e = ep_bf16_pack_weights((const uint16_t *)(rows.p + off_w[i]), (uint16_t *)(base + off_w[i]), dim_n[i], dim_k[i], nullptr);
+            if (e == hipSuccess)
+                e = hipMemcpyAsync(base + off_v[0], rows.p + off_v[0], layer_bytes - off_v[0], hipMemcpyDeviceToDevice, nullptr);
+        } else {
+            e = hipMemcpy(base, stage_buf.data(), layer_bytes, hipMemcpyHostToDevice);
+        }
         if (e != hipSuccess)
             return fail(ep_fail(EP_ERR_HIP, "parameter upload failed: %s", hipGetErrorString(e)));
         LayerDev &d = st->layers[l];
@@ -399,6 +420,9 @@ extern "C" ep_status ep_stage_create(const ep_vit_config *cfg, int32_t layer_beg
         d.ln2_g = (const float *)(base + off_v[4]); d.ln2_b = (const float *)(base + off_v[5]);
         d.b_fc1 = (const float *)(base + off_v[6]); d.b_fc2 = (const float *)(base + off_v[7]);
     }
+    // forwards run on streams of their own
+    if (st->bf16 && (e = hipStreamSynchronize(nullptr)) != hipSuccess)
+        return fail(ep_fail(EP_ERR_HIP, "parameter upload failed: %s", hipGetErrorString(e)));
     *out = st;
     return EP_OK;
 }

@@ -266,8 +266,18 @@ extern "C" ep_status ep_embed_create(const ep_embed_config *cfg, const void *w_p
         for (int d = 0; d < D; ++d)
             std::memcpy(wp.data() + (size_t)d * e->Kp * psz, (const char *)w_patch + (size_t)d * e->K * psz, (size_t)e->K * psz);
         std::vector<float> v;
-        if ((he = hipMemcpy(e->w, wp.data(), wp.size(), hipMemcpyHostToDevice)) != hipSuccess)
-            return fail(ep_fail(EP_ERR_HIP, "upload failed: %s", hipGetErrorString(he)));
+        if (bf16) {                                  // row by row into a block of their own, from there into fragment order
+            char *rows = nullptr;
+            if ((he = hipMalloc((void **)&rows, wp.size())) != hipSuccess)
+                return fail(ep_fail(EP_ERR_OOM, "hipMalloc of %zu bytes failed: %s", wp.size(), hipGetErrorString(he)));
+            he = hipMemcpy(rows, wp.data(), wp.size(), hipMemcpyHostToDevice);
+            if (he == hipSuccess) he = ep_bf16_pack_weights((const uint16_t *)rows, (uint16_t *)e->w, D, e->Kp, nullptr);
+            if (he == hipSuccess) he = hipStreamSynchronize(nullptr);
+            (void)hipFree(rows);
+        } else {
+            he = hipMemcpy(e->w, wp.data(), wp.size(), hipMemcpyHostToDevice);
+        }
+        if (he != hipSuccess) return fail(ep_fail(EP_ERR_HIP, "upload failed: %s", hipGetErrorString(he)));
         widen(b_patch, D, cfg->param_dtype, v);
         if ((he = hipMemcpy(e->b, v.data(), (size_t)D * 4, hipMemcpyHostToDevice)) != hipSuccess)
             return fail(ep_fail(EP_ERR_HIP, "upload failed: %s", hipGetErrorString(he)));
@@ -423,7 +433,7 @@ extern "C" ep_status ep_head_forward(ep_head_t *h, const void *x, int32_t B, voi
     }
     if (h->bf16) {
         EP_HIP(ep_bf16_layernorm(rows, ld, h->g, h->beta, c.ln_eps, (uint16_t *)h->z, B, D, s));
-        EP_HIP(ep_bf16_gemm_skinny((const uint16_t *)h->z, (const uint16_t *)h->w, h->b, nullptr, logits, B, NC, D,
+        EP_HIP(ep_bf16_gemm_skinny((const uint16_t *)h->z, (const uint16_t *)h->w, false, h->b, nullptr, logits, B, NC, D,
                                    EPI_BIAS_F32, s));
     } else {
         EP_HIP(ep_f32_layernorm(rows, ld, h->g, h->beta, c.ln_eps, (float *)h->z, B, D, s));

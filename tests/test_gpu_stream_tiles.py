@@ -1,0 +1,33 @@
+"""GPU parity of the dense layers whose tiles are at most 128 columns wide (loader waves, weights in fragment order) where
+their pipelines are shorter than they are deep and where rows end inside a tile: K of one to nine steps of 64, one row to
+one past a tile.  Against the checker on the first and the last image; the tolerance is the bf16 path's."""
+import pytest
+
+import oracle
+from paper_2110_14895_amd import synth
+from tests import harness as H
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("T,D,Hh,M,B", [
+    (1, 64, 1, 64, 1),          # one row, one K step everywhere
+    (17, 64, 1, 128, 1),        # one and two steps
+    (64, 128, 2, 192, 1),       # two and three: whole tiles of 64 rows
+    (65, 192, 3, 256, 1),       # three and four, one row past
+    (64, 256, 4, 320, 3),       # four and five
+    (127, 320, 4, 384, 1),      # five and six, d_head 80
+    (129, 448, 7, 512, 1),      # seven and eight
+    (193, 128, 2, 576, 7),      # two and nine, 192-row tiles' remainder
+    (197, 512, 8, 1024, 13),    # K ranges
+])
+def test_short_k_and_ragged_rows(T, D, Hh, M, B):
+    sh = synth.custom_shape(f"stream_{T}_{D}", 2, D, Hh, M, T)
+    p = [synth.layer_params(sh, i, bf16=True, randomize_affine=True, w_std=0.05) for i in range(2)]
+    x = synth.activations(sh, B, bf16=True)
+    st = H.make_stage(sh, p, 0, 2, B, bf16=True)
+    got = H.run_stage(st, x)
+    pick = sorted({0, B - 1})
+    ref = oracle.stage_forward(H.oracle_cfg(sh), p, x[pick])
+    for k, i in enumerate(pick):
+        assert H.rel_err(got[i], ref[k]) <= H.TOL_BF16, i
