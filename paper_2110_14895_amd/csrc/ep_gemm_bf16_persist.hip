@@ -13,33 +13,32 @@
 //   - K advances in steps of 64 (rows of 128 bytes = whole cache lines, which the
 //     L2 -> LDS path moves ~1.6x faster than half lines).  A step's A and W
 //     panels go from global memory straight into LDS with buffer_load ... lds
-//     (no register staging), two stages; the loads a wave issues per step are
-//     slipped one by one between MFMAs, dealt over three quarters of a step:
-//     the first right after the barrier that retires the stage they overwrite,
-//     the rest in the first two quarters of the following step (a burst of all
-//     of them holds every wave at the door of the memory pipeline at once); the
-//     last of them still has half a step to land.
-//   - LDS rows are 8 chunks of 16 bytes; chunk c of row r sits at slot
-//     c ^ f(r), f(r) = (r & 7) ^ ((r >> 3) & 1): the 16-byte fragment reads of 16
-//     consecutive rows are conflict-free on the 64-bank LDS (with the K chunks
-//     dealt to the quarters of a wave in the order 0, 2, 1, 3).  The W panel holds
-//     the fragments that the weights are stored in (ep_gemm_bf16_tile.h), 1 KB to a
-//     load, and is read lane by lane.
+//     (no register staging), two stages.  The A panel has rows of 8 chunks of 16
+//     bytes, chunk c of row r at slot c ^ swz(r); the W panel holds the fragments that
+//     the weights are stored in (ep_gemm_bf16_tile.h), read lane by lane.
 //   - The matrix instruction is v_mfma_f32_16x16x32_bf16: at the power limit
 //     the chip runs the same flops about 15 % faster in this form than as
-//     32 x 32 x 16.  A 32-wide slice of the wave tile is multiplied in four
-//     units of (half the activation fragments) x (half the weight fragments),
-//     ordered so that consecutive units share one of their halves; the
-//     registers of a retired half take the fragments needed two units later,
-//     every LDS read is issued between two MFMAs at least a unit ahead of its
-//     use, and a wave has no phase without matrix work except the one barrier
-//     per step.
+//     32 x 32 x 16.
+//   - A step is multiplied in units of 32 columns of each wave.  What a unit has used is free in
+//     every wave at the next unit's barrier and is refilled then, a few loads at a time, for
+//     the step after next: a load has one to nearly two steps to land, where one
+//     barrier a step left the last loads of a step half a step.  Waits count the
+//     loads that may still be on their way (Tile::in_flight).
+//   - Fragments are read again between the matrix instructions as soon as their last product is out, 8 to
+//     12 instructions ahead of their use, so that one step's worth of activations and one unit's of
+//     weights is all that registers hold.
+// What bounds it: power.  Against the loop with one barrier a step (both in turn, us): 8192 cubed 747 -> 725 (1516
+// TFLOP/s), 16384 x 5120 x 1280 + GELU in 256-wide tiles 198 -> 185, 16384 x 1280 x 5120 + residual 174 -> 166, 16384 x
+// 1280 x 1280 + residual 70.3 -> 65.6, 65792 rows 744 -> 720 and 774 -> 730.  Moving its barrier, its loads or its
+// reads by a few instructions, wave priorities and wider groups of tile rows change nothing any more; the chip
+// lowers its clock as the matrix pipe gets busier (75 % busy at 1.50 GHz, 76 % at 1.58, a library kernel 91 % at 1.39, all
+// under a profiler).  Then the residual epilogue at 6.7 TB/s.
 // Epilogue: 32 x 32 blocks of accumulators (+bias, GELU) are transposed through the
 // W part of the LDS stage the tile's last step has just retired (4 KB per wave),
 // so that global stores and residual loads are whole row segments; the refill of
 // the stage's A part for the next tile is already under way meanwhile (issued
-// before the epilogue, like after any other step), the rest follows it.  The
-// tile's bias values wait in LDS (loaded there during the K loop).
+// before the epilogue, like after any other step), the rest follows it.  The next tile's first step does
+// not wait for the stores.  The tile's bias values wait in LDS (loaded there during the K loop).
 //
 // Operand roles are swapped (MFMA A = W fragment, B = activation fragment) so
 // that a lane owns 4 consecutive output columns of one row.
@@ -57,51 +56,44 @@
 // 16 rows by 32 columns, as narrow as it takes to give every workgroup one; K
 // dealt to the 8 waves, fixed-order sum through LDS), which saves the launch and
 // ramp of a second kernel when M is a few rows more than a multiple of 256.
-#include "ep_kernels.h"
-#include "ep_device.h"
+#include "ep_gemm_bf16_tile.h"
 #include "ep_gemm_bf16_skinny_tile.h"
 #include "ep_launch.h"
 
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
+using namespace ep_tile;
 
-constexpr int BM = 256, BK = 64, STAGES = 2;
-constexpr int NW = 8;                                // waves
-constexpr int CPR = BK / 8;                          // 8 chunks of 16 B per LDS row
-constexpr int NUM_XCD = 8;
-constexpr int GROUP_M = 4;
+constexpr int BM = 256, STAGES = 2;
+constexpr int NW = 8;                                // waves, 4 x 2: 64 rows by half the columns each
 
-// Tile shape: BN columns, waves laid out WM x WN, wave tile (BM/WM) x (BN/WN).
-template <int BN_, int WM_, int WN_>
+// What a wave may have in flight.  A tile is 256 x BN, BN = 64 NU; a K step is multiplied in NU units of 32 columns of the
+// wave.  Region j of a stage's W panel is what the waves read for their unit j: 8 KB, a load to a wave.
+template <int BN_>
 struct Tile {
-    static constexpr int BN = BN_, WM = WM_, WN = WN_;
-    static constexpr int MI = BM / WM / 32, NI = BN / WN / 32;        // 32 x 32 blocks of the wave tile (epilogue)
-    static constexpr int MI16 = 2 * MI, NI16 = 2 * NI;                // 16 x 16 accumulators per wave
+    static constexpr int BN = BN_, NU = BN / 64;
     static constexpr int A_STAGE = BM * CPR, W_STAGE = BN * CPR;      // uint4 per stage and operand
     static constexpr int STAGE_U4 = A_STAGE + W_STAGE;
-    static constexpr int LDA = BM / 8 / NW, LDW = BN / 8 / NW;        // loads per wave per step (8 rows each)
+    static constexpr int LDA = BM / 8 / NW;                           // A loads of a wave and step, 64 rows each
     static constexpr size_t SMEM = (size_t)(STAGES * STAGE_U4 + BN / 4) * sizeof(uint4);   // stages + the tile's bias
-    static_assert(WM * WN == NW && BM % (WM * 32) == 0 && BN % (WN * 32) == 0 && BN % (8 * NW) == 0, "tile shape");
-    // A step's loads are dealt over three groups (a burst of all of them holds every wave at the memory
-    // pipeline's door at once): [0, P0) right after the barrier that retires the stage they fill, [P0, P1)
-    // in the first unit of the next step and [P1, LDA+LDW) in its third unit - or, in the `early` variant
-    // of the kernel, one load more in the first group and the last group in the second unit.  The early
-    // variant serves launches of a single round of tiles, where every operand line is a first touch for
-    // its L2 and takes longer to arrive (FC2 at 16448 rows: -5.8 us); where a workgroup walks several
-    // tiles and finds the W panels of its earlier ones in L2, it costs time (FC1 at 65792 rows: +4.5 %).
-    template <bool EARLY>
-    struct Deal {
-        static constexpr int P0 = EARLY ? 4 : 3, P1 = P0 + 3, LAST_UNIT = EARLY ? 1 : 2;
-        static_assert(P1 < LDA + LDW, "three groups of loads");
-        // the first group refills the A part of a retired stage while the epilogue stages through its W part
-        static_assert(P0 <= LDA, "first loads: A panel only");
-    };
-    static_assert(W_STAGE >= NW * 256, "4 KB of epilogue staging per wave in the W part of a stage");
+    static_assert(BN % 64 == 0 && NU >= 4 && W_STAGE >= NW * 256, "4 KB of epilogue staging per wave in the W part of a stage");
+    // A loads that go out in unit j, and in units 1 .. j - 1
+    static constexpr int a_in(int j) { return j < 1 ? 0 : (LDA * j + NU - 2) / (NU - 1) - (LDA * (j - 1) + NU - 2) / (NU - 1); }
+    static constexpr int a_before(int j) { return j <= 1 ? 0 : a_in(j - 1) + a_before(j - 1); }
+    // Loads of step k go out while step k - 2 is multiplied (the A panel and region j - 1 of W in unit j >= 1, once every
+    // wave has passed that far) and in unit 0 of step k - 1 (region NU - 1); in the last step of a tile all W regions
+    // but that one wait until its epilogue, which stages through them, is over.  The number of loads that may be in flight at
+    // the barrier of unit j: those behind the ones that unit reads (region j + 1, or the next step's region 0 and A
+    // panel), in whichever of the two orders leaves fewer.
+    static constexpr int in_flight(int j, bool last)
+    {
+        const int here = (j >= 1 ? 1 : 0) + a_before(j) + (last || j < 2 ? 0 : j - 1);          // of this step so far
+        if (j == NU - 1) return 1 + here;
+        return (j + 1 < NU - 1 ? NU - 2 - j : 0) + LDA + NU - 1 + here;
+    }
 };
-typedef Tile<256, 2, 4> Tile256;                     // wave tile 128 x 64
-typedef Tile<320, 4, 2> Tile320;                     // wave tile 64 x 160
+typedef Tile<256> Tile256;
+typedef Tile<320> Tile320;
 
 }  // namespace
 
@@ -112,25 +104,20 @@ static __device__ unsigned long long g_clock_sample[4];
 
 namespace {
 
-#define EP_WAIT_VMCNT0() __builtin_amdgcn_s_waitcnt(0x0 | (0x0 << 14) | (0x7 << 4) | (0xF << 8))
-#define EP_WAIT_LGKMCNT0() __builtin_amdgcn_s_waitcnt(0xF | (0x3 << 14) | (0x7 << 4) | (0x0 << 8))
-#define EP_SCHED_FENCE() __builtin_amdgcn_sched_barrier(0)
+enum StepKind { STEP_FIRST, STEP_MIDDLE, STEP_LAST };               // of a tile's K steps
 
-__device__ inline int swz(int row) { return (row & 7) ^ ((row >> 3) & 1); }
-
-template <class T, int EPI, bool EARLY>
+template <class T, int EPI>
 __global__ __launch_bounds__(NW * 64, 1) void gemm_bf16_persistent_kernel(
     const uint16_t *__restrict__ A, const uint16_t *__restrict__ W, const float *__restrict__ bias,
     const float *resid, void *Cout, int M, int m_rows, int N, int K, int tiles_m, int tiles_n, int tail_rows, int tail_tm)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
-    constexpr int BN = T::BN, WN = T::WN, MI = T::MI, NI = T::NI;
-    constexpr int A_STAGE = T::A_STAGE, STAGE_U4 = T::STAGE_U4, LDA = T::LDA, LDW = T::LDW;
-    typedef typename T::template Deal<EARLY> Deal;
-    constexpr int NLD = LDA + LDW, P0 = Deal::P0, P1 = Deal::P1, LAST_UNIT = Deal::LAST_UNIT;
+    constexpr int BN = T::BN, NU = T::NU, MI = 2, NI = NU;            // 32 x 32 blocks of the wave tile (epilogue)
+    constexpr int A_STAGE = T::A_STAGE, STAGE_U4 = T::STAGE_U4, LDA = T::LDA;
+    constexpr bool RESID = EPI == EPI_BIAS_RESID;
+    constexpr int ESZ = RESID ? 4 : 2, STORES = MI * NI * (RESID ? 4 : 2);      // of a wave and tile
 
     extern __shared__ uint4 lds[];                   // [STAGES][A panel | W panel]
-    typedef __attribute__((address_space(3))) void *lds_ptr;
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform: wave-derived addressing stays scalar
@@ -138,7 +125,7 @@ __global__ __launch_bounds__(NW * 64, 1) void gemm_bf16_persistent_kernel(
         g_clock_sample[0] = clock64();
         g_clock_sample[1] = wall_clock64();
     }
-    const int wm0 = (wave / WN) * (MI * 32), wn0 = (wave % WN) * (NI * 32);
+    const int wm0 = (wave >> 1) * 64, wn0 = (wave & 1) * (NU * 32);
 
     // ---- this workgroup's tile list: tile j has logical id j*G + (w%8)*(G/8) + w/8
     const int G = gridDim.x;                         // multiple of 8
@@ -147,7 +134,6 @@ __global__ __launch_bounds__(NW * 64, 1) void gemm_bf16_persistent_kernel(
     if (first_id >= total && tail_rows == 0) return;
     const int n_my = first_id < total ? (total - first_id + G - 1) / G : 0;
     const int KT = K / BK;
-    const int total_it = n_my * KT;
 
     auto tile_origin = [&](int seq, int &m0, int &n0) {
         const int id = seq * G + first_id;
@@ -160,47 +146,36 @@ __global__ __launch_bounds__(NW * 64, 1) void gemm_bf16_persistent_kernel(
         n0 = (in_group / rows) * BN;
     };
 
-    // ---- load stream: one K step ahead of the multiply stream
-    const __amdgpu_buffer_rsrc_t a_rs =
-        __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(A), 0, (int)((size_t)M * K * 2), 0x00020000);
-    const __amdgpu_buffer_rsrc_t w_rs =
-        __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(W), 0, (int)((size_t)N * K * 2), 0x00020000);
-    constexpr int OOB = 0x7FFFFFF0;
-    // load i of a wave fills panel rows (i*NW + wave)*8 .. +7; lane l lands at row l/8, slot l%8 and
-    // fetches chunk slot ^ swz(row); swz sees the row only through l/8 and the parity of wave (NW
-    // is even), so one per-lane offset serves every i.  Out-of-range handling relies on the per-lane
-    // (VGPR) offset alone, which the buffer bounds check always covers.
-    const int row_lane = wave * 8 + (lane >> 3);
-    const int lane_off = (row_lane * K + ((lane & 7) ^ swz(row_lane)) * 8) * 2;
-    const int istride = NW * 8 * K * 2;              // bytes between loads i and i+1
+    // ---- load stream: two K steps ahead of the multiply stream.  The tile's panels are buffers that end behind row M - 1
+    // and column N - 1 (whole weight fragments, so that check is wave-uniform); past the last tile they are empty.
+    const int row_a = wave * 8 + (lane >> 3);        // load i fills panel rows i * 64 + wave * 8 .. + 7
+    const int off_a = row_a * K * 2 + ((lane & 7) ^ swz(row_a)) * 16;
+    const int lane16 = lane * 16;
+    const int w_col = (wave >> 2) * (32 * NU) + (wave >> 1 & 1) * 16;  // region j: the fragment of columns w_col + j * 32 .. + 15
+    const int w_frag = w_col * K * 2 + (wave & 1) * FRAG_BYTES;        // .. of slice wave % 2, bytes from the tile's first
+    const char *a_base = nullptr, *w_base = nullptr;
+    uint32_t a_bytes = 0;
+    int w_cols = 0;                                  // valid columns of the tile
     int ld_seq = 0, ld_kt = 0, ld_stage = 0;
-    int a_tile = OOB, w_tile = OOB;                  // byte offset of the tile's first A / W row, or OOB
-    int a_rows = 0, w_rows = 0;                      // valid panel rows of the tile
-    auto set_load_tile = [&](int seq) {
+    auto set_load_tile = [&](int seq) EP_INLINE {
         int m0 = 0, n0 = 0;
         const bool live = seq < n_my;
         if (live) tile_origin(seq, m0, n0);
-        a_tile = live ? m0 * K * 2 : OOB;
-        w_tile = live ? n0 * K * 2 : OOB;
-        a_rows = live ? M - m0 : 0;
-        w_rows = live ? N - n0 : 0;
+        a_base = reinterpret_cast<const char *>(A) + (size_t)m0 * K * 2;
+        w_base = reinterpret_cast<const char *>(W) + (size_t)n0 * K * 2;
+        a_bytes = live ? (uint32_t)(M - m0) * (uint32_t)K * 2u : 0u;
+        w_cols = live ? N - n0 : 0;
     };
-    // which: 0 .. LDA-1 = A panel, LDA .. LDA+LDW-1 = W panel
-    auto issue_one = [&](int which) {
-        const int koff = ld_kt * (BK * 2);
-        uint4 *dst = lds + ld_stage * STAGE_U4;
-        if (which < LDA) {
-            const bool ok = which * NW * 8 + row_lane < a_rows;
-            const int vo = ok ? lane_off + a_tile + which * istride : OOB;
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rs, (lds_ptr)(dst + (which * NW + wave) * 64), 16, vo, koff, 0, 0);
-        } else {                                     // weight fragment i * NW + wave of the panel, [BN / 16][slice]
-            const int f = (which - LDA) * NW + wave;
-            const bool ok = (f >> 1) * 16 < w_rows;  // wave-uniform
-            const int vo = ok ? lane * 16 + w_tile + (f >> 1) * K * 32 + (f & 1) * 1024 : OOB;
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(w_rs, (lds_ptr)(dst + A_STAGE + f * 64), 16, vo, ld_kt * 2048, 0, 0);
-        }
+    auto issue_a = [&](int i) EP_INLINE {
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(make_rsrc(a_base, a_bytes), (lds_ptr)(lds + ld_stage * STAGE_U4 + (i * NW + wave) * 64), 16,
+                                                 off_a + i * (128 * K), ld_kt * (BK * 2), 0, 0);
     };
-    auto advance_load = [&]() {
+    auto issue_w = [&](int j, int kt, int stage) EP_INLINE {
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(make_rsrc(w_base, w_col + j * 32 < w_cols ? 0x7FFFFFFFu : 0u),
+                                                 (lds_ptr)(lds + stage * STAGE_U4 + A_STAGE + (j * NW + wave) * 64), 16, lane16,
+                                                 w_frag + j * (64 * K) + kt * (NS * FRAG_BYTES), 0, 0);
+    };
+    auto advance_load = [&]() EP_INLINE {
         ld_stage ^= 1;
         if (++ld_kt == KT) {
             ld_kt = 0;
@@ -208,63 +183,27 @@ __global__ __launch_bounds__(NW * 64, 1) void gemm_bf16_persistent_kernel(
         }
     };
 
-    // ---- fragments and accumulators (v_mfma_f32_16x16x32_bf16).  A fragment is 16 panel rows by 32 of K
-    // (lane l: row l % 16, one 8-element K chunk per quarter l / 16 of the wave); accumulator (wi, ai) <->
-    // columns wi*16 + 4*(l/16) + i, row ai*16 + l%16.  A 32-wide slice of the wave tile is multiplied in four
-    // units (P half, H half): P is the side with fewer fragments, both sides are split in halves, and the
-    // units run (a,0) (b,0) (b,1) (a,1) with a, b swapping from slice to slice, so that from one unit to the
-    // next only one half changes and the registers of the half just retired take the fragments needed two
-    // units later: one slice's worth of fragment registers in all, every read a unit or more ahead.
-    constexpr int MI16 = T::MI16, NI16 = T::NI16;
-    constexpr bool P_ACT = MI16 <= NI16;
-    constexpr int PH = (P_ACT ? MI16 : NI16) / 2, HH = (P_ACT ? NI16 : MI16) / 2;
-    constexpr int UM = PH * HH;                      // MFMAs per unit
-    static_assert(PH + 2 * HH <= 2 * UM && 2 * HH <= UM && (UM + 1) / 2 >= P0 && (UM + 1) / 2 >= P1 - P0 &&
-                      (UM + 1) / 2 >= NLD - P1,
-                  "reads and loads fit between the MFMAs of their units");
-    // quarter g4 of the wave multiplies K chunk kc4 of a slice (any assignment works as long as both
-    // operands use it); 0, 2, 1, 3 keeps the 16-byte reads of the four quarters off each other's banks.
-    // The offsets are derived again after every epilogue (from a lane index the compiler cannot see
-    // through), so that they do not occupy registers while a tile is stored.
-    int p_off[2], h_off[2];                          // per 32-wide slice
-    auto derive_read_offsets = [&]() {
+    // ---- fragments and accumulators (v_mfma_f32_16x16x32_bf16).  A unit multiplies two weight fragments a slice (32
+    // columns of the wave) with the four activation fragments a slice of its 64 rows, weight fragment by weight fragment:
+    // each is read again, for the next unit, as soon as its four products are out, 12 matrix instructions ahead of
+    // its use; in the last unit of a step the activation fragments follow each other in the same way, eight ahead.
+    int p_off[NS], h_off;
+    auto derive_read_offsets = [&]() EP_INLINE {     // again after every epilogue: no registers while a tile is stored
         int le = lane;
         asm volatile("" : "+v"(le));
         const int l15 = le & 15, g4 = le >> 4;
-        const int fsw = swz(l15), kc4 = ((g4 & 1) << 1) | (g4 >> 1);
 #pragma unroll
-        for (int sl = 0; sl < 2; ++sl) {
-            const int act = (wm0 + l15) * CPR + ((sl * 4 + kc4) ^ fsw), wei = A_STAGE + wn0 * CPR + sl * 64 + le;
-            p_off[sl] = P_ACT ? act : wei;
-            h_off[sl] = P_ACT ? wei : act;
-        }
+        for (int sl = 0; sl < NS; ++sl) p_off[sl] = (wm0 + l15) * CPR + ((sl * 4 + kchunk(g4)) ^ swz(l15));
+        h_off = A_STAGE + (wave & 1) * 256 + le;
     };
     derive_read_offsets();
-    bf16x8 fp[2][PH], fh[2][HH];
-    f32x4 acc[NI16][MI16];
-    auto read_p = [&](const uint4 *base, int slice, int half, int j) {
-        fp[half][j] = __builtin_bit_cast(bf16x8, base[p_off[slice] + (half * PH + j) * 16 * CPR]);
+    bf16x8 fp[4][NS], fh[2][NS];
+    f32x4 acc[2 * NU][4];
+    auto read_p = [&](const uint4 *stage, int p, int sl) EP_INLINE {
+        fp[p][sl] = __builtin_bit_cast(bf16x8, stage[p_off[sl] + p * 16 * CPR]);
     };
-    auto read_h = [&](const uint4 *base, int slice, int half, int j) {
-        fh[half][j] = __builtin_bit_cast(bf16x8, base[h_off[slice] + (half * HH + j) * 16 * CPR]);
-    };
-    auto zero_acc = [&]() {
-#pragma unroll
-        for (int wi = 0; wi < NI16; ++wi)
-#pragma unroll
-            for (int ai = 0; ai < MI16; ++ai)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) acc[wi][ai][i] = 0.f;
-    };
-    // MFMA q of unit (hp, hh): the P fragments back and forth under each H fragment, so that consecutive
-    // MFMAs share one operand (a little faster than changing both)
-    auto mfma_one = [&](int hp, int hh, int q) {
-        const int jh = q / PH, jp = (jh & 1) ? PH - 1 - q % PH : q % PH;
-        const int ip = hp * PH + jp, ih = hh * HH + jh;
-        if (P_ACT)
-            acc[ih][ip] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fh[hh][jh], fp[hp][jp], acc[ih][ip], 0, 0, 0);
-        else
-            acc[ip][ih] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fp[hp][jp], fh[hh][jh], acc[ip][ih], 0, 0, 0);
+    auto read_h = [&](const uint4 *stage, int j, int h, int sl) EP_INLINE {
+        fh[h][sl] = __builtin_bit_cast(bf16x8, stage[h_off + (j * NW + h * 2 + sl) * 64]);
     };
 
     // The BN bias values of a tile sit in LDS behind the stages, brought there with 4-byte
@@ -286,9 +225,10 @@ __global__ __launch_bounds__(NW * 64, 1) void gemm_bf16_persistent_kernel(
         return *reinterpret_cast<const float4 *>(bias_lds + col + 4 * g4);
     };
 
-    // ---- epilogue of the tile at (m0, n0); `stage` has just been retired and is free LDS.
-    // It goes by 32 x 32 blocks: four accumulators (wj, aj) each.
-    auto epilogue = [&](int m0, int n0, int stage) {
+    // ---- epilogue of the tile at (m0, n0); the W part of `stage` has just been retired and is free LDS.
+    // It goes by 32 x 32 blocks: four accumulators (wj, aj) each.  The tile's rows of C (and of the residual) are buffers
+    // that end behind row m_rows - 1; columns past N lie past any end.  No branches: the next step counts the stores.
+    auto epilogue = [&](int m0, int n0, int stage) EP_INLINE {
         // the lane-dependent addressing of the epilogue is derived afresh for every tile from a lane index
         // the compiler cannot see through: otherwise it computes all of it ahead of the K loop, where the
         // values do not fit in registers next to the accumulators and come back from scratch memory
@@ -296,17 +236,19 @@ __global__ __launch_bounds__(NW * 64, 1) void gemm_bf16_persistent_kernel(
         asm volatile("" : "+v"(le));
         const int l15 = le & 15, g4 = le >> 4, lane = le;
         uint4 *stg = lds + stage * STAGE_U4 + A_STAGE + wave * 256; // 4 KB of the W panel's part
+        const uint32_t tile_bytes = (uint32_t)(min(BM, m_rows - m0) * N * ESZ);
+        const __amdgpu_buffer_rsrc_t c_rs = make_rsrc(reinterpret_cast<const char *>(Cout) + (size_t)m0 * N * ESZ, tile_bytes);
+        const __amdgpu_buffer_rsrc_t r_rs = RESID ? make_rsrc(resid + (size_t)m0 * N, tile_bytes) : c_rs;
 #pragma unroll
         for (int mi = 0; mi < MI; ++mi) {
 #pragma unroll
             for (int ni = 0; ni < NI; ++ni) {
-                const int nblk = n0 + wn0 + ni * 32, mblk = m0 + wm0 + mi * 32;
-                if (EPI == EPI_BIAS_RESID) {
-                    // block [32 m][32 n] fp32: rows of 128 B = 8 chunks of 4 floats
-                    float *C = reinterpret_cast<float *>(Cout);
-                    float4 bq[2];
+                const int nblk = n0 + wn0 + ni * 32, mblk = wm0 + mi * 32;
+                float4 bq[2];
 #pragma unroll
-                    for (int wj = 0; wj < 2; ++wj) bq[wj] = bias4(wn0 + ni * 32 + wj * 16, g4);
+                for (int wj = 0; wj < 2; ++wj) bq[wj] = bias4(wn0 + ni * 32 + wj * 16, g4);
+                if (RESID) {
+                    // block [32 m][32 n] fp32: rows of 128 B = 8 chunks of 4 floats
 #pragma unroll
                     for (int aj = 0; aj < 2; ++aj)
 #pragma unroll
@@ -318,29 +260,23 @@ __global__ __launch_bounds__(NW * 64, 1) void gemm_bf16_persistent_kernel(
                                 make_float4(c[0] + bb.x, c[1] + bb.y, c[2] + bb.z, c[3] + bb.w);
                         }
                     const int rrow = lane >> 3, rc = lane & 7;      // read-back: 8 rows x 8 chunks per pass
-                    float4 v[4], x[4];
+                    const int n = nblk + rc * 4, past = n < N ? 0 : PAST_END;
+                    f32x4 v[4], x[4];
+                    int off[4];
 #pragma unroll
                     for (int p = 0; p < 4; ++p) {
-                        const int r = p * 8 + rrow, m = mblk + r, n = nblk + rc * 4;
-                        x[p] = make_float4(0.f, 0.f, 0.f, 0.f);
-                        if (m < m_rows && n < N) x[p] = *reinterpret_cast<const float4 *>(resid + (size_t)m * N + n);
-                        v[p] = *reinterpret_cast<const float4 *>(&stg[r * 8 + (rc ^ (r & 7))]);
+                        const int r = p * 8 + rrow;
+                        off[p] = ((mblk + r) * N + n) * 4 + past;
+                        x[p] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r_rs, off[p], 0, 0));
+                        v[p] = *reinterpret_cast<const f32x4 *>(&stg[r * 8 + (rc ^ (r & 7))]);
                     }
 #pragma unroll
-                    for (int p = 0; p < 4; ++p) {
-                        const int r = p * 8 + rrow, m = mblk + r, n = nblk + rc * 4;
-                        if (m < m_rows && n < N)
-                            *reinterpret_cast<float4 *>(C + (size_t)m * N + n) =
-                                make_float4(v[p].x + x[p].x, v[p].y + x[p].y, v[p].z + x[p].z, v[p].w + x[p].w);
-                    }
+                    for (int p = 0; p < 4; ++p)
+                        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v[p] + x[p]), c_rs, off[p], 0, 0);
                 } else {
                     // block [32 m][32 n] bf16: rows of 64 B = 4 chunks of 8 bf16; chunk c of row r sits at slot
                     // c ^ ((r >> 2) & 3): four rows span the 64 banks, so the 8-byte writes of 32 rows meet two to
                     // a bank (the best a 64-byte row stride allows) and the 16-byte reads of 4 rows not at all
-                    uint16_t *C = reinterpret_cast<uint16_t *>(Cout);
-                    float4 bq[2];
-#pragma unroll
-                    for (int wj = 0; wj < 2; ++wj) bq[wj] = bias4(wn0 + ni * 32 + wj * 16, g4);
 #pragma unroll
                     for (int aj = 0; aj < 2; ++aj)
 #pragma unroll
@@ -358,11 +294,12 @@ __global__ __launch_bounds__(NW * 64, 1) void gemm_bf16_persistent_kernel(
                             reinterpret_cast<uint2 *>(&stg[r * 4 + ((wj * 2 + (g4 >> 1)) ^ ((r >> 2) & 3))])[g4 & 1] = o;
                         }
                     const int rrow = lane >> 2, rc = lane & 3;      // read-back: 16 rows x 4 chunks per pass
+                    const int n = nblk + rc * 8, past = n < N ? 0 : PAST_END;
 #pragma unroll
                     for (int p = 0; p < 2; ++p) {
-                        const int r = p * 16 + rrow, m = mblk + r, n = nblk + rc * 8;
-                        const uint4 v = stg[r * 4 + (rc ^ ((r >> 2) & 3))];
-                        if (m < m_rows && n < N) *reinterpret_cast<uint4 *>(C + (size_t)m * N + n) = v;
+                        const int r = p * 16 + rrow;
+                        const u32x4 v = *reinterpret_cast<const u32x4 *>(&stg[r * 4 + (rc ^ ((r >> 2) & 3))]);
+                        __builtin_amdgcn_raw_buffer_store_b128(v, c_rs, ((mblk + r) * N + n) * 2 + past, 0, 0);
                     }
                 }
             }
@@ -371,10 +308,12 @@ __global__ __launch_bounds__(NW * 64, 1) void gemm_bf16_persistent_kernel(
 
     // ---- prologue: step 0 into stage 0
     set_load_tile(0);
-#pragma unroll
-    for (int q = 0; q < LDA + LDW; ++q) issue_one(q);
-    advance_load();
     issue_bias(0);
+#pragma unroll
+    for (int i = 0; i < LDA; ++i) issue_a(i);
+#pragma unroll
+    for (int j = 0; j < NU; ++j) issue_w(j, 0, 0);
+    advance_load();
 
     // ---- rows [m_rows, m_rows + tail_rows): tail_tm x 32 tiles, dealt to the workgroups from the end
     // of the tile order backwards (those are the ones with a tile less when the tiles do not divide).  They come
@@ -399,79 +338,87 @@ __global__ __launch_bounds__(NW * 64, 1) void gemm_bf16_persistent_kernel(
         }
     }
 
-    // ---- step 0 has landed, first fragments; then the first loads of step 1 into stage 1
-    zero_acc();
-    EP_WAIT_VMCNT0();
+    // ---- step 1 into stage 1, all but the region that step 0 sends for; once step 0 is there, the first fragments
+#pragma unroll
+    for (int i = 0; i < LDA; ++i) issue_a(i);
+#pragma unroll
+    for (int j = 0; j < NU - 1; ++j) issue_w(j, ld_kt, ld_stage);
+    EP_WAIT_VMCNT(NU - 1 + LDA);                     // (a tile's first step does not wait for its own panels, see below)
+    EP_WAIT_LGKMCNT0();
     __builtin_amdgcn_s_barrier();
+    EP_SCHED_FENCE();
 #pragma unroll
-    for (int j = 0; j < PH; ++j) read_p(lds, 0, 0, j);
+    for (int h = 0; h < 2; ++h)
 #pragma unroll
-    for (int j = 0; j < HH; ++j) read_h(lds, 0, 0, j);
+        for (int sl = 0; sl < NS; ++sl) read_h(lds, 0, h, sl);
 #pragma unroll
-    for (int q = 0; q < P0; ++q) issue_one(q);
+    for (int sl = 0; sl < NS; ++sl)
+#pragma unroll
+        for (int p = 0; p < 4; ++p) read_p(lds, p, sl);
+    EP_SCHED_FENCE();
 
-    int c_seq = 0, c_kt = 0;
-    for (int it = 0; it < total_it; ++it) {
-        const uint4 *cur = lds + (it & 1) * STAGE_U4;
-        const uint4 *nxt = lds + ((it + 1) & 1) * STAGE_U4;
-        const bool tile_end = c_kt == KT - 1;
-        // two 32-wide slices of four units; the stage swap sits before the last two units of the step
-#pragma unroll
-        for (int s = 0; s < 2; ++s) {
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int pa = s, pb = s ^ 1;                   // P half of units 0, 3 and of units 1, 2
-                const int hp = (u == 0 || u == 3) ? pa : pb, hh = u >> 1;
-                const bool post = s == 1 && u >= 2;
-                if (s == 1 && u == 2) {
-                    advance_load();
-                    // all my reads of this stage are done; the next step has landed; swap
-                    EP_WAIT_LGKMCNT0();
-                    EP_WAIT_VMCNT0();
+    int stage = 0;
+    // One step.  The load stream stands at the step after this one when it begins (its region NU - 1 goes out first) and moves
+    // on behind unit 0.
+    auto step = [&](auto kind_c) EP_INLINE {
+        constexpr int KIND = decltype(kind_c)::value;
+        constexpr bool LAST = KIND == STEP_LAST;
+        const uint4 *cur = lds + stage * STAGE_U4;
+        const uint4 *nxt = lds + (stage ^ 1) * STAGE_U4;
+        static_for<NU>([&](auto j_c) EP_INLINE {
+            constexpr int j = decltype(j_c)::value;
+            constexpr bool end = j == NU - 1;
+            static_for<16>([&](auto m_c) EP_INLINE {
+                constexpr int m = decltype(m_c)::value, h = m >> 3, sl = m >> 2 & 1, p = (m >> 2 & 1) ? 3 - (m & 3) : m & 3;
+                f32x4 &c = acc[2 * j + h][p];
+                if constexpr (KIND == STEP_FIRST && sl == 0)
+                    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fh[h][sl], fp[p][sl], f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+                else
+                    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fh[h][sl], fp[p][sl], c, 0, 0, 0);
+                EP_SCHED_FENCE();
+                if constexpr (m == 3) {
+                    // what this unit reads has landed, in everyone's part; everyone is done with what unit j - 1
+                    // multiplied.  In the first step of a tile the stores of the tile before it may still be on their way (before the first
+                    // tile there are none, and step 0 has landed).
+                    if constexpr (LAST && end) EP_WAIT_LGKMCNT0();         // the stage's W part becomes staging
+                    EP_WAIT_VMCNT(T::in_flight(j, LAST) + (KIND == STEP_FIRST && !end ? STORES : 0));
                     __builtin_amdgcn_s_barrier();
-                }
-                const uint4 *src = post ? nxt : cur;            // units 2, 3 read the slice after this one
-                const int rs = u < 2 ? s : (s ^ 1);
-#pragma unroll
-                for (int q = 0; q < UM; ++q) {
-                    mfma_one(hp, hh, q);
-                    if (s == 0 && u == 0 && q == 0) EP_SCHED_FENCE();   // the step's first MFMA waits for old reads only
-                    // fragment reads: the P half of unit 1 first, the H half of units 2, 3 at every other
-                    // MFMA of units 0, 1; the next slice's H half at every other MFMA of unit 2 and its P half
-                    // at the start of unit 3 (the loads below take the MFMA slots in between)
-                    if (u == 0 && q < PH) read_p(src, rs, pb, q);
-                    if (u < 2) {
-                        const int t = u * UM + q - PH;          // slots after the P reads
-                        if (t >= 0 && (t & 1) && (t >> 1) < HH) read_h(src, rs, 1, t >> 1);
-                    }
-                    if (u == 2 && (q & 1) && (q >> 1) < HH) read_h(src, rs, 0, q >> 1);
-                    if (u == 3 && q < PH) read_p(src, rs, pb, q);
-                    if ((q & 1) == 0) {                         // the loads keep their spacing of two MFMA slots
-                        const int k = q >> 1;
-                        if (s == 0 && u == 0 && P0 + k < P1) issue_one(P0 + k);
-                        if (s == 0 && u == LAST_UNIT && P1 + k < NLD) issue_one(P1 + k);
-                        if (post && u == 2 && k < P0) issue_one(k);
-                    }
                     EP_SCHED_FENCE();
                 }
-            }
-        }
-        if (tile_end) {
-            int m0, n0;
-            tile_origin(c_seq, m0, n0);
-            epilogue(m0, n0, it & 1);
-            zero_acc();
-            c_kt = 0;
-            ++c_seq;
-            EP_WAIT_LGKMCNT0();
-            __builtin_amdgcn_s_barrier();           // every wave is done with the staging area and the bias
-            issue_bias(c_seq);
-            derive_read_offsets();
-        } else {
-            ++c_kt;
-        }
+                if constexpr ((m & 3) == 3) {
+                    if constexpr (end) read_h(nxt, 0, h, sl);
+                    else read_h(cur, j + 1, h, sl);
+                }
+                if constexpr (end && h == 1) read_p(nxt, p, sl);
+                if constexpr (j == 0 && m == 5) {
+                    issue_w(NU - 1, ld_kt, ld_stage);
+                    advance_load();
+                }
+                if constexpr (j > 0 && m >= 5 && (m & 1)) {
+                    constexpr int q = (m - 5) / 2;
+                    if constexpr (q < T::a_in(j)) issue_a(T::a_before(j) + q);
+                    else if constexpr (q == T::a_in(j) && !LAST) issue_w(j - 1, ld_kt, ld_stage);
+                }
+                EP_SCHED_FENCE();
+            });
+        });
+        stage ^= 1;
+    };
+    for (int c_seq = 0; c_seq < n_my; ++c_seq) {
+        step(std::integral_constant<int, STEP_FIRST>{});
+        for (int kt = 1; kt < KT - 1; ++kt) step(std::integral_constant<int, STEP_MIDDLE>{});
+        step(std::integral_constant<int, STEP_LAST>{});
+        int m0, n0;
+        tile_origin(c_seq, m0, n0);
+        epilogue(m0, n0, stage ^ 1);
+        EP_WAIT_LGKMCNT0();
+        __builtin_amdgcn_s_barrier();                // every wave is done with the staging area and the bias
+#pragma unroll
+        for (int j = 0; j < NU - 1; ++j) issue_w(j, ld_kt, ld_stage);
+        issue_bias(c_seq + 1);
+        derive_read_offsets();
     }
-    EP_WAIT_VMCNT0();                               // drain the last (empty) loads before LDS is released
+    EP_WAIT_VMCNT(0);                                // drain the last (empty) loads before LDS is released
     if (blockIdx.x == 0 && tid == 0) {
         g_clock_sample[2] = clock64();
         g_clock_sample[3] = wall_clock64();
@@ -490,11 +437,11 @@ hipError_t resident_grid(int *grid)
     return hipSuccess;
 }
 
-template <class T, int EPI, bool EARLY>
+template <class T, int EPI>
 hipError_t launch_persistent(const uint16_t *A, const uint16_t *W, const float *bias, const float *resid,
                              void *C, int M, int m_rows, int N, int K, int tail_rows, int g_grid, hipStream_t s)
 {
-    auto kern = gemm_bf16_persistent_kernel<T, EPI, EARLY>;
+    auto kern = gemm_bf16_persistent_kernel<T, EPI>;
     static EpSmemLimit smem_limit;
     const hipError_t e = smem_limit.ensure(reinterpret_cast<const void *>(kern), (int)T::SMEM);
     if (e != hipSuccess) return e;
@@ -511,15 +458,10 @@ hipError_t launch_tile(const uint16_t *A, const uint16_t *W, const float *bias, 
     int g_grid = 0;
     const hipError_t e = resident_grid(&g_grid);
     if (e != hipSuccess) return e;
-    // a single round of tiles: the variant that sends a step's loads out earlier
-    const bool early = (int64_t)((m_rows + BM - 1) / BM) * ((N + T::BN - 1) / T::BN) <= g_grid;
-    switch (epi * 2 + (early ? 1 : 0)) {
-    case EPI_BIAS * 2: return launch_persistent<T, EPI_BIAS, false>(A, W, bias, resid, C, M, m_rows, N, K, tail_rows, g_grid, s);
-    case EPI_BIAS * 2 + 1: return launch_persistent<T, EPI_BIAS, true>(A, W, bias, resid, C, M, m_rows, N, K, tail_rows, g_grid, s);
-    case EPI_BIAS_GELU * 2: return launch_persistent<T, EPI_BIAS_GELU, false>(A, W, bias, resid, C, M, m_rows, N, K, tail_rows, g_grid, s);
-    case EPI_BIAS_GELU * 2 + 1: return launch_persistent<T, EPI_BIAS_GELU, true>(A, W, bias, resid, C, M, m_rows, N, K, tail_rows, g_grid, s);
-    case EPI_BIAS_RESID * 2: return launch_persistent<T, EPI_BIAS_RESID, false>(A, W, bias, resid, C, M, m_rows, N, K, tail_rows, g_grid, s);
-    case EPI_BIAS_RESID * 2 + 1: return launch_persistent<T, EPI_BIAS_RESID, true>(A, W, bias, resid, C, M, m_rows, N, K, tail_rows, g_grid, s);
+    switch (epi) {
+    case EPI_BIAS: return launch_persistent<T, EPI_BIAS>(A, W, bias, resid, C, M, m_rows, N, K, tail_rows, g_grid, s);
+    case EPI_BIAS_GELU: return launch_persistent<T, EPI_BIAS_GELU>(A, W, bias, resid, C, M, m_rows, N, K, tail_rows, g_grid, s);
+    case EPI_BIAS_RESID: return launch_persistent<T, EPI_BIAS_RESID>(A, W, bias, resid, C, M, m_rows, N, K, tail_rows, g_grid, s);
     }
     return hipErrorInvalidValue;
 }
