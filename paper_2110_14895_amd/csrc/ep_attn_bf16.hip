@@ -66,10 +66,20 @@ struct StreamShape {
     static constexpr int LPW = PARTB / 1024;         // ... per loader wave: one takes the K parts, the other the V parts
     static constexpr int KS = (DH + 31) / 32;        // 32-component steps of the first product
     static constexpr int EB = DH / 16;               // 16-component blocks of the output
+    static constexpr bool SWZ = ROWB == 128;         // 16-byte pieces of a row change places (see piece)
     static constexpr size_t smem = (size_t)NBUF * BUFB;
     static_assert(DH % 16 == 0 && PARTB % 1024 == 0 && NLOADER == 2, "chunk parts are whole loads, one loader per part");
     static_assert(DEPTH * LPW <= 63, "the loaders' counted wait fits the vmcnt field");
 };
+
+// Where piece c (16 bytes) of row r of a K or V part sits.  Rows of 128 bytes start at one of two banks and every read here goes
+// across rows, so at d_head 64 the pieces of eight consecutive rows are dealt to all places of a row (without it bank conflicts
+// were 20 to 27 % of the kernel's clocks); rows of 160 bytes spread by themselves.
+template <int DH>
+__device__ inline int piece(int r, int c)
+{
+    return StreamShape<DH>::SWZ ? c ^ (r & 7) ^ ((r >> 3) & 1) : c;
+}
 
 // maximum over lanes l, l ^ 16, l ^ 32, l ^ 48 (the four quarters of the wave hold the keys of one query):
 // v_permlane16_swap exchanges the odd 16-lane rows of its first operand with the even rows of its
@@ -130,10 +140,18 @@ __device__ __forceinline__ void attn_pass(const u32x4 (&qf)[NQB][StreamShape<DH>
     bf16x8 ones;
 #pragma unroll
     for (int i = 0; i < 8; ++i) ones[i] = (__bf16)1.0f;
+    asm volatile("" : "+v"(ones));                    // four registers, not moves in every step
     // lane's part of the V^T fragment addressing: source lane s = l % 16 of quarter g supplies row 4g + s/4,
     // elements 4 (s % 4) .. + 3 of the 16-component block
-    const int v_lane = (4 * g + (l15 >> 2)) * ROWB + (l15 & 3) * 8;
-    const int k_lane = l15 * ROWB + g * 16;
+    // (blocks of 32 and of 16 rows further on keep the places of the pieces)
+    int v_lane[EB], k_lane[KS];
+    {
+        const int r = 4 * g + (l15 >> 2);
+#pragma unroll
+        for (int eb = 0; eb < EB; ++eb) v_lane[eb] = r * ROWB + piece<DH>(r, eb * 2 + ((l15 >> 1) & 1)) * 16 + (l15 & 1) * 8;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) k_lane[ks] = l15 * ROWB + piece<DH>(l15, ks * 4 + g) * 16;
+    }
 
     float mref[NQB];                                                // reference maximum, in scaled log2 units
 #pragma unroll
@@ -152,8 +170,31 @@ __device__ __forceinline__ void attn_pass(const u32x4 (&qf)[NQB][StreamShape<DH>
         const char *Vb = Kb + PARTB;
         if (c == (nch > 1 ? 1 : 0)) mid();
         const int nsub = min(SUBS, (T - c * CK + 31) / 32); // 32-key steps that hold a key (wave-uniform)
+        // K fragments of a 32-key step, and V^T fragments.  At d_head 64 they are sent for a softmax ahead of their use, which a
+        // wave that is alone on its SIMD would otherwise wait for (577 tokens, 24 pairs: 9.5 -> 8.7 us a launch); at 80 the
+        // registers run out (64 images of 257 tokens 49 -> 62 us).
+        bf16x8 kf[KS][2], vf[EB];
+        auto read_k = [&](int sub) {
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+                for (int kb = 0; kb < 2; ++kb)
+                    kf[ks][kb] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(Kb + k_lane[ks] + (sub * 32 + kb * 16) * ROWB));
+        };
+        auto read_v = [&](int sub) {
+#pragma unroll
+            for (int eb = 0; eb < EB; ++eb) {
+                typedef __attribute__((address_space(3))) s16x4 *tr_ptr;
+                typedef short s16x8 __attribute__((ext_vector_type(8)));
+                const char *vp = Vb + v_lane[eb] + (sub * 32) * ROWB;
+                const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((tr_ptr)(vp));
+                const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((tr_ptr)(vp + 16 * ROWB));
+                const s16x8 both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+                vf[eb] = __builtin_bit_cast(bf16x8, both);
+            }
+        };
         // S^T = K . Q^T: s[kb][qb][i] <-> key key0 + kb*16 + 4g + i, query q0 + qb*16 + l15
-        auto scores = [&](int sub, f32x4 (&s)[2][NQB]) {
+        auto scores = [&](f32x4 (&s)[2][NQB]) {
 #pragma unroll
             for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
@@ -161,28 +202,40 @@ __device__ __forceinline__ void attn_pass(const u32x4 (&qf)[NQB][StreamShape<DH>
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
-                for (int kb = 0; kb < 2; ++kb) {
-                    const bf16x8 kf = __builtin_bit_cast(
-                        bf16x8, *reinterpret_cast<const uint4 *>(Kb + k_lane + (sub * 32 + kb * 16) * ROWB + ks * 64));
+                for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
                     for (int qb = 0; qb < NQB; ++qb)
-                        s[kb][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, __builtin_bit_cast(bf16x8, qf[qb][ks]), s[kb][qb], 0, 0, 0);
-                }
+                        s[kb][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[ks][kb], __builtin_bit_cast(bf16x8, qf[qb][ks]), s[kb][qb], 0, 0, 0);
         };
         // With one query block a wave is alone on its SIMD and one step after the other is a chain: there the next
         // step's scores are on the matrix pipe while this step's go through the vector ALU (577 tokens, 24 pairs:
         // twelve layers 774 -> 764 us).  With two blocks and two or three waves to a SIMD it gains nothing, and at
         // d_head 80 the registers run out (three layers of 256 images 7945 -> 7971).
         constexpr bool AHEAD = NQB == 1;
+        constexpr bool EARLY = DH == 64;
         f32x4 sc[AHEAD ? 2 : 1][2][NQB];
-        if (AHEAD) scores(0, sc[0]);
+        if (EARLY || AHEAD) read_k(0);
+        if (AHEAD) {
+            scores(sc[0]);
+            if (EARLY && nsub > 1) read_k(1);
+        }
 #pragma unroll
         for (int sub = 0; sub < SUBS; ++sub) {
             if (sub >= nsub) break;                         // nothing but padding from here on
-            if (!AHEAD)
-                scores(sub, sc[0]);
-            else if (sub + 1 < SUBS && sub + 1 < nsub)
-                scores(sub + 1, sc[AHEAD ? (sub + 1) & 1 : 0]);
+            if (!AHEAD) {
+                if (!EARLY) read_k(sub);
+                scores(sc[0]);
+            }
+            if (EARLY) read_v(sub);
+            if (AHEAD && sub + 1 < SUBS && sub + 1 < nsub) {
+                if (!EARLY) read_k(sub + 1);
+                scores(sc[AHEAD ? (sub + 1) & 1 : 0]);
+            }
+            if (EARLY) {
+                constexpr int next = AHEAD ? 2 : 1;         // the step whose scores come next
+                if (sub + next < SUBS && sub + next < nsub) read_k(sub + next);
+                __builtin_amdgcn_sched_barrier(0);
+            }
             f32x4 (&s)[2][NQB] = sc[AHEAD ? sub & 1 : 0];
             const int key0 = c * CK + sub * 32;
             if (key0 + 32 > T) {                            // wave-uniform: keys to mask in the last step only
@@ -227,19 +280,12 @@ __device__ __forceinline__ void attn_pass(const u32x4 (&qf)[NQB][StreamShape<DH>
                 pf[qb] = __builtin_bit_cast(bf16x8, pw);
             }
             // ---- O^T += V^T . P^T and the denominators
+            if (!EARLY) read_v(sub);
 #pragma unroll
-            for (int eb = 0; eb < EB; ++eb) {
-                typedef __attribute__((address_space(3))) s16x4 *tr_ptr;
-                const char *vp = Vb + v_lane + (sub * 32) * ROWB + eb * 32;
-                const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((tr_ptr)(vp));
-                const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((tr_ptr)(vp + 16 * ROWB));
-                typedef short s16x8 __attribute__((ext_vector_type(8)));
-                const s16x8 both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-                const bf16x8 vf = __builtin_bit_cast(bf16x8, both);
+            for (int eb = 0; eb < EB; ++eb)
 #pragma unroll
                 for (int qb = 0; qb < NQB; ++qb)
-                    acc_o[eb][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, pf[qb], acc_o[eb][qb], 0, 0, 0);
-            }
+                    acc_o[eb][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[eb], pf[qb], acc_o[eb][qb], 0, 0, 0);
 #pragma unroll
             for (int qb = 0; qb < NQB; ++qb)
                 acc_sum[qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pf[qb], acc_sum[qb], 0, 0, 0);
@@ -372,7 +418,7 @@ __global__ __launch_bounds__((MAXQW + NLOADER) * 64) void attn_stream_kernel(con
     if (loader) {
         // ---- loader waves: loader 0 brings the K part of every chunk, loader 1 the V part, LPW loads of
         // 1 KB each (64 lanes x 16 bytes, contiguous in LDS); lane l of load s fetches the 16 bytes at linear
-        // byte s*1024 + 16 l of the part, i.e. row lin / ROWB, byte lin % ROWB of the row.  Rows at or past T
+        // byte s*1024 + 16 l of the part, i.e. row lin / ROWB, piece(lin % ROWB / 16) of the row.  Rows at or past T
         // lie past the end of the buffer descriptor (per-lane offset, which the bounds check covers) and read
         // as zeros.
         const int lw = wave - nqw;
@@ -380,7 +426,7 @@ __global__ __launch_bounds__((MAXQW + NLOADER) * 64) void attn_stream_kernel(con
 #pragma unroll
         for (int s = 0; s < LPW; ++s) {
             const int lin = s * 1024 + lane * 16;
-            goff[s] = (lin / ROWB) * row_bytes + lin % ROWB;
+            goff[s] = (lin / ROWB) * row_bytes + piece<DH>(lin / ROWB, lin % ROWB / 16) * 16;      // (its own inverse)
         }
         int pf_unit = unit, pf_pair = unit / ng, pf_chunk = 0;       // the next chunk to fetch
         auto issue = [&](int buf) {
@@ -434,8 +480,11 @@ __global__ __launch_bounds__((MAXQW + NLOADER) * 64) void attn_stream_kernel(con
 // (microseconds per launch, before -> after, T = 197, d_head 64: 16 pairs 8.5 -> 5.5, 80 pairs 8.8 -> 6.7, 128
 // pairs 8.9 -> 7.4; T = 577: 24 pairs 35.1 -> 10.9, 96 pairs 36.3 -> 22.0; T = 257, d_head 80: 16 pairs
 // 10.9 -> 6.0); a second round of units would cost more than it saves (160 pairs at T = 197: 9.4 us with one group,
-// 12.0 with two).  Tiles of 16 queries where they leave the busiest SIMD with fewer 16-query blocks than tiles of
-// 32 (96 pairs at T = 257: 9.5 against 10.3 us), up to nine waves: every wave reads all keys and values from LDS
+// 12.0 with two).  In one round of units tiles of 16 queries, up to nine waves: a step of 32 keys is a chain (reads, scores, maximum,
+// exponentials, second product) that takes a lone wave some 1100 clocks for two blocks of 16 queries and 650 for one,
+// and two waves of one block to a SIMD fill each other's waits (80 pairs at T = 197, three groups of five waves: 6.4 us
+// against 7.1 with three waves of 32; 48 pairs at T = 577 12.2 against 13.0; 64 pairs at T = 257, d_head 80, 8.0 against
+// 9.0).  Beyond nine every wave's reading all keys and values from LDS costs more
 // (60 pairs at T = 577: ten waves of 16 queries take 16.7 us, five of 32 15.8).  More than 320 queries to a group
 // do not fit the query waves of a workgroup.  No more groups than hold a query: 17 tiles (T = 257) in groups of two are
 // nine, and the workgroups of seven more would bring in all keys and values for nothing.
@@ -449,7 +498,7 @@ AttnPlan plan_attention(int64_t pairs, int T, int n_cu)
     if (most <= ng_min) return {32, ng_min};
     const int ng = most < t16 ? most : t16;
     const int w32 = (t32 + ng - 1) / ng, w16 = (t16 + ng - 1) / ng;     // tiles to a group
-    if (w16 <= 9 && (w16 + 3) / 4 < 2 * ((w32 + 3) / 4)) return {16, (t16 + w16 - 1) / w16};
+    if (w16 <= 9) return {16, (t16 + w16 - 1) / w16};
     return {32, (t32 + w32 - 1) / w32};
 }
 
