@@ -2,8 +2,9 @@
 // exactness matters more than speed: fp32 operands, products and sums everywhere.
 // The matrix products run on v_mfma_f32_16x16x4_f32 (fp32 in, fp32 accumulation,
 // twice the vector ALU's unpacked rate):
-//   dense layers   few tiles: 16 x 16 or 32 x 32 outputs per workgroup, K dealt to its four waves, operands straight
-//                  from memory into fragments, LayerNorm of the input rows done on the way where it comes first;
+//   dense layers   few tiles: 16 x 16 to 32 x 32 outputs per workgroup, K dealt to its four waves, each with its own part
+//                  of LDS, LayerNorm of the input rows done on the way where it comes first;
+//                  many rows behind a LayerNorm, K <= 384: 64 rows per workgroup, normalised and kept in registers;
 //                  many tiles: 64 x 32 outputs, K panels through LDS;
 //   attention      16 queries to a wave, online softmax: 16 to a workgroup whose four waves share the keys and merge at
 //                  the end while queries are few, else 64 to a workgroup whose waves each meet all keys.
@@ -163,7 +164,7 @@ __device__ inline bool f32_tile_of(int tiles_n, int tiles, int *tm, int *tn)
 }
 inline dim3 f32_tile_grid(int64_t tiles) { return dim3((unsigned)((tiles + 7) / 8 * 8)); }
 
-// Few tiles: one 16 MI x 16 MI tile per workgroup.  Such a launch is a chain of latencies (a 65-row layer has 60 to
+// Few tiles: one 16 MR x 16 MC tile per workgroup.  Such a launch is a chain of latencies (a 65-row layer has 60 to
 // 240 tiles of 16 x 16), so no wave waits for another on the way in: the 16-wide K slices are dealt to the four waves
 // and each brings its own from memory into its own part of LDS (buffer_load ... lds, R slices ahead, four lanes to
 // a 64-byte row piece; fragments loaded straight into registers would have every lane of a quarter wave on a row of its
@@ -174,15 +175,15 @@ inline dim3 f32_tile_grid(int64_t tiles) { return dim3((unsigned)((tiles + 7) / 
 // the launch of LayerNorm and a trip through memory.
 // LDS rows are 64 bytes, four rows to all the banks: piece c of row r sits at slot c ^ (r >> 2 & 3), so that the
 // 16-byte reads of 16 rows meet no bank twice.
-template <int MI, int LN>
+template <int MR, int MC, int LN>
 struct F32Direct {
-    static constexpr int T = 16 * MI, R = LN ? LN : (MI == 1 ? 6 : 4), LP = T + 4;
-    static constexpr int SLICE = 2 * T * 4;                         // 16-byte pieces of a slice: A rows, then W rows
-    static constexpr size_t ring = (size_t)4 * R * SLICE * 16, sums = (size_t)4 * T * LP * 4;
+    static constexpr int TR = 16 * MR, TC = 16 * MC, R = LN ? LN : (MR + MC == 2 ? 6 : 4), LP = TC + 4;
+    static constexpr int SLICE = (TR + TC) * 4;                         // 16-byte pieces of a slice: A rows, then W rows
+    static constexpr size_t ring = (size_t)4 * R * SLICE * 16, sums = (size_t)4 * TR * LP * 4;
     static constexpr size_t smem = ring > sums ? ring : sums;       // the sums reuse the ring
 };
 
-template <int MI, int EPI, int LN>
+template <int MR, int MC, int EPI, int LN>
 __global__ __launch_bounds__(256) void gemm_f32_direct_kernel(const float *__restrict__ A, const float *__restrict__ ln_g,
                                                               const float *__restrict__ ln_b, float eps,
                                                               const float *__restrict__ W, const float *__restrict__ bias,
@@ -190,19 +191,19 @@ __global__ __launch_bounds__(256) void gemm_f32_direct_kernel(const float *__res
                                                               int tiles, int vec)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
-    using S = F32Direct<MI, LN>;
-    constexpr int T = S::T, R = S::R;
+    using S = F32Direct<MR, MC, LN>;
+    constexpr int TR = S::TR, TC = S::TC, R = S::R;
     extern __shared__ uint4 lds_raw[];
-    __shared__ float stat[2][4][T];
+    __shared__ float stat[2][4][TR];
     typedef __attribute__((address_space(3))) void *lds_ptr;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l15 = lane & 15, g = lane >> 4;
     int tm, tn;
     if (!f32_tile_of(tiles_n, tiles, &tm, &tn)) return;
-    const int64_t m0 = (int64_t)tm * T;
-    const int n0 = tn * T;
+    const int64_t m0 = (int64_t)tm * TR;
+    const int n0 = tn * TC;
     const int nsl = (K + 15) / 16, my = (nsl - wave + 3) / 4;       // slices of all, of this wave (wave, wave + 4, ...)
     // rows past M or N lie past the end of the panel's descriptor, pieces past K get such an offset: both read as zeros
-    const int am = (int)(M - m0 < T ? M - m0 : T), wn = N - n0 < T ? N - n0 : T;
+    const int am = (int)(M - m0 < TR ? M - m0 : TR), wn = N - n0 < TC ? N - n0 : TC;
     const __amdgpu_buffer_rsrc_t a_rs = make_rsrc(A + m0 * K, am * K * 4), w_rs = make_rsrc(W + (int64_t)n0 * K, wn * K * 4);
     uint4 *ring = lds_raw + wave * R * S::SLICE;
     const int lrow = lane >> 2, lk = ((lane & 3) ^ ((lrow >> 2) & 3)) * 4;
@@ -210,27 +211,27 @@ __global__ __launch_bounds__(256) void gemm_f32_direct_kernel(const float *__res
         uint4 *dst = ring + (t % R) * S::SLICE;
         const int k = (wave + 4 * t) * 16 + lk;
 #pragma unroll
-        for (int i = 0; i < MI; ++i) {
+        for (int i = 0; i < MR || i < MC; ++i) {
             const int off = k < K ? ((i * 16 + lrow) * K + k) * 4 : F32_OOB;
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rs, (lds_ptr)(dst + i * 64), 16, off, 0, 0, 0);
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(w_rs, (lds_ptr)(dst + T * 4 + i * 64), 16, off, 0, 0, 0);
+            if (i < MR) __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rs, (lds_ptr)(dst + i * 64), 16, off, 0, 0, 0);
+            if (i < MC) __builtin_amdgcn_raw_ptr_buffer_load_lds(w_rs, (lds_ptr)(dst + TR * 4 + i * 64), 16, off, 0, 0, 0);
         }
     };
     const int rd = l15 * 4 + (g ^ ((l15 >> 2) & 3));
     auto frag = [&](int t, int part, int i) {                       // part 0: A rows, 1: W rows
-        return reinterpret_cast<const frag4 *>(ring + (t % R) * S::SLICE)[part * T * 4 + i * 64 + rd];
+        return reinterpret_cast<const frag4 *>(ring + (t % R) * S::SLICE)[part * TR * 4 + i * 64 + rd];
     };
 
-    f32x4 acc[MI][MI];
+    f32x4 acc[MC][MR];
 #pragma unroll
-    for (int ni = 0; ni < MI; ++ni)
+    for (int ni = 0; ni < MC; ++ni)
 #pragma unroll
-        for (int mi = 0; mi < MI; ++mi) acc[ni][mi] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int mi = 0; mi < MR; ++mi) acc[ni][mi] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int t = 0; t < R; ++t) issue(t);
 
     if (LN) {
-        frag4 fa[R][MI], gg[R], bb[R];
+        frag4 fa[R][MR], gg[R], bb[R];
         const __amdgpu_buffer_rsrc_t g_rs = make_rsrc(ln_g, K * 4), b_rs = make_rsrc(ln_b, K * 4);
         auto col = [&](int t) { return (wave + 4 * t) * 16 + 4 * g; };          // first k of this lane in slice t
 #pragma unroll
@@ -242,12 +243,12 @@ __global__ __launch_bounds__(256) void gemm_f32_direct_kernel(const float *__res
 #pragma unroll
         for (int t = 0; t < R; ++t)
 #pragma unroll
-            for (int i = 0; i < MI; ++i) fa[t][i] = frag(t, 0, i);
-        float mean[MI], inv[MI];
+            for (int i = 0; i < MR; ++i) fa[t][i] = frag(t, 0, i);
+        float mean[MR], inv[MR];
 #pragma unroll
         for (int pass = 0; pass < 2; ++pass) {
 #pragma unroll
-            for (int i = 0; i < MI; ++i) {
+            for (int i = 0; i < MR; ++i) {
                 float s = 0.f;
 #pragma unroll
                 for (int t = 0; t < R; ++t) {
@@ -265,7 +266,7 @@ __global__ __launch_bounds__(256) void gemm_f32_direct_kernel(const float *__res
             }
             __syncthreads();
 #pragma unroll
-            for (int i = 0; i < MI; ++i) {
+            for (int i = 0; i < MR; ++i) {
                 const int r = i * 16 + l15;
                 const float s = ((stat[pass][0][r] + stat[pass][1][r]) + (stat[pass][2][r] + stat[pass][3][r])) / (float)K;
                 if (pass == 0) mean[i] = s;
@@ -274,30 +275,31 @@ __global__ __launch_bounds__(256) void gemm_f32_direct_kernel(const float *__res
         }
 #pragma unroll
         for (int t = 0; t < R; ++t) {
-            frag4 fw[MI];
+            frag4 fw[MC];
 #pragma unroll
-            for (int i = 0; i < MI; ++i) {
-                fw[i] = frag(t, 1, i);
-                fa[t][i] = fa[t][i] * inv[i] * gg[t] + bb[t];       // zero beyond K: gain and shift are
-            }
+            for (int i = 0; i < MC; ++i) fw[i] = frag(t, 1, i);
 #pragma unroll
-            for (int ni = 0; ni < MI; ++ni)
+            for (int i = 0; i < MR; ++i) fa[t][i] = fa[t][i] * inv[i] * gg[t] + bb[t];     // zero beyond K: gain and shift are
 #pragma unroll
-                for (int mi = 0; mi < MI; ++mi) acc[ni][mi] = mfma_slice(fw[ni], fa[t][mi], acc[ni][mi]);
+            for (int ni = 0; ni < MC; ++ni)
+#pragma unroll
+                for (int mi = 0; mi < MR; ++mi) acc[ni][mi] = mfma_slice(fw[ni], fa[t][mi], acc[ni][mi]);
         }
     } else {
         for (int t = 0; t < my; ++t) {
             // slice t has landed once at most the loads of the R - 1 slices after it are in flight
-            constexpr int V = (R - 1) * 2 * MI;
+            constexpr int V = (R - 1) * (MR + MC);
             __builtin_amdgcn_s_waitcnt((V & 0xF) | (V >> 4 << 14) | (0x7 << 4) | (0xF << 8));
             asm volatile("" ::: "memory");
-            frag4 fa[MI], fw[MI];
+            frag4 fa[MR], fw[MC];
 #pragma unroll
-            for (int i = 0; i < MI; ++i) { fa[i] = frag(t, 0, i); fw[i] = frag(t, 1, i); }
+            for (int i = 0; i < MR; ++i) fa[i] = frag(t, 0, i);
 #pragma unroll
-            for (int ni = 0; ni < MI; ++ni)
+            for (int i = 0; i < MC; ++i) fw[i] = frag(t, 1, i);
 #pragma unroll
-                for (int mi = 0; mi < MI; ++mi) acc[ni][mi] = mfma_slice(fw[ni], fa[mi], acc[ni][mi]);
+            for (int ni = 0; ni < MC; ++ni)
+#pragma unroll
+                for (int mi = 0; mi < MR; ++mi) acc[ni][mi] = mfma_slice(fw[ni], fa[mi], acc[ni][mi]);
             __builtin_amdgcn_s_waitcnt(0xF | (0x3 << 14) | (0x7 << 4) | (0x0 << 8));       // lgkmcnt: the slice has been read
             asm volatile("" ::: "memory");
             issue(t + R);                                           // past the last slice: zeros, to keep the count
@@ -307,16 +309,16 @@ __global__ __launch_bounds__(256) void gemm_f32_direct_kernel(const float *__res
 
     // acc[ni][mi][i] <-> column ni*16 + 4 g + i, row mi*16 + l15
     __syncthreads();
-    float (*part)[T][S::LP] = reinterpret_cast<float (*)[T][S::LP]>(lds_raw);
+    float (*part)[TR][S::LP] = reinterpret_cast<float (*)[TR][S::LP]>(lds_raw);
 #pragma unroll
-    for (int mi = 0; mi < MI; ++mi)
+    for (int mi = 0; mi < MR; ++mi)
 #pragma unroll
-        for (int ni = 0; ni < MI; ++ni)
+        for (int ni = 0; ni < MC; ++ni)
             *reinterpret_cast<float4 *>(&part[wave][mi * 16 + l15][ni * 16 + g * 4]) =
                 make_float4(acc[ni][mi][0], acc[ni][mi][1], acc[ni][mi][2], acc[ni][mi][3]);
     __syncthreads();
-    for (int id = tid; id < T * T / 4; id += 256) {
-        const int r = id / (T / 4), c = id % (T / 4) * 4;
+    for (int id = tid; id < TR * TC / 4; id += 256) {
+        const int r = id / (TC / 4), c = id % (TC / 4) * 4;
         float v[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) v[i] = (part[0][r][c + i] + part[1][r][c + i]) + (part[2][r][c + i] + part[3][r][c + i]);
@@ -413,6 +415,151 @@ __global__ __launch_bounds__(256, 4) void gemm_f32_tile_kernel(const float *__re
             const float v[4] = {acc[ni][mi][0], acc[ni][mi][1], acc[ni][mi][2], acc[ni][mi][3]};
             if (m < M && n < N) store_four<EPI>(v, bias, resid, C, m, n, N, vec);
         }
+#endif
+}
+
+// LayerNorm and the dense layer after it, many rows, K <= 16 NS: 64 rows to a workgroup, which stay in registers (each of
+// its eight waves holds 16 of them, all K, normalised there: a row's sums need two shuffles and no exchange between
+// waves) while the weights pass by in steps of 32 columns, 16 for each half of the waves.  Three steps of weights in
+// LDS, two on their way: the first is fetched with the rows, the other two use the rows' place once those are in registers.
+// LDS: chunks of 32 k, rows of eight 16-byte pieces, placed and dealt to the quarters of a wave as in the tile kernel.
+// Every load of the loop goes to LDS; what goes to registers (gain, shift, bias) is waited for before it begins.
+//   What bounds it: the matrix instructions of a step (1.3 us at full clock, 1.7 to 2.3 measured), before them the rows'
+// way from memory and their sums, about a step's time.  The halves of the waves share the SIMDs and store in turns, one
+// while the other multiplies.  Before: LayerNorm as a launch of its own and the 64 x 32 tiles: 1576 x 576 x 192
+// 10.1 us, now 8.4; 1576 x 768 x 192 with GELU 13.1, now 11.4; 6304 x 768 x 192 32.1, now 27.3; 394 x 1536 x 384, then
+// on 32 x 32 tiles, 17.8, now 13.6.  Four sums per output: against 64 bits 1.2e-7 where one long sum had 2.1e-7.
+template <int NS>
+struct F32Rows {
+    static constexpr int T = 64, CN = 32, MAX_STEPS = 32;
+    static constexpr int A_PIECES = NS / 2 * T * 8, W_PIECES = NS / 2 * CN * 8;
+    static constexpr int A_LOADS = A_PIECES / 512, W_LOADS = W_PIECES / 512;      // of each wave
+    static constexpr size_t smem = (size_t)(A_PIECES + W_PIECES) * 16;            // rows | step 0; later steps 1 and 2 | step 0
+    static_assert(A_PIECES == 2 * W_PIECES && A_PIECES % 512 == 0 && W_PIECES % 512 == 0, "");
+};
+
+template <int NS, int EPI>
+__global__ __launch_bounds__(512, NS <= 12 ? 4 : 2) void gemm_f32_rows_kernel(
+    const float *__restrict__ A, const float *__restrict__ ln_g, const float *__restrict__ ln_b, float eps,
+    const float *__restrict__ W, const float *__restrict__ bias, float *C, int64_t M, int N, int K, int steps, int groups,
+    int tiles, int vec)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    using S = F32Rows<NS>;
+    extern __shared__ uint4 lds_raw[];
+    __shared__ __align__(16) float gs[NS * 16], bs[NS * 16], cs[S::MAX_STEPS * S::CN];
+    typedef __attribute__((address_space(3))) void *lds_ptr;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l15 = lane & 15, g = lane >> 4;
+    int tm, tg;
+    if (!f32_tile_of(groups, tiles, &tm, &tg)) return;
+    const int64_t m0 = (int64_t)tm * S::T;
+    const int n0 = tg * steps * S::CN;
+    auto swz = [](int r) { return (r & 7) ^ ((r >> 3) & 1); };
+    // rows past M or N lie past the end of the panel's descriptor, pieces past K get such an offset: both read as zeros
+    const int am = (int)(M - m0 < S::T ? M - m0 : S::T), wn = N - n0 < steps * S::CN ? N - n0 : steps * S::CN;
+    const __amdgpu_buffer_rsrc_t a_rs = make_rsrc(A + m0 * K, am * K * 4), w_rs = make_rsrc(W + (int64_t)n0 * K, wn * K * 4);
+    auto slot = [&](int st) { return st % 3 == 0 ? S::A_PIECES : (st % 3 - 1) * S::W_PIECES; };
+    auto load = [&](__amdgpu_buffer_rsrc_t rs, int dst, int chunk, int row0, int first) {   // rows row0 .. + 7 of a panel in LDS
+        const int r = row0 + (lane >> 3), k = chunk * 32 + ((lane & 7) ^ swz(r)) * 4;
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr)(lds_raw + dst), 16, k < K ? ((first + r) * K + k) * 4 : F32_OOB, 0, 0, 0);
+    };
+    auto issue = [&](int st) {                                      // past the last step: zeros, to keep the count
+#pragma unroll
+        for (int i = 0; i < S::W_LOADS; ++i) {
+            const int id = i * 8 + wave;
+            load(w_rs, slot(st) + id * 64, id / 4, id % 4 * 8, st * S::CN);
+        }
+    };
+#pragma unroll
+    for (int i = 0; i < S::A_LOADS; ++i) load(a_rs, (i * 8 + wave) * 64, i, wave * 8, 0);
+    issue(0);
+    if (tid < NS * 16) {
+        gs[tid] = tid < K ? ln_g[tid] : 0.f;
+        bs[tid] = tid < K ? ln_b[tid] : 0.f;
+    }
+    for (int i = tid; i < steps * S::CN; i += 512) cs[i] = n0 + i < N ? bias[n0 + i] : 0.f;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+
+    const int kc4 = ((g & 1) << 1) | (g >> 1), rg = wave & 3, half = wave >> 2;
+    frag4 fa[NS];
+#pragma unroll
+    for (int s = 0; s < NS; ++s)
+        fa[s] = reinterpret_cast<const frag4 *>(lds_raw)[((s >> 1) * S::T + rg * 16 + l15) * 8 + (((s & 1) * 4 + kc4) ^ swz(l15))];
+    __syncthreads();                                                // every wave has its rows: steps 1 and 2 may land on them
+    issue(1);
+    issue(2);
+    float mean = 0.f, inv = 0.f;
+#pragma unroll
+    for (int pass = 0; pass < 2; ++pass) {
+        float p[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            if (pass == 1) {                                        // K % 4 == 0: a piece is inside or outside as a whole
+                const float in = s * 16 + kc4 * 4 < K ? 1.f : 0.f;
+                fa[s] = (fa[s] - mean) * in;
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) p[j] += pass == 1 ? fa[s][j] * fa[s][j] : fa[s][j];
+        }
+        float sum = (p[0] + p[1]) + (p[2] + p[3]);
+        sum += __shfl_xor(sum, 16, WAVE);
+        sum += __shfl_xor(sum, 32, WAVE);
+        if (pass == 0) mean = sum / (float)K;
+        else inv = 1.0f / sqrtf(sum / (float)K + eps);
+    }
+#pragma unroll
+    for (int s = 0; s < NS; ++s)                                    // zero beyond K: gain and shift are
+        fa[s] = fa[s] * inv * *reinterpret_cast<const frag4 *>(&gs[s * 16 + kc4 * 4]) + *reinterpret_cast<const frag4 *>(&bs[s * 16 + kc4 * 4]);
+
+    const int64_t m = m0 + rg * 16 + l15;
+    f32x4 acc[4];
+    auto store = [&](int st) __attribute__((always_inline)) {
+        const int cl = st * S::CN + half * 16 + g * 4, n = n0 + cl;
+        if (m < M && n < N) {
+            float v[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                v[i] = (acc[0][i] + acc[1][i]) + (acc[2][i] + acc[3][i]) + cs[cl + i];
+                if (EPI == EPI_BIAS_GELU) v[i] = gelu_erf(v[i]);
+            }
+            float *c = C + m * N + n;
+            if (vec) {
+                *reinterpret_cast<float4 *>(c) = make_float4(v[0], v[1], v[2], v[3]);
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (n + i < N) c[i] = v[i];
+            }
+        }
+    };
+    for (int st = 0; st < steps; ++st) {
+        if (st > 0) {
+            // this step has landed once at most the next one's loads are in flight (a store between them only makes
+            // the wait longer), for all waves at the barrier; the step before it has been read by then
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_s_waitcnt(S::W_LOADS | (0x7 << 4) | (0x0 << 8));
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+            issue(st + 2);
+            if (half) store(st - 1);                                // while the other half multiplies
+        }
+        const frag4 *Wb = reinterpret_cast<const frag4 *>(lds_raw + slot(st)) + (half * 16 + l15) * 8;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < NS; s += 2) {                           // a chunk of 32 k; four sums, so that products overlap
+            const frag4 w0 = Wb[(s >> 1) * S::CN * 8 + (kc4 ^ swz(l15))], w1 = Wb[(s >> 1) * S::CN * 8 + ((4 + kc4) ^ swz(l15))];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                acc[s & 2] = __builtin_amdgcn_mfma_f32_16x16x4f32(w0[j], fa[s][j], acc[s & 2], 0, 0, 0);
+                acc[(s & 2) + 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(w1[j], fa[s + 1][j], acc[(s & 2) + 1], 0, 0, 0);
+            }
+        }
+        if (!half) store(st);
+    }
+    if (half) store(steps - 1);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                // the loads past the last step, before LDS goes away
 #endif
 }
 
@@ -723,18 +870,19 @@ namespace {
 // tiles of t x t outputs
 int64_t square_tiles(int64_t M, int N, int t) { return ((M + t - 1) / t) * ((N + t - 1) / t); }
 
-template <int MI, int EPI, int LN>
+template <int MR, int MC, int EPI, int LN>
 hipError_t launch_f32_direct(const float *A, const float *g, const float *b, float eps, const float *W, const float *bias,
                              const float *resid, float *C, int64_t M, int N, int K, int vec, hipStream_t s)
 {
-    using S = F32Direct<MI, LN>;
-    auto kern = gemm_f32_direct_kernel<MI, EPI, LN>;
+    using S = F32Direct<MR, MC, LN>;
+    auto kern = gemm_f32_direct_kernel<MR, MC, EPI, LN>;
     static EpSmemLimit smem_limit;
     const hipError_t e = smem_limit.ensure(reinterpret_cast<const void *>(kern), (int)S::smem);
     if (e != hipSuccess) return e;
-    const int64_t tiles = square_tiles(M, N, S::T);
-    hipLaunchKernelGGL(kern, f32_tile_grid(tiles), dim3(256), S::smem, s, A, g, b, eps, W, bias, resid, C, M, N, K,
-                       (N + S::T - 1) / S::T, (int)tiles, vec);
+    const int tiles_n = (N + S::TC - 1) / S::TC;
+    const int64_t tiles = (M + S::TR - 1) / S::TR * tiles_n;
+    hipLaunchKernelGGL(kern, f32_tile_grid(tiles), dim3(256), S::smem, s, A, g, b, eps, W, bias, resid, C, M, N, K, tiles_n,
+                       (int)tiles, vec);
     return hipGetLastError();
 }
 
@@ -752,9 +900,14 @@ hipError_t launch_f32_gemm(const float *A, const float *W, const float *bias, co
         // one deit_small image 45.4 against 44.5), tiles of 32 up to three (four deit_small images 70.9 us per layer
         // against 89.2 with twice as many, whose K panels every workgroup brings in on its own), then the LDS tiles.
         if (t16 <= 2 * cus) {
-            return launch_f32_direct<1, EPI, 0>(A, nullptr, nullptr, 0.f, W, bias, resid, C, M, N, K, vec, s);
+            return launch_f32_direct<1, 1, EPI, 0>(A, nullptr, nullptr, 0.f, W, bias, resid, C, M, N, K, vec, s);
         } else if (t32 <= 3 * cus) {
-            return launch_f32_direct<2, EPI, 0>(A, nullptr, nullptr, 0.f, W, bias, resid, C, M, N, K, vec, s);
+            // half as tall where that leaves the fullest compute unit less to do (1576 x 192 x 768 9.9 -> 9.2 us, three
+            // halves instead of two tiles to a unit; 788 x 384 x 1536 17.1 -> 16.1)
+            const int64_t t16x32 = (M + 15) / 16 * ((N + 31) / 32);
+            if ((t16x32 + cus - 1) / cus < 2 * ((t32 + cus - 1) / cus))
+                return launch_f32_direct<1, 2, EPI, 0>(A, nullptr, nullptr, 0.f, W, bias, resid, C, M, N, K, vec, s);
+            return launch_f32_direct<2, 2, EPI, 0>(A, nullptr, nullptr, 0.f, W, bias, resid, C, M, N, K, vec, s);
         } else {
             const int tiles_n = (N + FN - 1) / FN, tiles = (int)((M + FT - 1) / FT) * tiles_n;
             hipLaunchKernelGGL(gemm_f32_tile_kernel<EPI>, f32_tile_grid(tiles), dim3(256), FS * (FT + FN) * FK * sizeof(float), s, A, W,
@@ -784,6 +937,31 @@ hipError_t ep_f32_gemm(const float *A, const float *W, const float *bias, const 
 
 namespace {
 
+template <int NS, int EPI>
+hipError_t launch_f32_rows(const float *x, const float *g, const float *b, float eps, const float *W, const float *bias, float *C,
+                           int64_t M, int N, int K, int vec, int cus, hipStream_t s)
+{
+    using S = F32Rows<NS>;
+    auto kern = gemm_f32_rows_kernel<NS, EPI>;
+    static EpSmemLimit smem_limit;
+    const hipError_t e = smem_limit.ensure(reinterpret_cast<const void *>(kern), (int)S::smem);
+    if (e != hipSuccess) return e;
+    const int64_t panels = (M + S::T - 1) / S::T;
+    const int all = (N + S::CN - 1) / S::CN;
+    // steps of a workgroup: bringing the rows in and normalising them takes about as long as a step
+    int best = 1;
+    int64_t cost = INT64_MAX;
+    for (int n = 1; n <= S::MAX_STEPS && n <= all; ++n) {
+        const int64_t c = (panels * ((all + n - 1) / n) + cus - 1) / cus * (n + 1);
+        if (c < cost) { cost = c; best = n; }
+    }
+    const int groups = (all + best - 1) / best;
+    const int64_t tiles = panels * groups;
+    hipLaunchKernelGGL(kern, f32_tile_grid(tiles), dim3(512), S::smem, s, x, g, b, eps, W, bias, C, M, N, K, best, groups,
+                       (int)tiles, vec);
+    return hipGetLastError();
+}
+
 template <int EPI>
 hipError_t launch_f32_ln_gemm(const float *x, const float *g, const float *b, float eps, const float *W, const float *bias,
                               float *C, int64_t M, int N, int K, hipStream_t s)
@@ -792,12 +970,16 @@ hipError_t launch_f32_ln_gemm(const float *x, const float *g, const float *b, fl
     const hipError_t e = ep_device_cu_count(&cus);
     if (e != hipSuccess) return e;
     const int vec = N % 4 == 0 && aligned16(bias) && aligned16(C);
-    const int64_t t16 = square_tiles(M, N, 16);
-    if (t16 <= 2 * cus)
-        return K <= 192 ? launch_f32_direct<1, EPI, 3>(x, g, b, eps, W, bias, nullptr, C, M, N, K, vec, s)
-                        : launch_f32_direct<1, EPI, 6>(x, g, b, eps, W, bias, nullptr, C, M, N, K, vec, s);
-    return K <= 192 ? launch_f32_direct<2, EPI, 3>(x, g, b, eps, W, bias, nullptr, C, M, N, K, vec, s)
-                    : launch_f32_direct<2, EPI, 6>(x, g, b, eps, W, bias, nullptr, C, M, N, K, vec, s);
+    if (square_tiles(M, N, 16) <= 2 * cus)
+        return K <= 192 ? launch_f32_direct<1, 1, EPI, 3>(x, g, b, eps, W, bias, nullptr, C, M, N, K, vec, s)
+                        : launch_f32_direct<1, 1, EPI, 6>(x, g, b, eps, W, bias, nullptr, C, M, N, K, vec, s);
+    // a row of tiles of 32 normalises its rows again and again: past three to a unit (K <= 192: 788 x 768 8.5 us against
+    // 8.9 with 64 rows, 1040 x 768 10.4 against 9.2) or one (394 x 1536 x 384 17.8 against 13.6)
+    if (square_tiles(M, N, 32) <= (K <= 192 ? 3 : 1) * cus)
+        return K <= 192 ? launch_f32_direct<2, 2, EPI, 3>(x, g, b, eps, W, bias, nullptr, C, M, N, K, vec, s)
+                        : launch_f32_direct<2, 2, EPI, 6>(x, g, b, eps, W, bias, nullptr, C, M, N, K, vec, s);
+    return K <= 192 ? launch_f32_rows<12, EPI>(x, g, b, eps, W, bias, C, M, N, K, vec, cus, s)
+                    : launch_f32_rows<24, EPI>(x, g, b, eps, W, bias, C, M, N, K, vec, cus, s);
 }
 
 }  // namespace
@@ -806,9 +988,12 @@ bool ep_f32_ln_gemm_supported(const float *x, const float *W, int64_t M, int N, 
 {
     int cus = 0;
     if (ep_device_cu_count(&cus) != hipSuccess) return false;
-    // where tiles of 32 serve the dense layer anyway (4 tiny images 28.1 us per layer against 33.0 with LayerNorm on its
-    // own; four deit_small images, past this line, 95 against 87)
-    return K % 4 == 0 && K <= 384 && M > 0 && N > 0 && aligned16(x) && aligned16(W) && square_tiles(M, N, 32) <= 3 * cus;
+    // any number of rows up to 192 wide; wider ones leave room for one workgroup of 64 rows on a compute unit, which is the
+    // better way up to 24 tiles of 32 to a unit (3152 x 1536 x 384 44.6 us against 48.1 with LayerNorm on its own,
+    // 6304 x 1152 x 384 64 against 61)
+    const int64_t t32 = square_tiles(M, N, 32);
+    return K % 4 == 0 && K <= 384 && M > 0 && N > 0 && aligned16(x) && aligned16(W) && t32 < (1 << 24) &&
+           (K <= 192 || t32 <= 24 * cus);
 }
 
 hipError_t ep_f32_ln_gemm(const float *x, const float *g, const float *b, float eps, const float *W, const float *bias, float *C,
