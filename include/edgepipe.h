@@ -317,7 +317,8 @@ void ep_head_destroy(ep_head_t *head);
  * width and token count, and the out_dtype of a stage must be the in_dtype of the
  * next; every stage must have max_batch >= micro_batch.  The pipeline borrows the
  * handles (the caller destroys them after the pipeline) and owns its streams,
- * events and boundary buffers.
+ * events and boundary buffers, and for bf16 stages and small micro-batches the
+ * workspace (at most 1.2 GB) to take several of them through a stage at once.
  *
  * ep_pipeline_run: x_in (DEVICE) holds n_micro micro-batches back to back,
  * [n_micro * micro_batch, T, D] in the first stage's in_dtype; x_out (DEVICE)

@@ -1,0 +1,15 @@
+// Micro-batches taken through a stage together, for the pipeline; ep_stage.hip.
+#pragma once
+#include <hip/hip_runtime.h>
+
+#include "edgepipe.h"
+
+// How many micro-batches of `micro` images the stage takes through its layers at once at most, with the bits it gives each
+// on its own.  1: none, because a micro-batch is large enough by itself or because the bits would differ (fp32 path, whose
+// sums over K are split according to the rows there are).
+int32_t ep_stage_group_limit(const ep_stage_t *stage, int32_t micro);
+// Workspace bytes of `count` of them.
+size_t ep_stage_group_bytes(const ep_stage_t *stage, int32_t micro, int32_t count);
+// ep_stage_forward of count * micro images with the intermediates in `ws` (256-byte aligned, ep_stage_group_bytes).
+ep_status ep_stage_forward_group(ep_stage_t *stage, const void *x_in, int32_t micro, int32_t count, void *x_out, void *ws,
+                                 hipStream_t stream);

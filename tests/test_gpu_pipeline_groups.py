@@ -1,0 +1,66 @@
+"""Micro-batches that a pipeline takes through its stages in groups: the bits are those of each micro-batch on its own,
+whatever the number of groups, the K ranges of the second MLP layer, the boundary types and the caller's stream."""
+import numpy as np
+import pytest
+
+from paper_2110_14895_amd import binding, synth
+from tests import harness as H
+from tests.test_gpu_pipeline import build, layers_of
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("T,D,Hh,M,cuts,mb,n_micro,boundary_bf16", [
+    (197, 768, 12, 3072, (0, 1, 2), 8, 9, False),       # two K ranges; groups of three and of two lanes' turns
+    (197, 1024, 16, 4096, (0, 2), 1, 7, False),         # one stage, four K ranges, one group
+    (257, 320, 4, 1280, (0, 1, 2), 2, 5, True),         # d_head 80, bf16 between the stages
+    (65, 128, 2, 512, (0, 1, 2, 3), 100, 13, False),    # more micro-batches than two groups hold
+    (577, 384, 6, 1536, (0, 1, 2), 14, 5, True),        # micro-batches near the largest that are grouped
+    (577, 384, 6, 1536, (0, 1, 2), 15, 3, False),       # the first past it
+])
+def test_groups_equal_single_micro_batches(T, D, Hh, M, cuts, mb, n_micro, boundary_bf16):
+    import torch
+    sh = synth.custom_shape(f"groups_{T}_{D}", cuts[-1], D, Hh, M, T)
+    stages = build(sh, layers_of(sh, cuts[-1], True), cuts, mb, bf16=True, boundary_bf16=boundary_bf16)
+    pipe = binding.Pipeline(stages, mb)
+    xin = H.to_device(synth.activations(sh, mb * n_micro, bf16=True), True)
+    shape = (mb * n_micro, T, D)
+    want = torch.empty(shape, dtype=torch.float32, device="cuda")
+    s = torch.cuda.current_stream()
+    for m in range(n_micro):                             # a run of one micro-batch goes through the stages as it is
+        pipe.run(xin[m * mb:(m + 1) * mb], 1, want[m * mb:(m + 1) * mb], s)
+    torch.cuda.synchronize()
+    want = want.cpu().numpy()
+    side = torch.cuda.Stream()
+    for n in (n_micro, 2, n_micro - 1):
+        out = torch.full(shape, float("nan"), dtype=torch.float32, device="cuda")
+        side.wait_stream(s)
+        with torch.cuda.stream(side):
+            pipe.run(xin, n, out, side)
+        side.synchronize()
+        got = out.cpu().numpy()
+        np.testing.assert_array_equal(got[:n * mb], want[:n * mb])
+        assert np.isnan(got[n * mb:]).all()
+    pipe.destroy()
+
+
+def test_groups_in_a_graph():
+    import torch
+    sh = synth.custom_shape("groups_graph", 2, 256, 4, 512, 65)
+    mb, n_micro = 4, 6
+    stages = build(sh, layers_of(sh, 2, True), (0, 1, 2), mb, bf16=True)
+    pipe = binding.Pipeline(stages, mb)
+    xin = H.to_device(synth.activations(sh, mb * n_micro, bf16=True), True)
+    out = torch.empty((mb * n_micro, 65, 256), dtype=torch.float32, device="cuda")
+    pipe.run(xin, n_micro, out, torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    want = out.clone()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        pipe.run(xin, n_micro, out, torch.cuda.current_stream())
+    for _ in range(3):
+        out.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want)
+    pipe.destroy()
