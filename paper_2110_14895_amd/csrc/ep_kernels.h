@@ -80,6 +80,12 @@ int ep_bf16_gemm_splits(int64_t M, int N, int K);
 struct EpDensePlan { int32_t splits, persistent, bm, bn, per_cu; int64_t m_main; };      // per_cu: workgroups to a unit
 extern "C" void ep_query_dense_plan(int64_t M, int32_t N, int32_t K, int32_t epi, EpDensePlan *out);
 
+// LayerNorm of x and the dense layer behind it (bias, or bias and GELU) in one launch, narrow models (ep_gemm_bf16_rows.hip):
+// the bits of ep_bf16_layernorm and ep_bf16_gemm
+bool ep_bf16_ln_gemm_supported(int64_t M, int N, int K);
+hipError_t ep_bf16_ln_gemm(const float *x, const float *g, const float *b, float eps, const uint16_t *W, const float *bias, void *C,
+                           int64_t M, int N, int K, int epi, hipEvent_t after_main, hipStream_t s);
+
 // persistent kernel for large problems (ep_gemm_bf16_persist.hip): 256 x BN tiles, BN = tile_bn
 // (256 or 320).  The tile walk covers rows
 // [0, m_rows); with fuse_tail the same launch also computes rows [m_rows, M) as 64 x 32 tiles.

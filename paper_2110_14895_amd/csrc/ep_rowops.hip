@@ -97,7 +97,8 @@ __global__ __launch_bounds__(256) void ln_bf16_kernel(float *__restrict__ x, int
         const int c = lane + i * LPR;
         if (!GUARD || c < nvec) {
             v[i].x -= mean; v[i].y -= mean; v[i].z -= mean; v[i].w -= mean;
-            q += (v[i].x * v[i].x + v[i].y * v[i].y) + (v[i].z * v[i].z + v[i].w * v[i].w);
+            // which products are rounded is not left to the compiler: ep_gemm_bf16_rows.hip gives the same bits
+            q += __builtin_fmaf(v[i].x, v[i].x, v[i].y * v[i].y) + __builtin_fmaf(v[i].z, v[i].z, v[i].w * v[i].w);
         }
     }
     const float inv = 1.0f / sqrtf(row_sum<LPR>(q) / (float)D + eps);

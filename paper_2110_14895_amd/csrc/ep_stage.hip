@@ -203,24 +203,31 @@ ep_status run_layer(ep_stage *st, const Workspace &w, const LayerDev &L, const f
     if (after) *after = {1, nullptr};
     if (st->bf16) {
         uint16_t *a = (uint16_t *)w.a, *big = (uint16_t *)w.big;
+        // a LayerNorm done inside the dense layer behind it leaves its own bracket empty
+        const bool plain1 = !xin16 && !(before && before->splits > 1);
+        const bool fuse1 = plain1 && ep_bf16_ln_gemm_supported(R, 3 * D, D), fuse2 = ep_bf16_ln_gemm_supported(R, M, D);
         if (xin16)
             EP_TRACED(EP_K_LN1, ep_bf16_layernorm_widen(xin16, w.x, L.ln1_g, L.ln1_b, c.ln_eps, a, R, D, s));
-        else if (before && before->splits > 1)
+        else if (!plain1)
             EP_TRACED(EP_K_LN1, ep_bf16_layernorm_sum(w.x, w.part, before->splits, before->bias, L.ln1_g, L.ln1_b,
                                                       c.ln_eps, a, R, D, s));
         else
-            EP_TRACED(EP_K_LN1, ep_bf16_layernorm(xin, D, L.ln1_g, L.ln1_b, c.ln_eps, a, R, D, s));
+            EP_TRACED(EP_K_LN1, fuse1 ? hipSuccess : ep_bf16_layernorm(xin, D, L.ln1_g, L.ln1_b, c.ln_eps, a, R, D, s));
         EP_TRACED_GEMM(EP_K_QKV, EP_K_QKV_MAIN,
-                       ep_bf16_gemm(a, (const uint16_t *)L.w_qkv, L.b_qkv, nullptr, big, R, 3 * D, D, EPI_BIAS,
-                                    ts_.after_main(), s));
+                       fuse1 ? ep_bf16_ln_gemm(xin, L.ln1_g, L.ln1_b, c.ln_eps, (const uint16_t *)L.w_qkv, L.b_qkv, big, R,
+                                               3 * D, D, EPI_BIAS, ts_.after_main(), s)
+                             : ep_bf16_gemm(a, (const uint16_t *)L.w_qkv, L.b_qkv, nullptr, big, R, 3 * D, D, EPI_BIAS,
+                                            ts_.after_main(), s));
         EP_TRACED(EP_K_ATTN, ep_bf16_attention(big, a, B, T, D, H, s));
         EP_TRACED_GEMM(EP_K_PROJ, EP_K_PROJ_MAIN,
                        ep_bf16_gemm(a, (const uint16_t *)L.w_o, L.b_o, xin, w.x, R, D, D, EPI_BIAS_RESID,
                                     ts_.after_main(), s));
-        EP_TRACED(EP_K_LN2, ep_bf16_layernorm(w.x, D, L.ln2_g, L.ln2_b, c.ln_eps, a, R, D, s));
+        EP_TRACED(EP_K_LN2, fuse2 ? hipSuccess : ep_bf16_layernorm(w.x, D, L.ln2_g, L.ln2_b, c.ln_eps, a, R, D, s));
         EP_TRACED_GEMM(EP_K_FC1, EP_K_FC1_MAIN,
-                       ep_bf16_gemm(a, (const uint16_t *)L.w_fc1, L.b_fc1, nullptr, big, R, M, D, EPI_BIAS_GELU,
-                                    ts_.after_main(), s));
+                       fuse2 ? ep_bf16_ln_gemm(w.x, L.ln2_g, L.ln2_b, c.ln_eps, (const uint16_t *)L.w_fc1, L.b_fc1, big, R, M, D,
+                                               EPI_BIAS_GELU, ts_.after_main(), s)
+                             : ep_bf16_gemm(a, (const uint16_t *)L.w_fc1, L.b_fc1, nullptr, big, R, M, D, EPI_BIAS_GELU,
+                                            ts_.after_main(), s));
         int sp = w.part ? fc2_splits(c, w.ranges_of ? w.ranges_of : B) : 1;
         if ((size_t)sp * R * D * 4 > w.part_bytes) sp = 1;      // never beyond what the workspace holds
         if (sp > 1) {
@@ -243,7 +250,6 @@ ep_status run_layer(ep_stage *st, const Workspace &w, const LayerDev &L, const f
         }
     } else {
         float *a = (float *)w.a, *big = (float *)w.big;
-        // a LayerNorm done inside the dense layer behind it leaves its own bracket empty
         const bool fuse1 = ep_f32_ln_gemm_supported(xin, (const float *)L.w_qkv, R, 3 * D, D);
         const bool fuse2 = ep_f32_ln_gemm_supported(w.x, (const float *)L.w_fc1, R, M, D);
         EP_TRACED(EP_K_LN1, fuse1 ? hipSuccess : ep_f32_layernorm(xin, D, L.ln1_g, L.ln1_b, c.ln_eps, a, R, D, s));
