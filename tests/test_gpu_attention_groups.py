@@ -1,6 +1,6 @@
 """GPU parity of attention where a group has up to nine tiles of 16 queries (one for each of its waves) and where it
 has more, the first size past it: the rows of keys and values placed for d_head 64 and for 80.  One layer whose MLP
-branch is switched off, against the checker on the first and the last image; the tolerance is the bf16 path's."""
+branch is switched off, against the oracle on the first and the last image; the tolerance is the bf16 path's."""
 import numpy as np
 import pytest
 
