@@ -17,7 +17,7 @@ pytestmark = pytest.mark.gpu
     (197, 128, 2, 1),      # 2 pairs: 16 x 13, one tile to a workgroup
     (15, 128, 2, 3),       # a single, partly filled tile
     (197, 128, 2, 40),     # 80 pairs: 16 x 3, a last group of three tiles next to groups of five
-    (197, 128, 2, 64),     # 128 pairs: 32 x 2, a last group of three tiles next to four
+    (197, 128, 2, 64),     # 128 pairs: 16 x 2, seven and six tiles
     (257, 320, 4, 4),      # 16 pairs of d_head 80: 16 x 9, the last group a single tile next to groups of two
     (577, 128, 2, 6),      # 12 pairs: 16 x 19, a last group of one tile next to groups of two
     (257, 320, 4, 24),     # 96 pairs of d_head 80: 16 x 2, nine and eight tiles
