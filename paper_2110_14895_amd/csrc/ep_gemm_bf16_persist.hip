@@ -47,7 +47,7 @@
 // workgroups of an XCD take 32 consecutive tiles of an order that walks groups
 // of 4 tile rows column by column, so that they share A and W panels in L2.
 //
-// Requirements: K % 64 == 0, K >= 128, N % 16 == 0; M*K*2, N*K*2 < 2^31.  Rows
+// Requirements: K % 64 == 0, K >= 128, N % 16 == 0, N < 2^20; M*K*2, N*K*2 < 2^31.  Rows
 // past M and columns past N are read as zeros (per-lane buffer offsets beyond
 // the end of the buffer) and never stored.  `m_rows` <= M limits the rows the
 // tile walk computes.  The remaining rows are left to the caller, or, with
@@ -497,7 +497,8 @@ hipError_t ep_bf16_gemm_persistent_clock(double *shader_mhz, double *seconds)
 
 bool ep_bf16_gemm_persistent_supported(int64_t M, int N, int K)
 {
-    return M > 0 && N > 0 && K >= 2 * BK && K % BK == 0 && N % 16 == 0 &&
+    // N: the epilogue addresses a tile's rows of C with 32 bits and sends columns past N beyond them (PAST_END)
+    return M > 0 && N > 0 && N < MAX_TILE_N && K >= 2 * BK && K % BK == 0 && N % 16 == 0 &&
            M * (int64_t)K * 2 < 0x7FFFFFF0ll && (int64_t)N * K * 2 < 0x7FFFFFF0ll && M * (int64_t)N < (1ll << 31);
 }
 

@@ -56,6 +56,17 @@ def test_large_residual_layers_run_on_the_persistent_kernel(rows, n, k):
     assert dense_plan(rows, n, k, EPI_BIAS_RESID).persistent
 
 
+# A tile's rows of the output are addressed with 32 bits up to 2^20 columns; wider layers (embeddings) run as 64 x 32 tiles
+@pytest.mark.parametrize("n", [(1 << 20) - 64, 1 << 20, 1052736, 1500032, 1 << 21, (1 << 22) + 64])
+def test_layers_of_a_million_columns_do_not_run_on_the_persistent_kernel(n):
+    for k in (64, 128, 192, 960):
+        for rows in (1, 64, 255, 256, 300, 511, 512, 1000, 2047):
+            if rows * n >= 1 << 31 or n * k * 2 >= 0x7FFFFFF0:
+                continue
+            for epi in (EPI_BIAS, EPI_BIAS_GELU, EPI_BIAS_RESID):
+                assert n < 1 << 20 or not dense_plan(rows, n, k, epi).persistent, (rows, k, epi)
+
+
 @pytest.mark.parametrize("pairs", [1, 2, 16, 24, 32, 36, 60, 96, 128, 140, 255, 256, 257, 272, 4096])
 def test_every_attention_group_holds_a_query(pairs):
     f = binding.lib().ep_query_attention_plan

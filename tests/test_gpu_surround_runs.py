@@ -57,6 +57,37 @@ def test_embedding_of_a_million_columns(d, channels):
     assert H.rel_err(out.cpu().numpy(), ref) <= H.TOL_BF16
 
 
+# The same with 256 rows: tiles as tall as any kernel has them, in a layer whose rows of the output are 4 MB each, the last
+# columns not a whole tile.  Against the same products in 64 bits of the bf16 operands: sums of 108 products in fp32 stay
+# within 111 roundings of 2^-24 of the sum of the terms' magnitudes, here 4 to 7, so within 5e-5.
+def test_embedding_of_a_million_columns_and_many_rows():
+    import torch
+    d, patch, size = 1052736, 6, 96
+    T, K = 257, 108
+    rng = np.random.default_rng(11)
+    bits = synth.f32_to_bf16_bits(rng.standard_normal(65521, dtype=np.float32) * 0.05)       # a prime: no two rows alike
+    prm = {n: np.resize(np.roll(bits, 1000 * i), s) for i, (n, s) in
+           enumerate((("w_patch", (d, K)), ("b_patch", (d,)), ("cls", (d,)), ("pos", (T, d))))}
+    emb = binding.Embed(size, patch, 3, d, binding.EP_BF16, binding.EP_F32, prm, 1)
+    img = synth.images(1, 3, size, seed=2)
+    out = torch.full((T, d), float("nan"), dtype=torch.float32, device="cuda")
+    emb.forward(torch.from_numpy(img).cuda(), 1, out, torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    emb.destroy()
+
+    def up(a):
+        return torch.from_numpy(a.view(np.int16)).cuda().view(torch.bfloat16).double()
+
+    g = size // patch
+    rows = torch.from_numpy(img).cuda().to(torch.bfloat16).double().view(3, g, patch, g, patch).permute(1, 3, 0, 2, 4).reshape(g * g, K)
+    for c in range(0, d, 1 << 16):
+        e = min(c + (1 << 16), d)
+        pos = up(np.ascontiguousarray(prm["pos"][:, c:e]))
+        ref = torch.cat([up(prm["cls"][c:e])[None] + pos[:1], rows @ up(prm["w_patch"][c:e]).T.contiguous() + up(prm["b_patch"][c:e]) + pos[1:]])
+        err = (out[:, c:e].double() - ref).abs().max().item()
+        assert err <= 5e-5, (c, err)
+
+
 @pytest.mark.parametrize("bf16", [False, True])
 @pytest.mark.parametrize("shift", [0, 1])
 def test_head_takes_tokens_where_they_lie(bf16, shift):
