@@ -49,11 +49,14 @@ hipError_t ep_f32_to_bf16(const float *in, uint16_t *out, int64_t n, hipStream_t
 hipError_t ep_bf16_pack_weights(const uint16_t *w, uint16_t *p, int N, int K, hipStream_t s);
 // A bf16 [M, K], W bf16 [N, K] in fragment order; out bf16 (EPI_BIAS, EPI_BIAS_GELU) or fp32 (EPI_BIAS_RESID).
 // K % 64 == 0, N % 16 == 0.
+// one_order: every output is one sum over K in order, whatever M is; otherwise a persistent launch may deal its last rows
+// in narrow tiles, which add up eight sums (ep_bf16_gemm_narrow_rows tells how many rows).
 // after_main: if non-null, recorded on s right after the launch (it covers the rows
 // ep_bf16_gemm_main_rows reports: all of them).
 hipError_t ep_bf16_gemm(const uint16_t *A, const uint16_t *W, const float *bias,
-                        const float *resid, void *C, int64_t M, int N, int K, int epi,
+                        const float *resid, void *C, int64_t M, int N, int K, int epi, bool one_order,
                         hipEvent_t after_main, hipStream_t s);
+int64_t ep_bf16_gemm_narrow_rows(int64_t M, int N, int K, int epi);
 int64_t ep_bf16_gemm_main_rows(int64_t M, int N, int K);
 // qkv bf16 [B*T, 3D] -> o bf16 [B*T, D]; d_head 64 or 80, T <= 4096 (K and V stream through LDS in chunks)
 hipError_t ep_bf16_attention(const uint16_t *qkv, uint16_t *o, int B, int T, int D, int H,
@@ -79,6 +82,8 @@ int ep_bf16_gemm_splits(int64_t M, int N, int K);
 // persistent launch are the narrow tiles in front of its walk.
 struct EpDensePlan { int32_t splits, persistent, bm, bn, per_cu; int64_t m_main; };      // per_cu: workgroups to a unit
 extern "C" void ep_query_dense_plan(int64_t M, int32_t N, int32_t K, int32_t epi, EpDensePlan *out);
+// the same with one_order, never cut
+extern "C" void ep_query_dense_plan_one_order(int64_t M, int32_t N, int32_t K, int32_t epi, EpDensePlan *out);
 
 // LayerNorm of x and the dense layer behind it (bias, or bias and GELU) in one launch, narrow models (ep_gemm_bf16_rows.hip):
 // the bits of ep_bf16_layernorm and ep_bf16_gemm

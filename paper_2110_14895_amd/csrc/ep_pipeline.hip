@@ -20,7 +20,9 @@
 // on a stream with a workspace of its own, so that the uneven last rounds and
 // the row kernels of one meet dense layers of the other (one at a time: ViT-Large,
 // four micro-batches of 24, 3.46 against 3.17 ms).  Micro-batches that fill the
-// chip by themselves, fp32 stages and a run of one keep the schedule above.
+// chip by themselves, ones with narrow tiles at the end of a dense layer (their
+// sums depend on where a row lies), fp32 stages and a run of one keep the schedule
+// above.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

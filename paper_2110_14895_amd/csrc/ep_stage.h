@@ -6,8 +6,10 @@
 
 // How many micro-batches of `micro` images the stage takes through its layers at once at most, with the bits it gives each
 // on its own.  1: none, because a micro-batch is large enough by itself or because the bits would differ (fp32 path, whose
-// sums over K are split according to the rows there are).
+// sums over K are split according to the rows there are; a micro-batch that has a dense layer with narrow tiles).
 int32_t ep_stage_group_limit(const ep_stage_t *stage, int32_t micro);
+// the same for a stage of that configuration; for tests
+extern "C" int32_t ep_query_group_limit(const ep_vit_config *cfg, int32_t micro);
 // Workspace bytes of `count` of them.
 size_t ep_stage_group_bytes(const ep_stage_t *stage, int32_t micro, int32_t count);
 // ep_stage_forward of count * micro images with the intermediates in `ws` (256-byte aligned, ep_stage_group_bytes).

@@ -52,7 +52,7 @@ struct Workspace {
     void *big;
     float *part;
     size_t part_bytes;
-    int32_t ranges_of = 0;                 // images whose K ranges the forward uses; 0: its own
+    int32_t ranges_of = 0;                 // a group: the images of a micro-batch, whose K ranges it uses; 0: no group
 };
 
 struct ep_stage {
@@ -203,6 +203,7 @@ ep_status run_layer(ep_stage *st, const Workspace &w, const LayerDev &L, const f
     if (after) *after = {1, nullptr};
     if (st->bf16) {
         uint16_t *a = (uint16_t *)w.a, *big = (uint16_t *)w.big;
+        const bool one_order = w.ranges_of != 0;                // several micro-batches: each as it would be alone
         // a LayerNorm done inside the dense layer behind it leaves its own bracket empty
         const bool plain1 = !xin16 && !(before && before->splits > 1);
         const bool fuse1 = plain1 && ep_bf16_ln_gemm_supported(R, 3 * D, D), fuse2 = ep_bf16_ln_gemm_supported(R, M, D);
@@ -217,17 +218,17 @@ ep_status run_layer(ep_stage *st, const Workspace &w, const LayerDev &L, const f
                        fuse1 ? ep_bf16_ln_gemm(xin, L.ln1_g, L.ln1_b, c.ln_eps, (const uint16_t *)L.w_qkv, L.b_qkv, big, R,
                                                3 * D, D, EPI_BIAS, ts_.after_main(), s)
                              : ep_bf16_gemm(a, (const uint16_t *)L.w_qkv, L.b_qkv, nullptr, big, R, 3 * D, D, EPI_BIAS,
-                                            ts_.after_main(), s));
+                                            one_order, ts_.after_main(), s));
         EP_TRACED(EP_K_ATTN, ep_bf16_attention(big, a, B, T, D, H, s));
         EP_TRACED_GEMM(EP_K_PROJ, EP_K_PROJ_MAIN,
                        ep_bf16_gemm(a, (const uint16_t *)L.w_o, L.b_o, xin, w.x, R, D, D, EPI_BIAS_RESID,
-                                    ts_.after_main(), s));
+                                    one_order, ts_.after_main(), s));
         EP_TRACED(EP_K_LN2, fuse2 ? hipSuccess : ep_bf16_layernorm(w.x, D, L.ln2_g, L.ln2_b, c.ln_eps, a, R, D, s));
         EP_TRACED_GEMM(EP_K_FC1, EP_K_FC1_MAIN,
                        fuse2 ? ep_bf16_ln_gemm(w.x, L.ln2_g, L.ln2_b, c.ln_eps, (const uint16_t *)L.w_fc1, L.b_fc1, big, R, M, D,
                                                EPI_BIAS_GELU, ts_.after_main(), s)
                              : ep_bf16_gemm(a, (const uint16_t *)L.w_fc1, L.b_fc1, nullptr, big, R, M, D, EPI_BIAS_GELU,
-                                            ts_.after_main(), s));
+                                            one_order, ts_.after_main(), s));
         int sp = w.part ? fc2_splits(c, w.ranges_of ? w.ranges_of : B) : 1;
         if ((size_t)sp * R * D * 4 > w.part_bytes) sp = 1;      // never beyond what the workspace holds
         if (sp > 1) {
@@ -246,7 +247,7 @@ ep_status run_layer(ep_stage *st, const Workspace &w, const LayerDev &L, const f
         } else {
             EP_TRACED_GEMM(EP_K_FC2, EP_K_FC2_MAIN,
                            ep_bf16_gemm(big, (const uint16_t *)L.w_fc2, L.b_fc2, w.x, xout, R, D, M, EPI_BIAS_RESID,
-                                        ts_.after_main(), s));
+                                        one_order, ts_.after_main(), s));
         }
     } else {
         float *a = (float *)w.a, *big = (float *)w.big;
@@ -508,7 +509,9 @@ extern "C" ep_status ep_stage_forward_static(ep_stage_t *st, const void *x_in, i
 }
 
 // ---- several micro-batches at once: rows are independent of each other, and every kernel of the bf16 path adds up a row
-// in the same order whatever the rows beside it, but for the K ranges of the second MLP layer, which stay the micro-batch's
+// in the same order whatever the rows beside it, but for two things: the K ranges of the second MLP layer, which stay the
+// micro-batch's, and the narrow tiles of a persistent launch, which a group's dense layers do without; a micro-batch that
+// has them on its own is not grouped
 namespace {
 
 // Micro-batches of up to MICRO_ROWS rows; a group of up to GROUP_ROWS rows, GROUP_ELEMS activations of the widest
@@ -527,15 +530,35 @@ size_t group_part_bytes(const ep_vit_config &c, int32_t micro, int32_t count)
 
 }  // namespace
 
-int32_t ep_stage_group_limit(const ep_stage_t *st, int32_t micro)
+namespace {
+
+// whether a dense layer of a micro-batch on its own has narrow tiles
+bool has_narrow_rows(const ep_vit_config &c, int32_t micro)
 {
-    const ep_vit_config &c = st->cfg;
+    const int64_t R = (int64_t)micro * c.n_tokens;
+    const int D = c.d_model, M = c.d_mlp;
+    const int sp = fc2_splits(c, micro);
+    // q|k|v goes without its LayerNorm behind a bf16 input and behind sums over K ranges
+    const bool qkv = !ep_bf16_ln_gemm_supported(R, 3 * D, D) || c.in_dtype == EP_BF16 || sp > 1;
+    return (qkv && ep_bf16_gemm_narrow_rows(R, 3 * D, D, EPI_BIAS) > 0) || ep_bf16_gemm_narrow_rows(R, D, D, EPI_BIAS_RESID) > 0 ||
+           (!ep_bf16_ln_gemm_supported(R, M, D) && ep_bf16_gemm_narrow_rows(R, M, D, EPI_BIAS_GELU) > 0) ||
+           (sp == 1 && ep_bf16_gemm_narrow_rows(R, D, M, EPI_BIAS_RESID) > 0);
+}
+
+int32_t group_limit(const ep_vit_config &c, int32_t micro)
+{
     const int64_t rows = (int64_t)micro * c.n_tokens, wide = std::max(3 * (int64_t)c.d_model, (int64_t)c.d_mlp);
-    if (!st->bf16 || rows > MICRO_ROWS) return 1;
+    if (c.param_dtype != EP_BF16 || rows > MICRO_ROWS || has_narrow_rows(c, micro)) return 1;
     int64_t n = std::min(GROUP_ROWS, GROUP_ELEMS / wide) / rows;
     while (n > 1 && (!bf16_rows_fit(c, n * rows) || group_part_bytes(c, micro, (int32_t)n) > GROUP_SUM_BYTES)) --n;
     return n < 1 ? 1 : (int32_t)n;
 }
+
+}  // namespace
+
+int32_t ep_stage_group_limit(const ep_stage_t *st, int32_t micro) { return group_limit(st->cfg, micro); }
+
+extern "C" int32_t ep_query_group_limit(const ep_vit_config *cfg, int32_t micro) { return group_limit(*cfg, micro); }
 
 size_t ep_stage_group_bytes(const ep_stage_t *st, int32_t micro, int32_t count)
 {

@@ -315,7 +315,7 @@ extern "C" ep_status ep_embed_forward(ep_embed_t *e, const void *images, int32_t
         launch_gather((const float *)images, (uint16_t *)e->rows, R, c, e->G, e->K, e->Kp, s);
         EP_HIP(hipGetLastError());
         EP_HIP(ep_bf16_gemm((const uint16_t *)e->rows, (const uint16_t *)e->w, e->b, e->posb, e->tmp, R, D, e->Kp,
-                            EPI_BIAS_RESID, nullptr, s));
+                            EPI_BIAS_RESID, false, nullptr, s));
     } else {
         launch_gather((const float *)images, (float *)e->rows, R, c, e->G, e->K, e->Kp, s);
         EP_HIP(hipGetLastError());

@@ -18,9 +18,9 @@ class DensePlan(C.Structure):
             (f"/{self.splits}" if self.splits > 1 else "")
 
 
-def dense_plan(rows, n, k, epi):
+def dense_plan(rows, n, k, epi, one_order=False):
     p = DensePlan()
-    f = binding.lib().ep_query_dense_plan
+    f = binding.lib().ep_query_dense_plan_one_order if one_order else binding.lib().ep_query_dense_plan
     f.argtypes, f.restype = [C.c_int64, C.c_int32, C.c_int32, C.c_int32, C.POINTER(DensePlan)], None
     f(rows, n, k, epi, C.byref(p))
     return p
@@ -65,6 +65,47 @@ def test_layers_of_a_million_columns_do_not_run_on_the_persistent_kernel(n):
                 continue
             for epi in (EPI_BIAS, EPI_BIAS_GELU, EPI_BIAS_RESID):
                 assert n < 1 << 20 or not dense_plan(rows, n, k, epi).persistent, (rows, k, epi)
+
+
+def group_limit(d, heads, m, t, micro, in_dtype=binding.EP_F32, param_dtype=binding.EP_BF16):
+    cfg = binding.VitConfig(1, d, heads, m, t, 1e-6, param_dtype, in_dtype, binding.EP_F32).c_struct()
+    f = binding.lib().ep_query_group_limit
+    f.argtypes, f.restype = [C.c_void_p, C.c_int32], C.c_int32
+    return f(C.addressof(cfg), micro)
+
+
+# Micro-batches that a pipeline takes together get the bits of each on its own: neither alone nor together may a dense layer
+# have narrow tiles, whose sums are put together otherwise (a second MLP layer cut into K ranges never has)
+@pytest.mark.parametrize("in_dtype", [binding.EP_F32, binding.EP_BF16])
+@pytest.mark.parametrize("d,heads,m,t", [(192, 3, 768, 197), (384, 6, 1536, 197), (512, 8, 2048, 197), (768, 12, 3072, 197),
+                                         (768, 12, 3072, 577), (1024, 16, 4096, 197), (1280, 16, 5120, 257)])
+def test_grouped_micro_batches_have_no_narrow_tiles(d, heads, m, t, in_dtype):
+    grouped = alone = 0
+    for micro in range(1, 16384 // t + 2):
+        rows, limit = micro * t, group_limit(d, heads, m, t, micro, in_dtype)
+        layers = [(d, d, EPI_BIAS_RESID)]
+        if d > 384 or in_dtype == binding.EP_BF16:           # otherwise LayerNorm goes with them
+            layers.append((3 * d, d, EPI_BIAS))
+        if d > 384:
+            layers.append((m, d, EPI_BIAS_GELU))
+        if dense_plan(rows, d, m, EPI_PARTIAL).splits == 1:
+            layers.append((d, m, EPI_BIAS_RESID))
+        if limit == 1:
+            alone += any(dense_plan(rows, *l).m_main < rows for l in layers)
+            continue
+        assert rows <= 1 << 14
+        grouped += 1
+        for n in range(1, limit + 1):
+            for l in layers:
+                assert dense_plan(n * rows, *l, one_order=n > 1).m_main == n * rows, (micro, n, l)
+    assert grouped > 0
+    assert alone > 0 or d <= 384
+
+
+def test_what_is_not_grouped():
+    assert group_limit(192, 3, 768, 197, 8, param_dtype=binding.EP_F32) == 1            # fp32
+    assert group_limit(384, 6, 1536, 577, 28) == 2 and group_limit(384, 6, 1536, 577, 29) == 1         # 2^14 rows
+    assert group_limit(768, 12, 3072, 197, 41) > 1 and group_limit(768, 12, 3072, 197, 42) == 1        # narrow tiles alone
 
 
 @pytest.mark.parametrize("pairs", [1, 2, 16, 24, 32, 36, 60, 96, 128, 140, 255, 256, 257, 272, 4096])

@@ -17,6 +17,14 @@ pytestmark = pytest.mark.gpu
     (65, 128, 2, 512, (0, 1, 2, 3), 100, 13, False),    # more micro-batches than two groups hold
     (577, 384, 6, 1536, (0, 1, 2), 14, 5, True),        # micro-batches near the largest that are grouped
     (577, 384, 6, 1536, (0, 1, 2), 15, 3, False),       # the first past it
+    # rows of one micro-batch, or of several together, that leave a persistent launch rows past its tile walk, which it would
+    # deal in narrow tiles with eight sums to an output
+    (197, 768, 12, 3072, (0, 1, 2), 14, 3, False),      # 82 in q|k|v of three together
+    (197, 768, 12, 3072, (0, 1, 2), 7, 6, True),        # the same of six
+    (197, 1024, 16, 4096, (0, 1), 7, 3, False),         # 41 in the first MLP layer of three, K ranges
+    (257, 1280, 16, 5120, (0, 1), 4, 3, False),         # 12 in the first MLP layer of three, d_head 80
+    (197, 512, 8, 2048, (0, 1, 2), 42, 2, False),       # 82 in the first MLP layer of one alone
+    (197, 512, 8, 2048, (0, 1), 55, 3, False),          # 83 in q|k|v of one alone, none of three
 ])
 def test_groups_equal_single_micro_batches(T, D, Hh, M, cuts, mb, n_micro, boundary_bf16):
     import torch
