@@ -418,9 +418,9 @@ __global__ __launch_bounds__(256, 4) void gemm_f32_tile_kernel(const float *__re
 #endif
 }
 
-// LayerNorm and the dense layer after it, many rows, K <= 16 NS: 64 rows to a workgroup, which stay in registers (each of
-// its eight waves holds 16 of them, all K, normalised there: a row's sums need two shuffles and no exchange between
-// waves) while the weights pass by in steps of 32 columns, 16 for each half of the waves.  Three steps of weights in
+// LayerNorm and the dense layer after it, many rows, K <= 16 NS (NS the next multiple of four): 64 rows to a workgroup,
+// which stay in registers (each of its eight waves holds 16 of them, all K, normalised there: a row's sums need two shuffles
+// and no exchange between waves) while the weights pass by in steps of 32 columns, 16 for each half of the waves.  Three steps of weights in
 // LDS, two on their way: the first is fetched with the rows, the other two use the rows' place once those are in registers.
 // LDS: chunks of 32 k, rows of eight 16-byte pieces, placed and dealt to the quarters of a wave as in the tile kernel.
 // Every load of the loop goes to LDS; what goes to registers (gain, shift, bias) is waited for before it begins.
@@ -940,27 +940,64 @@ hipError_t ep_f32_gemm(const float *A, const float *W, const float *bias, const 
 
 namespace {
 
+constexpr int F32_ROWS = 64, F32_STEP = 32, F32_MAX_STEPS = 32;     // F32Rows' panel, columns of a step and most steps
+
+// Steps of a workgroup of the rows kernel, and those of the fullest compute unit in all: bringing the rows in and normalising
+// them takes about as long as a step
+struct F32RowsSteps { int steps; int64_t unit; };
+F32RowsSteps f32_rows_steps(int64_t M, int N, int cus)
+{
+    const int64_t panels = (M + F32_ROWS - 1) / F32_ROWS;
+    const int all = (N + F32_STEP - 1) / F32_STEP;
+    F32RowsSteps best = {1, INT64_MAX};
+    for (int n = 1; n <= F32_MAX_STEPS && n <= all; ++n) {
+        const int64_t c = (panels * ((all + n - 1) / n) + cus - 1) / cus * (n + 1);
+        if (c < best.unit) best = {n, c};
+    }
+    return best;
+}
+
+inline int f32_rows_depth(int K) { return (K + 63) / 64 * 64; }    // what the rows kernel multiplies of it: whole F32Rows<4 n>
+
+// LayerNorm and the dense layer behind it: how
+enum F32LnRoute { F32_TWO_LAUNCHES = 0, F32_TILES_16 = 1, F32_TILES_32 = 2, F32_ROWS_IN_REGISTERS = 3 };
+
+// K % 4 == 0, K <= 384.  A row of tiles of 16 or 32 normalises its rows again and again: past two and three of them to a unit
+// (K <= 192: 788 x 768 8.5 us against 8.9 with 64 rows, 1040 x 768 10.4 against 9.2) or one of 32 (394 x 1536 x 384 17.8 against
+// 13.6) the rows kernel, where it pays.  It saves a launch and the rows' trip through memory, and loses to the 64 x 32 tiles
+// what it multiplies past K, and beyond 192 deep, with room for one workgroup on a unit, some of their rate: its steps against
+// two for the launch, 0.85 for each tile a unit would have, in the measure of the depth, and 5.5 for each panel's LayerNorm.  Over 1095
+// shapes (K = 16 to 384, N = 2 to 8 K, 65 to 25216 rows) 11 % faster on average than two launches (or 32-wide tiles) and 14 %
+// slower at worst (2364 x 400 x 200 12.2 -> 14.0 us).  Depths that fill it up to 192 always go there: 7 % slower at worst
+// (4728 x 1536 x 192 38.8 -> 41.4), 0.6 of the time at best (12608 x 96 x 32 10.2 -> 6.3).  With no depths but 192 and 384 and no
+// rule up to 192, 25216 x 256 x 32 took 36.8 us where two launches take 22.9, 25216 x 768 x 96 84.1 for 60.5.
+F32LnRoute f32_ln_route(int64_t M, int N, int K, int cus)
+{
+    const int64_t t32 = square_tiles(M, N, 32);
+    if (square_tiles(M, N, 16) <= 2 * cus) return F32_TILES_16;
+    if (t32 <= (K <= 192 ? 3 : 1) * cus) return F32_TILES_32;
+    const int depth = f32_rows_depth(K);
+    const int64_t panels = (M + F32_ROWS - 1) / F32_ROWS, tiles = panels * ((N + F32_STEP - 1) / F32_STEP);
+    const bool fills = K <= 64 || (K <= 192 && depth - K < 16);
+    if (fills || f32_rows_steps(M, N, cus).unit <= 2.0 + (0.85 * tiles * K / depth + 5.5 * panels) / cus) return F32_ROWS_IN_REGISTERS;
+    return t32 <= 3 * cus ? F32_TILES_32 : F32_TWO_LAUNCHES;
+}
+
 template <int NS, int EPI>
 hipError_t launch_f32_rows(const float *x, const float *g, const float *b, float eps, const float *W, const float *bias, float *C,
                            int64_t M, int N, int K, int vec, int cus, hipStream_t s)
 {
     using S = F32Rows<NS>;
+    static_assert(S::T == F32_ROWS && S::CN == F32_STEP && S::MAX_STEPS == F32_MAX_STEPS, "as planned");
     auto kern = gemm_f32_rows_kernel<NS, EPI>;
     static EpSmemLimit smem_limit;
     const hipError_t e = smem_limit.ensure(reinterpret_cast<const void *>(kern), (int)S::smem);
     if (e != hipSuccess) return e;
     const int64_t panels = (M + S::T - 1) / S::T;
-    const int all = (N + S::CN - 1) / S::CN;
-    // steps of a workgroup: bringing the rows in and normalising them takes about as long as a step
-    int best = 1;
-    int64_t cost = INT64_MAX;
-    for (int n = 1; n <= S::MAX_STEPS && n <= all; ++n) {
-        const int64_t c = (panels * ((all + n - 1) / n) + cus - 1) / cus * (n + 1);
-        if (c < cost) { cost = c; best = n; }
-    }
-    const int groups = (all + best - 1) / best;
+    const int all = (N + S::CN - 1) / S::CN, steps = f32_rows_steps(M, N, cus).steps;
+    const int groups = (all + steps - 1) / steps;
     const int64_t tiles = panels * groups;
-    hipLaunchKernelGGL(kern, f32_tile_grid(tiles), dim3(512), S::smem, s, x, g, b, eps, W, bias, C, M, N, K, best, groups,
+    hipLaunchKernelGGL(kern, f32_tile_grid(tiles), dim3(512), S::smem, s, x, g, b, eps, W, bias, C, M, N, K, steps, groups,
                        (int)tiles, vec);
     return hipGetLastError();
 }
@@ -973,16 +1010,28 @@ hipError_t launch_f32_ln_gemm(const float *x, const float *g, const float *b, fl
     const hipError_t e = ep_device_cu_count(&cus);
     if (e != hipSuccess) return e;
     const int vec = N % 4 == 0 && aligned16(bias) && aligned16(C);
-    if (square_tiles(M, N, 16) <= 2 * cus)
+    switch (f32_ln_route(M, N, K, cus)) {
+    case F32_TILES_16:
         return K <= 192 ? launch_f32_direct<1, 1, EPI, 3>(x, g, b, eps, W, bias, nullptr, C, M, N, K, vec, s)
                         : launch_f32_direct<1, 1, EPI, 6>(x, g, b, eps, W, bias, nullptr, C, M, N, K, vec, s);
-    // a row of tiles of 32 normalises its rows again and again: past three to a unit (K <= 192: 788 x 768 8.5 us against
-    // 8.9 with 64 rows, 1040 x 768 10.4 against 9.2) or one (394 x 1536 x 384 17.8 against 13.6)
-    if (square_tiles(M, N, 32) <= (K <= 192 ? 3 : 1) * cus)
+    case F32_TILES_32:
         return K <= 192 ? launch_f32_direct<2, 2, EPI, 3>(x, g, b, eps, W, bias, nullptr, C, M, N, K, vec, s)
                         : launch_f32_direct<2, 2, EPI, 6>(x, g, b, eps, W, bias, nullptr, C, M, N, K, vec, s);
-    return K <= 192 ? launch_f32_rows<12, EPI>(x, g, b, eps, W, bias, C, M, N, K, vec, cus, s)
-                    : launch_f32_rows<24, EPI>(x, g, b, eps, W, bias, C, M, N, K, vec, cus, s);
+    case F32_ROWS_IN_REGISTERS:
+#define EP_F32_ROWS(NS) return launch_f32_rows<NS, EPI>(x, g, b, eps, W, bias, C, M, N, K, vec, cus, s)
+        switch (f32_rows_depth(K)) {
+        case 64: EP_F32_ROWS(4);
+        case 128: EP_F32_ROWS(8);
+        case 192: EP_F32_ROWS(12);
+        case 256: EP_F32_ROWS(16);
+        case 320: EP_F32_ROWS(20);
+        case 384: EP_F32_ROWS(24);
+        }
+#undef EP_F32_ROWS
+        break;
+    case F32_TWO_LAUNCHES: break;
+    }
+    return hipErrorInvalidValue;
 }
 
 }  // namespace
@@ -991,13 +1040,11 @@ bool ep_f32_ln_gemm_supported(const float *x, const float *W, int64_t M, int N, 
 {
     int cus = 0;
     if (ep_device_cu_count(&cus) != hipSuccess) return false;
-    // any number of rows up to 192 wide; wider ones leave room for one workgroup of 64 rows on a compute unit, which is the
-    // better way up to 24 tiles of 32 to a unit (3152 x 1536 x 384 44.6 us against 48.1 with LayerNorm on its own,
-    // 6304 x 1152 x 384 64 against 61)
-    const int64_t t32 = square_tiles(M, N, 32);
-    return K % 4 == 0 && K <= 384 && M > 0 && N > 0 && aligned16(x) && aligned16(W) && t32 < (1 << 24) &&
-           (K <= 192 || t32 <= 24 * cus);
+    return K % 4 == 0 && K <= 384 && M > 0 && N > 0 && aligned16(x) && aligned16(W) && square_tiles(M, N, 32) < (1 << 24) &&
+           f32_ln_route(M, N, K, cus) != F32_TWO_LAUNCHES;
 }
+
+extern "C" int32_t ep_query_f32_ln_route(int64_t M, int32_t N, int32_t K, int32_t cus) { return f32_ln_route(M, N, K, cus); }
 
 hipError_t ep_f32_ln_gemm(const float *x, const float *g, const float *b, float eps, const float *W, const float *bias, float *C,
                           int64_t M, int N, int K, int epi, hipStream_t s)

@@ -21,10 +21,13 @@ hipError_t ep_f32_layernorm(const float *x, int64_t ldx, const float *g, const f
                             int64_t rows, int D, hipStream_t s);
 hipError_t ep_f32_gemm(const float *A, const float *W, const float *bias, const float *resid,
                        float *C, int64_t M, int N, int K, int epi, hipStream_t s);
-// C = LN(x) . W^T + bias (EPI_BIAS or EPI_BIAS_GELU) in one launch, for problems of few tiles and K <= 384
+// C = LN(x) . W^T + bias (EPI_BIAS or EPI_BIAS_GELU) in one launch, where that pays and K <= 384
 bool ep_f32_ln_gemm_supported(const float *x, const float *W, int64_t M, int N, int K);
 hipError_t ep_f32_ln_gemm(const float *x, const float *g, const float *b, float eps, const float *W, const float *bias,
                           float *C, int64_t M, int N, int K, int epi, hipStream_t s);
+// what becomes of the two (x and W on 16 bytes, K % 4 == 0, K <= 384) on `cus` compute units, for tests: 0 two launches, 1 and 2
+// tiles of 16 and of 32, 3 rows kept in registers
+extern "C" int32_t ep_query_f32_ln_route(int64_t M, int32_t N, int32_t K, int32_t cus);
 hipError_t ep_f32_attention(const float *qkv, float *o, int B, int T, int D, int H, hipStream_t s);
 
 // ---- bf16 path -------------------------------------------------------------

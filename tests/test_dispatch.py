@@ -108,6 +108,23 @@ def test_what_is_not_grouped():
     assert group_limit(768, 12, 3072, 197, 41) > 1 and group_limit(768, 12, 3072, 197, 42) == 1        # narrow tiles alone
 
 
+def f32_ln_route(rows, n, k, cus=256):
+    f = binding.lib().ep_query_f32_ln_route
+    f.argtypes, f.restype = [C.c_int64, C.c_int32, C.c_int32, C.c_int32], C.c_int32
+    return f(rows, n, k, cus)
+
+
+# fp32 LayerNorm and dense layer: 0 in two launches (the rows kernel up to 1.6 times as long), 3 rows in registers (two launches
+# up to 1.6 times as long), 1 and 2 tiles of 16 and 32 that normalise on the way
+@pytest.mark.parametrize("rows,n,k,route", [
+    (65, 768, 192, 1), (591, 768, 192, 2), (394, 288, 96, 1),
+    (25216, 768, 96, 0), (9456, 1600, 200, 0), (6304, 1792, 224, 0), (25216, 1600, 160, 0), (12608, 1536, 384, 0), (2364, 2560, 320, 0),
+    (12608, 96, 32, 3), (25216, 256, 32, 3), (6304, 768, 192, 3), (25216, 192, 64, 3), (394, 1536, 384, 3), (1182, 600, 200, 3),
+])
+def test_fp32_layernorm_and_dense_layer(rows, n, k, route):
+    assert f32_ln_route(rows, n, k) == route
+
+
 @pytest.mark.parametrize("pairs", [1, 2, 16, 24, 32, 36, 60, 96, 128, 140, 255, 256, 257, 272, 4096])
 def test_every_attention_group_holds_a_query(pairs):
     f = binding.lib().ep_query_attention_plan
