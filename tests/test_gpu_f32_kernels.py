@@ -83,3 +83,23 @@ def test_f32_trace_of_a_layernorm_inside_a_dense_layer():
         np.testing.assert_array_equal(H.run_stage(st, x), want)
         n, sec = st.trace_end()
         assert n == 2 and sec >= 0
+
+
+def test_f32_attention_on_the_largest_grid():
+    """2^24 - 1 (image, head) pairs of one token, a workgroup each: 256 threads less than a grid may have.  61455 images,
+    the same 61 over and over: the checker on those, and every other one their bits."""
+    import torch
+    n, B = 61, 61455
+    sh = synth.custom_shape("f32k_grid", 1, 1092, 273, 4, 1)
+    layers = [synth.layer_params(sh, 0, randomize_affine=True, w_std=0.1)]
+    x = synth.activations(sh, n)
+    st = H.make_stage(sh, layers, 0, 1, B, bf16=False)
+    xin = torch.from_numpy(np.resize(x, (B, 1, 1092))).cuda()
+    out = torch.full_like(xin, float("nan"))
+    st.forward(xin, B, out, torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    assert H.rel_err(out[:n].cpu().numpy(), oracle.stage_forward(H.oracle_cfg(sh), layers, x)) <= H.TOL_F32
+    k = B // n * n
+    assert torch.equal(out[:k].view(-1, n, 1092), out[:n].view(1, n, 1092).expand(k // n, n, 1092))
+    assert torch.equal(out[k:], out[:B - k])
+    st.destroy()
