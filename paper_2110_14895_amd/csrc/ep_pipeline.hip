@@ -19,10 +19,10 @@
 // where the sizes and the times stand).  Two groups are under way at once, each
 // on a stream with a workspace of its own, so that the uneven last rounds and
 // the row kernels of one meet dense layers of the other (one at a time: ViT-Large,
-// four micro-batches of 24, 3.46 against 3.17 ms).  Micro-batches that fill the
-// chip by themselves, ones with narrow tiles at the end of a dense layer (their
-// sums depend on where a row lies), fp32 stages and a run of one keep the schedule
-// above.
+// four micro-batches of 24, 3.46 against 3.17 ms); a single stage has one stream
+// and takes one group at a time.  Micro-batches that fill the chip by themselves,
+// ones with narrow tiles at the end of a dense layer (their sums depend on where
+// a row lies), fp32 stages and a run of one keep the schedule above.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -44,11 +44,12 @@ struct ep_pipeline {
     size_t elems = 0;                      // micro_batch * T * D
     size_t in_bytes = 0, out_bytes = 0;    // of one micro-batch
     int32_t group = 1;                     // most micro-batches taken together
+    int lanes = 1;                         // groups under way at once, each on a stage's stream
     char *group_mem = nullptr;             // for each lane the workspace of a group, shared by the stages as they run
     size_t group_ws = 0, group_edge = 0;   // in turn, and two boundaries; their bytes
 };
 
-constexpr int LANES = 2;                   // groups under way at once
+constexpr int LANES = 2;                   // of pipelines that have as many stages
 
 #define EP_HIP(call)                                                                         \
     do {                                                                                     \
@@ -142,7 +143,8 @@ extern "C" ep_status ep_pipeline_create(int32_t n_stages, ep_stage_t *const *sta
     if (group > 1) {
         for (ep_stage_t *st : p->stages) p->group_ws = std::max(p->group_ws, ep_stage_group_bytes(st, micro_batch, group));
         if (n_stages > 1) p->group_edge = (p->elems * group * 4 + 255) / 256 * 256;
-        if (hipMalloc((void **)&p->group_mem, LANES * (p->group_ws + 2 * p->group_edge)) == hipSuccess) {
+        p->lanes = std::min(LANES, (int)n_stages);
+        if (hipMalloc((void **)&p->group_mem, p->lanes * (p->group_ws + 2 * p->group_edge)) == hipSuccess) {
             p->group = group;
         } else {
             p->group_mem = nullptr;
@@ -160,7 +162,7 @@ ep_status run_groups(ep_pipeline *p, const char *x_in, int32_t n_micro, char *x_
 {
     const int S = (int)p->stages.size();
     const int32_t groups = (n_micro + p->group - 1) / p->group;
-    const int lanes = std::min(std::min(groups, LANES), (int)p->streams.size());
+    const int lanes = std::min(groups, p->lanes);
     EP_HIP(hipEventRecord(p->start, caller));
     for (int l = 0; l < lanes; ++l) EP_HIP(hipStreamWaitEvent(p->streams[l], p->start, 0));
     for (int32_t i = 0, m = 0; i < groups; ++i) {

@@ -5,6 +5,7 @@ import pytest
 
 from paper_2110_14895_amd import binding, synth
 from tests import harness as H
+from tests.test_dispatch import group_limit
 from tests.test_gpu_pipeline import build, layers_of
 
 pytestmark = pytest.mark.gpu
@@ -49,6 +50,21 @@ def test_groups_equal_single_micro_batches(T, D, Hh, M, cuts, mb, n_micro, bound
         got = out.cpu().numpy()
         np.testing.assert_array_equal(got[:n * mb], want[:n * mb])
         assert np.isnan(got[n * mb:]).all()
+    pipe.destroy()
+
+
+def test_a_single_stage_has_memory_for_one_group():
+    """Its one stream takes one group at a time: no second workspace (13 micro-batches: 20488 rows, 2 K ranges, 346 MB)."""
+    import torch
+    sh = synth.custom_shape("groups_memory", 1, 768, 12, 3072, 197)
+    stages = build(sh, layers_of(sh, 1, True), (0, 1), 8, bf16=True)
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    pipe = binding.Pipeline(stages, 8)
+    used = free - torch.cuda.mem_get_info()[0]
+    rows = 8 * 197 * group_limit(768, 12, 3072, 197, 8, in_dtype=binding.EP_BF16)
+    one = rows * (4 * 768 + 2 * 768 + 2 * 3072 + 2 * 4 * 768)
+    assert one <= used < 1.5 * one
     pipe.destroy()
 
 
