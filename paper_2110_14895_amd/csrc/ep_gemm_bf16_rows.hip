@@ -122,14 +122,16 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_bf16_rows_kernel(const float 
             for (int i = 0; i < NV; ++i)
                 if (in(i)) {
                     v[t][i] -= mean;
-                    // which products are rounded is not left to the compiler: as in ln_bf16_kernel
+                    // which products are rounded is not left to the compiler, here and below: as in ln_bf16_kernel
                     q += __builtin_fmaf(v[t][i][0], v[t][i][0], v[t][i][1] * v[t][i][1]) + __builtin_fmaf(v[t][i][2], v[t][i][2], v[t][i][3] * v[t][i][3]);
                 }
             const float inv = 1.0f / sqrtf(lanes_sum<LPR>(q) / (float)S::K + eps);
 #pragma unroll
             for (int i = 0; i < NV; ++i)
                 if (in(i)) {
-                    const f32x4 y = v[t][i] * inv * gg[i] + bb[i];
+                    f32x4 y;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) y[j] = __builtin_fmaf(v[t][i][j] * inv, gg[i][j], bb[i][j]);
                     const int c = lr + i * LPR;      // float4 c of the row: half of chunk c / 2
                     reinterpret_cast<uint2 *>(lds + r * S::CH + S::slot(r, c >> 1))[c & 1] = make_uint2(pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3]));
                 }

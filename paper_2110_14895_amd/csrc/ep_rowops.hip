@@ -97,7 +97,7 @@ __global__ __launch_bounds__(256) void ln_bf16_kernel(float *__restrict__ x, int
         const int c = lane + i * LPR;
         if (!GUARD || c < nvec) {
             v[i].x -= mean; v[i].y -= mean; v[i].z -= mean; v[i].w -= mean;
-            // which products are rounded is not left to the compiler: ep_gemm_bf16_rows.hip gives the same bits
+            // which products are rounded is not left to the compiler, here and below: ep_gemm_bf16_rows.hip gives the same bits
             q += __builtin_fmaf(v[i].x, v[i].x, v[i].y * v[i].y) + __builtin_fmaf(v[i].z, v[i].z, v[i].w * v[i].w);
         }
     }
@@ -111,8 +111,8 @@ __global__ __launch_bounds__(256) void ln_bf16_kernel(float *__restrict__ x, int
         if (!GUARD || c < nvec) {
             const float4 gg = g4[c], bb = b4[c];
             uint2 o;
-            o.x = pack_bf16x2(v[i].x * inv * gg.x + bb.x, v[i].y * inv * gg.y + bb.y);
-            o.y = pack_bf16x2(v[i].z * inv * gg.z + bb.z, v[i].w * inv * gg.w + bb.w);
+            o.x = pack_bf16x2(__builtin_fmaf(v[i].x * inv, gg.x, bb.x), __builtin_fmaf(v[i].y * inv, gg.y, bb.y));
+            o.y = pack_bf16x2(__builtin_fmaf(v[i].z * inv, gg.z, bb.z), __builtin_fmaf(v[i].w * inv, gg.w, bb.w));
             yr[c] = o;
         }
     }

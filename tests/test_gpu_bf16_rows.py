@@ -1,11 +1,13 @@
 """GPU parity of LayerNorm and the dense layer behind it in one launch (narrow bf16 models: 128 rows to a workgroup, 32
-columns of a wave at a time), at the edges of rows, columns and depth, against the oracle on the first and the last image.
-The tolerance is the bf16 path's."""
+columns of a wave at a time), at the edges of rows, columns and depth, against the oracle on the first and the last image
+(the tolerance is the bf16 path's), and bit for bit against the two launches."""
+import numpy as np
 import pytest
 
 import oracle
 from paper_2110_14895_amd import synth
 from tests import harness as H
+from tests.test_dispatch import EPI_BIAS, EPI_BIAS_GELU, dense_plan
 
 pytestmark = pytest.mark.gpu
 
@@ -28,3 +30,33 @@ def test_layernorm_inside_a_dense_layer(T, D, Hh, M, B, in_bf16):
     ref = oracle.stage_forward(H.oracle_cfg(sh), layers, x[pick])
     for k, i in enumerate(pick):
         assert H.rel_err(got[i], ref[k]) <= H.TOL_BF16, i
+
+
+# A stage that takes bf16 normalises its input in the launch that widens it and runs q|k|v behind that; the same values in fp32
+# go through the one launch.  Panels of 64 and of 128 rows, the last one rarely whole, every depth.
+@pytest.mark.parametrize("T,D,Hh,B", [
+    (65, 64, 1, 1), (65, 64, 1, 150), (129, 128, 2, 20), (65, 128, 2, 600), (197, 192, 3, 2), (577, 192, 3, 71), (197, 256, 4, 7),
+    (197, 256, 4, 70), (257, 320, 4, 6), (257, 320, 4, 60), (197, 384, 6, 24), (197, 384, 6, 64),
+])
+def test_bits_of_two_launches(T, D, Hh, B):
+    assert dense_plan(T * B, 3 * D, D, EPI_BIAS).m_main == T * B        # no rows that add up in another order
+    sh = synth.custom_shape(f"rowbits_{T}_{D}", 1, D, Hh, 64, T)
+    p = [synth.layer_params(sh, 0, bf16=True, randomize_affine=True, w_std=0.05)]
+    x = synth.activations(sh, B, bf16=True)
+    two = H.run_stage(H.make_stage(sh, p, 0, 1, B, bf16=True, in_bf16=True), x)
+    one = H.run_stage(H.make_stage(sh, p, 0, 1, B, bf16=True, in_bf16=False), x)
+    np.testing.assert_array_equal(one, two)
+
+
+# The first MLP layer, with GELU: past 256 wide, up to 1023 rows take two launches and more rows one
+@pytest.mark.parametrize("T,D,Hh", [(197, 320, 4), (197, 384, 6)])
+def test_bits_of_two_launches_with_gelu(T, D, Hh):
+    B, few = 40, 5
+    assert dense_plan(T * few, 512, D, EPI_BIAS_GELU).m_main == T * few < 1024 <= T * B
+    sh = synth.custom_shape(f"rowgelu_{T}_{D}", 1, D, Hh, 512, T)       # 512 deep: the second MLP layer is never cut
+    p = [synth.layer_params(sh, 0, bf16=True, randomize_affine=True, w_std=0.05)]
+    x = synth.activations(sh, B, bf16=True)
+    st = H.make_stage(sh, p, 0, 1, B, bf16=True)
+    one = H.run_stage(st, x)
+    for i in range(0, B, few):
+        np.testing.assert_array_equal(H.run_stage(st, x[i:i + few]), one[i:i + few])
