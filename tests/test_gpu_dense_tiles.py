@@ -2,7 +2,9 @@
 compute units, on the shapes named beside it (asked of the dispatcher, so that a change of its costs cannot move a case
 to other kernels unnoticed), rows and columns rarely whole numbers of tiles.  Between them the cases run every shape with every
 epilogue it is chosen for.  Against the checker on the first, a middle and the last image (the last one sits in the
-partly filled tile row); the tolerance is the bf16 path's."""
+partly filled tile row); the tolerance is the bf16 path's.  128x128 and 128x128x2 are one kernel at two prices.  Up to 384 wide the
+first MLP layer, with its LayerNorm, is a kernel of its own (test_gpu_bf16_rows.py) and the third shape is not run; the last
+cases hold the shapes with GELU at 448."""
 import pytest
 
 import oracle
@@ -47,6 +49,14 @@ def shapes_of(rows, d, m):
     (50, 448, 7, 192, 90, "256x128 64x64x2 64x64x2 64x64x2"),
     (577, 128, 2, 448, 86, "128x128x2 128x128x2 P256x256 256x128"),
     (577, 256, 4, 576, 57, "P256x256 192x256 P256x320+121 192x256"),
+    (257, 448, 7, 2048, 8, "128x128 64x64x2 192x128 64x64x2"),
+    (257, 448, 7, 2048, 12, "192x128 64x128x2 256x128 64x128x2"),
+    (197, 448, 7, 2048, 21, "192x128 64x64x2 256x192 64x64x2"),
+    (257, 448, 7, 1792, 25, "256x192 128x128 192x256 128x128"),
+    (257, 448, 7, 2048, 24, "256x192 128x128 256x256 128x128"),
+    (197, 448, 7, 2048, 63, "P256x320 256x128 P256x256 256x128"),
+    (65, 448, 7, 2048, 127, "256x192 192x128 P256x256+63 192x128"),
+    (257, 448, 7, 2048, 36, "P256x256 192x128 P256x320+36 192x128"),
 ])
 def test_tile_shapes(T, D, Hh, M, B, shapes):
     assert shapes_of(T * B, D, M) == shapes

@@ -1,5 +1,7 @@
 """Micro-batches that a pipeline takes through its stages in groups: the bits are those of each micro-batch on its own,
-whatever the number of groups, the K ranges of the second MLP layer, the boundary types and the caller's stream."""
+whatever the number of groups, the K ranges of the second MLP layer, the boundary types and the caller's stream.  `limit` is the
+number of micro-batches a group may have (1: none are grouped), asked of the library, so that a change of the limits cannot
+move a case to another schedule unnoticed; two groups run side by side."""
 import numpy as np
 import pytest
 
@@ -11,24 +13,29 @@ from tests.test_gpu_pipeline import build, layers_of
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("T,D,Hh,M,cuts,mb,n_micro,boundary_bf16", [
-    (197, 768, 12, 3072, (0, 1, 2), 8, 9, False),       # two K ranges; groups of three and of two lanes' turns
-    (197, 1024, 16, 4096, (0, 2), 1, 7, False),         # one stage, four K ranges, one group
-    (257, 320, 4, 1280, (0, 1, 2), 2, 5, True),         # d_head 80, bf16 between the stages
-    (65, 128, 2, 512, (0, 1, 2, 3), 100, 13, False),    # more micro-batches than two groups hold
-    (577, 384, 6, 1536, (0, 1, 2), 14, 5, True),        # micro-batches near the largest that are grouped
-    (577, 384, 6, 1536, (0, 1, 2), 15, 3, False),       # the first past it
+@pytest.mark.parametrize("T,D,Hh,M,cuts,mb,n_micro,boundary_bf16,limit", [
+    (197, 768, 12, 3072, (0, 1, 2), 8, 9, False, 13),       # two K ranges, one group
+    (197, 768, 12, 3072, (0, 1, 2), 8, 14, False, 13),      # two K ranges, two groups of seven side by side
+    (197, 1024, 16, 4096, (0, 2), 1, 7, False, 41),         # one stage, four K ranges, one group
+    (65, 512, 8, 4096, (0, 2), 16, 47, False, 15),          # one stage, four K ranges, four groups one after the other
+    (257, 320, 4, 1280, (0, 1, 2), 2, 5, True, 63),         # d_head 80, bf16 between the stages
+    (65, 128, 2, 512, (0, 1, 2, 3), 100, 13, False, 5),     # more micro-batches than two groups hold
+    (577, 384, 6, 1536, (0, 1, 2), 14, 5, True, 4),         # groups of three and of two
+    (577, 384, 6, 1536, (0, 1, 2), 15, 3, False, 3),        # one group of as many as it may have
+    (577, 384, 6, 1536, (0, 1, 2), 28, 3, False, 2),        # 16156 rows, near the largest micro-batches that are grouped
+    (577, 384, 6, 1536, (0, 1, 2), 29, 3, False, 1),        # 16733, the first past 2^14: one by one
     # rows of one micro-batch, or of several together, that leave a persistent launch rows past its tile walk, which it would
     # deal in narrow tiles with eight sums to an output
-    (197, 768, 12, 3072, (0, 1, 2), 14, 3, False),      # 82 in q|k|v of three together
-    (197, 768, 12, 3072, (0, 1, 2), 7, 6, True),        # the same of six
-    (197, 1024, 16, 4096, (0, 1), 7, 3, False),         # 41 in the first MLP layer of three, K ranges
-    (257, 1280, 16, 5120, (0, 1), 4, 3, False),         # 12 in the first MLP layer of three, d_head 80
-    (197, 512, 8, 2048, (0, 1, 2), 42, 2, False),       # 82 in the first MLP layer of one alone
-    (197, 512, 8, 2048, (0, 1), 55, 3, False),          # 83 in q|k|v of one alone, none of three
+    (197, 768, 12, 3072, (0, 1, 2), 14, 3, False, 7),      # 82 in q|k|v of three together
+    (197, 768, 12, 3072, (0, 1, 2), 7, 6, True, 7),        # the same of six
+    (197, 1024, 16, 4096, (0, 1), 7, 3, False, 5),         # 41 in the first MLP layer of three, K ranges
+    (257, 1280, 16, 5120, (0, 1), 4, 3, False, 6),         # 12 in the first MLP layer of three, d_head 80
+    (197, 512, 8, 2048, (0, 1, 2), 42, 2, False, 1),       # 82 in the first MLP layer of one alone
+    (197, 512, 8, 2048, (0, 1), 55, 3, False, 1),          # 83 in q|k|v of one alone, none of three
 ])
-def test_groups_equal_single_micro_batches(T, D, Hh, M, cuts, mb, n_micro, boundary_bf16):
+def test_groups_equal_single_micro_batches(T, D, Hh, M, cuts, mb, n_micro, boundary_bf16, limit):
     import torch
+    assert {group_limit(D, Hh, M, T, mb, in_dtype=i) for i in (binding.EP_BF16, binding.EP_F32)} == {limit}
     sh = synth.custom_shape(f"groups_{T}_{D}", cuts[-1], D, Hh, M, T)
     stages = build(sh, layers_of(sh, cuts[-1], True), cuts, mb, bf16=True, boundary_bf16=boundary_bf16)
     pipe = binding.Pipeline(stages, mb)
@@ -68,10 +75,11 @@ def test_a_single_stage_has_memory_for_one_group():
     pipe.destroy()
 
 
-def test_groups_in_a_graph():
+@pytest.mark.parametrize("mb,n_micro,limit", [(4, 6, 126), (126, 7, 4)])        # one group; two, forked and joined
+def test_groups_in_a_graph(mb, n_micro, limit):
     import torch
     sh = synth.custom_shape("groups_graph", 2, 256, 4, 512, 65)
-    mb, n_micro = 4, 6
+    assert group_limit(256, 4, 512, 65, mb, in_dtype=binding.EP_BF16) == limit
     stages = build(sh, layers_of(sh, 2, True), (0, 1, 2), mb, bf16=True)
     pipe = binding.Pipeline(stages, mb)
     xin = H.to_device(synth.activations(sh, mb * n_micro, bf16=True), True)
