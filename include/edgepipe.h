@@ -194,9 +194,11 @@ typedef enum {
  * Start timing one kernel of the layer: until ep_stage_trace_end, every launch
  * of `kernel` made by ep_stage_forward on this stage is bracketed by a pair of
  * events recorded on the forward's stream (at most max_launches pairs, created
- * here; later launches run untimed).  On the fp32 path a LayerNorm may run
- * inside the dense layer behind it; its own bracket is then empty.  Tracing one kernel at a time keeps the
- * other kernels' launches back to back.
+ * here; later launches run untimed).  A LayerNorm may run inside the dense layer
+ * behind it, on either path; its own bracket is then empty.  A pipeline run that
+ * takes micro-batches in groups makes, and times, one launch a group, and brackets
+ * of two groups under way overlap in time.  Tracing one kernel at a time keeps
+ * the other kernels' launches back to back.
  */
 ep_status ep_stage_trace_begin(ep_stage_t *stage, int32_t kernel, int32_t max_launches);
 /*
@@ -308,9 +310,13 @@ void ep_head_destroy(ep_head_t *head);
 /*
  * Pipeline of stages on this device (section 3.1: parts T_1 .. T_n of consecutive
  * layers, micro-batches flowing through them; Eq. 2: the period is set by the
- * slowest part).  The runtime of the paper minus the network: one stream per
- * stage, two boundary buffers per stage boundary, events for "micro-batch m has
- * left stage k" and for the reuse of a boundary buffer.
+ * slowest part).  The runtime of the paper minus the network.  Micro-batches of
+ * bf16 stages that leave the device idle go through the stages in groups of
+ * several, two groups under way at once (one where there is one stage), each on
+ * a stream with a workspace and boundaries of its own.  Others, and a run of one,
+ * go one by one: one stream per stage, two boundary buffers per stage boundary,
+ * events for "micro-batch m has left stage k" and for the reuse of a boundary
+ * buffer.
  *
  * ep_pipeline_create: `stages` (HOST array of n_stages handles, 1..64) in pipeline
  * order; consecutive stages must cover consecutive layer ranges of the same
@@ -325,7 +331,8 @@ void ep_head_destroy(ep_head_t *head);
  * receives them in the last stage's out_dtype.  Enqueue only: the work is
  * ordered after what `stream` holds at the call, and `stream` is made to wait
  * for the last micro-batch; no host synchronisation.  Results are those of
- * running the stages one after the other on each micro-batch.  A stage must
+ * running the stages one after the other on each micro-batch, bit for bit, in
+ * groups or not.  A stage must
  * not be used elsewhere while a run is in flight.  Streams have default priority.
  */
 typedef struct ep_pipeline ep_pipeline_t;

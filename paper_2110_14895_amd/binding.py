@@ -292,8 +292,8 @@ class Head:
 
 
 class Pipeline:
-    """ep_pipeline_*: stages on one device, micro-batches flowing through them on one stream per
-    stage.  Borrows the Stage objects (keep them alive; destroy the pipeline first)."""
+    """ep_pipeline_*: stages on one device, micro-batches flowing through them in groups where they
+    are small, otherwise on one stream per stage.  Borrows the Stage objects (keep them alive; destroy the pipeline first)."""
 
     def __init__(self, stages, micro_batch: int):
         self._stages = list(stages)

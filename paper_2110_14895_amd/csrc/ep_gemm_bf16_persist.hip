@@ -27,12 +27,17 @@
 //   - Fragments are read again between the matrix instructions as soon as their last product is out, 8 to
 //     12 instructions ahead of their use, so that one step's worth of activations and one unit's of
 //     weights is all that registers hold.
-// What bounds it: power.  Against the loop with one barrier a step (both in turn, us): 8192 cubed 747 -> 725 (1516
-// TFLOP/s), 16384 x 5120 x 1280 + GELU in 256-wide tiles 198 -> 185, 16384 x 1280 x 5120 + residual 174 -> 166, 16384 x
-// 1280 x 1280 + residual 70.3 -> 65.6, 65792 rows 744 -> 720 and 774 -> 730.  Moving its barrier, its loads or its
-// reads by a few instructions, wave priorities and wider groups of tile rows change nothing any more; the chip
-// lowers its clock as the matrix pipe gets busier (75 % busy at 1.50 GHz, 76 % at 1.58, a library kernel 91 % at 1.39, all
-// under a profiler).  Then the residual epilogue at 6.7 TB/s.
+// What bounds it: waiting, then the clock.  Under counters (profiles/vit_huge_b64_sq_counters.md) the matrix pipe is busy 58
+// (proj and FC2), 62 (FC1) and 67 % (q|k|v) of the clocks of ViT-Huge's layers on 64 images at 1.9 GHz, and no more on 256; a
+// loop of nothing but matrix instructions keeps it 97 % busy at the same clock.  The waves spend 42 to 47 % of their cycles
+// in s_waitcnt, and all workgroups reach the epilogue together (the residual one moves 6.7 TB/s meanwhile).  The clock
+// takes over where a K loop is long: 8192 cubed, launched as 256-wide tiles, 82 % busy at 1.65 GHz, a library kernel 92 % at
+// 1.60.  Against the loop with one barrier a step (both in turn, us): 8192 cubed 747 -> 725 (1472 -> 1516 TFLOP/s), 16384 x
+// 5120 x 1280 + GELU in 256-wide tiles 198 -> 185, 16384 x 1280 x 5120 + residual 174 -> 166, 16384 x 1280 x 1280 + residual
+// 70.3 -> 65.6, 65792 rows 744 -> 720 and 774 -> 730.  Moving its barrier, its loads or its reads by a few instructions, wave
+// priorities and wider groups of tile rows changed nothing.
+//   Its waits count loads and stores in the order in which they are sent out: panel loads to LDS, the epilogue's stores, the
+// next tile's loads.  Residual loads (to registers) lie between stores that use them, so none is under way when a step counts.
 // Epilogue: 32 x 32 blocks of accumulators (+bias, GELU) are transposed through the
 // W part of the LDS stage the tile's last step has just retired (4 KB per wave),
 // so that global stores and residual loads are whole row segments; the refill of

@@ -51,7 +51,7 @@ hipError_t ep_f32_to_bf16(const float *in, uint16_t *out, int64_t n, hipStream_t
 // below but the classifier takes its weights; N % 16 == 0, K % 32 == 0
 hipError_t ep_bf16_pack_weights(const uint16_t *w, uint16_t *p, int N, int K, hipStream_t s);
 // A bf16 [M, K], W bf16 [N, K] in fragment order; out bf16 (EPI_BIAS, EPI_BIAS_GELU) or fp32 (EPI_BIAS_RESID).
-// K % 64 == 0, N % 16 == 0.
+// K % 64 == 0, N % 16 == 0; from N = 2^20 on EPI_BIAS_RESID only.
 // one_order: every output is one sum over K in order, whatever M is; otherwise a persistent launch may deal its last rows
 // in narrow tiles, which add up eight sums (ep_bf16_gemm_narrow_rows tells how many rows).
 // after_main: if non-null, recorded on s right after the launch (it covers the rows
