@@ -87,7 +87,7 @@ def test_f32_trace_of_a_layernorm_inside_a_dense_layer():
 
 def test_f32_attention_on_the_largest_grid():
     """2^24 - 1 (image, head) pairs of one token, a workgroup each: 256 threads less than a grid may have.  61455 images,
-    the same 61 over and over: the checker on those, and every other one their bits."""
+    the same 61 over and over: the oracle on those, and every other one their bits."""
     import torch
     n, B = 61, 61455
     sh = synth.custom_shape("f32k_grid", 1, 1092, 273, 4, 1)

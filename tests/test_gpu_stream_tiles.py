@@ -2,7 +2,8 @@
 their pipelines are shorter than they are deep and where rows end inside a tile: K of one to nine steps of 64, one row to
 one past a tile.  `shapes` is what the dispatcher runs on 256 compute units (tiles of q|k|v, projection, first and second
 MLP layer as in test_gpu_dense_tiles.py, whose cases hold every shape at greater depths); behind a first layer, and in every
-first MLP layer here up to 256 wide, LayerNorm and the dense layer are one launch of another kernel.  Against the checker on the first and the last image; the tolerance is the bf16 path's."""
+first MLP layer here up to 256 wide, LayerNorm and the dense layer are one launch of another kernel.  Against the oracle on
+the first and the last image; the tolerance is the bf16 path's."""
 import pytest
 
 import oracle
