@@ -1,20 +1,27 @@
-// LayerNorm and the dense layer behind it in one launch, narrow models: the q|k|v projection and the first MLP layer
-// (paper section 2.1) where K = d_model is at most 384.
+// LayerNorm and the dense layer behind it in one launch: the q|k|v projection and the first MLP layer (paper section 2.1)
+// of models up to 1024 wide.
 //
 //   C[M, N] = LN(x)[M, K] . W[N, K]^T + bias[N]   (+ erf GELU), bf16 out
 //
-// A workgroup brings 64 or 128 rows of the fp32 residual stream in, normalises them (the arithmetic and the order of the
-// sums of ln_bf16_kernel, so the same bits) and keeps them in LDS as bf16, all K of them: 96 KB for 128 rows at K = 384.
-// Behind that one barrier its eight waves have nothing to wait for: each takes 32 columns at a time, the weights straight
-// into registers (fragment order, a ring of R slices that runs on from one set of columns to the next), the rows from
-// LDS, the result out through a staging area of its own.
+// A workgroup brings 64 to 128 rows of the fp32 residual stream in, normalises them (the arithmetic and the order of the
+// sums of ln_bf16_kernel, so the same bits) and keeps them in LDS as bf16, all K of them: 96 KB for 128 rows at K = 384,
+// 128 KB for 64 at K = 1024.  Behind that one barrier its eight waves have nothing to wait for: each takes 32 columns at a
+// time, the weights straight into registers (fragment order, a ring of R slices that runs on from one set of columns to
+// the next), the rows from LDS, the result out through a staging area of its own.
 //
 // What bounds it: bringing the rows in (196 KB of fp32 for 128 rows at K = 384, 1.5 us at the 57 bytes a clock of a
-// compute unit), then the matrix instructions, 2.6 us a set of columns for 128 rows of them.  A K of two to twelve slices
+// compute unit), then the matrix instructions, 2.6 us a set of columns for 128 rows of them; from K = 512 on, with fewer rows,
+// the weights on their way into the registers (64 bytes a clock of a unit for 64 rows at the matrix pipe's rate, of the 42
+// that arrive from L2).  All workgroups go through the columns in the same order, so what an XCD has under way of weights that are
+// not in its L2 is no more than what one or two workgroups have, and the launch waits for memory with every set; where few
+// groups share a panel the workgroups of an XCD therefore touch all weights between them while their rows come in, a line to a lane
+// (weights from memory: 6304 x 2304 x 768 33.5 -> 30.8 us, 12608 x 2304 x 768 72.3 -> 54.2, 12608 x 1152 x 384 23.6 -> 20.3,
+// 7880 x 3072 x 1024 68.2 -> 55.7).  A K of two to twelve slices
 // is too short for a tile with a prologue and an epilogue of its own, and LayerNorm was a launch and two trips through
 // memory.  LayerNorm and the dense layer, then this, in us: 1576 x 576 x 192 6.0 and 4.7, 6304 x 576 x 192 9.6 and 6.5,
-// 12672 x 768 x 192 with GELU 18.7 and 12.8, 6304 x 1536 x 384 with GELU 21.8 and 15.4, 4728 x 1152 x 384 14.9 and 10.4,
-// 50688 x 1152 x 384 72.9 and 64.5.
+// 12672 x 768 x 192 with GELU 18.7 and 12.8, 6304 x 1536 x 384 with GELU 21.8 and 15.0, 4728 x 1152 x 384 13.7 and 9.6,
+// 50688 x 1152 x 384 72.9 and 64.5, 6344 x 1536 x 512 22.5 and 15.8, 3172 x 2304 x 768 22.4 and 18.5, 12608 x 3072 x 768
+// with GELU 76.2 and 73.2, 7880 x 3072 x 1024 64.7 and 55.7.
 #include <cstdint>
 #include "ep_gemm_bf16_tile.h"
 #include "ep_launch.h"
@@ -32,8 +39,9 @@ template <int LPR>
 __device__ inline float lanes_sum(float v)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
-    static_assert(LPR == 16 || LPR == 32, "");
-    if (LPR == 32) v += __shfl_xor(v, 16, 64);
+    static_assert(LPR == 16 || LPR == 32 || LPR == 64, "");
+    if (LPR == 64) v += __shfl_xor(v, 32, 64);
+    if (LPR >= 32) v += __shfl_xor(v, 16, 64);
     auto add = [&](auto n) EP_INLINE {
         v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x120 + decltype(n)::value, 0xF, 0xF, false));
     };
@@ -49,14 +57,27 @@ __device__ inline float lanes_sum(float v)
 template <int KS>
 struct Rows {
     static constexpr int K = KS * 32, CH = KS * 4;                     // chunks of a row
-    static constexpr int R = KS % 6 == 0 ? 6 : KS % 5 == 0 ? 5 : KS % 4 == 0 ? 4 : KS;   // slices of weights in registers
-    static constexpr int LPR = K <= 256 ? 16 : 32, NV = (K + 4 * LPR - 1) / (4 * LPR);   // as ln_bf16_kernel's
+    // slices of weights in registers
+    static constexpr int R = KS >= 16 && KS % 8 == 0 ? 8 : KS % 6 == 0 ? 6 : KS % 5 == 0 ? 5 : KS % 4 == 0 ? 4 : KS;
+    static constexpr int LPR = K <= 256 ? 16 : K <= 512 ? 32 : 64, NV = (K + 4 * LPR - 1) / (4 * LPR);   // as ln_bf16_kernel's
     // chunk c of row r, so that the 16-byte reads of 16 rows meet no bank twice: rows of whole 256 bytes all begin at
     // the same bank, others at every second one
     __device__ static int slot(int r, int c) { return K % 128 == 0 ? (c & ~15) | ((c ^ r) & 15) : (c & ~7) | ((c & 7) ^ swz(r)); }
 };
 
+// the staging areas of the waves take what LDS the rows leave: passes of 32 rows, or of 16
 template <int KS, int BM, int EPI>
+struct RowsOut {
+    static constexpr size_t ROWS = (size_t)BM * Rows<KS>::CH * 16;
+    static constexpr int PASS = ROWS + NW * WaveOut<BM / 16, NI, EPI>::LDS_BYTES <= 160 * 1024 ? 32 : 16;
+    typedef WaveOut<BM / 16, NI, EPI, PASS> Out;
+    static constexpr size_t LDS_BYTES = ROWS + NW * Out::LDS_BYTES;
+    static_assert(LDS_BYTES <= 160 * 1024, "LDS of a compute unit");
+};
+
+// TOUCH: the workgroups of an XCD bring the weights into its L2 between them (a template argument: as a branch it cost the
+// launches that do not touch 2 % of twelve DeiT layers)
+template <int KS, int BM, int EPI, bool TOUCH>
 __global__ __launch_bounds__(NW * 64, 2) void gemm_bf16_rows_kernel(const float *x, const float *__restrict__ ln_g,
                                                                     const float *__restrict__ ln_b, float eps, const uint16_t *W,
                                                                     const float *bias, void *Cout, int M, int N, int units, int per,
@@ -65,7 +86,7 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_bf16_rows_kernel(const float 
 #if defined(__HIP_DEVICE_COMPILE__)
     using S = Rows<KS>;
     constexpr int MI = BM / 16;
-    typedef WaveOut<MI, NI, EPI> Out;
+    typedef typename RowsOut<KS, BM, EPI>::Out Out;
     extern __shared__ uint4 lds[];                   // BM rows, then the waves' staging areas
     // consecutive workgroups go to different XCDs: each takes a contiguous run of (panel, group)
     const int total = panels * groups, run = (total + NUM_XCD - 1) / NUM_XCD;
@@ -84,6 +105,25 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_bf16_rows_kernel(const float 
 #pragma unroll
         for (int ni = 0; ni < NI; ++ni)
             wf[r][ni] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rs, lane * 16 + (u * NI + ni) * block, s * FRAG_BYTES, 0));
+        asm volatile("" ::: "memory");
+    };
+
+    // ---- weights, touched: 128 bytes to a lane, behind the rows and the first slices, so that nothing waits for them but the
+    // slices after those; what is past NT loads of a wave comes in as it is needed
+    constexpr int NT = !TOUCH ? 1 : S::K >= 1024 ? 6 : S::K >= 512 ? 4 : 2;
+    int touched[NT];
+#pragma unroll
+    for (int i = 0; i < NT; ++i) touched[i] = 0;
+    auto touch_weights = [&]() EP_INLINE {
+        const int xcd = (int)(blockIdx.x % NUM_XCD), wgs = min(run, total - xcd * run);       // workgroups on this XCD
+        const uint32_t bytes = (uint32_t)nb * (uint32_t)block, lines = (bytes + 127) / 128;
+        const uint32_t mine = (lines + wgs * NW - 1) / (wgs * NW), first = ((blockIdx.x / NUM_XCD) * NW + wave) * mine;
+        const __amdgpu_buffer_rsrc_t rs = make_rsrc(W, bytes);
+#pragma unroll
+        for (int i = 0; i < NT; ++i) {
+            const uint32_t l = (uint32_t)(i * 64 + lane);
+            touched[i] = (int)__builtin_amdgcn_raw_buffer_load_b32(rs, l < mine && first + l < lines ? (int)((first + l) * 128) : OOB, 0, 0);
+        }
         asm volatile("" ::: "memory");
     };
 
@@ -109,6 +149,7 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_bf16_rows_kernel(const float 
         }
 #pragma unroll
         for (int s = 0; s < S::R; ++s) load_w(u0 + wave, s, s);
+        if constexpr (TOUCH) touch_weights();
 #pragma unroll
         for (int t = 0; t < IT; ++t) {
             const int r = (t * NW + wave) * AT + lane / LPR;
@@ -173,44 +214,71 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_bf16_rows_kernel(const float 
         });
         out.template store<0>(acc, stg);
     }
+#pragma unroll
+    for (int i = 0; i < (TOUCH ? NT : 0); ++i) asm volatile("" ::"v"(touched[i]));      // here at the latest they have to have arrived
 #endif
+}
+
+template <int KS, int BM, int EPI, bool TOUCH>
+hipError_t launch_as(const float *x, const float *g, const float *b, float eps, const uint16_t *W, const float *bias, void *C,
+                     int M, int N, int units, int per, int groups, hipStream_t s)
+{
+    auto kern = gemm_bf16_rows_kernel<KS, BM, EPI, TOUCH>;
+    constexpr size_t smem = RowsOut<KS, BM, EPI>::LDS_BYTES;
+    static EpSmemLimit smem_limit;
+    const hipError_t e = smem_limit.ensure(reinterpret_cast<const void *>(kern), (int)smem);
+    if (e != hipSuccess) return e;
+    const int64_t panels = (M + BM - 1) / BM, total = panels * groups;
+    hipLaunchKernelGGL(kern, dim3((unsigned)((total + NUM_XCD - 1) / NUM_XCD * NUM_XCD)), dim3(NW * 64), smem, s, x, g, b, eps, W, bias,
+                       C, M, N, units, per, groups, (int)panels);
+    return hipGetLastError();
 }
 
 template <int KS, int BM, int EPI>
 hipError_t launch_rows(const float *x, const float *g, const float *b, float eps, const uint16_t *W, const float *bias, void *C,
                        int M, int N, int groups, hipStream_t s)
 {
-    auto kern = gemm_bf16_rows_kernel<KS, BM, EPI>;
-    constexpr size_t smem = (size_t)BM * Rows<KS>::CH * 16 + NW * WaveOut<BM / 16, NI, EPI>::LDS_BYTES;
-    static_assert(smem <= 160 * 1024, "LDS of a compute unit");
-    static EpSmemLimit smem_limit;
-    const hipError_t e = smem_limit.ensure(reinterpret_cast<const void *>(kern), (int)smem);
-    if (e != hipSuccess) return e;
-    const int64_t panels = (M + BM - 1) / BM;
-    const int units = (N + UC - 1) / UC;
-    const int per = (units + groups - 1) / groups;
+    const int units = (N + UC - 1) / UC, per = (units + groups - 1) / groups;
     groups = (units + per - 1) / per;
-    const int64_t total = panels * groups;
-    hipLaunchKernelGGL(kern, dim3((unsigned)((total + NUM_XCD - 1) / NUM_XCD * NUM_XCD)), dim3(NW * 64), smem, s, x, g, b, eps, W, bias,
-                       C, M, N, units, per, groups, (int)panels);
-    return hipGetLastError();
+    // Touching pays where a workgroup goes through many columns behind few others' (weights from memory, without and with: 6304 x
+    // 2304 x 768 in three groups 33.5 and 30.8 us, 3152 x 4096 x 1024 in four 43.4 and 39.4, in five 38.0 and 39.5, 3152 x 2304 x
+    // 768 in six 18.8 and 19.8, 6304 x 1152 x 384, 442 KB to a workgroup, in two 12.1 and 12.4) and every XCD has all groups.
+    if constexpr (KS > 8)
+        if (groups <= 4 && (int64_t)per * UC * KS * 64 >= 600 * 1024 && M / BM >= NUM_XCD)
+            return launch_as<KS, BM, EPI, true>(x, g, b, eps, W, bias, C, M, N, units, per, groups, s);
+    return launch_as<KS, BM, EPI, false>(x, g, b, eps, W, bias, C, M, N, units, per, groups, s);
 }
 
-// Rows of a panel and the column groups that share one: rounds of workgroups, each of them as long as the sets of columns
-// a wave takes and one more, for bringing the rows in; 64 rows take half as long at twice the weights from L2 (0.48
-// for 0.55: 6304 x 1152 x 384 14.7 -> 12.9 us, but 18912 x 1152 x 384 28.1 -> 34.1, 50688 x 1152 x 384 65 -> 77).
-struct RowsPlan { int bm, groups; double cost; };
+// Rows of a panel, 64 or as many as LDS holds, by the modelled microseconds of a launch: rounds of workgroups, each of them
+// bringing the rows in, then the sets of columns that a wave takes (matrix instructions) and the columns of the workgroup
+// (weights on their way).  Fitted to 4700 launches of 217 to 39440 rows, K = 64 to 1024, N = 3 K and 4 K: 8 % off a launch, the
+// choice 0.8 % off the fastest of all heights and groups.  A panel is shared by as many column groups as leave one round of
+// workgroups.  (One set of columns more or less for one round more or less, the rule before, took 128 rows in five groups
+// for 6344 x 1152 x 384, 13.1 us, where 64 in two take 11.6; and groups of a whole set of columns at least, 1025 x 1152 x 384
+// 7.4 us, where 64 rows in fifteen groups take 6.6.)
+struct RowsPlan { int bm, groups; double us; };
 
-RowsPlan plan_rows(int64_t M, int N, int cus)
+double rows_us(int64_t M, int N, int K, bool gelu, int bm, int groups, int cus)
 {
-    const int units = (N + UC - 1) / UC;
+    const int units = (N + UC - 1) / UC, per = (units + groups - 1) / groups;
+    const int64_t wgs = (M + bm - 1) / bm * ((units + per - 1) / per);
+    const double rounds = (double)((wgs + cus - 1) / cus), sets = (per + NW - 1) / NW, part = (double)per / NW;
+    const double k = K / 1024.0, b = bm / 64.0;
+    return 3.3 + 0.32e-6 * M * N + 0.75 * wgs / cus * k * b +
+           rounds * (0.2 + b * k * (2.1 + 5.8 * k) + part * k * (1.24 + 2.29 * b) + sets * k * (0.69 * b + 0.49 * k) +
+                     (gelu ? b * (0.14 * part + 0.38 * sets) : 0.0));
+}
+
+RowsPlan plan_rows(int64_t M, int N, int K, bool gelu, int cus)
+{
     RowsPlan best = {0, 0, 1e30};
-    for (int bm : {128, 64})
-        for (int n = 1; n * NW < units + NW; ++n) {
-            const int64_t panels = (M + bm - 1) / bm;
-            const double c = (bm == 128 ? 1.0 : 0.55) * ((panels * n + cus - 1) / cus) * ((units + n * NW - 1) / (n * NW) + 1);
-            if (c < best.cost) best = {bm, n, c};
-        }
+    for (int bm : {K <= 384 ? 128 : K <= 512 ? 96 : K <= 768 ? 80 : 0, 64}) {
+        if (!bm) continue;
+        const int64_t n = cus / ((M + bm - 1) / bm), units = (N + UC - 1) / UC;
+        const int groups = (int)(n < 1 ? 1 : n < units ? n : units);
+        const double us = rows_us(M, N, K, gelu, bm, groups, cus);
+        if (us < best.us) best = {bm, groups, us};
+    }
     return best;
 }
 
@@ -218,30 +286,52 @@ template <int EPI>
 hipError_t launch_k(const float *x, const float *g, const float *b, float eps, const uint16_t *W, const float *bias, void *C,
                     int M, int N, int K, int cus, hipStream_t s)
 {
-    const RowsPlan p = plan_rows(M, N, cus);
-#define EP_ROWS(KS) \
-    return p.bm == 128 ? launch_rows<KS, 128, EPI>(x, g, b, eps, W, bias, C, M, N, p.groups, s) \
-                       : launch_rows<KS, 64, EPI>(x, g, b, eps, W, bias, C, M, N, p.groups, s)
-    switch (K) {
-    case 64: EP_ROWS(2);
-    case 128: EP_ROWS(4);
-    case 192: EP_ROWS(6);
-    case 256: EP_ROWS(8);
-    case 320: EP_ROWS(10);
-    case 384: EP_ROWS(12);
-    }
+    const RowsPlan p = plan_rows(M, N, K, EPI == EPI_BIAS_GELU, cus);
+#define EP_ROWS(KS, BM) \
+    if (K == KS * 32 && p.bm == BM) return launch_rows<KS, BM, EPI>(x, g, b, eps, W, bias, C, M, N, p.groups, s)
+    EP_ROWS(2, 128); EP_ROWS(2, 64);
+    EP_ROWS(4, 128); EP_ROWS(4, 64);
+    EP_ROWS(6, 128); EP_ROWS(6, 64);
+    EP_ROWS(8, 128); EP_ROWS(8, 64);
+    EP_ROWS(10, 128); EP_ROWS(10, 64);
+    EP_ROWS(12, 128); EP_ROWS(12, 64);
+    EP_ROWS(16, 96); EP_ROWS(16, 64);
+    EP_ROWS(24, 80); EP_ROWS(24, 64);
+    EP_ROWS(32, 64);
 #undef EP_ROWS
     return hipErrorInvalidValue;
 }
 
+// The depths there are, and from how many to how many rows the one launch is the faster one.  Few rows take longer to bring in
+// than a launch is worth (LayerNorm and its dense layer, then this, us: 394 x 1152 x 384 6.3 and 6.2, 808 x 2304 x 768 9.8 and
+// 11.0; weights from memory, twelve ViT-Base layers on 8, 12, 14 and 16 images 786, 997, 1113 and 1199, with it 800, 1012, 1076 and 1129;
+// 24 ViT-Large layers on 12, 20, 32 and 40 2599, 3444, 5100 and 5960, with it 2671, 3510, 4943 and 5665).  Of more rows tiles of 256
+// columns ask for a quarter of the weights: 25256 x 3072 x 768 129 and 135, 9456 x 4096 x 1024 89 and 106.
+bool rows_depth(int64_t M, int K)
+{
+    switch (K) {
+    case 64: case 128: case 192: case 256: return true;
+    case 320: case 384: return M >= 500;
+    case 512: return M >= 500 && M <= 20000;
+    case 768: return M >= 2600 && M <= 20000;
+    case 1024: return M >= 5500 && M <= 8192;
+    }
+    return false;
+}
+
 }  // namespace
 
-// Wider rows take longer to bring in than a few of them are worth (LayerNorm and its dense layer, then this: 394 x 1152 x 384
-// 6.3 and 6.7 us, 788 x 960 x 320 7.1 and 7.3, 1182 x 1152 x 384 7.5 and 7.0; 394 x 576 x 192 5.5 and 4.5).
 bool ep_bf16_ln_gemm_supported(int64_t M, int N, int K)
 {
-    return K % 64 == 0 && K >= 64 && K <= 384 && N % 16 == 0 && N < MAX_TILE_N && M * N < (1ll << 31) && (int64_t)N * K * 2 < 0x7FFFFFF0ll &&
-           (K <= 256 || M >= 1024);
+    return rows_depth(M, K) && N % 16 == 0 && N < MAX_TILE_N && M * N < (1ll << 31) && (int64_t)N * K * 2 < 0x7FFFFFF0ll;
+}
+
+extern "C" int32_t ep_query_ln_gemm_plan(int64_t M, int32_t N, int32_t K, int32_t epi, int32_t cus, int32_t *groups)
+{
+    if (M <= 0 || N <= 0 || !ep_bf16_ln_gemm_supported(M, N, K)) return 0;
+    const RowsPlan p = plan_rows(M, N, K, epi == EPI_BIAS_GELU, cus);
+    *groups = p.groups;
+    return p.bm;
 }
 
 hipError_t ep_bf16_ln_gemm(const float *x, const float *g, const float *b, float eps, const uint16_t *W, const float *bias, void *C,

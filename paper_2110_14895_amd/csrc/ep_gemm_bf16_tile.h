@@ -97,14 +97,14 @@ __device__ inline TileOf tile_of(int tiles_m, int tiles_n, int ranges)
 // rows apart, and the address pipe takes 64 cycles for an access that it takes 16 for when four lanes share 64
 // bytes: 16 instead of 64 bytes a clock for a compute unit, 2 us for the 64 KB of fp32 outputs of a 128 x 128 tile and
 // as much for its residual.
-template <int MI, int NI, int EPI>
+template <int MI, int NI, int EPI, int MAX_PASS = 32>
 struct WaveOut {
     static constexpr bool RES = EPI == EPI_BIAS_RESID;
     static constexpr int ESZ = RES || EPI == EPI_PARTIAL ? 4 : 2;
     static constexpr int ROW = NI * 16 * ESZ;                          // bytes of a row of the wave's part
     static constexpr int LPR = ROW / 16;                               // lanes to a row
     static constexpr int PITCH = ROW + 16;                             // in LDS: rows shifted by four banks
-    static constexpr int PASS = MI % 2 == 0 && ROW <= 128 ? 32 : 16;   // rows of a pass
+    static constexpr int PASS = MI % 2 == 0 && ROW <= 128 && MAX_PASS == 32 ? 32 : 16;   // rows of a pass
     static constexpr int NPASS = MI * 16 / PASS, PP = PASS * LPR / 64; // passes; accesses of a lane and pass
     static constexpr size_t LDS_BYTES = 2 * PASS * PITCH;              // two passes take turns
     static_assert(PASS * LPR % 64 == 0, "whole accesses");

@@ -538,10 +538,12 @@ bool has_narrow_rows(const ep_vit_config &c, int32_t micro)
     const int64_t R = (int64_t)micro * c.n_tokens;
     const int D = c.d_model, M = c.d_mlp;
     const int sp = fc2_splits(c, micro);
-    // q|k|v goes without its LayerNorm behind a bf16 input and behind sums over K ranges
-    const bool qkv = !ep_bf16_ln_gemm_supported(R, 3 * D, D) || c.in_dtype == EP_BF16 || sp > 1;
+    // q|k|v goes without its LayerNorm behind a bf16 input and behind sums over K ranges; wider models run it, and the first
+    // MLP layer, in one launch with LayerNorm between two numbers of rows only
+    const bool narrow = D <= 384;
+    const bool qkv = !narrow || !ep_bf16_ln_gemm_supported(R, 3 * D, D) || c.in_dtype == EP_BF16 || sp > 1;
     return (qkv && ep_bf16_gemm_narrow_rows(R, 3 * D, D, EPI_BIAS) > 0) || ep_bf16_gemm_narrow_rows(R, D, D, EPI_BIAS_RESID) > 0 ||
-           (!ep_bf16_ln_gemm_supported(R, M, D) && ep_bf16_gemm_narrow_rows(R, M, D, EPI_BIAS_GELU) > 0) ||
+           (!(narrow && ep_bf16_ln_gemm_supported(R, M, D)) && ep_bf16_gemm_narrow_rows(R, M, D, EPI_BIAS_GELU) > 0) ||
            (sp == 1 && ep_bf16_gemm_narrow_rows(R, D, M, EPI_BIAS_RESID) > 0);
 }
 
