@@ -99,8 +99,8 @@ __global__ __launch_bounds__((NW + NL) * 64, WAVES_PER_SIMD) void gemm_bf16_stre
     const int block = K * 32;                        // bytes of the fragments of 16 columns
     const char *w_base = reinterpret_cast<const char *>(W) + (size_t)min(nb0, nb) * block;
     const uint32_t w_bytes = nb0 < nb ? (uint32_t)(nb - nb0) * (uint32_t)block : 0u;
-    // fragments of A: RA of them, each sent for RA blocks ahead
-    constexpr int RA = MI > 12 ? MI / 2 : MI;
+    // fragments of A: RA of them, each sent for RA blocks ahead; RA divides the fragments of a step
+    constexpr int RA = MI <= 13 ? MI : MI == 15 ? 10 : MI / 2;
     static_assert(NS * MI % RA == 0, "a step's fragments end with the registers");
     bf16x8 wf[D][NS][NI], af[RA];
     // fragment (slice, ni) of step kt.  Steps past the last read an empty buffer.  The empty assembly keeps the loads
@@ -246,16 +246,24 @@ hipError_t ep_bf16_pack_weights(const uint16_t *w, uint16_t *p, int N, int K, hi
     return hipGetLastError();
 }
 
-// bm x bn: a tile shape of the dispatcher's table, 128 columns or fewer.  Up to 128 x 128 two workgroups fit a compute unit
-// (three waves to a SIMD, 168 registers).
+// bm x bn: a tile shape of the dispatcher's table, 128 columns or fewer, or one of the heights between.  Up to 128 x 128 two
+// workgroups fit a compute unit (three waves to a SIMD, 168 registers).
 hipError_t ep_bf16_gemm_stream(int bm, int bn, const uint16_t *A, const uint16_t *W, const float *bias, const float *resid,
                                void *C, int64_t M, int N, int K, int splits, int epi, hipStream_t s)
 {
     if (bm == 64 && bn == 64) return launch_epi<64, 64, 8, 4, 3>(A, W, bias, resid, C, (int)M, N, K, splits, epi, s);
     if (bm == 64 && bn == 128) return launch_epi<64, 128, 6, 4, 3>(A, W, bias, resid, C, (int)M, N, K, splits, epi, s);
+    if (bm == 80 && bn == 128) return launch_epi<80, 128, 6, 4, 3>(A, W, bias, resid, C, (int)M, N, K, splits, epi, s);
+    if (bm == 96 && bn == 128) return launch_epi<96, 128, 5, 3, 3>(A, W, bias, resid, C, (int)M, N, K, splits, epi, s);
     if (bm == 128 && bn == 128) return launch_epi<128, 128, 4, 3, 3>(A, W, bias, resid, C, (int)M, N, K, splits, epi, s);
     if (epi == EPI_BIAS_GELU) return hipErrorInvalidValue;
+    if (bm == 144 && bn == 128) return launch_epi<144, 128, 6, 3, 2>(A, W, bias, resid, C, (int)M, N, K, splits, epi, s);
+    if (bm == 160 && bn == 128) return launch_epi<160, 128, 6, 3, 2>(A, W, bias, resid, C, (int)M, N, K, splits, epi, s);
+    if (bm == 176 && bn == 128) return launch_epi<176, 128, 5, 3, 2>(A, W, bias, resid, C, (int)M, N, K, splits, epi, s);
     if (bm == 192 && bn == 128) return launch_epi<192, 128, 5, 3, 2>(A, W, bias, resid, C, (int)M, N, K, splits, epi, s);
+    if (bm == 208 && bn == 128) return launch_epi<208, 128, 5, 3, 2>(A, W, bias, resid, C, (int)M, N, K, splits, epi, s);
+    if (bm == 224 && bn == 128) return launch_epi<224, 128, 5, 3, 2>(A, W, bias, resid, C, (int)M, N, K, splits, epi, s);
+    if (bm == 240 && bn == 128) return launch_epi<240, 128, 4, 3, 2>(A, W, bias, resid, C, (int)M, N, K, splits, epi, s);
     if (bm == 256 && bn == 128) return launch_epi<256, 128, 4, 3, 2>(A, W, bias, resid, C, (int)M, N, K, splits, epi, s);
     return hipErrorInvalidValue;
 }
