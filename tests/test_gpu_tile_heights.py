@@ -27,6 +27,8 @@ pytestmark = pytest.mark.gpu
     (65, 1280, 768, 62, 2, (0, 176, 96)),
     (65, 1280, 768, 74, 2, (0, 208, 0)),
     (257, 768, 768, 34, 2, (0, 224, 0)),
+    (197, 384, 768, 32, 2, (0, 80, 0)),
+    (197, 384, 768, 64, 2, (0, 80, 0)),
     (50, 1280, 768, 113, 2, (0, 240, 0)),
 ])
 def test_bits_of_another_height(T, D, M, B, few, heights):
