@@ -24,6 +24,9 @@
 // 6304 x 384 x 1536 17.1 -> 14.1.  The same sums in the same order.  Deeper rings than these gain nothing, nor do
 // one loader or four.
 //
+// RANGES: K is gone through in ranges of k_len, each with a sum of its own that is added to those before it: the bits of
+// EPI_PARTIAL and of whoever adds its ranges up, without their way through memory, at twice the accumulators.
+//
 // Rows past M and columns past N read as zeros and are never stored.  K % 64 == 0 and N % 16 == 0.
 #include "ep_gemm_bf16_tile.h"
 #include "ep_launch.h"
@@ -34,7 +37,7 @@ using namespace ep_tile;
 
 constexpr int NW = 4, NL = 2;                        // multiplying waves, loader waves
 
-template <int BM, int BN, int S, int D, int WAVES_PER_SIMD, int EPI>
+template <int BM, int BN, int S, int D, int WAVES_PER_SIMD, int EPI, bool RANGES>
 __global__ __launch_bounds__((NW + NL) * 64, WAVES_PER_SIMD) void gemm_bf16_stream_kernel(
     const uint16_t *A, const uint16_t *W, const float *bias, const float *resid, void *Cout, int M, int N, int K, int k_len,
     int tiles_m, int tiles_n)
@@ -48,7 +51,7 @@ __global__ __launch_bounds__((NW + NL) * 64, WAVES_PER_SIMD) void gemm_bf16_stre
 
     const TileOf t = tile_of(tiles_m, tiles_n, EPI == EPI_PARTIAL ? K / k_len : 1);
     if (!t.live) return;
-    const int m0 = t.m * BM, n0 = t.n * BN, k0 = t.range * k_len, KT = k_len / BK;
+    const int m0 = t.m * BM, n0 = t.n * BN, k0 = t.range * k_len, KT = (RANGES ? K : k_len) / BK;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 
@@ -100,7 +103,7 @@ __global__ __launch_bounds__((NW + NL) * 64, WAVES_PER_SIMD) void gemm_bf16_stre
     const char *w_base = reinterpret_cast<const char *>(W) + (size_t)min(nb0, nb) * block;
     const uint32_t w_bytes = nb0 < nb ? (uint32_t)(nb - nb0) * (uint32_t)block : 0u;
     // fragments of A: RA of them, each sent for RA blocks ahead; RA divides the fragments of a step
-    constexpr int RA = MI <= 13 ? MI : MI == 15 ? 10 : MI / 2;
+    constexpr int RA = RANGES && MI == 10 ? 4 : MI <= 13 ? MI : MI == 15 ? 10 : MI / 2;
     static_assert(NS * MI % RA == 0, "a step's fragments end with the registers");
     bf16x8 wf[D][NS][NI], af[RA];
     // fragment (slice, ni) of step kt.  Steps past the last read an empty buffer.  The empty assembly keeps the loads
@@ -120,7 +123,7 @@ __global__ __launch_bounds__((NW + NL) * 64, WAVES_PER_SIMD) void gemm_bf16_stre
     typedef WaveOut<MI, NI, EPI> Out;
     // the residual is fetched ahead of the K loop where registers hold it (a launch of a dozen steps would otherwise end
     // with one more trip to memory), a pass of rows of it otherwise
-    constexpr int FREE = (WAVES_PER_SIMD == 3 ? 128 : 216) - NI * MI * 4 - MI * 4 - D * NS * NI * 4;     // registers
+    constexpr int FREE = (WAVES_PER_SIMD == 3 ? 128 : 216) - (RANGES ? 2 : 1) * NI * MI * 4 - MI * 4 - D * NS * NI * 4;     // registers
     constexpr int FIT = FREE > 0 ? FREE / (Out::PP * 4) : 0, AHEAD = !Out::RES ? 0 : FIT < Out::NPASS ? FIT : Out::NPASS;
     Out out;
     out.init(Cout, resid, bias, m0, BM, 0, wn0, M, N, (size_t)t.range * M, lane);
@@ -138,6 +141,8 @@ __global__ __launch_bounds__((NW + NL) * 64, WAVES_PER_SIMD) void gemm_bf16_stre
     for (int ni = 0; ni < NI; ++ni)
 #pragma unroll
         for (int mi = 0; mi < MI; ++mi) acc[ni][mi] = f32x4{0.f, 0.f, 0.f, 0.f};
+    f32x4 sum[RANGES ? NI : 1][RANGES ? MI : 1];     // of the ranges that are over
+    int left = k_len / BK;                           // steps of the range
 
     __builtin_amdgcn_s_barrier();
     EP_SCHED_FENCE();
@@ -177,6 +182,19 @@ __global__ __launch_bounds__((NW + NL) * 64, WAVES_PER_SIMD) void gemm_bf16_stre
             EP_SCHED_FENCE();
         });
         slot = next;
+        if constexpr (RANGES)
+            if (--left == 0) {
+                left = k_len / BK;
+                const bool first = kt < left;
+#pragma unroll
+                for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+                    for (int mi = 0; mi < MI; ++mi) {
+                        sum[ni][mi] = first ? acc[ni][mi] : sum[ni][mi] + acc[ni][mi];
+                        acc[ni][mi] = f32x4{0.f, 0.f, 0.f, 0.f};
+                    }
+                EP_SCHED_FENCE();
+            }
     };
     int kt = 0;
     for (; kt + D <= KT; kt += D)
@@ -187,22 +205,23 @@ __global__ __launch_bounds__((NW + NL) * 64, WAVES_PER_SIMD) void gemm_bf16_stre
 
     EP_WAIT_LGKMCNT0();
     __builtin_amdgcn_s_barrier();                    // everyone is done with the ring
-    out.template store<AHEAD>(acc, reinterpret_cast<char *>(lds) + wave * Out::LDS_BYTES);
+    if constexpr (RANGES) out.template store<AHEAD>(sum, reinterpret_cast<char *>(lds) + wave * Out::LDS_BYTES);
+    else out.template store<AHEAD>(acc, reinterpret_cast<char *>(lds) + wave * Out::LDS_BYTES);
 #endif
 }
 
-template <int BM, int BN, int S, int D, int WAVES_PER_SIMD, int EPI>
+template <int BM, int BN, int S, int D, int WAVES_PER_SIMD, int EPI, bool RANGES = false>
 hipError_t launch_cfg(const uint16_t *A, const uint16_t *W, const float *bias, const float *resid, void *C, int M, int N,
                       int K, int splits, hipStream_t s)
 {
-    auto kern = gemm_bf16_stream_kernel<BM, BN, S, D, WAVES_PER_SIMD, EPI>;
+    auto kern = gemm_bf16_stream_kernel<BM, BN, S, D, WAVES_PER_SIMD, EPI, RANGES>;
     constexpr size_t ring = (size_t)S * BM * CPR * sizeof(uint4), stage = NW * WaveOut<BM / 16, BN / NW / 16, EPI>::LDS_BYTES;
     constexpr size_t smem = ring > stage ? ring : stage;
     static_assert(smem <= 160 * 1024, "LDS of a compute unit");
     static EpSmemLimit smem_limit;
     const hipError_t e = smem_limit.ensure(reinterpret_cast<const void *>(kern), (int)smem);
     if (e != hipSuccess) return e;
-    const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN, total = tiles_m * tiles_n * splits;
+    const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN, total = tiles_m * tiles_n * (RANGES ? 1 : splits);
     hipLaunchKernelGGL(kern, dim3((total + NUM_XCD - 1) / NUM_XCD * NUM_XCD), dim3((NW + NL) * 64), smem, s, A, W, bias, resid, C,
                        M, N, K, K / splits, tiles_m, tiles_n);
     return hipGetLastError();
@@ -265,5 +284,15 @@ hipError_t ep_bf16_gemm_stream(int bm, int bn, const uint16_t *A, const uint16_t
     if (bm == 224 && bn == 128) return launch_epi<224, 128, 5, 3, 2>(A, W, bias, resid, C, (int)M, N, K, splits, epi, s);
     if (bm == 240 && bn == 128) return launch_epi<240, 128, 4, 3, 2>(A, W, bias, resid, C, (int)M, N, K, splits, epi, s);
     if (bm == 256 && bn == 128) return launch_epi<256, 128, 4, 3, 2>(A, W, bias, resid, C, (int)M, N, K, splits, epi, s);
+    return hipErrorInvalidValue;
+}
+
+// heights whose second set of sums the registers hold (160 rows with a longer ring of fragments, and 80 two to a unit, spill); 64 were
+// modelled to be the fastest for one of 3500 layers
+hipError_t ep_bf16_gemm_stream_ranges(int bm, const uint16_t *A, const uint16_t *W, const float *bias, const float *resid, float *C,
+                                      int64_t M, int N, int K, int splits, hipStream_t s)
+{
+    if (bm == 128) return launch_cfg<128, 128, 6, 3, 2, EPI_BIAS_RESID, true>(A, W, bias, resid, C, (int)M, N, K, splits, s);
+    if (bm == 160) return launch_cfg<160, 128, 6, 3, 2, EPI_BIAS_RESID, true>(A, W, bias, resid, C, (int)M, N, K, splits, s);
     return hipErrorInvalidValue;
 }

@@ -76,6 +76,11 @@ hipError_t ep_fill_pattern(float *x, int64_t n, hipStream_t s);
 // K % (64 * splits) == 0
 hipError_t ep_bf16_gemm_partial(const uint16_t *A, const uint16_t *W, float *part, int64_t M, int N, int K,
                                 int splits, hipStream_t s);
+// ep_bf16_gemm_partial over many rows (a group of micro-batches) and the sum of its ranges, bias and residual in one launch, the same
+// bits: the height of its tiles, 0 where two launches are the faster way
+extern "C" int32_t ep_query_ranges_height(int64_t M, int32_t N, int32_t K, int32_t splits);
+hipError_t ep_bf16_gemm_ranges(const uint16_t *A, const uint16_t *W, const float *bias, const float *resid, float *C, int64_t M, int N,
+                               int K, int splits, hipStream_t s);
 // how many ranges the dispatcher wants for a dense layer with fp32 output (1: ep_bf16_gemm as it is); the sums of the
 // ranges never take more than EP_RANGE_SUM_BYTES, and layers of more than EP_RANGE_SUM_ROWS rows are not cut
 constexpr int64_t EP_RANGE_SUM_BYTES = 32 << 20, EP_RANGE_SUM_ROWS = 1 << 15;
@@ -115,6 +120,9 @@ hipError_t ep_bf16_gemm_persistent_clock(double *shader_mhz, double *seconds);
 // dense layers of small and middling batches (ep_gemm_bf16_stream.hip) with the dispatcher's bm x bn tiles, bn <= 128
 hipError_t ep_bf16_gemm_stream(int bm, int bn, const uint16_t *A, const uint16_t *W, const float *bias, const float *resid,
                                void *C, int64_t M, int N, int K, int splits, int epi, hipStream_t s);
+// bias and residual, K in `splits` ranges as ep_bf16_gemm_partial and its reader add them up
+hipError_t ep_bf16_gemm_stream_ranges(int bm, const uint16_t *A, const uint16_t *W, const float *bias, const float *resid, float *C,
+                                      int64_t M, int N, int K, int splits, hipStream_t s);
 
 // short-M kernel (ep_gemm_bf16_skinny.hip): 64 x 32 tiles, K dealt to the 8 waves of a workgroup
 bool ep_bf16_gemm_skinny_supported(int64_t M, int N, int K);

@@ -231,7 +231,12 @@ ep_status run_layer(ep_stage *st, const Workspace &w, const LayerDev &L, const f
                                             one_order, ts_.after_main(), s));
         int sp = w.part ? fc2_splits(c, w.ranges_of ? w.ranges_of : B) : 1;
         if ((size_t)sp * R * D * 4 > w.part_bytes) sp = 1;      // never beyond what the workspace holds
-        if (sp > 1) {
+        if (sp > 1 && one_order && ep_query_ranges_height(R, D, M, sp) > 0) {
+            // a group: the ranges of a micro-batch one after the other in one launch
+            TraceScope ts_(st, EP_K_FC2, EP_K_FC2_MAIN, s);
+            EP_HIP(ep_bf16_gemm_ranges(big, (const uint16_t *)L.w_fc2, L.b_fc2, w.x, xout, R, D, M, sp, s));
+            if (ts_.after_main()) EP_HIP(hipEventRecord(ts_.after_main(), s));
+        } else if (sp > 1) {
             // few tiles and a long K: one workgroup per (K range, tile); the sums are added by the next
             // layer's first LayerNorm, or here when nobody follows
             TraceScope ts_(st, EP_K_FC2, EP_K_FC2_MAIN, s);

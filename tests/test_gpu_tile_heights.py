@@ -1,14 +1,17 @@
-"""GPU parity of dense layers on tiles of the heights between 64, 128, 192 and 256 rows: every height with every epilogue that takes it,
+"""GPU parity of dense layers on tiles of the heights between 64, 128, 192 and 256 rows, and of K ranges that follow each other in one
+workgroup: every height with every epilogue that takes it,
 the last tile row rarely whole.  The height is asked of the library.  Rows add up in the same order whatever the height, so
 an image gives the same bits in a micro-batch that runs on other heights; sums over K ranges are held against the oracle (the tolerance
 is the bf16 path's)."""
+import ctypes as C
+
 import numpy as np
 import pytest
 
 import oracle
-from paper_2110_14895_amd import synth
+from paper_2110_14895_amd import binding, synth
 from tests import harness as H
-from tests.test_dispatch import EPI_BIAS, EPI_BIAS_GELU, EPI_BIAS_RESID, EPI_PARTIAL, dense_plan
+from tests.test_dispatch import EPI_BIAS, EPI_BIAS_GELU, EPI_BIAS_RESID, EPI_PARTIAL, dense_plan, group_limit
 
 pytestmark = pytest.mark.gpu
 
@@ -68,3 +71,32 @@ def test_sums_over_k_ranges(T, D, M, B, height):
     ref = oracle.stage_forward(H.oracle_cfg(sh), [w], x[pick])
     for k, i in enumerate(pick):
         assert H.rel_err(got[i], ref[k]) <= H.TOL_BF16, i
+
+
+# K ranges of a micro-batch one after the other in one launch over a group of them: the bits of the sums that go through memory
+@pytest.mark.parametrize("T,D,M,mb,n,splits,height,out_bf16", [
+    (197, 1024, 4096, 2, 10, 2, 128, False),
+    (197, 1024, 4096, 2, 11, 2, 160, True),
+    (65, 1024, 4096, 4, 11, 4, 128, True),
+    (65, 1024, 4096, 4, 16, 4, 160, False),
+    (65, 1024, 4096, 1, 35, 8, 128, False),
+])
+def test_ranges_of_a_group_in_one_launch(T, D, M, mb, n, splits, height, out_bf16):
+    import torch
+    f = binding.lib().ep_query_ranges_height
+    f.argtypes, f.restype = [C.c_int64, C.c_int32, C.c_int32, C.c_int32], C.c_int32
+    assert dense_plan(T * mb, D, M, EPI_PARTIAL).splits == splits
+    assert f(T * mb * n, D, M, splits) == height and f(T * mb, D, M, splits) == 0 and n <= group_limit(D, D // 64, M, T, mb)
+    sh = synth.custom_shape(f"group_ranges_{T}_{D}", 2, D, D // 64, M, T)
+    p = [synth.layer_params(sh, l, bf16=True, randomize_affine=True, w_std=0.02) for l in range(2)]
+    st = H.make_stage(sh, p, 0, 2, mb, bf16=True, out_bf16=out_bf16)
+    pipe = binding.Pipeline([st], mb)
+    x = H.to_device(synth.activations(sh, mb * n, bf16=True), True)
+    out = [torch.empty(x.shape, dtype=torch.bfloat16 if out_bf16 else torch.float32, device="cuda") for _ in range(2)]
+    s = torch.cuda.current_stream()
+    pipe.run(x, n, out[0], s)
+    for i in range(n):
+        st.forward(x[i * mb:(i + 1) * mb], mb, out[1][i * mb:(i + 1) * mb], s)
+    torch.cuda.synchronize()
+    assert torch.equal(out[0], out[1])
+    pipe.destroy()
