@@ -302,28 +302,42 @@ hipError_t launch_k(const float *x, const float *g, const float *b, float eps, c
     return hipErrorInvalidValue;
 }
 
-// The depths there are, and from how many to how many rows the one launch is the faster one.  Few rows take longer to bring in
-// than a launch is worth (LayerNorm and its dense layer, then this, us: 394 x 1152 x 384 6.3 and 6.2, 808 x 2304 x 768 9.8 and
-// 11.0; weights from memory, twelve ViT-Base layers on 8, 12, 14 and 16 images 786, 997, 1113 and 1199, with it 800, 1012, 1076 and 1129;
-// 24 ViT-Large layers on 12, 20, 32 and 40 2599, 3444, 5100 and 5960, with it 2671, 3510, 4943 and 5665).  Of more rows tiles of 256
-// columns ask for a quarter of the weights: 25256 x 3072 x 768 129 and 135, 9456 x 4096 x 1024 89 and 106.
-bool rows_depth(int64_t M, int K)
+// The depths there are, and where the one launch is the faster one.  Few rows take longer to bring in than a launch is worth; wide layers
+// are matrix work that tiles of 256 columns do with a quarter of the weights' traffic, and so are many rows; and the launch itself loses
+// where its panels just begin another round.  A layer's time inside a stage, with FC1 in two launches against one
+// (profiles/layernorm_dense_one_launch.md):
+//   K = 384    N = 12 K at 505 rows 1.03, 32 K 0.96, from 1010 rows on 1.00 and more
+//   K = 512    N = 4 K at 505 rows 0.99, at 2525 1.07; 12 K at 505 rows 0.97, at 1010 1.06; 16 K at 505 and 1010 0.95 and 1.01; 32 K at 8080 0.95
+//   K = 768    N = 4 K at 2626 rows 1.04 and at 10302 (129 panels of 80 rows: one group, half the chip) 0.97, 8 K 1.06 and 0.93, 12 K 1.03 and 0.89,
+//              8 K at 12625 1.00, 12 K at 11110 0.92, 16 K at 9595 0.98; two launches 129 us and one 135 at 25256 rows of 4 K
+//   K = 1024   N = 4 K at 5555 rows 0.97, at 6161 1.02; 5 K at 6363 0.96, 8 K 0.94, 12 K 0.89; two launches 89 us and one 106 at 9456 rows of 4 K
+// At 1024, layers past 2304 columns lose where tiles of 256 rows on their own are one nearly whole round: q|k|v at 6161 rows 0.99 and at 6565
+// 1.02, N = 2.75 K at 5757 0.97 and at 5959 1.01.
+bool one_launch_pays(int64_t M, int N, int K)
 {
+    const double wide = (double)N / K;
     switch (K) {
     case 64: case 128: case 192: case 256: return true;
-    case 320: case 384: return M >= 500;
-    case 512: return M >= 500 && M <= 20000;
-    case 768: return M >= 2600 && M <= 20000;
-    case 1024: return M >= 5500 && M <= 8192;
+    case 320: case 384: return M >= 1024 || (M >= 500 && wide <= 16.0);
+    case 512: return M <= 20000 && ((M >= 500 && wide <= 8.0) || (M >= 1000 && wide <= 16.0));
+    case 768: return M >= 2600 && M <= 20000 && (M <= 10240 ? wide <= 12.0 : wide <= 3.0 || (M > 10752 && wide <= 8.0));
+    case 1024: break;
+    default: return false;
     }
-    return false;
+    if (M < 5500 || M > 8192 || wide > 4.0 || (wide > 3.5 && M <= 5888)) return false;
+    const int64_t cus = ep_bf16_gemm_persistent_workgroups(), rows = (M + 255) / 256;
+    for (int bn : {256, 320}) {
+        const int64_t tiles = rows * ((N + bn - 1) / bn);
+        if (N > 2304 && tiles <= cus && 8 * tiles >= 7 * cus) return false;
+    }
+    return true;
 }
 
 }  // namespace
 
 bool ep_bf16_ln_gemm_supported(int64_t M, int N, int K)
 {
-    return rows_depth(M, K) && N % 16 == 0 && N < MAX_TILE_N && M * N < (1ll << 31) && (int64_t)N * K * 2 < 0x7FFFFFF0ll;
+    return one_launch_pays(M, N, K) && N % 16 == 0 && N < MAX_TILE_N && M * N < (1ll << 31) && (int64_t)N * K * 2 < 0x7FFFFFF0ll;
 }
 
 extern "C" int32_t ep_query_ln_gemm_plan(int64_t M, int32_t N, int32_t K, int32_t epi, int32_t cus, int32_t *groups)

@@ -137,3 +137,25 @@ def test_every_attention_group_holds_a_query(pairs):
         assert qw.value in (16, 32) and 1 <= to_a_group <= 10, t        # the query waves of a workgroup
         assert (ng.value - 1) * to_a_group < tiles, t
         assert pairs * ng.value <= 256 or ng.value == -(-t // 320), t   # one round of units, or as few groups as fit
+
+
+def ln_plan(rows, n, k, epi):
+    """Rows of a panel and column groups of LayerNorm and a dense layer in one launch; (0, 0): two launches."""
+    f = binding.lib().ep_query_ln_gemm_plan
+    f.argtypes, f.restype = [C.c_int64, C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.POINTER(C.c_int32)], C.c_int32
+    groups = C.c_int32()
+    return f(rows, n, k, epi, 256, C.byref(groups)), groups.value
+
+
+# In one launch with its LayerNorm a wide MLP's first layer takes up to 1.5 times as long, and so do some of few rows or little more than a round
+@pytest.mark.parametrize("rows,n,k,one", [
+    (394, 1152, 384, 0), (500, 6144, 384, 1), (600, 12288, 384, 0), (1024, 12288, 384, 1), (17, 8192, 256, 1),
+    (499, 1536, 512, 0), (500, 4096, 512, 1), (606, 6144, 512, 0), (1000, 8192, 512, 1), (8080, 16384, 512, 0), (20001, 2048, 512, 0),
+    (2599, 2304, 768, 0), (2600, 9216, 768, 1), (9595, 12288, 768, 0), (10240, 3072, 768, 1), (10241, 3072, 768, 0), (10302, 2304, 768, 1),
+    (10752, 3072, 768, 0), (10753, 6144, 768, 1), (11110, 9216, 768, 0), (20001, 2304, 768, 0),
+    (5499, 1024, 1024, 0), (5500, 2304, 1024, 1), (5888, 4096, 1024, 0), (5889, 4096, 1024, 1), (6363, 5120, 1024, 0), (8192, 16384, 1024, 0),
+    (8193, 3072, 1024, 0), (5632, 3072, 1024, 1), (5633, 3072, 1024, 0), (6400, 3072, 1024, 0), (6401, 3072, 1024, 1), (5888, 2816, 1024, 0),
+    (5889, 2816, 1024, 1), (1576, 2304, 576, 0), (6304, 2688, 896, 0),
+])
+def test_layernorm_and_dense_layer_in_one_launch(rows, n, k, one):
+    assert all((ln_plan(rows, n, k, epi)[0] > 0) == one for epi in (EPI_BIAS, EPI_BIAS_GELU))
