@@ -269,8 +269,32 @@ double rows_us(int64_t M, int N, int K, bool gelu, int bm, int groups, int cus)
                      (gelu ? b * (0.14 * part + 0.38 * sets) : 0.0));
 }
 
+// Narrow models from 2^14 rows on: rounds of workgroups times the sets of columns that a wave takes and one more, for the rows; 64 rows at
+// 0.55.  There the one round of 128-row panels that the model above is held to leaves up to half of the units without work, and several
+// groups in two rounds are the faster way (with GELU 21814 x 2048 x 256 44.5 us and, in two groups, 37.4, 20037 x 1536 x 384 in three
+// 44.4 and 41.8; 23279 x 960 x 320 27.6 and 25.4), which the model, 10 to 20 % short for 128 rows, does not rank.  Of 478 layers from 2^14 rows to 60000 this
+// rule is 1.7 % off the fastest of all heights and groups, the model 2.1; below, 1 to 8 % and 1 %.
+RowsPlan plan_many_narrow_rows(int64_t M, int N, int cus)
+{
+    const int units = (N + UC - 1) / UC;
+    RowsPlan best = {0, 0, 1e30};
+    for (int bm : {128, 64})
+        for (int n = 1; n * NW < units + NW; ++n) {
+            const int64_t rounds = ((M + bm - 1) / bm * n + cus - 1) / cus, sets = (units + n * NW - 1) / (n * NW);
+            const double cost = (bm == 128 ? 1.0 : 0.55) * rounds * (sets + 1);
+            if (cost < best.us) best = {bm, n, cost};
+        }
+    return best;
+}
+
 RowsPlan plan_rows(int64_t M, int N, int K, bool gelu, int cus)
 {
+    // 384 wide, the model's plan is still the faster one where a round of 128 rows takes two thirds of the units (22458 and 24428 rows of
+    // DeiT-Small, a layer: 141 and 146 us; lower panels, which read the weights twice as often, 149 and 153) and, but for MLPs of 8 K and
+    // more, past that round (33884 rows: 245 and 249 us)
+    const int64_t tall = (M + 127) / 128;
+    const bool model = K > 320 && 3 * tall >= 2 * cus && (tall <= cus || N <= 4 * K);
+    if (K <= 384 && M >= 1 << 14 && !model) return plan_many_narrow_rows(M, N, cus);
     RowsPlan best = {0, 0, 1e30};
     for (int bm : {K <= 384 ? 128 : K <= 512 ? 96 : K <= 768 ? 80 : 0, 64}) {
         if (!bm) continue;

@@ -159,3 +159,14 @@ def ln_plan(rows, n, k, epi):
 ])
 def test_layernorm_and_dense_layer_in_one_launch(rows, n, k, one):
     assert all((ln_plan(rows, n, k, epi)[0] > 0) == one for epi in (EPI_BIAS, EPI_BIAS_GELU))
+
+
+# Narrow models of many rows: several column groups in two rounds where one round of 128-row panels leaves units without work
+@pytest.mark.parametrize("rows,n,k,epi,plan", [
+    (16383, 1536, 384, EPI_BIAS_GELU, (64, 1)), (20037, 1536, 384, EPI_BIAS_GELU, (128, 3)), (21814, 2048, 256, EPI_BIAS_GELU, (64, 2)),
+    (23279, 960, 320, EPI_BIAS, (64, 2)),
+    (22458, 1536, 384, EPI_BIAS_GELU, (128, 1)), (34249, 1536, 384, EPI_BIAS_GELU, (64, 1)), (34249, 3072, 384, EPI_BIAS_GELU, (64, 2)),
+    (22458, 1536, 192, EPI_BIAS_GELU, (64, 2)), (36053, 1536, 192, EPI_BIAS_GELU, (64, 2)), (50432, 1152, 384, EPI_BIAS, (128, 1)), (50432, 768, 192, EPI_BIAS_GELU, (128, 1)),
+])
+def test_panels_of_many_narrow_rows(rows, n, k, epi, plan):
+    assert ln_plan(rows, n, k, epi) == plan
