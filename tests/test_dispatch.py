@@ -170,3 +170,16 @@ def test_layernorm_and_dense_layer_in_one_launch(rows, n, k, one):
 ])
 def test_panels_of_many_narrow_rows(rows, n, k, epi, plan):
     assert ln_plan(rows, n, k, epi) == plan
+
+
+# Heights between the table's past the layers that they were fitted to: long K keeps one round of wide tiles, few rows without GELU keep theirs
+@pytest.mark.parametrize("rows,n,k,epi,shape", [
+    (12462, 1024, 12800, EPI_BIAS_RESID, "256x256"), (8312, 1536, 30784, EPI_BIAS_RESID, "256x256"), (5504, 2048, 21568, EPI_BIAS_RESID, "256x192"),
+    (11212, 1024, 25792, EPI_BIAS_RESID, "192x256"), (157, 12288, 3072, EPI_BIAS, "128x128"), (146, 1536, 28160, EPI_PARTIAL, "128x128/8"),
+    (199, 12288, 768, EPI_BIAS, "128x128"),
+    # on either side of the lines, and long K in more than a round or on narrow tiles
+    (8637, 1536, 6144, EPI_BIAS_RESID, "208x128"), (19823, 1024, 28992, EPI_BIAS_RESID, "208x128"), (2188, 1280, 12736, EPI_BIAS_RESID, "96x128"),
+    (259, 1280, 25600, EPI_PARTIAL, "96x128/8"), (184, 15360, 1280, EPI_BIAS_GELU, "96x128"),
+])
+def test_heights_past_their_fit(rows, n, k, epi, shape):
+    assert str(dense_plan(rows, n, k, epi)) == shape
