@@ -178,8 +178,18 @@ def test_panels_of_many_narrow_rows(rows, n, k, epi, plan):
     (11212, 1024, 25792, EPI_BIAS_RESID, "192x256"), (157, 12288, 3072, EPI_BIAS, "128x128"), (146, 1536, 28160, EPI_PARTIAL, "128x128/8"),
     (199, 12288, 768, EPI_BIAS, "128x128"),
     # on either side of the lines, and long K in more than a round or on narrow tiles
-    (8637, 1536, 6144, EPI_BIAS_RESID, "208x128"), (19823, 1024, 28992, EPI_BIAS_RESID, "208x128"), (2188, 1280, 12736, EPI_BIAS_RESID, "96x128"),
+    (6400, 1536, 5120, EPI_BIAS_RESID, "256x192"), (5757, 1536, 6144, EPI_BIAS_RESID, "144x128"), (19823, 1024, 28992, EPI_BIAS_RESID, "208x128"), (2188, 1280, 12736, EPI_BIAS_RESID, "96x128"),
     (259, 1280, 25600, EPI_PARTIAL, "96x128/8"), (184, 15360, 1280, EPI_BIAS_GELU, "96x128"),
 ])
 def test_heights_past_their_fit(rows, n, k, epi, shape):
     assert str(dense_plan(rows, n, k, epi)) == shape
+
+
+# One round of wide tiles whose outputs fill three quarters of the chip is the faster one inside a stage, and so is any at 768 columns
+@pytest.mark.parametrize("rows,n,k,shape", [
+    (10280, 1280, 5120, "256x256"), (12608, 1024, 4096, "256x256"), (9456, 1024, 4096, "256x192"), (9850, 1024, 4096, "256x192"), (11032, 768, 3072, "256x192"),
+    (9595, 1024, 8192, "256x192"), (7575, 1280, 5120, "256x192"),
+    (8989, 1024, 4096, "144x128"), (6868, 1280, 5120, "144x128"), (5555, 1536, 6144, "144x128"), (19700, 1024, 4096, "208x128"),
+])
+def test_one_round_of_wide_residual_tiles(rows, n, k, shape):
+    assert str(dense_plan(rows, n, k, EPI_BIAS_RESID)) == shape
