@@ -2,24 +2,19 @@
 few rows: every height of a panel, with a last panel that is rarely whole and column groups of less than a set of columns up to
 all of them.  Bit for bit against the two launches, with the height asked of the library, and against the oracle (the tolerance is the
 bf16 path's)."""
-import ctypes as C
-
 import numpy as np
 import pytest
 
 import oracle
-from paper_2110_14895_amd import binding, synth
+from paper_2110_14895_amd import synth
 from tests import harness as H
-from tests.test_dispatch import EPI_BIAS, EPI_BIAS_GELU, dense_plan
+from tests.test_dispatch import EPI_BIAS, EPI_BIAS_GELU, dense_plan, ln_plan
 
 pytestmark = pytest.mark.gpu
 
 
 def panel_rows(rows, n, k, epi):
-    f = binding.lib().ep_query_ln_gemm_plan
-    f.argtypes, f.restype = [C.c_int64, C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.POINTER(C.c_int32)], C.c_int32
-    groups = C.c_int32()
-    return f(rows, n, k, epi, 256, C.byref(groups))
+    return ln_plan(rows, n, k, epi)[0]
 
 
 # q|k|v: a stage that takes bf16 normalises its input where it widens it, the same values in fp32 go through the one launch
