@@ -2,9 +2,9 @@
 compute units, on the shapes named beside it (asked of the dispatcher, so that a change of its costs cannot move a case
 to other kernels unnoticed), rows and columns rarely whole numbers of tiles.  Between them the cases run every shape with every
 epilogue it is chosen for.  Against the checker on the first, a middle and the last image (the last one sits in the
-partly filled tile row); the tolerance is the bf16 path's.  128x128 and 128x128x2 are one kernel at two prices.  Up to 384 wide the
-first MLP layer, with its LayerNorm, is a kernel of its own (test_gpu_bf16_rows.py) and the third shape is not run; the last
-cases hold the shapes with GELU at 448."""
+partly filled tile row); the tolerance is the bf16 path's.  128x128 and 128x128x2 are one kernel at two prices.  Up to 256 wide, and from 500 rows on
+at 320, 384 and 512, the first MLP layer, with its LayerNorm, is a kernel of its own (test_gpu_bf16_rows.py, test_gpu_wide_rows.py) and the
+third shape is not run; the cases at 448 and 576 hold the shapes with GELU."""
 import pytest
 
 import oracle
@@ -32,6 +32,7 @@ def shapes_of(rows, d, m):
     (197, 384, 6, 1536, 26, "192x128 64x128x2 128x128x2 64x128x2"),
     (197, 256, 4, 768, 64, "256x192 128x128x2 256x192 128x128"),
     (197, 512, 8, 2048, 32, "256x192 128x128 256x256 128x128"),
+    (197, 576, 9, 2304, 32, "256x192 128x128 256x256 128x128"),
     (257, 320, 4, 1280, 64, "P256x320 128x128x2 P256x320+64 256x128"),
     (197, 448, 7, 1792, 48, "P256x256 192x128 P256x320 192x128"),
     (65, 320, 5, 1536, 1, "64x64x2 64x64x2 64x64x2 64x64x2/2"),

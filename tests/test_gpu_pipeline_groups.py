@@ -30,8 +30,11 @@ pytestmark = pytest.mark.gpu
     (197, 768, 12, 3072, (0, 1, 2), 7, 6, True, 7),        # the same of six
     (197, 1024, 16, 4096, (0, 1), 7, 3, False, 5),         # 41 in the first MLP layer of three, K ranges
     (257, 1280, 16, 5120, (0, 1), 4, 3, False, 6),         # 12 in the first MLP layer of three, d_head 80
-    (197, 512, 8, 2048, (0, 1, 2), 42, 2, False, 1),       # 82 in the first MLP layer of one alone
-    (197, 512, 8, 2048, (0, 1), 55, 3, False, 1),          # 83 in q|k|v of one alone, none of three
+    (197, 576, 9, 2304, (0, 1, 2), 42, 2, False, 1),       # 82 in the first MLP layer of one alone
+    (197, 576, 9, 2304, (0, 1), 55, 3, False, 1),          # 83 in q|k|v of one alone, none of three
+    # the same for a launch of its own, which these are not behind their LayerNorm: past 384 wide the limit does not ask
+    (197, 512, 8, 2048, (0, 1, 2), 42, 2, False, 1),       # the first MLP layer
+    (197, 512, 8, 2048, (0, 1), 55, 3, False, 1),          # q|k|v, on its own behind the bf16 input
 ])
 def test_groups_equal_single_micro_batches(T, D, Hh, M, cuts, mb, n_micro, boundary_bf16, limit):
     import torch

@@ -1,8 +1,8 @@
 """GPU parity of the dense layers whose tiles are at most 128 columns wide (loader waves, weights in fragment order) where
 their pipelines are shorter than they are deep and where rows end inside a tile: K of one to nine steps of 64, one row to
 one past a tile.  `shapes` is what the dispatcher runs on 256 compute units (tiles of q|k|v, projection, first and second
-MLP layer as in test_gpu_dense_tiles.py, whose cases hold every shape at greater depths); behind a first layer, and in every
-first MLP layer here up to 256 wide, LayerNorm and the dense layer are one launch of another kernel.  Against the oracle on
+MLP layer as in test_gpu_dense_tiles.py, whose cases hold every shape at greater depths); up to 256 wide, and at the 2561 rows of
+512, every first MLP layer here and q|k|v behind a first layer are one launch of another kernel with their LayerNorm.  Against the oracle on
 the first and the last image; the tolerance is the bf16 path's."""
 import pytest
 
@@ -26,6 +26,7 @@ pytestmark = pytest.mark.gpu
     (129, 448, 7, 512, 1, SMALL),      # seven and eight
     (193, 128, 2, 576, 7, SMALL),      # two and nine
     (197, 512, 8, 1024, 13, "128x128 64x128x2 128x128 64x128x2"),        # eight and sixteen
+    (197, 448, 7, 1024, 13, "128x128 64x128x2 128x128 64x128x2"),        # seven and sixteen, with GELU too
     (193, 64, 1, 64, 100, "192x128 64x64x2 64x64x2 64x64x2"),            # 192 rows, one step, a remainder of 100
     (193, 128, 2, 64, 200, "128x128x2 192x128 64x64x2 192x128"),         # 192 rows with a residual, two steps and one
     (193, 64, 1, 1024, 1, "64x64x2 64x64x2 64x64x2 64x64x2/2"),          # two K ranges of eight steps

@@ -24,6 +24,7 @@ pytestmark = pytest.mark.gpu
     (50, 1280, 768, 13, 2, (96, 0, 0)),
     (50, 1024, 768, 29, 2, (160, 0, 0)),
     (257, 1280, 768, 5, 2, (176, 0, 0)),
+    (239, 1280, 768, 7, 2, (224, 80, 0)),
     (50, 1024, 768, 42, 2, (240, 80, 0)),
     (50, 1280, 768, 65, 2, (0, 144, 80)),
     (50, 768, 768, 121, 2, (0, 160, 0)),
@@ -80,6 +81,9 @@ def test_sums_over_k_ranges(T, D, M, B, height):
     (65, 1024, 4096, 4, 11, 4, 128, True),
     (65, 1024, 4096, 4, 16, 4, 160, False),
     (65, 1024, 4096, 1, 35, 8, 128, False),
+    (257, 1280, 5120, 4, 6, 4, 128, False),     # 80 K steps: two past the unrolled three
+    (257, 1280, 5120, 4, 6, 4, 128, True),
+    (197, 768, 3072, 8, 8, 2, 160, False),      # 48: none
 ])
 def test_ranges_of_a_group_in_one_launch(T, D, M, mb, n, splits, height, out_bf16):
     import torch
