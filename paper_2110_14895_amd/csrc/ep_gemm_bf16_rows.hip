@@ -1,5 +1,5 @@
 // LayerNorm and the dense layer behind it in one launch: the q|k|v projection and the first MLP layer (paper section 2.1)
-// of models up to 1024 wide.
+// of models that are 64 to 384 wide in steps of 64, 512, 768 or 1024, between the limits of one_launch_pays.
 //
 //   C[M, N] = LN(x)[M, K] . W[N, K]^T + bias[N]   (+ erf GELU), bf16 out
 //
@@ -15,13 +15,14 @@
 // that arrive from L2).  All workgroups go through the columns in the same order, so what an XCD has under way of weights that are
 // not in its L2 is no more than what one or two workgroups have, and the launch waits for memory with every set; where few
 // groups share a panel the workgroups of an XCD therefore touch all weights between them while their rows come in, a line to a lane
-// (weights from memory: 6304 x 2304 x 768 33.5 -> 30.8 us, 12608 x 2304 x 768 72.3 -> 54.2, 12608 x 1152 x 384 23.6 -> 20.3,
-// 7880 x 3072 x 1024 68.2 -> 55.7).  A K of two to twelve slices
+// (weights from memory: 12608 x 2304 x 768 65.5 -> 51.1 us, 7880 x 3072 x 1024 63.9 -> 54.4; over 2500 launches 0.79 of the time at 768
+// wide in one group and at 1024 in two, 0.87, 0.92 and 0.97 at 768 in two, three and four, 1.00 at 384 in one, 0.98 and 1.03 at 512 in
+// one and two).  A K of two to twelve slices
 // is too short for a tile with a prologue and an epilogue of its own, and LayerNorm was a launch and two trips through
-// memory.  LayerNorm and the dense layer, then this, in us: 1576 x 576 x 192 6.0 and 4.7, 6304 x 576 x 192 9.6 and 6.5,
-// 12672 x 768 x 192 with GELU 18.7 and 12.8, 6304 x 1536 x 384 with GELU 21.8 and 15.0, 4728 x 1152 x 384 13.7 and 9.6,
-// 50688 x 1152 x 384 72.9 and 64.5, 6344 x 1536 x 512 22.5 and 15.8, 3172 x 2304 x 768 22.4 and 18.5, 12608 x 3072 x 768
-// with GELU 76.2 and 73.2, 7880 x 3072 x 1024 64.7 and 55.7.
+// memory.  LayerNorm and the dense layer, then this, in us, launches back to back with weights from memory: 6304 x 576 x 192 9.0 and 6.0,
+// 12672 x 768 x 192 with GELU 18.0 and 12.4, 6304 x 1536 x 384 with GELU 21.3 and 15.4 (17.3 inside a DeiT-Small stage), 4728 x 1152 x 384
+// 14.0 and 9.9, 50688 x 1152 x 384 72.6 and 67.3, 6344 x 1536 x 512 22.6 and 16.4, 3172 x 2304 x 768 21.4 and 18.8, 12608 x 3072 x 768
+// with GELU 70.7 and 70.2, 7880 x 3072 x 1024 59.5 and 54.4.
 #include <cstdint>
 #include "ep_gemm_bf16_tile.h"
 #include "ep_launch.h"
@@ -240,9 +241,9 @@ hipError_t launch_rows(const float *x, const float *g, const float *b, float eps
 {
     const int units = (N + UC - 1) / UC, per = (units + groups - 1) / groups;
     groups = (units + per - 1) / per;
-    // Touching pays where a workgroup goes through many columns behind few others' (weights from memory, without and with: 6304 x
-    // 2304 x 768 in three groups 33.5 and 30.8 us, 3152 x 4096 x 1024 in four 43.4 and 39.4, in five 38.0 and 39.5, 3152 x 2304 x
-    // 768 in six 18.8 and 19.8, 6304 x 1152 x 384, 442 KB to a workgroup, in two 12.1 and 12.4) and every XCD has all groups.
+    // Touching pays where a workgroup goes through many columns behind few others' (figures above; when it was introduced, without and
+    // with: 3152 x 4096 x 1024 in four groups 43.4 and 39.4 us, in five 38.0 and 39.5, 3152 x 2304 x 768 in six 18.8 and 19.8,
+    // 6304 x 1152 x 384, 442 KB to a workgroup, in two 12.1 and 12.4) and every XCD has all groups.
     if constexpr (KS > 8)
         if (groups <= 4 && (int64_t)per * UC * KS * 64 >= 600 * 1024 && M / BM >= NUM_XCD)
             return launch_as<KS, BM, EPI, true>(x, g, b, eps, W, bias, C, M, N, units, per, groups, s);
@@ -251,11 +252,11 @@ hipError_t launch_rows(const float *x, const float *g, const float *b, float eps
 
 // Rows of a panel, 64 or as many as LDS holds, by the modelled microseconds of a launch: rounds of workgroups, each of them
 // bringing the rows in, then the sets of columns that a wave takes (matrix instructions) and the columns of the workgroup
-// (weights on their way).  Fitted to 4700 launches of 217 to 39440 rows, K = 64 to 1024, N = 3 K and 4 K: 8 % off a launch, the
-// choice 0.8 % off the fastest of all heights and groups.  A panel is shared by as many column groups as leave one round of
-// workgroups.  (One set of columns more or less for one round more or less, the rule before, took 128 rows in five groups
-// for 6344 x 1152 x 384, 13.1 us, where 64 in two take 11.6; and groups of a whole set of columns at least, 1025 x 1152 x 384
-// 7.4 us, where 64 rows in fifteen groups take 6.6.)
+// (weights on their way).  Fitted to 4700 launches of 217 to 39440 rows, K = 64 to 1024, N = 3 K and 4 K: 8 % off a launch.  A panel is shared
+// by as many column groups as leave one round of workgroups.  The choice is 0.9 to 1.1 % off the fastest of all heights and groups up to
+// 16000 rows of narrow models and 0 to 1 % off from 512 wide on.  (Rounds times sets, below, takes 128 rows in five groups for 6344 x 1152 x 384,
+// 14.3 us, where 64 in two take 12.7; and groups of a whole set of columns at least, 1025 x 1152 x 384 7.3 us, where 64 rows in fifteen
+// groups take 6.5.)
 struct RowsPlan { int bm, groups; double us; };
 
 double rows_us(int64_t M, int N, int K, bool gelu, int bm, int groups, int cus)
@@ -272,8 +273,8 @@ double rows_us(int64_t M, int N, int K, bool gelu, int bm, int groups, int cus)
 // Narrow models from 2^14 rows on: rounds of workgroups times the sets of columns that a wave takes and one more, for the rows; 64 rows at
 // 0.55.  There the one round of 128-row panels that the model above is held to leaves up to half of the units without work, and several
 // groups in two rounds are the faster way (with GELU 21814 x 2048 x 256 44.5 us and, in two groups, 37.4, 20037 x 1536 x 384 in three
-// 44.4 and 41.8; 23279 x 960 x 320 27.6 and 25.4), which the model, 10 to 20 % short for 128 rows, does not rank.  Of 478 layers from 2^14 rows to 60000 this
-// rule is 1.7 % off the fastest of all heights and groups, the model 2.1; below, 1 to 8 % and 1 %.
+// 44.4 and 41.8; 23279 x 960 x 320 27.6 and 25.4), which the model, 10 to 20 % short for 128 rows, does not rank.  Of 478 layers from
+// 2^14 rows to 60000 this rule is 1.7 % off the fastest of all heights and groups, the model 2.1; below, 1 to 8 % and 1 %.
 RowsPlan plan_many_narrow_rows(int64_t M, int N, int cus)
 {
     const int units = (N + UC - 1) / UC;
@@ -333,8 +334,8 @@ hipError_t launch_k(const float *x, const float *g, const float *b, float eps, c
 //   K = 384    N = 12 K at 505 rows 1.03, 32 K 0.96, from 1010 rows on 1.00 and more
 //   K = 512    N = 4 K at 505 rows 0.99, at 2525 1.07; 12 K at 505 rows 0.97, at 1010 1.06; 16 K at 505 and 1010 0.95 and 1.01; 32 K at 8080 0.95
 //   K = 768    N = 4 K at 2626 rows 1.04 and at 10302 (129 panels of 80 rows: one group, half the chip) 0.97, 8 K 1.06 and 0.93, 12 K 1.03 and 0.89,
-//              8 K at 12625 1.00, 12 K at 11110 0.92, 16 K at 9595 0.98; two launches 129 us and one 135 at 25256 rows of 4 K
-//   K = 1024   N = 4 K at 5555 rows 0.97, at 6161 1.02; 5 K at 6363 0.96, 8 K 0.94, 12 K 0.89; two launches 89 us and one 106 at 9456 rows of 4 K
+//              8 K at 12625 1.00, 12 K at 11110 0.92, 16 K at 9595 0.98; two launches 139 us and one 147 at 25256 rows of 4 K
+//   K = 1024   N = 4 K at 5555 rows 0.97, at 6161 1.02; 5 K at 6363 0.96, 8 K 0.94, 12 K 0.89; two launches 85 us and one 106 at 9456 rows of 4 K
 // At 1024, layers past 2304 columns lose where tiles of 256 rows on their own are one nearly whole round: q|k|v at 6161 rows 0.99 and at 6565
 // 1.02, N = 2.75 K at 5757 0.97 and at 5959 1.01.
 bool one_launch_pays(int64_t M, int N, int K)

@@ -527,6 +527,8 @@ namespace {
 constexpr int64_t MICRO_ROWS = 1 << 14, GROUP_ROWS = 1 << 15, GROUP_ELEMS = 1 << 26;
 constexpr size_t GROUP_SUM_BYTES = (size_t)128 << 20;
 
+// for any count, also those whose ranges follow each other in one launch (ViT-Base, micro-batches of 8: 3, 4 and 6 to 13 of them): a run's
+// groups may be smaller
 size_t group_part_bytes(const ep_vit_config &c, int32_t micro, int32_t count)
 {
     const int sp = fc2_splits(c, micro);
@@ -537,14 +539,15 @@ size_t group_part_bytes(const ep_vit_config &c, int32_t micro, int32_t count)
 
 namespace {
 
-// whether a dense layer of a micro-batch on its own has narrow tiles
+// whether a dense layer of a micro-batch on its own has narrow tiles, or past 384 wide would have if LayerNorm did not go with it
 bool has_narrow_rows(const ep_vit_config &c, int32_t micro)
 {
     const int64_t R = (int64_t)micro * c.n_tokens;
     const int D = c.d_model, M = c.d_mlp;
     const int sp = fc2_splits(c, micro);
     // q|k|v goes without its LayerNorm behind a bf16 input and behind sums over K ranges; wider models run it, and the first
-    // MLP layer, in one launch with LayerNorm between two numbers of rows only
+    // MLP layer, in one launch with LayerNorm between two numbers of rows only, which is not asked here: 33, 42 and 55 images of
+    // ViT-Base are not grouped though neither launch has narrow tiles
     const bool narrow = D <= 384;
     const bool qkv = !narrow || !ep_bf16_ln_gemm_supported(R, 3 * D, D) || c.in_dtype == EP_BF16 || sp > 1;
     return (qkv && ep_bf16_gemm_narrow_rows(R, 3 * D, D, EPI_BIAS) > 0) || ep_bf16_gemm_narrow_rows(R, D, D, EPI_BIAS_RESID) > 0 ||
