@@ -40,6 +40,12 @@
 //                   rounded probabilities, i.e. of the weights actually applied).
 // The last 32-component step of a head width that is not a multiple of 32 (80)
 // reads past the row into the next row (finite data) against zeros in Q.
+//
+// Weights touched.  The launches behind this one walk K in step with each other, every step's weights are new to all of them at once, and where they
+// come from memory each step waits a part of that trip (FC2 of ViT-Large on 16 images, 64 steps: 36 us, and 28 where its 8 MB
+// are in the memory-side cache; DeiT-Small on 32, 24 steps and 1.2 MB: 15.6 and 11.8).  This kernel is bound by its vector ALU, and memory idles
+// meanwhile, so a wave of each workgroup more brings the weights of the rest of the layer and of the next q|k|v projection into that cache (the stage
+// decides where that pays: touch_weights in ep_stage.hip).  The launch itself takes 2 to 3 us longer for 25 MB (64 components a head).
 #include "ep_kernels.h"
 #include "ep_device.h"
 #include "ep_launch.h"
@@ -57,6 +63,7 @@ constexpr int NBUF = 5;                              // chunk buffers in the rin
 constexpr int DEPTH = NBUF - 1;                      // chunks in flight ahead of the one being consumed
 constexpr int NLOADER = 2;                           // loader waves
 constexpr int MAXQW = 10;                            // query waves
+constexpr uint32_t MAX_TOUCH = 1u << 30;             // offsets of touched lines are 32-bit
 
 template <int DH>
 struct StreamShape {
@@ -379,11 +386,13 @@ __device__ __forceinline__ void attn_wave(const uint16_t *__restrict__ qkv, uint
     }
 }
 
-// QW: queries of a query wave (32 or 16)
-template <int DH, int QW>
+// QW: queries of a query wave (32 or 16).  TOUCH: a last wave touches weights (a template argument: as a branch it cost a stage of
+// single images, which does not, 0.9 %)
+template <int DH, int QW, bool TOUCH>
 __global__ __launch_bounds__((MAXQW + NLOADER) * 64) void attn_stream_kernel(const uint16_t *__restrict__ qkv,
                                                                              uint16_t *__restrict__ o, int T, int D, int H,
-                                                                             int n_units, int ng, float scale_log2e)
+                                                                             int n_units, int ng, float scale_log2e,
+                                                                             EpTouch touch)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
     using S = StreamShape<DH>;
@@ -394,7 +403,7 @@ __global__ __launch_bounds__((MAXQW + NLOADER) * 64) void attn_stream_kernel(con
 
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int nqw = (int)(blockDim.x >> 6) - NLOADER;              // query waves of this launch
+    const int nqw = (int)(blockDim.x >> 6) - NLOADER - (TOUCH ? 1 : 0);      // query waves of this launch
     const bool loader = wave >= nqw;                               // wave-uniform
     const int row_bytes = 3 * D * 2;
     const int seg_bytes = (T - 1) * row_bytes + DH * 2;            // first to last byte of a head's q, k or v
@@ -414,6 +423,26 @@ __global__ __launch_bounds__((MAXQW + NLOADER) * 64) void attn_stream_kernel(con
     if (unit >= unit_end) return;                                  // whole workgroup
     const int my_units = (unit_end - unit + unit_step - 1) / unit_step;
     const int total = my_units * nch;                              // chunk steps = barriers, the same for every wave
+
+    if (TOUCH && wave == nqw + NLOADER) {
+        // ---- the wave that touches the weights of the launches behind this one, a line to a lane, FLIGHT lines at a time, and ends: the
+        // barriers behind the first are without it
+        constexpr uint32_t LINE = 128;
+        constexpr int FLIGHT = 4;
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(touch.p), 0, (int)touch.bytes, 0x00020000);
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();              // behind the first chunk, which everyone waits for
+        asm volatile("" ::: "memory");
+        const uint32_t step = gridDim.x * 64 * LINE;
+        for (uint32_t at = blockIdx.x * 64 * LINE; at < touch.bytes; at += FLIGHT * step) {
+            uint32_t v[FLIGHT];
+#pragma unroll
+            for (int i = 0; i < FLIGHT; ++i) v[i] = __builtin_amdgcn_raw_buffer_load_b32(rs, (int)(at + i * step + lane * LINE), 0, 0);
+#pragma unroll
+            for (int i = 0; i < FLIGHT; ++i) asm volatile("" ::"v"(v[i]));
+        }
+        return;
+    }
 
     if (loader) {
         // ---- loader waves: loader 0 brings the K part of every chunk, loader 1 the V part, LPW loads of
@@ -502,16 +531,18 @@ AttnPlan plan_attention(int64_t pairs, int T, int n_cu)
     return {32, (t32 + w32 - 1) / w32};
 }
 
-template <int DH, int QW>
-hipError_t launch_stream(const uint16_t *qkv, uint16_t *o, int B, int T, int D, int H, int ng, int n_cu, hipStream_t s)
+int query_waves(int T, int qw, int ng) { return ((T + qw - 1) / qw + ng - 1) / ng; }
+
+template <int DH, int QW, bool TOUCH>
+hipError_t launch_as(const uint16_t *qkv, uint16_t *o, int B, int T, int D, int H, int ng, int n_cu, EpTouch touch, hipStream_t s)
 {
     using S = StreamShape<DH>;
-    auto kern = attn_stream_kernel<DH, QW>;
+    auto kern = attn_stream_kernel<DH, QW, TOUCH>;
     static EpSmemLimit smem_limit;
     const hipError_t e = smem_limit.ensure(reinterpret_cast<const void *>(kern), (int)S::smem);
     if (e != hipSuccess) return e;
-    const int tiles = (T + QW - 1) / QW, nqw = (tiles + ng - 1) / ng;
-    if (nqw > MAXQW) return hipErrorInvalidValue;
+    const int nqw = query_waves(T, QW, ng);
+    if (nqw + (TOUCH ? 1 : 0) > MAXQW) return hipErrorInvalidValue;
     const float scale_log2e = 1.4426950408889634f / sqrtf((float)DH);
     const int64_t n_units = (int64_t)B * H * ng;
     if (n_units > 0x7FFFFFFF) return hipErrorInvalidValue;
@@ -519,20 +550,29 @@ hipError_t launch_stream(const uint16_t *qkv, uint16_t *o, int B, int T, int D, 
     // of two take 15.3 us where 256 workgroups, 16 of them with a second unit, take 16.2
     const int64_t rounds = (n_units + n_cu - 1) / n_cu;
     const int grid = (int)((n_units + rounds - 1) / rounds);
-    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3((nqw + NLOADER) * 64), S::smem, s, qkv, o, T, D, H, (int)n_units, ng,
-                       scale_log2e);
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3((nqw + NLOADER + (TOUCH ? 1 : 0)) * 64), S::smem, s, qkv, o, T, D, H, (int)n_units, ng,
+                       scale_log2e, touch);
     return hipGetLastError();
 }
 
+template <int DH, int QW>
+hipError_t launch_stream(const uint16_t *qkv, uint16_t *o, int B, int T, int D, int H, int ng, int n_cu, EpTouch touch, hipStream_t s)
+{
+    // where the query waves leave room for a wave more: all do but those of 289 to 320 tokens and, of higher counts, the like
+    if (touch.bytes && touch.bytes <= MAX_TOUCH && query_waves(T, QW, ng) < MAXQW)
+        return launch_as<DH, QW, true>(qkv, o, B, T, D, H, ng, n_cu, touch, s);
+    return launch_as<DH, QW, false>(qkv, o, B, T, D, H, ng, n_cu, touch, s);
+}
+
 template <int DH>
-hipError_t launch_attention(const uint16_t *qkv, uint16_t *o, int B, int T, int D, int H, hipStream_t s)
+hipError_t launch_attention(const uint16_t *qkv, uint16_t *o, int B, int T, int D, int H, EpTouch touch, hipStream_t s)
 {
     int n_cu = 0;
     const hipError_t e = ep_device_cu_count(&n_cu);
     if (e != hipSuccess) return e;
     const AttnPlan p = plan_attention((int64_t)B * H, T, n_cu);
-    return p.qw == 32 ? launch_stream<DH, 32>(qkv, o, B, T, D, H, p.ng, n_cu, s)
-                      : launch_stream<DH, 16>(qkv, o, B, T, D, H, p.ng, n_cu, s);
+    return p.qw == 32 ? launch_stream<DH, 32>(qkv, o, B, T, D, H, p.ng, n_cu, touch, s)
+                      : launch_stream<DH, 16>(qkv, o, B, T, D, H, p.ng, n_cu, touch, s);
 }
 
 }  // namespace
@@ -549,14 +589,14 @@ bool ep_bf16_attention_supported(int T, int d_head)
     return T >= 1 && T <= 4096 && (d_head == 64 || d_head == 80);
 }
 
-hipError_t ep_bf16_attention(const uint16_t *qkv, uint16_t *o, int B, int T, int D, int H, hipStream_t s)
+hipError_t ep_bf16_attention(const uint16_t *qkv, uint16_t *o, int B, int T, int D, int H, EpTouch touch, hipStream_t s)
 {
     if (B <= 0) return hipSuccess;
     if (H <= 0 || D % H != 0 || !ep_bf16_attention_supported(T, D / H)) return hipErrorInvalidValue;
     if ((int64_t)B * H > 0x7FFFFFFF || (int64_t)T * 3 * D * 2 >= 0x7FFFFFF0ll) return hipErrorInvalidValue;
     switch (D / H) {
-    case 64: return launch_attention<64>(qkv, o, B, T, D, H, s);
-    case 80: return launch_attention<80>(qkv, o, B, T, D, H, s);
+    case 64: return launch_attention<64>(qkv, o, B, T, D, H, touch, s);
+    case 80: return launch_attention<80>(qkv, o, B, T, D, H, touch, s);
     }
     return hipErrorInvalidValue;
 }

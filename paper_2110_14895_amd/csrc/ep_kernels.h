@@ -61,8 +61,14 @@ hipError_t ep_bf16_gemm(const uint16_t *A, const uint16_t *W, const float *bias,
                         hipEvent_t after_main, hipStream_t s);
 int64_t ep_bf16_gemm_narrow_rows(int64_t M, int N, int K, int epi);
 int64_t ep_bf16_gemm_main_rows(int64_t M, int N, int K);
+// whether its steps of K wait where the weights come from memory: tiles of up to 128 rows, whose weights are a microsecond ahead, and
+// those of 192 and 256 columns, two steps; not the persistent kernel nor the higher tiles of 128 columns.  splits: the K ranges it is cut into
+enum EpWeightWait { EP_WAITS_NOT = 0, EP_WAITS = 1, EP_WAITS_LARGE = 2 };        // LARGE: of 192 and 256 columns
+EpWeightWait ep_bf16_gemm_weight_wait(int64_t M, int N, int K, int epi, int splits, bool one_order);
+// device memory that later launches read and a launch may bring nearer (it is not written, and nothing is kept); no bytes: none
+struct EpTouch { const void *p; uint32_t bytes; };
 // qkv bf16 [B*T, 3D] -> o bf16 [B*T, D]; d_head 64 or 80, T <= 4096 (K and V stream through LDS in chunks)
-hipError_t ep_bf16_attention(const uint16_t *qkv, uint16_t *o, int B, int T, int D, int H,
+hipError_t ep_bf16_attention(const uint16_t *qkv, uint16_t *o, int B, int T, int D, int H, EpTouch touch,
                              hipStream_t s);
 bool ep_bf16_attention_supported(int T, int d_head);
 // How attention deals the queries of `pairs` (image, head) pairs on `cus` compute units: tiles of qw queries, ng groups
