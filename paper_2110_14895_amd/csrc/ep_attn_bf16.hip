@@ -584,6 +584,14 @@ extern "C" void ep_query_attention_plan(int64_t pairs, int32_t T, int32_t cus, i
     *ng = p.ng;
 }
 
+bool ep_bf16_attention_touches(int64_t pairs, int T)
+{
+    int n_cu = 0;
+    if (pairs <= 0 || T <= 0 || ep_device_cu_count(&n_cu) != hipSuccess) return false;
+    const AttnPlan p = plan_attention(pairs, T, n_cu);
+    return query_waves(T, p.qw, p.ng) < MAXQW;
+}
+
 bool ep_bf16_attention_supported(int T, int d_head)
 {
     return T >= 1 && T <= 4096 && (d_head == 64 || d_head == 80);

@@ -3,7 +3,7 @@
 //
 //   C[M, N] = LN(x)[M, K] . W[N, K]^T + bias[N]   (+ erf GELU), bf16 out
 //
-// A workgroup brings 64 to 128 rows of the fp32 residual stream in, normalises them (the arithmetic and the order of the
+// A workgroup brings 64 to 128 rows (32 where there are few: launch_few) of the fp32 residual stream in, normalises them (the arithmetic and the order of the
 // sums of ln_bf16_kernel, so the same bits) and keeps them in LDS as bf16, all K of them: 96 KB for 128 rows at K = 384,
 // 128 KB for 64 at K = 1024.  Behind that one barrier its eight waves have nothing to wait for: each takes 32 columns at a
 // time, the weights straight into registers (fragment order, a ring of R slices that runs on from one set of columns to
@@ -17,7 +17,7 @@
 // groups share a panel the workgroups of an XCD therefore touch all weights between them while their rows come in, a line to a lane
 // (weights from memory: 12608 x 2304 x 768 65.5 -> 51.1 us, 7880 x 3072 x 1024 63.9 -> 54.4; over 2500 launches 0.79 of the time at 768
 // wide in one group and at 1024 in two, 0.87, 0.92 and 0.97 at 768 in two, three and four, 1.00 at 384 in one, 0.98 and 1.03 at 512 in
-// one and two).  A K of two to twelve slices
+// one and two), unless attention in front has touched them (ep_attn_bf16.hip): then it only costs, 2 to 4 % of a ViT-Base layer on 20 to 96 images.  A K of two to twelve slices
 // is too short for a tile with a prologue and an epilogue of its own, and LayerNorm was a launch and two trips through
 // memory.  LayerNorm and the dense layer, then this, in us, launches back to back with weights from memory: 6304 x 576 x 192 9.0 and 6.0,
 // 12672 x 768 x 192 with GELU 18.0 and 12.4, 6304 x 1536 x 384 with GELU 21.3 and 15.4 (17.3 inside a DeiT-Small stage), 4728 x 1152 x 384
@@ -31,7 +31,7 @@ namespace {
 
 using namespace ep_tile;
 
-constexpr int NW = 8, UC = 32, NI = UC / 16;         // waves, columns of a wave at a time
+constexpr int NW = 8, UC = 32;                       // waves, columns of a wave at a time (16 for few rows)
 
 // The sum over LPR lanes, added up as the exchanges of ln_bf16_kernel add it (lane ^ LPR / 2, ... lane ^ 1): from 16 lanes on
 // rotations of a row of 16 do what they do, as the values repeat every 8, 4 and 2 lanes by then, and need no LDS (1576
@@ -67,7 +67,7 @@ struct Rows {
 };
 
 // the staging areas of the waves take what LDS the rows leave: passes of 32 rows, or of 16
-template <int KS, int BM, int EPI>
+template <int KS, int BM, int NI, int EPI>
 struct RowsOut {
     static constexpr size_t ROWS = (size_t)BM * Rows<KS>::CH * 16;
     static constexpr int PASS = ROWS + NW * WaveOut<BM / 16, NI, EPI>::LDS_BYTES <= 160 * 1024 ? 32 : 16;
@@ -78,7 +78,7 @@ struct RowsOut {
 
 // TOUCH: the workgroups of an XCD bring the weights into its L2 between them (a template argument: as a branch it cost the
 // launches that do not touch 2 % of twelve DeiT layers)
-template <int KS, int BM, int EPI, bool TOUCH>
+template <int KS, int BM, int NI, int R, int EPI, bool TOUCH>
 __global__ __launch_bounds__(NW * 64, 2) void gemm_bf16_rows_kernel(const float *x, const float *__restrict__ ln_g,
                                                                     const float *__restrict__ ln_b, float eps, const uint16_t *W,
                                                                     const float *bias, void *Cout, int M, int N, int units, int per,
@@ -86,8 +86,8 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_bf16_rows_kernel(const float 
 {
 #if defined(__HIP_DEVICE_COMPILE__)
     using S = Rows<KS>;
-    constexpr int MI = BM / 16;
-    typedef typename RowsOut<KS, BM, EPI>::Out Out;
+    constexpr int MI = BM / 16, COLS = 16 * NI;
+    typedef typename RowsOut<KS, BM, NI, EPI>::Out Out;
     extern __shared__ uint4 lds[];                   // BM rows, then the waves' staging areas
     // consecutive workgroups go to different XCDs: each takes a contiguous run of (panel, group)
     const int total = panels * groups, run = (total + NUM_XCD - 1) / NUM_XCD;
@@ -97,10 +97,10 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_bf16_rows_kernel(const float 
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int l15 = lane & 15, g4 = lane >> 4;
 
-    // ---- weights: slice s of columns 32 u .. + 31, two fragments; sets past the last read an empty buffer
+    // ---- weights: slice s of columns COLS u .. + COLS - 1; sets past the last read an empty buffer
     const int nb = N / 16;
     constexpr int block = S::K * 32;                 // bytes of the fragments of 16 columns
-    bf16x8 wf[S::R][NI];
+    bf16x8 wf[R][NI];
     auto load_w = [&](int u, int s, int r) EP_INLINE {
         const __amdgpu_buffer_rsrc_t rs = make_rsrc(W, u < u1 ? (uint32_t)nb * (uint32_t)block : 0u);
 #pragma unroll
@@ -149,7 +149,7 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_bf16_rows_kernel(const float 
             bb[i] = in(i) ? reinterpret_cast<const f32x4 *>(ln_b)[lr + i * LPR] : f32x4{0.f, 0.f, 0.f, 0.f};
         }
 #pragma unroll
-        for (int s = 0; s < S::R; ++s) load_w(u0 + wave, s, s);
+        for (int s = 0; s < R; ++s) load_w(u0 + wave, s, s);
         if constexpr (TOUCH) touch_weights();
 #pragma unroll
         for (int t = 0; t < IT; ++t) {
@@ -183,15 +183,20 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_bf16_rows_kernel(const float 
 
     // ---- columns
     char *stg = reinterpret_cast<char *>(lds + BM * S::CH) + wave * Out::LDS_BYTES;
-    bf16x8 af[MI];
+    // rows of the slices ahead: one where it has eight products to land, more where it has two
+    constexpr int AD = NI * MI >= 8 ? 1 : KS % 4 ? 2 : 4;
+    static_assert(KS % AD == 0, "a set of columns begins with the first register");
+    bf16x8 af[AD][MI];
     auto read_a = [&](int s, int mi) EP_INLINE {
-        af[mi] = __builtin_bit_cast(bf16x8, lds[(mi * 16 + l15) * S::CH + S::slot(l15, s * 4 + kchunk(g4))]);
+        af[s % AD][mi] = __builtin_bit_cast(bf16x8, lds[(mi * 16 + l15) * S::CH + S::slot(l15, s * 4 + kchunk(g4))]);
     };
 #pragma unroll
-    for (int mi = 0; mi < MI; ++mi) read_a(0, mi);
+    for (int s = 0; s < AD; ++s)
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi) read_a(s, mi);
     for (int u = u0 + wave; u < u1; u += NW) {
         Out out;
-        out.init(Cout, nullptr, bias, m0, BM, 0, u * UC, M, N, 0, lane);
+        out.init(Cout, nullptr, bias, m0, BM, 0, u * COLS, M, N, 0, lane);
         f32x4 acc[NI][MI];
 #pragma unroll
         for (int ni = 0; ni < NI; ++ni)
@@ -199,14 +204,14 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_bf16_rows_kernel(const float 
             for (int mi = 0; mi < MI; ++mi) acc[ni][mi] = f32x4{0.f, 0.f, 0.f, 0.f};
         EP_SCHED_FENCE();
         static_for<KS>([&](auto s_c) EP_INLINE {
-            constexpr int s = decltype(s_c)::value, r = s % S::R, ahead = s + S::R;
+            constexpr int s = decltype(s_c)::value, r = s % R, ahead = s + R;
             static_for<MI>([&](auto m_c) EP_INLINE {
                 constexpr int mi = decltype(m_c)::value;
 #pragma unroll
                 for (int ni = 0; ni < NI; ++ni)
-                    acc[ni][mi] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[r][ni], af[mi], acc[ni][mi], 0, 0, 0);
+                    acc[ni][mi] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[r][ni], af[s % AD][mi], acc[ni][mi], 0, 0, 0);
                 EP_SCHED_FENCE();
-                read_a(s + 1 == KS ? 0 : s + 1, mi);
+                read_a((s + AD) % KS, mi);
                 EP_SCHED_FENCE();
             });
             if constexpr (ahead < KS) load_w(u, ahead, r);
@@ -220,12 +225,12 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_bf16_rows_kernel(const float 
 #endif
 }
 
-template <int KS, int BM, int EPI, bool TOUCH>
+template <int KS, int BM, int NI, int R, int EPI, bool TOUCH>
 hipError_t launch_as(const float *x, const float *g, const float *b, float eps, const uint16_t *W, const float *bias, void *C,
                      int M, int N, int units, int per, int groups, hipStream_t s)
 {
-    auto kern = gemm_bf16_rows_kernel<KS, BM, EPI, TOUCH>;
-    constexpr size_t smem = RowsOut<KS, BM, EPI>::LDS_BYTES;
+    auto kern = gemm_bf16_rows_kernel<KS, BM, NI, R, EPI, TOUCH>;
+    constexpr size_t smem = RowsOut<KS, BM, NI, EPI>::LDS_BYTES;
     static EpSmemLimit smem_limit;
     const hipError_t e = smem_limit.ensure(reinterpret_cast<const void *>(kern), (int)smem);
     if (e != hipSuccess) return e;
@@ -237,17 +242,18 @@ hipError_t launch_as(const float *x, const float *g, const float *b, float eps, 
 
 template <int KS, int BM, int EPI>
 hipError_t launch_rows(const float *x, const float *g, const float *b, float eps, const uint16_t *W, const float *bias, void *C,
-                       int M, int N, int groups, hipStream_t s)
+                       int M, int N, int groups, bool touched, hipStream_t s)
 {
     const int units = (N + UC - 1) / UC, per = (units + groups - 1) / groups;
     groups = (units + per - 1) / per;
     // Touching pays where a workgroup goes through many columns behind few others' (figures above; when it was introduced, without and
     // with: 3152 x 4096 x 1024 in four groups 43.4 and 39.4 us, in five 38.0 and 39.5, 3152 x 2304 x 768 in six 18.8 and 19.8,
-    // 6304 x 1152 x 384, 442 KB to a workgroup, in two 12.1 and 12.4) and every XCD has all groups.
+    // 6304 x 1152 x 384, 442 KB to a workgroup, in two 12.1 and 12.4) and every XCD has all groups.  Weights that are in the memory-side cache are
+    // not touched again (a layer of ViT-Base on 32 images 133.7 us with both, 130.3 without, ViT-Large on 40 232.6 and 226.5).
     if constexpr (KS > 8)
-        if (groups <= 4 && (int64_t)per * UC * KS * 64 >= 600 * 1024 && M / BM >= NUM_XCD)
-            return launch_as<KS, BM, EPI, true>(x, g, b, eps, W, bias, C, M, N, units, per, groups, s);
-    return launch_as<KS, BM, EPI, false>(x, g, b, eps, W, bias, C, M, N, units, per, groups, s);
+        if (!touched && groups <= 4 && (int64_t)per * UC * KS * 64 >= 600 * 1024 && M / BM >= NUM_XCD)
+            return launch_as<KS, BM, UC / 16, Rows<KS>::R, EPI, true>(x, g, b, eps, W, bias, C, M, N, units, per, groups, s);
+    return launch_as<KS, BM, UC / 16, Rows<KS>::R, EPI, false>(x, g, b, eps, W, bias, C, M, N, units, per, groups, s);
 }
 
 // Rows of a panel, 64 or as many as LDS holds, by the modelled microseconds of a launch: rounds of workgroups, each of them
@@ -288,8 +294,25 @@ RowsPlan plan_many_narrow_rows(int64_t M, int N, int cus)
     return best;
 }
 
+// Up to FEW_ROWS rows of models up to 384 wide in panels of 32, one round of workgroups (a layer inside a stage, microseconds, in panels of 64 rows or two launches
+// and so: DeiT-Small on 1 image 30.2 and 28.3, 4 32.8 and 30.9, 8 37.0 and 34.9, 12 39.7 and 39.3, 16 46.2 and 46.5, 24 51.8 and 61.1; DeiT-Tiny on 1 image 23.1 and
+// 21.1, 8 25.5 and 23.9, 12 26.2 and 25.5, 16 level, 24 31.6 and 34.5), and up to FEW_OUTPUTS of them (384 wide with an MLP of 8 K 3.0 million 35.4 and 34.6, 4.8 level,
+// 7.3 43.9 and 46.0; of 16 K 3.6 36.1 and 35.4, 6.1 41.4 and 42.0; 256 wide of 16 K 2.4 30.2 and 29.2, 4.0 31.5 and 31.8); 320 and 384 wide not past
+// 16 K (384 of 32 K on 1 image 36.9 in two launches and 38.8).
+constexpr int FEW_BM = 32, FEW_ROWS = 2560;
+constexpr int64_t FEW_OUTPUTS = 3800000;
+
+bool few_rows(int64_t M, int N, int K)
+{
+    return K <= 384 && N >= 4 * K && M <= FEW_ROWS && M * N <= FEW_OUTPUTS && (K <= 256 || N <= 16 * K);
+}
+
 RowsPlan plan_rows(int64_t M, int N, int K, bool gelu, int cus)
 {
+    if (few_rows(M, N, K)) {
+        const int64_t n = cus / ((M + FEW_BM - 1) / FEW_BM), units = N / 16;
+        return {FEW_BM, (int)(n < 1 ? 1 : n < units ? n : units), 0.0};
+    }
     // 384 wide, the model's plan is still the faster one where a round of 128 rows takes two thirds of the units (22458 and 24428 rows of
     // DeiT-Small, a layer: 141 and 146 us; lower panels, which read the weights twice as often, 149 and 153) and, but for MLPs of 8 K and
     // more, past that round (33884 rows: 245 and 249 us)
@@ -307,13 +330,26 @@ RowsPlan plan_rows(int64_t M, int N, int K, bool gelu, int cus)
     return best;
 }
 
+// Few rows of narrow models: panels of 32 rows, and 16 columns to a wave, so that a workgroup has at most a set or two of them, whose weights
+// are under way, all K of them, while the rows come in.
+template <int KS, int EPI>
+hipError_t launch_few(const float *x, const float *g, const float *b, float eps, const uint16_t *W, const float *bias, void *C,
+                      int M, int N, int groups, hipStream_t s)
+{
+    const int units = N / 16, per = (units + groups - 1) / groups;
+    return launch_as<KS, FEW_BM, 1, KS, EPI, false>(x, g, b, eps, W, bias, C, M, N, units, per, (units + per - 1) / per, s);
+}
+
 template <int EPI>
 hipError_t launch_k(const float *x, const float *g, const float *b, float eps, const uint16_t *W, const float *bias, void *C,
-                    int M, int N, int K, int cus, hipStream_t s)
+                    int M, int N, int K, int cus, bool touched, hipStream_t s)
 {
     const RowsPlan p = plan_rows(M, N, K, EPI == EPI_BIAS_GELU, cus);
+#define EP_FEW(KS) if (K == KS * 32 && p.bm == FEW_BM) return launch_few<KS, EPI>(x, g, b, eps, W, bias, C, M, N, p.groups, s)
+    EP_FEW(2); EP_FEW(4); EP_FEW(6); EP_FEW(8); EP_FEW(10); EP_FEW(12);
+#undef EP_FEW
 #define EP_ROWS(KS, BM) \
-    if (K == KS * 32 && p.bm == BM) return launch_rows<KS, BM, EPI>(x, g, b, eps, W, bias, C, M, N, p.groups, s)
+    if (K == KS * 32 && p.bm == BM) return launch_rows<KS, BM, EPI>(x, g, b, eps, W, bias, C, M, N, p.groups, touched, s)
     EP_ROWS(2, 128); EP_ROWS(2, 64);
     EP_ROWS(4, 128); EP_ROWS(4, 64);
     EP_ROWS(6, 128); EP_ROWS(6, 64);
@@ -333,9 +369,12 @@ hipError_t launch_k(const float *x, const float *g, const float *b, float eps, c
 // (profiles/layernorm_dense_one_launch.md):
 //   K = 384    N = 12 K at 505 rows 1.03, 32 K 0.96, from 1010 rows on 1.00 and more
 //   K = 512    N = 4 K at 505 rows 0.99, at 2525 1.07; 12 K at 505 rows 0.97, at 1010 1.06; 16 K at 505 and 1010 0.95 and 1.01; 32 K at 8080 0.95
-//   K = 768    N = 4 K at 2626 rows 1.04 and at 10302 (129 panels of 80 rows: one group, half the chip) 0.97, 8 K 1.06 and 0.93, 12 K 1.03 and 0.89,
+//   K = 768    weights touched, N = 4 K: two launches 64.1 us and one 64.5 at 1773 rows, 68.1 and 65.5 at 1970, 77.2 and 74.9 at 2561; q|k|v 68.1 and 69.9 at 1970
+//              N = 4 K at 2626 rows 1.04 and at 10302 (129 panels of 80 rows: one group, half the chip) 0.97, 8 K 1.06 and 0.93, 12 K 1.03 and 0.89,
 //              8 K at 12625 1.00, 12 K at 11110 0.92, 16 K at 9595 0.98; two launches 139 us and one 147 at 25256 rows of 4 K
-//   K = 1024   N = 4 K at 5555 rows 0.97, at 6161 1.02; 5 K at 6363 0.96, 8 K 0.94, 12 K 0.89; two launches 85 us and one 106 at 9456 rows of 4 K
+//   K = 1024   weights touched, N = 4 K: 84.3 and 84.3 at 1576 rows, 92.2 and 90.6 at 1773, 94.6 and 92.6 at 1970, 110.1 and 110.3 at 2561, 118 and 118.7 at 2955, 121.2 and 120.3 at
+//              3152, 137.5 and 136.5 at 3940, 166.9 and 162.8 at 4925, 174.1 and 175.3 at 5122
+//              N = 4 K at 5555 rows 0.97, at 6161 1.02; 5 K at 6363 0.96, 8 K 0.94, 12 K 0.89; two launches 85 us and one 106 at 9456 rows of 4 K
 // At 1024, layers past 2304 columns lose where tiles of 256 rows on their own are one nearly whole round: q|k|v at 6161 rows 0.99 and at 6565
 // 1.02, N = 2.75 K at 5757 0.97 and at 5959 1.01.
 bool one_launch_pays(int64_t M, int N, int K)
@@ -343,10 +382,12 @@ bool one_launch_pays(int64_t M, int N, int K)
     const double wide = (double)N / K;
     switch (K) {
     case 64: case 128: case 192: case 256: return true;
-    case 320: case 384: return M >= 1024 || (M >= 500 && wide <= 16.0);
+    case 320: case 384: return M >= 1024 || (M >= 500 && wide <= 16.0) || few_rows(M, N, K);
     case 512: return M <= 20000 && ((M >= 500 && wide <= 8.0) || (M >= 1000 && wide <= 16.0));
-    case 768: return M >= 2600 && M <= 20000 && (M <= 10240 ? wide <= 12.0 : wide <= 3.0 || (M > 10752 && wide <= 8.0));
-    case 1024: break;
+    case 768: return M >= (wide >= 4.0 ? 1900 : 2600) && M <= 20000 && (M <= 10240 ? wide <= 12.0 : wide <= 3.0 || (M > 10752 && wide <= 8.0));
+    case 1024:
+        if (wide == 4.0 && M >= 1750 && M <= 4950) return true;
+        break;
     default: return false;
     }
     if (M < 5500 || M > 8192 || wide > 4.0 || (wide > 3.5 && M <= 5888)) return false;
@@ -374,15 +415,15 @@ extern "C" int32_t ep_query_ln_gemm_plan(int64_t M, int32_t N, int32_t K, int32_
 }
 
 hipError_t ep_bf16_ln_gemm(const float *x, const float *g, const float *b, float eps, const uint16_t *W, const float *bias, void *C,
-                           int64_t M, int N, int K, int epi, hipEvent_t after_main, hipStream_t s)
+                           int64_t M, int N, int K, int epi, bool touched, hipEvent_t after_main, hipStream_t s)
 {
     if (M <= 0 || N <= 0) return hipSuccess;
     if (!ep_bf16_ln_gemm_supported(M, N, K) || (epi != EPI_BIAS && epi != EPI_BIAS_GELU)) return hipErrorInvalidValue;
     int cus = 0;
     hipError_t e = ep_device_cu_count(&cus);
     if (e != hipSuccess) return e;
-    e = epi == EPI_BIAS ? launch_k<EPI_BIAS>(x, g, b, eps, W, bias, C, (int)M, N, K, cus, s)
-                        : launch_k<EPI_BIAS_GELU>(x, g, b, eps, W, bias, C, (int)M, N, K, cus, s);
+    e = epi == EPI_BIAS ? launch_k<EPI_BIAS>(x, g, b, eps, W, bias, C, (int)M, N, K, cus, touched, s)
+                        : launch_k<EPI_BIAS_GELU>(x, g, b, eps, W, bias, C, (int)M, N, K, cus, touched, s);
     if (e != hipSuccess) return e;
     if (after_main) e = hipEventRecord(after_main, s);
     return e;

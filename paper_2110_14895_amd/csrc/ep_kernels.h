@@ -63,13 +63,16 @@ int64_t ep_bf16_gemm_narrow_rows(int64_t M, int N, int K, int epi);
 int64_t ep_bf16_gemm_main_rows(int64_t M, int N, int K);
 // whether its steps of K wait where the weights come from memory: tiles of up to 128 rows, whose weights are a microsecond ahead, and
 // those of 192 and 256 columns, two steps; not the persistent kernel nor the higher tiles of 128 columns.  splits: the K ranges it is cut into
-enum EpWeightWait { EP_WAITS_NOT = 0, EP_WAITS = 1, EP_WAITS_LARGE = 2 };        // LARGE: of 192 and 256 columns
+// RANGES: it is, and waits; PERSISTENT, HIGH: it does not; LARGE: tiles of 192 and 256 columns
+enum EpWeightWait { EP_WAITS_PERSISTENT, EP_WAITS_HIGH, EP_WAITS, EP_WAITS_RANGES, EP_WAITS_LARGE };
 EpWeightWait ep_bf16_gemm_weight_wait(int64_t M, int N, int K, int epi, int splits, bool one_order);
 // device memory that later launches read and a launch may bring nearer (it is not written, and nothing is kept); no bytes: none
 struct EpTouch { const void *p; uint32_t bytes; };
 // qkv bf16 [B*T, 3D] -> o bf16 [B*T, D]; d_head 64 or 80, T <= 4096 (K and V stream through LDS in chunks)
 hipError_t ep_bf16_attention(const uint16_t *qkv, uint16_t *o, int B, int T, int D, int H, EpTouch touch,
                              hipStream_t s);
+// whether a launch over these has a wave to spare that touches
+bool ep_bf16_attention_touches(int64_t pairs, int T);
 bool ep_bf16_attention_supported(int T, int d_head);
 // How attention deals the queries of `pairs` (image, head) pairs on `cus` compute units: tiles of qw queries, ng groups
 // of tiles to a pair; for tests
@@ -100,12 +103,12 @@ extern "C" void ep_query_dense_plan(int64_t M, int32_t N, int32_t K, int32_t epi
 extern "C" void ep_query_dense_plan_one_order(int64_t M, int32_t N, int32_t K, int32_t epi, EpDensePlan *out);
 
 // LayerNorm of x and the dense layer behind it (bias, or bias and GELU) in one launch, where that pays (ep_gemm_bf16_rows.hip):
-// the bits of ep_bf16_layernorm and ep_bf16_gemm
+// the bits of ep_bf16_layernorm and ep_bf16_gemm.  touched: the weights have been brought into the memory-side cache
 bool ep_bf16_ln_gemm_supported(int64_t M, int N, int K);
 // rows of a panel and the column groups that share one, on `cus` compute units; 0: two launches.  For tests
 extern "C" int32_t ep_query_ln_gemm_plan(int64_t M, int32_t N, int32_t K, int32_t epi, int32_t cus, int32_t *groups);
 hipError_t ep_bf16_ln_gemm(const float *x, const float *g, const float *b, float eps, const uint16_t *W, const float *bias, void *C,
-                           int64_t M, int N, int K, int epi, hipEvent_t after_main, hipStream_t s);
+                           int64_t M, int N, int K, int epi, bool touched, hipEvent_t after_main, hipStream_t s);
 
 // persistent kernel for large problems (ep_gemm_bf16_persist.hip): 256 x BN tiles, BN = tile_bn
 // (256 or 320).  The tile walk covers rows

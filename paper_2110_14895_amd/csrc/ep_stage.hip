@@ -183,8 +183,9 @@ struct TraceScope {
 #define EP_TRACED_GEMM(kernel, main_id, call) do { TraceScope ts_(st, kernel, main_id, s); EP_HIP(call); } while (0)
 
 // of weights that attention touches: half of the memory-side cache, and see touch_weights
-constexpr size_t TOUCH_MOST_BYTES = (size_t)128 << 20;
-constexpr double TOUCH_ROWS_PER_MB = 27.0;
+constexpr size_t TOUCH_MOST_BYTES = (size_t)128 << 20, TOUCH_LARGE_BYTES = (size_t)32 << 20;
+constexpr double TOUCH_ROWS_PER_MB = 27.0, TOUCH_RANGES_ROWS_PER_MB = 45.0, TOUCH_ALL_ROWS_PER_MB = 110.0;
+enum Touch { TOUCH_NONE, TOUCH_LONG, TOUCH_ALL };       // LONG: the projection and the second MLP layer
 
 // What a layer whose second MLP layer ran cut into K ranges has left for its successor: the residual stream
 // in w.x still lacks ((part[0] + ... + part[splits-1]) + bias).
@@ -192,22 +193,32 @@ struct PendingSum { int splits; const float *bias; };
 
 // Whether attention of a forward over R rows touches the weights of the launches behind it (why and how: ep_attn_bf16.hip).  A layer
 // of a stage whose weights come from memory, without and with, in us:
-//   It pays from some 27 rows to a MB of weights on, which the launch would otherwise be too short for (ViT-Large on 1 image 39.8 and 41.6, 2 47.9 and 47.4, 5
-// 62.1 and 61.9, 8 82.3 and 80.2; ViT-Huge on 1 55.2 and 58.5, 4 84.5 and 85.1, 6 111.3 and 107.2; ViT-Base on 2 41.4 and 40.8, 4 48.4 and 45.2, 8 64.6 and
-// 60.4, 16 89.2 and 79.7), at any rows up to 768 wide (DeiT-Small on 8 images 39.7 and 36.9, 32 66.4 and 57.3, 128 160.8 and 151.1, DeiT-Tiny on 256 135.4 and
-// 127.3, ViT-Base on 28 to 48 level, on 64 236 and 225), and past that where the second MLP layer waits for its weights: ViT-Large on 16 126.7 and 117.2, 48 288 and 279,
-// 64 382 and 374, ViT-Huge on 8 130.1 and 125.8, 32 354 and 350.  Where it does not, attention only takes longer (ViT-Large on 32 195.6 and 198.5,
-// ViT-Huge on 16 189.8 and 199.7, 64 635 and 642), and nearly so behind a persistent first MLP layer (ViT-Huge on 12 153.5 and 155.6).
-bool touch_weights(const ep_vit_config &c, const Workspace &w, int32_t B)
+//   It pays from some 27 rows to a MB of weights on, which the launch would otherwise be too short for (ViT-Large on 1 image 39.8 and 41.6; ViT-Huge on 1
+// 55.2 and 58.5; ViT-Base on 1 35.9 and 36.6, 2 41.4 and 40.8, 4 48.4 and 45.2, 8 64.6 and 60.4, 16 89.2 and 79.7), at any rows up to 768 wide (DeiT-Small on 8
+// images 39.7 and 36.9, 32 66.4 and 57.3, 128 160.8 and 151.1, DeiT-Tiny on 256 135.4 and 127.3, ViT-Base on 28 to 48 level, on 64 236 and 225), and past
+// that where LayerNorm goes with a dense layer or the second MLP layer waits for its weights: ViT-Large on 16 126.7 and 117.2, 48 288 and 279, 64 382 and 374,
+// ViT-Huge on 6 111.3 and 106.4, 8 130.1 and 125.8.  Cut into ranges of K that layer waits less, and ViT-Large on 5 images gains 3 % or loses 2, by the card; from 45 rows to
+// a MB on it gains (on 6 72.3 and 70.9, 8 82.3 and 79.3, 10 92.1 and 89.6).  Elsewhere attention only takes longer (ViT-Huge on 16 189.8 and 199.7, 64
+// 635 and 642; on 32, in 256 x 192 tiles, 354.5 and 350 on one card and 353 and 358 on another), and nearly so behind a persistent first MLP layer (ViT-Huge on 12 153.5 and 155.6).
+//   Past 768 wide below some 110 rows to a MB the projection and the second MLP layer are enough, 40 % of the bytes: ViT-Large on 8 images 79.3 for 80.2 with all, 10 89.5
+// for 91.4, 14 111.4 for 111.6, 16 118.6 for 117.2, ViT-Huge on 4 82.9 for 85.1, 6 106.4 for 107.2; ViT-Base on 4 images 46.4 for 45.2, 16 84.2 for 79.7.
+//   Dense layers that go with their LayerNorm touch their weights themselves otherwise, which takes them longer: ViT-Large on 28 images 180.7 and 178.6, 40 232.6
+// and 226.5, with its touching left out.
+Touch touch_weights(const ep_vit_config &c, const Workspace &w, int32_t B)
 {
     const int64_t R = (int64_t)B * c.n_tokens, D = c.d_model, M = c.d_mlp;
     const size_t bytes = 2 * (size_t)(4 * D * D + 2 * D * M);       // of a layer
-    if (!(c.param_dtype == EP_BF16) || bytes > TOUCH_MOST_BYTES || (double)R * 1e6 < TOUCH_ROWS_PER_MB * (double)bytes) return false;
-    if (D <= 768) return true;
+    const double rows_per_mb = (double)R * 1e6 / (double)bytes;
+    if (c.param_dtype != EP_BF16 || bytes > TOUCH_MOST_BYTES || rows_per_mb < TOUCH_ROWS_PER_MB) return TOUCH_NONE;
+    if (!ep_bf16_attention_touches((int64_t)B * c.n_heads, c.n_tokens)) return TOUCH_NONE;
+    if (D <= 768 || ep_bf16_ln_gemm_supported(R, 3 * D, D) || ep_bf16_ln_gemm_supported(R, M, D)) return D <= 768 || rows_per_mb >= TOUCH_ALL_ROWS_PER_MB ? TOUCH_ALL : TOUCH_LONG;
     const bool group = w.ranges_of != 0;
     const EpWeightWait fc2 = ep_bf16_gemm_weight_wait(R, D, M, EPI_BIAS_RESID, w.part ? fc2_splits(c, group ? w.ranges_of : B) : 1, group);
-    return fc2 == EP_WAITS_LARGE || (fc2 == EP_WAITS && (ep_bf16_ln_gemm_supported(R, M, D) ||
-                                                         ep_bf16_gemm_weight_wait(R, M, D, EPI_BIAS_GELU, 1, group) != EP_WAITS_NOT));
+    if (fc2 == EP_WAITS_PERSISTENT || fc2 == EP_WAITS_HIGH) return TOUCH_NONE;
+    if (fc2 == EP_WAITS_LARGE && bytes > TOUCH_LARGE_BYTES) return TOUCH_NONE;
+    if (fc2 == EP_WAITS_RANGES && rows_per_mb < TOUCH_RANGES_ROWS_PER_MB) return TOUCH_NONE;
+    if (fc2 != EP_WAITS_LARGE && ep_bf16_gemm_weight_wait(R, M, D, EPI_BIAS_GELU, 1, group) == EP_WAITS_PERSISTENT) return TOUCH_NONE;
+    return rows_per_mb >= TOUCH_ALL_ROWS_PER_MB ? TOUCH_ALL : TOUCH_LONG;
 }
 
 // One layer on R = B*T rows.  `xin` is the residual stream read by this layer
@@ -217,11 +228,11 @@ bool touch_weights(const ep_vit_config &c, const Workspace &w, int32_t B)
 // w.x, and *after says so with splits > 1); if null it finishes its output itself.
 // `xin16`: the stage's bf16 input in place of xin (which is w.x then and gets it as fp32).  `xout16`: where the layer
 // may leave its output as bf16 in place of xout; it says so in *narrowed.
-// `touch_rest`: attention touches the weights of this layer that come behind it and, if there is a `next` layer, its first
-// dense layer's, which lie behind them.
+// `touch`: weights that attention touches, of this layer and, if there is one, of the `next` layer's first dense layer; `touched`: so it was
+// for this layer's first one.
 ep_status run_layer(ep_stage *st, const Workspace &w, const LayerDev &L, const float *xin, float *xout, int B,
                     hipStream_t s, const PendingSum *before, PendingSum *after, const uint16_t *xin16 = nullptr,
-                    uint16_t *xout16 = nullptr, bool *narrowed = nullptr, bool touch_rest = false, const LayerDev *next = nullptr)
+                    uint16_t *xout16 = nullptr, bool *narrowed = nullptr, Touch touch = TOUCH_NONE, bool touched = false, const LayerDev *next = nullptr)
 {
     const ep_vit_config &c = st->cfg;
     const int T = c.n_tokens, D = c.d_model, M = c.d_mlp, H = c.n_heads;
@@ -242,20 +253,22 @@ ep_status run_layer(ep_stage *st, const Workspace &w, const LayerDev &L, const f
             EP_TRACED(EP_K_LN1, fuse1 ? hipSuccess : ep_bf16_layernorm(xin, D, L.ln1_g, L.ln1_b, c.ln_eps, a, R, D, s));
         EP_TRACED_GEMM(EP_K_QKV, EP_K_QKV_MAIN,
                        fuse1 ? ep_bf16_ln_gemm(xin, L.ln1_g, L.ln1_b, c.ln_eps, (const uint16_t *)L.w_qkv, L.b_qkv, big, R,
-                                               3 * D, D, EPI_BIAS, ts_.after_main(), s)
+                                               3 * D, D, EPI_BIAS, touched, ts_.after_main(), s)
                              : ep_bf16_gemm(a, (const uint16_t *)L.w_qkv, L.b_qkv, nullptr, big, R, 3 * D, D, EPI_BIAS,
                                             one_order, ts_.after_main(), s));
-        EpTouch touch = {L.w_o, 0};
-        if (next) touch.bytes = (uint32_t)((const char *)next->w_qkv + (size_t)3 * D * D * 2 - (const char *)L.w_o);
-        else if (touch_rest) touch.bytes = (uint32_t)((const char *)L.w_fc2 + (size_t)D * M * 2 - (const char *)L.w_o);
-        EP_TRACED(EP_K_ATTN, ep_bf16_attention(big, a, B, T, D, H, touch, s));
+        // in memory: projection, second MLP layer, first, the next layer's q|k|v
+        const char *touch_end = (const char *)L.w_o;
+        if (touch == TOUCH_LONG) touch_end = (const char *)L.w_fc2 + (size_t)D * M * 2;
+        if (touch == TOUCH_ALL) touch_end = next ? (const char *)next->w_qkv + (size_t)3 * D * D * 2 : (const char *)L.w_fc1 + (size_t)D * M * 2;
+        const EpTouch touched_here = {L.w_o, (uint32_t)(touch_end - (const char *)L.w_o)};
+        EP_TRACED(EP_K_ATTN, ep_bf16_attention(big, a, B, T, D, H, touched_here, s));
         EP_TRACED_GEMM(EP_K_PROJ, EP_K_PROJ_MAIN,
                        ep_bf16_gemm(a, (const uint16_t *)L.w_o, L.b_o, xin, w.x, R, D, D, EPI_BIAS_RESID,
                                     one_order, ts_.after_main(), s));
         EP_TRACED(EP_K_LN2, fuse2 ? hipSuccess : ep_bf16_layernorm(w.x, D, L.ln2_g, L.ln2_b, c.ln_eps, a, R, D, s));
         EP_TRACED_GEMM(EP_K_FC1, EP_K_FC1_MAIN,
                        fuse2 ? ep_bf16_ln_gemm(w.x, L.ln2_g, L.ln2_b, c.ln_eps, (const uint16_t *)L.w_fc1, L.b_fc1, big, R, M, D,
-                                               EPI_BIAS_GELU, ts_.after_main(), s)
+                                               EPI_BIAS_GELU, touch == TOUCH_ALL, ts_.after_main(), s)
                              : ep_bf16_gemm(a, (const uint16_t *)L.w_fc1, L.b_fc1, nullptr, big, R, M, D, EPI_BIAS_GELU,
                                             one_order, ts_.after_main(), s));
         int sp = w.part ? fc2_splits(c, w.ranges_of ? w.ranges_of : B) : 1;
@@ -381,13 +394,14 @@ extern "C" ep_status ep_stage_create(const ep_vit_config *cfg, int32_t layer_beg
         if (src != EP_OK) return fail(src);
     }
 
-    // ---- parameter block layout (per layer): dense weights, then fp32 vectors
+    // ---- parameter block layout (per layer): dense weights, q|k|v, projection, second and first MLP layer (what attention touches, touch_weights,
+    // is one range), then fp32 vectors
     const size_t n_w[4] = {(size_t)(3 * D * D), (size_t)(D * D), (size_t)(M * D), (size_t)(D * M)};
     const size_t n_v[8] = {(size_t)D, (size_t)D, (size_t)(3 * D), (size_t)D,
                            (size_t)D, (size_t)D, (size_t)M, (size_t)D};
     size_t layer_bytes = 0;
     size_t off_w[4], off_v[8];
-    for (int i = 0; i < 4; ++i) { off_w[i] = layer_bytes; layer_bytes += align_up(n_w[i] * wsz, 256); }
+    for (int i : {0, 1, 3, 2}) { off_w[i] = layer_bytes; layer_bytes += align_up(n_w[i] * wsz, 256); }
     for (int i = 0; i < 8; ++i) { off_v[i] = layer_bytes; layer_bytes += align_up(n_v[i] * 4, 256); }
     st->params_bytes = layer_bytes * nl;
     e = hipMalloc((void **)&st->params, st->params_bytes);
@@ -490,13 +504,13 @@ ep_status forward_on(ep_stage *st, const Workspace &w, const void *x_in, int32_t
     uint16_t *out16 = c.out_dtype == EP_BF16 ? (uint16_t *)x_out : nullptr;
     bool narrowed = false;
     PendingSum pending = {1, nullptr};
-    const bool touch = touch_weights(c, w, B);
+    const Touch touch = touch_weights(c, w, B);
     for (int l = 0; l < nl; ++l) {
         const bool last = l + 1 == nl;
         float *dst = (last && c.out_dtype == EP_F32) ? (float *)x_out : w.x;
         const PendingSum before = pending;
         ep_status rc = run_layer(st, w, st->layers[l], cur, dst, B, s, &before, last ? nullptr : &pending,
-                                 l == 0 ? in16 : nullptr, last ? out16 : nullptr, &narrowed, touch, touch && !last ? &st->layers[l + 1] : nullptr);
+                                 l == 0 ? in16 : nullptr, last ? out16 : nullptr, &narrowed, touch, touch == TOUCH_ALL && l > 0, !last ? &st->layers[l + 1] : nullptr);
         if (rc != EP_OK) return rc;
         cur = dst;
     }
