@@ -390,9 +390,9 @@ __device__ __forceinline__ void attn_wave(const uint16_t *__restrict__ qkv, uint
 // single images, which does not, 0.9 %)
 template <int DH, int QW, bool TOUCH>
 __global__ __launch_bounds__((MAXQW + NLOADER) * 64) void attn_stream_kernel(const uint16_t *__restrict__ qkv,
-                                                                             uint16_t *__restrict__ o, int T, int D, int H,
-                                                                             int n_units, int ng, float scale_log2e,
-                                                                             EpTouch touch)
+                                                                             uint16_t *__restrict__ o, int T, int D, int H, int ng,
+                                                                             int nqw, int grid, int each, int rest,
+                                                                             float scale_log2e, uint32_t touch_bytes, const void *touch)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
     using S = StreamShape<DH>;
@@ -403,7 +403,6 @@ __global__ __launch_bounds__((MAXQW + NLOADER) * 64) void attn_stream_kernel(con
 
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int nqw = (int)(blockDim.x >> 6) - NLOADER - (TOUCH ? 1 : 0);      // query waves of this launch
     const bool loader = wave >= nqw;                               // wave-uniform
     const int row_bytes = 3 * D * 2;
     const int seg_bytes = (T - 1) * row_bytes + DH * 2;            // first to last byte of a head's q, k or v
@@ -412,13 +411,15 @@ __global__ __launch_bounds__((MAXQW + NLOADER) * 64) void attn_stream_kernel(con
     // Workgroup w sits on XCD w % 8 (round-robin dispatch).  Each XCD gets a contiguous range of
     // units, as long as its share of the workgroups, so that the heads of an image, which
     // share cache lines of the qkv rows, meet in one L2; the workgroups of an XCD stride through it.
+    // nqw query waves; grid * each + rest units in all, rest < grid: the n-th share of the grid begins at each * n + rest * n / grid.
     int unit, unit_end, unit_step;
     {
-        const int x = blockIdx.x % 8, g8 = gridDim.x / 8, r8 = gridDim.x % 8;
+        const int x = blockIdx.x % 8, g8 = grid / 8, r8 = grid % 8;
         const int before = x * g8 + min(x, r8);                    // workgroups on the XCDs in front of this one
         unit_step = g8 + (x < r8 ? 1 : 0);                         // workgroups on this one
-        unit = (int)((int64_t)n_units * before / gridDim.x) + blockIdx.x / 8;
-        unit_end = (int)((int64_t)n_units * (before + unit_step) / gridDim.x);
+        auto begin = [&](int n) { return each * n + (int)((uint32_t)(rest * n) / (uint32_t)grid); };
+        unit = begin(before) + blockIdx.x / 8;
+        unit_end = begin(before + unit_step);
     }
     if (unit >= unit_end) return;                                  // whole workgroup
     const int my_units = (unit_end - unit + unit_step - 1) / unit_step;
@@ -429,12 +430,12 @@ __global__ __launch_bounds__((MAXQW + NLOADER) * 64) void attn_stream_kernel(con
         // barriers behind the first are without it
         constexpr uint32_t LINE = 128;
         constexpr int FLIGHT = 4;
-        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(touch.p), 0, (int)touch.bytes, 0x00020000);
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(touch), 0, (int)touch_bytes, 0x00020000);
         asm volatile("" ::: "memory");
         __builtin_amdgcn_s_barrier();              // behind the first chunk, which everyone waits for
         asm volatile("" ::: "memory");
-        const uint32_t step = gridDim.x * 64 * LINE;
-        for (uint32_t at = blockIdx.x * 64 * LINE; at < touch.bytes; at += FLIGHT * step) {
+        const uint32_t step = (uint32_t)grid * 64 * LINE;
+        for (uint32_t at = blockIdx.x * 64 * LINE; at < touch_bytes; at += FLIGHT * step) {
             uint32_t v[FLIGHT];
 #pragma unroll
             for (int i = 0; i < FLIGHT; ++i) v[i] = __builtin_amdgcn_raw_buffer_load_b32(rs, (int)(at + i * step + lane * LINE), 0, 0);
@@ -550,8 +551,8 @@ hipError_t launch_as(const uint16_t *qkv, uint16_t *o, int B, int T, int D, int 
     // of two take 15.3 us where 256 workgroups, 16 of them with a second unit, take 16.2
     const int64_t rounds = (n_units + n_cu - 1) / n_cu;
     const int grid = (int)((n_units + rounds - 1) / rounds);
-    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3((nqw + NLOADER + (TOUCH ? 1 : 0)) * 64), S::smem, s, qkv, o, T, D, H, (int)n_units, ng,
-                       scale_log2e, touch);
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3((nqw + NLOADER + (TOUCH ? 1 : 0)) * 64), S::smem, s, qkv, o, T, D, H, ng, nqw, grid,
+                       (int)(n_units / grid), (int)(n_units % grid), scale_log2e, touch.bytes, touch.p);
     return hipGetLastError();
 }
 

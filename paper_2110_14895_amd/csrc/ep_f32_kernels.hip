@@ -40,7 +40,7 @@ __global__ __launch_bounds__(256) void ln_f32_kernel(const float *__restrict__ x
                                                      float *__restrict__ y, int64_t rows, int D)
 {
     const int lane = threadIdx.x & (WAVE - 1);
-    const int64_t row = (int64_t)blockIdx.x * (blockDim.x / WAVE) + (threadIdx.x / WAVE);
+    const int64_t row = (int64_t)blockIdx.x * (256 / WAVE) + (threadIdx.x / WAVE);
     if (row >= rows) return;
     const float *xr = x + row * ldx;
     float s = 0.f;
@@ -63,7 +63,7 @@ __global__ __launch_bounds__(256) void ln_f32_vec_kernel(const float *__restrict
                                                          int64_t rows, int D)
 {
     const int lane = threadIdx.x & (WAVE - 1);
-    const int64_t row = (int64_t)blockIdx.x * (blockDim.x / WAVE) + (threadIdx.x / WAVE);
+    const int64_t row = (int64_t)blockIdx.x * (256 / WAVE) + (threadIdx.x / WAVE);
     if (row >= rows) return;
     const float4 *xr = reinterpret_cast<const float4 *>(x + row * ldx);
     const float4 *g4 = reinterpret_cast<const float4 *>(g), *b4 = reinterpret_cast<const float4 *>(b);
@@ -156,9 +156,9 @@ __device__ inline void store_four(const float (&v)[4], const float *bias, const 
 // Workgroup -> tile, columns fastest: workgroup w runs on XCD w % 8 (round-robin dispatch), and each XCD takes a
 // contiguous run of tiles, as long as its share of the workgroups, so that the tiles of a row panel meet in one L2.  One
 // workgroup to a tile and none beside (a grid may not have 2^32 threads).
-__device__ inline void f32_tile_of(int tiles_n, int *tm, int *tn)
+__device__ inline void f32_tile_of(int tiles_n, int tiles, int *tm, int *tn)
 {
-    const int xcd = blockIdx.x % 8, id = xcd * (int)(gridDim.x / 8) + min(xcd, (int)(gridDim.x % 8)) + (int)(blockIdx.x / 8);
+    const int xcd = blockIdx.x % 8, id = xcd * (tiles / 8) + min(xcd, tiles % 8) + (int)(blockIdx.x / 8);
     *tm = id / tiles_n;
     *tn = id - *tm * tiles_n;
 }
@@ -183,11 +183,10 @@ struct F32Direct {
 };
 
 template <int MR, int MC, int EPI, int LN>
-__global__ __launch_bounds__(256) void gemm_f32_direct_kernel(const float *__restrict__ A, const float *__restrict__ ln_g,
-                                                              const float *__restrict__ ln_b, float eps,
-                                                              const float *__restrict__ W, const float *__restrict__ bias,
-                                                              const float *resid, float *C, int64_t M, int N, int K, int tiles_n,
-                                                              int vec)
+__global__ __launch_bounds__(256) void gemm_f32_direct_kernel(const float *__restrict__ A, const float *__restrict__ W, int M, int N,
+                                                              int K, int tiles_n, int tiles, int vec,
+                                                              const float *__restrict__ ln_g, const float *__restrict__ ln_b,
+                                                              const float *__restrict__ bias, const float *resid, float *C, float eps)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
     using S = F32Direct<MR, MC, LN>;
@@ -197,7 +196,7 @@ __global__ __launch_bounds__(256) void gemm_f32_direct_kernel(const float *__res
     typedef __attribute__((address_space(3))) void *lds_ptr;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l15 = lane & 15, g = lane >> 4;
     int tm, tn;
-    f32_tile_of(tiles_n, &tm, &tn);
+    f32_tile_of(tiles_n, tiles, &tm, &tn);
     const int64_t m0 = (int64_t)tm * TR;
     const int n0 = tn * TC;
     const int nsl = (K + 15) / 16, my = (nsl - wave + 3) / 4;       // slices of all, of this wave (wave, wave + 4, ...)
@@ -335,16 +334,16 @@ __global__ __launch_bounds__(256) void gemm_f32_direct_kernel(const float *__res
 // 0, 2, 1, 3 to the quarters of a wave: the bf16 kernels' layout, free of bank conflicts.
 constexpr int FT = 64, FN = 32, FK = 32, FCH = FK / 4, FS = 2;
 template <int EPI>
-__global__ __launch_bounds__(256, 4) void gemm_f32_tile_kernel(const float *__restrict__ A, const float *__restrict__ W,
-                                                               const float *__restrict__ bias, const float *resid, float *C,
-                                                               int64_t M, int N, int K, int tiles_n, int vec)
+__global__ __launch_bounds__(256, 4) void gemm_f32_tile_kernel(const float *__restrict__ A, const float *__restrict__ W, int M,
+                                                               int N, int K, int tiles_n, int tiles, int vec,
+                                                               const float *__restrict__ bias, const float *resid, float *C)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
     extern __shared__ uint4 lds_raw[];                              // [FS][A panel | W panel], FT rows of FCH chunks each
     typedef __attribute__((address_space(3))) void *lds_ptr;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l15 = lane & 15, g = lane >> 4;
     int tm, tn;
-    f32_tile_of(tiles_n, &tm, &tn);
+    f32_tile_of(tiles_n, tiles, &tm, &tn);
     const int64_t m0 = (int64_t)tm * FT;
     const int n0 = tn * FN;
     constexpr int NI = FN / 32, STAGE = (FT + FN) * FCH;
@@ -439,9 +438,8 @@ struct F32Rows {
 
 template <int NS, int EPI>
 __global__ __launch_bounds__(512, NS <= 12 ? 4 : 2) void gemm_f32_rows_kernel(
-    const float *__restrict__ A, const float *__restrict__ ln_g, const float *__restrict__ ln_b, float eps,
-    const float *__restrict__ W, const float *__restrict__ bias, float *C, int64_t M, int N, int K, int steps, int groups,
-    int vec)
+    const float *__restrict__ A, const float *__restrict__ W, int M, int N, int K, int steps, int groups, int tiles,
+    const float *__restrict__ ln_g, const float *__restrict__ ln_b, const float *__restrict__ bias, float *C, float eps, int vec)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
     using S = F32Rows<NS>;
@@ -450,7 +448,7 @@ __global__ __launch_bounds__(512, NS <= 12 ? 4 : 2) void gemm_f32_rows_kernel(
     typedef __attribute__((address_space(3))) void *lds_ptr;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l15 = lane & 15, g = lane >> 4;
     int tm, tg;
-    f32_tile_of(groups, &tm, &tg);
+    f32_tile_of(groups, tiles, &tm, &tg);
     const int64_t m0 = (int64_t)tm * S::T;
     const int n0 = tg * steps * S::CN;
     auto swz = [](int r) { return (r & 7) ^ ((r >> 3) & 1); };
@@ -648,7 +646,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float *__restrict__
 // d_head % 4 == 0, d_head <= 64 NT; pieces past it are zeros.
 template <int NT, bool SPLIT>
 __global__ __launch_bounds__(256) void attn_f32_mfma_kernel(const float *__restrict__ qkv, float *__restrict__ o, int T, int D,
-                                                            int H, int groups)
+                                                            int H, int groups, int tiles)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
     constexpr int LP = 64 * NT + 4, CPR = 16 * NT;                  // padded output row; 16-byte pieces of a key row
@@ -660,7 +658,7 @@ __global__ __launch_bounds__(256) void attn_f32_mfma_kernel(const float *__restr
     // the groups of a pair on one XCD: its keys and values come past that L2 once (dealt to all eight XCDs: 24 pairs of 197
     // tokens 12.2 us, so 11.1; 96 of 65 8.3, so 7.3)
     int pair, grp;
-    f32_tile_of(groups, &pair, &grp);
+    f32_tile_of(groups, tiles, &pair, &grp);
     const int dh = D / H, q0 = (SPLIT ? grp : grp * 4 + wave) * 16, h = pair % H;
     if (q0 >= T) return;                                            // without SPLIT: a wave with no queries
     const int64_t b = pair / H;
@@ -883,7 +881,8 @@ hipError_t launch_f32_direct(const float *A, const float *g, const float *b, flo
     if (e != hipSuccess) return e;
     const int tiles_n = (N + S::TC - 1) / S::TC;
     const int64_t tiles = (M + S::TR - 1) / S::TR * tiles_n;
-    hipLaunchKernelGGL(kern, dim3((unsigned)tiles), dim3(256), S::smem, s, A, g, b, eps, W, bias, resid, C, M, N, K, tiles_n, vec);
+    hipLaunchKernelGGL(kern, dim3((unsigned)tiles), dim3(256), S::smem, s, A, W, (int)M, N, K, tiles_n, (int)tiles, vec, g, b, bias,
+                       resid, C, eps);
     return hipGetLastError();
 }
 
@@ -912,7 +911,7 @@ hipError_t launch_f32_gemm(const float *A, const float *W, const float *bias, co
         } else {
             const int tiles_n = (N + FN - 1) / FN, tiles = (int)((M + FT - 1) / FT) * tiles_n;
             hipLaunchKernelGGL(gemm_f32_tile_kernel<EPI>, dim3(tiles), dim3(256), FS * (FT + FN) * FK * sizeof(float), s, A, W,
-                               bias, resid, C, M, N, K, tiles_n, vec);
+                               (int)M, N, K, tiles_n, tiles, vec, bias, resid, C);
         }
         return hipGetLastError();
     }
@@ -995,7 +994,8 @@ hipError_t launch_f32_rows(const float *x, const float *g, const float *b, float
     const int all = (N + S::CN - 1) / S::CN, steps = f32_rows_steps(M, N, cus).steps;
     const int groups = (all + steps - 1) / steps;
     const int64_t tiles = panels * groups;
-    hipLaunchKernelGGL(kern, dim3((unsigned)tiles), dim3(512), S::smem, s, x, g, b, eps, W, bias, C, M, N, K, steps, groups, vec);
+    hipLaunchKernelGGL(kern, dim3((unsigned)tiles), dim3(512), S::smem, s, x, W, (int)M, N, K, steps, groups, (int)tiles, g, b, bias, C,
+                       eps, vec);
     return hipGetLastError();
 }
 
@@ -1072,7 +1072,7 @@ hipError_t ep_f32_attention(const float *qkv, float *o, int B, int T, int D, int
         const int groups = split ? t16 : (t16 + 3) / 4;
         const int64_t tiles = pairs * groups;
 #define EP_LAUNCH(NT, SPLIT) \
-    hipLaunchKernelGGL((attn_f32_mfma_kernel<NT, SPLIT>), dim3((unsigned)tiles), dim3(256), 0, s, qkv, o, T, D, H, groups)
+    hipLaunchKernelGGL((attn_f32_mfma_kernel<NT, SPLIT>), dim3((unsigned)tiles), dim3(256), 0, s, qkv, o, T, D, H, groups, (int)tiles)
         if (dh <= 64) { if (split) EP_LAUNCH(1, true); else EP_LAUNCH(1, false); }
         else { if (split) EP_LAUNCH(2, true); else EP_LAUNCH(2, false); }
 #undef EP_LAUNCH

@@ -79,14 +79,14 @@ struct RowsOut {
 // TOUCH: the workgroups of an XCD bring the weights into its L2 between them (a template argument: as a branch it cost the
 // launches that do not touch 2 % of twelve DeiT layers)
 template <int KS, int BM, int NI, int R, int EPI, bool TOUCH>
-__global__ __launch_bounds__(NW * 64, 2) void gemm_bf16_rows_kernel(const float *x, const float *__restrict__ ln_g,
-                                                                    const float *__restrict__ ln_b, float eps, const uint16_t *W,
-                                                                    const float *bias, void *Cout, int M, int N, int units, int per,
-                                                                    int groups, int panels)
+__global__ __launch_bounds__(NW * 64, 2) void gemm_bf16_rows_kernel(const float *x, const uint16_t *W, int M, int N, int per, int groups,
+                                                                    const float *__restrict__ ln_g, const float *__restrict__ ln_b,
+                                                                    float eps, const float *bias, void *Cout)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
     using S = Rows<KS>;
     constexpr int MI = BM / 16, COLS = 16 * NI;
+    const int units = (N + COLS - 1) / COLS, panels = (M + BM - 1) / BM;
     typedef typename RowsOut<KS, BM, NI, EPI>::Out Out;
     extern __shared__ uint4 lds[];                   // BM rows, then the waves' staging areas
     // consecutive workgroups go to different XCDs: each takes a contiguous run of (panel, group)
@@ -227,7 +227,7 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_bf16_rows_kernel(const float 
 
 template <int KS, int BM, int NI, int R, int EPI, bool TOUCH>
 hipError_t launch_as(const float *x, const float *g, const float *b, float eps, const uint16_t *W, const float *bias, void *C,
-                     int M, int N, int units, int per, int groups, hipStream_t s)
+                     int M, int N, int per, int groups, hipStream_t s)
 {
     auto kern = gemm_bf16_rows_kernel<KS, BM, NI, R, EPI, TOUCH>;
     constexpr size_t smem = RowsOut<KS, BM, NI, EPI>::LDS_BYTES;
@@ -235,8 +235,8 @@ hipError_t launch_as(const float *x, const float *g, const float *b, float eps, 
     const hipError_t e = smem_limit.ensure(reinterpret_cast<const void *>(kern), (int)smem);
     if (e != hipSuccess) return e;
     const int64_t panels = (M + BM - 1) / BM, total = panels * groups;
-    hipLaunchKernelGGL(kern, dim3((unsigned)((total + NUM_XCD - 1) / NUM_XCD * NUM_XCD)), dim3(NW * 64), smem, s, x, g, b, eps, W, bias,
-                       C, M, N, units, per, groups, (int)panels);
+    hipLaunchKernelGGL(kern, dim3((unsigned)((total + NUM_XCD - 1) / NUM_XCD * NUM_XCD)), dim3(NW * 64), smem, s, x, W, M, N, per, groups, g, b,
+                       eps, bias, C);
     return hipGetLastError();
 }
 
@@ -252,8 +252,8 @@ hipError_t launch_rows(const float *x, const float *g, const float *b, float eps
     // not touched again (a layer of ViT-Base on 32 images 133.7 us with both, 130.3 without, ViT-Large on 40 232.6 and 226.5).
     if constexpr (KS > 8)
         if (!touched && groups <= 4 && (int64_t)per * UC * KS * 64 >= 600 * 1024 && M / BM >= NUM_XCD)
-            return launch_as<KS, BM, UC / 16, Rows<KS>::R, EPI, true>(x, g, b, eps, W, bias, C, M, N, units, per, groups, s);
-    return launch_as<KS, BM, UC / 16, Rows<KS>::R, EPI, false>(x, g, b, eps, W, bias, C, M, N, units, per, groups, s);
+            return launch_as<KS, BM, UC / 16, Rows<KS>::R, EPI, true>(x, g, b, eps, W, bias, C, M, N, per, groups, s);
+    return launch_as<KS, BM, UC / 16, Rows<KS>::R, EPI, false>(x, g, b, eps, W, bias, C, M, N, per, groups, s);
 }
 
 // Rows of a panel, 64 or as many as LDS holds, by the modelled microseconds of a launch: rounds of workgroups, each of them
@@ -337,7 +337,7 @@ hipError_t launch_few(const float *x, const float *g, const float *b, float eps,
                       int M, int N, int groups, hipStream_t s)
 {
     const int units = N / 16, per = (units + groups - 1) / groups;
-    return launch_as<KS, FEW_BM, 1, KS, EPI, false>(x, g, b, eps, W, bias, C, M, N, units, per, (units + per - 1) / per, s);
+    return launch_as<KS, FEW_BM, 1, KS, EPI, false>(x, g, b, eps, W, bias, C, M, N, per, (units + per - 1) / per, s);
 }
 
 template <int EPI>

@@ -39,8 +39,7 @@ constexpr int NW = 4, NL = 2;                        // multiplying waves, loade
 
 template <int BM, int BN, int S, int D, int WAVES_PER_SIMD, int EPI, bool RANGES>
 __global__ __launch_bounds__((NW + NL) * 64, WAVES_PER_SIMD) void gemm_bf16_stream_kernel(
-    const uint16_t *A, const uint16_t *W, const float *bias, const float *resid, void *Cout, int M, int N, int K, int k_len,
-    int tiles_m, int tiles_n)
+    int M, int N, int K, int k_len, const uint16_t *A, const uint16_t *W, const float *bias, const float *resid, void *Cout)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
     constexpr int MI = BM / 16, NI = BN / NW / 16;   // 16 x 16 accumulators of a wave
@@ -49,7 +48,7 @@ __global__ __launch_bounds__((NW + NL) * 64, WAVES_PER_SIMD) void gemm_bf16_stre
     static_assert(BM % (8 * NL) == 0 && BN % (16 * NW) == 0 && S >= 2 && (S - 1) * L <= 63, "whole loads, vmcnt is six bits");
     extern __shared__ uint4 lds[];
 
-    const TileOf t = tile_of(tiles_m, tiles_n, EPI == EPI_PARTIAL ? K / k_len : 1);
+    const TileOf t = tile_of((M + BM - 1) / BM, (N + BN - 1) / BN, EPI == EPI_PARTIAL ? K / k_len : 1);
     if (!t.live) return;
     const int m0 = t.m * BM, n0 = t.n * BN, k0 = t.range * k_len, KT = (RANGES ? K : k_len) / BK;
     const int lane = threadIdx.x & 63;
@@ -222,8 +221,8 @@ hipError_t launch_cfg(const uint16_t *A, const uint16_t *W, const float *bias, c
     const hipError_t e = smem_limit.ensure(reinterpret_cast<const void *>(kern), (int)smem);
     if (e != hipSuccess) return e;
     const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN, total = tiles_m * tiles_n * (RANGES ? 1 : splits);
-    hipLaunchKernelGGL(kern, dim3((total + NUM_XCD - 1) / NUM_XCD * NUM_XCD), dim3((NW + NL) * 64), smem, s, A, W, bias, resid, C,
-                       M, N, K, K / splits, tiles_m, tiles_n);
+    hipLaunchKernelGGL(kern, dim3((total + NUM_XCD - 1) / NUM_XCD * NUM_XCD), dim3((NW + NL) * 64), smem, s, M, N, K, K / splits,
+                       A, W, bias, resid, C);
     return hipGetLastError();
 }
 

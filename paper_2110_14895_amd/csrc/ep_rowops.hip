@@ -57,11 +57,10 @@ __device__ inline float4 widen4(uint2 p)
 // passes is done here.  Widening a stage's bf16 input in a launch of its own cost 2 us a stage on 197 rows of 1024
 // and 4 us on 6304.
 template <int LPR, int NV, bool GUARD, int SUM>
-__global__ __launch_bounds__(256) void ln_bf16_kernel(float *__restrict__ x, int64_t ldx, const void *__restrict__ src,
-                                                      const float *__restrict__ bias,
-                                                      const float *__restrict__ g,
-                                                      const float *__restrict__ b, float eps,
-                                                      uint16_t *__restrict__ y, int64_t rows, int D)
+__global__ __launch_bounds__(256) void ln_bf16_kernel(float *__restrict__ x, int ldx, int rows, int D, float eps,
+                                                      const float *__restrict__ g, const float *__restrict__ b,
+                                                      uint16_t *__restrict__ y, const void *__restrict__ src,
+                                                      const float *__restrict__ bias)
 {
     const int lane = threadIdx.x & (LPR - 1);
     const int64_t row = (int64_t)blockIdx.x * (256 / LPR) + threadIdx.x / LPR;
@@ -124,7 +123,7 @@ __global__ __launch_bounds__(256) void residual_sum_kernel(const float *resid, c
                                                            const float *__restrict__ bias, void *out,
                                                            int64_t n4, int d4)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i >= n4) return;
     const float4 v =
         ranges_bias_resid<S>(reinterpret_cast<const float4 *>(part) + i, (size_t)n4,
@@ -138,7 +137,7 @@ __global__ __launch_bounds__(256) void residual_sum_kernel(const float *resid, c
 __global__ __launch_bounds__(256) void f32_to_bf16_kernel(const float *__restrict__ in,
                                                           uint16_t *__restrict__ out, int64_t n4)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i >= n4) return;
     const float4 v = reinterpret_cast<const float4 *>(in)[i];
     uint2 o;
@@ -156,7 +155,7 @@ hipError_t launch_ln(float *x, int64_t ldx, const void *src, int mode, const flo
     const unsigned grid = (unsigned)((rows + RPB - 1) / RPB);
     const bool ragged = D != 4 * LPR * NV;
 #define EP_LN_LAUNCH(GUARD, SUM) \
-    hipLaunchKernelGGL((ln_bf16_kernel<LPR, NV, GUARD, SUM>), dim3(grid), dim3(256), 0, s, x, ldx, src, bias, g, b, eps, y, rows, D)
+    hipLaunchKernelGGL((ln_bf16_kernel<LPR, NV, GUARD, SUM>), dim3(grid), dim3(256), 0, s, x, (int)ldx, (int)rows, D, eps, g, b, y, src, bias)
 #define EP_LN_LAUNCH_SUM(SUM) do { if (ragged) EP_LN_LAUNCH(true, SUM); else EP_LN_LAUNCH(false, SUM); } while (0)
     switch (mode) {
     case WIDEN: EP_LN_LAUNCH_SUM(WIDEN); break;
@@ -176,7 +175,7 @@ hipError_t layernorm_any(float *x, int64_t ldx, const void *src, int mode, const
                          float eps, uint16_t *y, int64_t rows, int D, hipStream_t s)
 {
     if (rows <= 0) return hipSuccess;
-    if (D % 4 != 0 || ldx % 4 != 0 || D <= 0 || D > 8 * 256) return hipErrorInvalidValue;
+    if (D % 4 != 0 || ldx % 4 != 0 || D <= 0 || D > 8 * 256 || rows > 0x7FFFFFFF || ldx > 0x7FFFFFFF) return hipErrorInvalidValue;
     // the fewest lanes to a row that keep it to four float4 a lane
 #define EP_LN(LPR, NV) return launch_ln<LPR, NV>(x, ldx, src, mode, bias, g, b, eps, y, rows, D, s)
     if (D <= 256) {
