@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 typedef float ep_f32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 ep_bf16x2 __attribute__((ext_vector_type(2)));
 
@@ -11,6 +13,27 @@ __device__ inline uint32_t pack_bf16x2(float lo, float hi)
 {
     const ep_f32x2 v = {lo, hi};
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, ep_bf16x2));
+}
+
+// The sum over the LPR lanes of a row, in all of them, as exchanges of lane ^ LPR / 2, ... lane ^ 1 add it up: from 16 lanes on
+// rotations of a row of 16 do what they do, as the values repeat every 8, 4 and 2 lanes by then, and need no LDS (1576
+// x 1152 x 384 in panels of 128 rows, LayerNorm and dense layer, 11.8 -> 11.2 us).
+template <int LPR>
+__device__ inline float lanes_sum(float v)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    static_assert(LPR == 16 || LPR == 32 || LPR == 64, "");
+    if (LPR == 64) v += __shfl_xor(v, 32, 64);
+    if (LPR >= 32) v += __shfl_xor(v, 16, 64);
+    auto add = [&](auto n) __attribute__((always_inline)) {
+        v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x120 + decltype(n)::value, 0xF, 0xF, false));
+    };
+    add(std::integral_constant<int, 8>{});
+    add(std::integral_constant<int, 4>{});
+    add(std::integral_constant<int, 2>{});
+    add(std::integral_constant<int, 1>{});
+#endif
+    return v;
 }
 
 // GELU with the exact (erf) definition, gelu(u) = u/2 * (1 + erf(u / sqrt 2)), evaluated as

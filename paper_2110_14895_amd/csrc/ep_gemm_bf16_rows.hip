@@ -33,27 +33,6 @@ using namespace ep_tile;
 
 constexpr int NW = 8, UC = 32;                       // waves, columns of a wave at a time (16 for few rows)
 
-// The sum over LPR lanes, added up as the exchanges of ln_bf16_kernel add it (lane ^ LPR / 2, ... lane ^ 1): from 16 lanes on
-// rotations of a row of 16 do what they do, as the values repeat every 8, 4 and 2 lanes by then, and need no LDS (1576
-// x 1152 x 384 in panels of 128 rows 11.8 -> 11.2 us).
-template <int LPR>
-__device__ inline float lanes_sum(float v)
-{
-#if defined(__HIP_DEVICE_COMPILE__)
-    static_assert(LPR == 16 || LPR == 32 || LPR == 64, "");
-    if (LPR == 64) v += __shfl_xor(v, 32, 64);
-    if (LPR >= 32) v += __shfl_xor(v, 16, 64);
-    auto add = [&](auto n) EP_INLINE {
-        v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x120 + decltype(n)::value, 0xF, 0xF, false));
-    };
-    add(std::integral_constant<int, 8>{});
-    add(std::integral_constant<int, 4>{});
-    add(std::integral_constant<int, 2>{});
-    add(std::integral_constant<int, 1>{});
-#endif
-    return v;
-}
-
 // K = 32 KS
 template <int KS>
 struct Rows {

@@ -86,9 +86,11 @@ __device__ inline TileOf tile_of(int tiles_m, int tiles_n, int ranges)
     const int group_sz = GROUP_M * tiles_n;
     const int group = lid / group_sz;
     const int first_m = group * GROUP_M;
-    const int rows = min(GROUP_M, tiles_m - first_m);
-    const int in_group = lid - group * group_sz;
-    return {range, first_m + in_group % rows, in_group / rows, true};
+    const uint32_t rows = (uint32_t)min(GROUP_M, tiles_m - first_m), in_group = (uint32_t)(lid - group * group_sz);
+    // in_group / rows, without a division (a division of two numbers is some 20 instructions one behind the other)
+    static_assert(GROUP_M == 4, "one to four rows");
+    const uint32_t n = rows == 3 ? (uint32_t)((uint64_t)in_group * 0x55555556u >> 32) : in_group >> (rows == 4 ? 2 : rows - 1);
+    return {range, first_m + (int)(in_group - n * rows), (int)n, true};
 }
 
 // How a wave's part of the result, MI x NI accumulators of 16 x 16 (operand roles are swapped, MFMA A = weights, so

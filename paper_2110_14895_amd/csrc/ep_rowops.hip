@@ -12,17 +12,6 @@
 
 namespace {
 
-constexpr int WAVE = 64;
-
-// sum over the LPR lanes of a row
-template <int LPR>
-__device__ inline float row_sum(float v)
-{
-#pragma unroll
-    for (int off = LPR / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, WAVE);
-    return v;
-}
-
 // What a dense layer whose K was cut into ranges left to do: ((part[0] + ... + part[splits-1]) + bias) + resid,
 // the ranges in index order (the same association as the epilogue of the uncut layer: sum, bias, residual).
 // The number of ranges is a template argument (2, 4 or 8) so that all loads of a lane are in flight together:
@@ -67,29 +56,41 @@ __global__ __launch_bounds__(256) void ln_bf16_kernel(float *__restrict__ x, int
     if (row >= rows) return;
     float4 *xr = reinterpret_cast<float4 *>(x + row * ldx);
     const int nvec = D >> 2;
-    float4 v[NV];
-    float s = 0.f;
+    float4 v[NV], gg[NV], bb[NV];
+    auto in = [&](int i) { return !GUARD || lane + i * LPR < nvec; };
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
         const int c = lane + i * LPR;
-        if (!GUARD || c < nvec) {
-            if (SUM == WIDEN) {
-                v[i] = widen4(reinterpret_cast<const uint2 *>(static_cast<const uint16_t *>(src) + row * D)[c]);
-                xr[c] = v[i];
-            } else {
-                v[i] = xr[c];
-            }
-            if (SUM > 0) {
-                v[i] = ranges_bias_resid<SUM >= 1 ? SUM : 1>(reinterpret_cast<const float4 *>(static_cast<const float *>(src) + row * D) + c,
-                                                            (size_t)rows * D / 4, reinterpret_cast<const float4 *>(bias)[c], v[i]);
-                xr[c] = v[i];
-            }
-            s += (v[i].x + v[i].y) + (v[i].z + v[i].w);
-        } else {
-            v[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-        }
+        v[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (!in(i)) continue;
+        if (SUM == WIDEN)
+            v[i] = widen4(reinterpret_cast<const uint2 *>(static_cast<const uint16_t *>(src) + row * D)[c]);
+        else
+            v[i] = xr[c];
+        if (SUM > 0)
+            v[i] = ranges_bias_resid<SUM >= 1 ? SUM : 1>(reinterpret_cast<const float4 *>(static_cast<const float *>(src) + row * D) + c,
+                                                        (size_t)rows * D / 4, reinterpret_cast<const float4 *>(bias)[c], v[i]);
     }
-    const float mean = row_sum<LPR>(s) / (float)D;
+    // gain and shift come behind the row and in front of its sums, behind which they would be one more trip to memory; the compiler moves plain
+    // loads there, and buffer loads not past the empty assembly
+#if defined(__HIP_DEVICE_COMPILE__)
+    const __amdgpu_buffer_rsrc_t g_rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(g), 0, D * 4, 0x00020000);
+    const __amdgpu_buffer_rsrc_t b_rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(b), 0, D * 4, 0x00020000);
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {                     // past the row: zeros
+        gg[i] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(g_rs, (lane + i * LPR) * 16, 0, 0));
+        bb[i] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(b_rs, (lane + i * LPR) * 16, 0, 0));
+    }
+#endif
+    asm volatile("" ::: "memory");
+    float s = 0.f;
+#pragma unroll
+    for (int i = 0; i < NV; ++i)
+        if (in(i)) {
+            if (SUM != 0) xr[lane + i * LPR] = v[i];
+            s += (v[i].x + v[i].y) + (v[i].z + v[i].w);
+        }
+    const float mean = lanes_sum<LPR>(s) / (float)D;
     float q = 0.f;
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
@@ -100,18 +101,15 @@ __global__ __launch_bounds__(256) void ln_bf16_kernel(float *__restrict__ x, int
             q += __builtin_fmaf(v[i].x, v[i].x, v[i].y * v[i].y) + __builtin_fmaf(v[i].z, v[i].z, v[i].w * v[i].w);
         }
     }
-    const float inv = 1.0f / sqrtf(row_sum<LPR>(q) / (float)D + eps);
-    const float4 *g4 = reinterpret_cast<const float4 *>(g);
-    const float4 *b4 = reinterpret_cast<const float4 *>(b);
+    const float inv = 1.0f / sqrtf(lanes_sum<LPR>(q) / (float)D + eps);
     uint2 *yr = reinterpret_cast<uint2 *>(y + row * D);
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
         const int c = lane + i * LPR;
         if (!GUARD || c < nvec) {
-            const float4 gg = g4[c], bb = b4[c];
             uint2 o;
-            o.x = pack_bf16x2(__builtin_fmaf(v[i].x * inv, gg.x, bb.x), __builtin_fmaf(v[i].y * inv, gg.y, bb.y));
-            o.y = pack_bf16x2(__builtin_fmaf(v[i].z * inv, gg.z, bb.z), __builtin_fmaf(v[i].w * inv, gg.w, bb.w));
+            o.x = pack_bf16x2(__builtin_fmaf(v[i].x * inv, gg[i].x, bb[i].x), __builtin_fmaf(v[i].y * inv, gg[i].y, bb[i].y));
+            o.y = pack_bf16x2(__builtin_fmaf(v[i].z * inv, gg[i].z, bb[i].z), __builtin_fmaf(v[i].w * inv, gg[i].w, bb[i].w));
             yr[c] = o;
         }
     }
