@@ -273,11 +273,11 @@ RowsPlan plan_many_narrow_rows(int64_t M, int N, int cus)
     return best;
 }
 
-// Up to FEW_ROWS rows of models up to 384 wide in panels of 32, one round of workgroups (a layer inside a stage, microseconds, in panels of 64 rows or two launches
-// and so: DeiT-Small on 1 image 30.2 and 28.3, 4 32.8 and 30.9, 8 37.0 and 34.9, 12 39.7 and 39.3, 16 46.2 and 46.5, 24 51.8 and 61.1; DeiT-Tiny on 1 image 23.1 and
-// 21.1, 8 25.5 and 23.9, 12 26.2 and 25.5, 16 level, 24 31.6 and 34.5), and up to FEW_OUTPUTS of them (384 wide with an MLP of 8 K 3.0 million 35.4 and 34.6, 4.8 level,
-// 7.3 43.9 and 46.0; of 16 K 3.6 36.1 and 35.4, 6.1 41.4 and 42.0; 256 wide of 16 K 2.4 30.2 and 29.2, 4.0 31.5 and 31.8); 320 and 384 wide not past
-// 16 K (384 of 32 K on 1 image 36.9 in two launches and 38.8).
+// First MLP layers (N from 4 K on) of up to FEW_ROWS rows and models up to 384 wide in panels of 32, one round of workgroups.  A layer inside a stage, microseconds, in panels of 64 rows or
+// two launches and so: DeiT-Small on 1 image 30.2 and 28.2, 4 32.9 and 31.2, 8 37.4 and 36.3, 12 40.4 and 39.8; DeiT-Tiny on 1 image 22.4 and 21.8, 8 25.3 and 24.7, 12 26.3
+// and 25.9.  With q|k|v in them too (another 0.4 to 1.4 us of DeiT-Small on 4 and 8 images; it keeps its panels of 64 rows and its two launches) and past the line, 16 images 46.2 and
+// 46.5, 24 51.8 and 61.1, DeiT-Tiny on 16 level, 24 31.6 and 34.5; by outputs, 384 wide with an MLP of 8 K 3.0 million 35.4 and 34.6, 4.8 level, 7.3 43.9 and 46.0, of 16 K 3.6
+// 36.1 and 35.4, 6.1 41.4 and 42.0, 256 wide of 16 K 2.4 30.2 and 29.2, 4.0 31.5 and 31.8.  320 and 384 wide not past 16 K (384 of 32 K on 1 image 36.9 in two launches and 38.8).
 constexpr int FEW_BM = 32, FEW_ROWS = 2560;
 constexpr int64_t FEW_OUTPUTS = 3800000;
 
