@@ -31,7 +31,7 @@ extern "C" int32_t ep_query_f32_ln_route(int64_t M, int32_t N, int32_t K, int32_
 hipError_t ep_f32_attention(const float *qkv, float *o, int B, int T, int D, int H, hipStream_t s);
 
 // ---- bf16 path -------------------------------------------------------------
-// x fp32 (row r at x + r * ldx, on 16 bytes) -> y bf16 [rows, D], fp32 statistics
+// x fp32 (row r at x + r * ldx, on 16 bytes, ldx < 2^31) -> y bf16 [rows, D], fp32 statistics
 hipError_t ep_bf16_layernorm(const float *x, int64_t ldx, const float *g, const float *b, float eps,
                              uint16_t *y, int64_t rows, int D, hipStream_t s);
 // The same after a dense layer whose K was cut into ranges (ep_bf16_gemm_partial): first

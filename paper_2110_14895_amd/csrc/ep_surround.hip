@@ -419,12 +419,12 @@ extern "C" ep_status ep_head_forward(ep_head_t *h, const void *x, int32_t B, voi
     hipStream_t s = (hipStream_t)stream;
     const ep_head_config &c = h->cfg;
     const int D = c.d_model, NC = c.n_classes;
-    // LayerNorm picks the class-token rows out of the tokens; on the bf16 path it reads 16-byte pieces, and tokens that
-    // do not lie on such are gathered first
+    // LayerNorm picks the class-token rows out of the tokens; on the bf16 path it reads 16-byte pieces and takes a stride of
+    // 32 bits, and tokens that do not lie on such pieces, or images of 2^31 elements and more, are gathered first
     const int64_t stride = (int64_t)c.n_tokens * D;
     const float *rows = (const float *)x;
     int64_t ld = stride;
-    if (h->bf16 && !aligned(x, 16)) {
+    if (h->bf16 && (!aligned(x, 16) || stride > INT32_MAX)) {
         const int64_t n = (int64_t)B * D;
         hipLaunchKernelGGL(head_gather_kernel, dim3(blocks_for(n)), dim3(256), 0, s, rows, h->rows, n, c.n_tokens, D);
         EP_HIP(hipGetLastError());

@@ -102,3 +102,22 @@ def test_head_takes_tokens_where_they_lie(bf16, shift):
     torch.cuda.synchronize()
     ref = oracle.head_forward(x, prm["ln_g"], prm["ln_b"], sh.ln_eps, prm["w_head"], prm["b_head"])
     assert H.rel_err(logits.cpu().numpy(), ref) <= (H.TOL_BF16 if bf16 else H.TOL_F32)
+
+
+# class tokens 2^31 floats apart and just below, where LayerNorm itself steps from one to the next; of one image no second row is there
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("T,B", [((1 << 21) - 1, 2), (1 << 21, 2), (1 << 21, 1)])
+def test_head_over_many_tokens(bf16, T, B):
+    import torch
+    d, nc = 1024, 16
+    prm = synth.surround_params(synth.custom_shape("headfar", 1, d, 16, 4 * d, 2), 2, 1, nc, 5, bf16=bf16)
+    head = binding.Head(d, T, nc, 1e-6, binding.EP_BF16 if bf16 else binding.EP_F32, synth.as_param_dtype(prm, bf16), B)
+    rows = (2.0 * synth.normal("head/far", B * d, 1)).reshape(B, 1, d).astype(np.float32)
+    x = torch.empty((B - 1) * T * d + d, dtype=torch.float32, device="cuda")
+    for i in range(B):
+        x[i * T * d:][:d] = torch.from_numpy(rows[i, 0]).cuda()
+    logits = torch.full((B, nc), float("nan"), dtype=torch.float32, device="cuda")
+    head.forward(x, B, logits, torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    ref = oracle.head_forward(rows, prm["ln_g"], prm["ln_b"], 1e-6, prm["w_head"], prm["b_head"])
+    assert H.rel_err(logits.cpu().numpy(), ref) <= (H.TOL_BF16 if bf16 else H.TOL_F32)
