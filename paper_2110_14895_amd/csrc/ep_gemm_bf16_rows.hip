@@ -351,9 +351,8 @@ hipError_t launch_k(const float *x, const float *g, const float *b, float eps, c
 //   K = 768    weights touched, N = 4 K: two launches 64.1 us and one 64.5 at 1773 rows, 68.1 and 65.5 at 1970, 77.2 and 74.9 at 2561; q|k|v 68.1 and 69.9 at 1970
 //              N = 4 K at 2626 rows 1.04 and at 10302 (129 panels of 80 rows: one group, half the chip) 0.97, 8 K 1.06 and 0.93, 12 K 1.03 and 0.89,
 //              8 K at 12625 1.00, 12 K at 11110 0.92, 16 K at 9595 0.98; two launches 139 us and one 147 at 25256 rows of 4 K
-//   K = 1024   weights touched, N = 4 K: 84.3 and 84.3 at 1576 rows, 92.2 and 90.6 at 1773, 94.6 and 92.6 at 1970, 110.1 and 110.3 at 2561, 118 and 118.7 at 2955, 121.2 and 120.3 at
-//              3152, 137.5 and 136.5 at 3940, 166.9 and 162.8 at 4925, 174.1 and 175.3 at 5122
-//              N = 4 K at 5555 rows 0.97, at 6161 1.02; 5 K at 6363 0.96, 8 K 0.94, 12 K 0.89; two launches 85 us and one 106 at 9456 rows of 4 K
+//   K = 1024   N = 3.5 to 5 K at 1576 to 5122 rows, one launch against two: 0.94 to 1.06 with no line between them, 1.01 to 1.05 where attention has
+//              not touched the weights; N = 4 K at 5555 rows 0.97, at 6161 1.02; 5 K at 6363 0.96, 8 K 0.94, 12 K 0.89; two launches 85 us and one 106 at 9456 rows of 4 K
 // At 1024, layers past 2304 columns lose where tiles of 256 rows on their own are one nearly whole round: q|k|v at 6161 rows 0.99 and at 6565
 // 1.02, N = 2.75 K at 5757 0.97 and at 5959 1.01.
 bool one_launch_pays(int64_t M, int N, int K)
@@ -364,9 +363,7 @@ bool one_launch_pays(int64_t M, int N, int K)
     case 320: case 384: return M >= 1024 || (M >= 500 && wide <= 16.0) || few_rows(M, N, K);
     case 512: return M <= 20000 && ((M >= 500 && wide <= 8.0) || (M >= 1000 && wide <= 16.0));
     case 768: return M >= (wide >= 4.0 ? 1900 : 2600) && M <= 20000 && (M <= 10240 ? wide <= 12.0 : wide <= 3.0 || (M > 10752 && wide <= 8.0));
-    case 1024:
-        if (wide == 4.0 && M >= 1750 && M <= 4950) return true;
-        break;
+    case 1024: break;
     default: return false;
     }
     if (M < 5500 || M > 8192 || wide > 4.0 || (wide > 3.5 && M <= 5888)) return false;

@@ -153,6 +153,7 @@ def ln_plan(rows, n, k, epi):
     (499, 1536, 512, 0), (500, 4096, 512, 1), (606, 6144, 512, 0), (1000, 8192, 512, 1), (8080, 16384, 512, 0), (20001, 2048, 512, 0),
     (2599, 2304, 768, 0), (2600, 9216, 768, 1), (9595, 12288, 768, 0), (10240, 3072, 768, 1), (10241, 3072, 768, 0), (10302, 2304, 768, 1),
     (10752, 3072, 768, 0), (10753, 6144, 768, 1), (11110, 9216, 768, 0), (20001, 2304, 768, 0),
+    (1750, 4096, 1024, 0), (3152, 4096, 1024, 0), (4616, 4096, 1024, 0), (4950, 4096, 1024, 0),       # up to 1.05 where weights are not touched
     (5499, 1024, 1024, 0), (5500, 2304, 1024, 1), (5888, 4096, 1024, 0), (5889, 4096, 1024, 1), (6363, 5120, 1024, 0), (8192, 16384, 1024, 0),
     (8193, 3072, 1024, 0), (5632, 3072, 1024, 1), (5633, 3072, 1024, 0), (6400, 3072, 1024, 0), (6401, 3072, 1024, 1), (5888, 2816, 1024, 0),
     (5889, 2816, 1024, 1), (1576, 2304, 576, 0), (6304, 2688, 896, 0),
