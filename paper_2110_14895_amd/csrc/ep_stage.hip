@@ -35,6 +35,20 @@ struct LayerDev {
 
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
+// A layer's parameters in a stage's block: dense weights, q|k|v, projection, second and first MLP layer (so that what attention touches,
+// touch_weights, is one range), then fp32 vectors.  n: elements, off: bytes from where the layer begins; weights are indexed q|k|v,
+// projection, first and second MLP layer
+struct LayerLayout { size_t n_w[4], off_w[4], n_v[8], off_v[8], bytes; };
+
+LayerLayout layer_layout(const ep_vit_config &c)
+{
+    const size_t D = c.d_model, M = c.d_mlp, wsz = c.param_dtype == EP_BF16 ? 2 : 4;
+    LayerLayout l = {{3 * D * D, D * D, M * D, D * M}, {}, {D, D, 3 * D, D, D, D, M, D}, {}, 0};
+    for (int i : {0, 1, 3, 2}) { l.off_w[i] = l.bytes; l.bytes += align_up(l.n_w[i] * wsz, 256); }
+    for (int i = 0; i < 8; ++i) { l.off_v[i] = l.bytes; l.bytes += align_up(l.n_v[i] * 4, 256); }
+    return l;
+}
+
 inline float bf16_bits_to_float(uint16_t h)
 {
     uint32_t u = (uint32_t)h << 16;
@@ -204,7 +218,8 @@ struct PendingSum { int splits; const float *bias; };
 // for 91.4, 14 111.4 for 111.6, 16 118.6 for 117.2, ViT-Huge on 4 82.9 for 85.1, 6 106.4 for 107.2; ViT-Base on 4 images 46.4 for 45.2, 16 84.2 for 79.7.
 //   Dense layers that go with their LayerNorm touch their weights themselves otherwise, which takes them longer: ViT-Large on 28 images 180.7 and 178.6, 40 232.6
 // and 226.5, with its touching left out.
-Touch touch_weights(const ep_vit_config &c, const Workspace &w, int32_t B)
+// ranges: whether the second MLP layer may be cut into ranges of K; ranges_of: of a group, the images of a micro-batch (0: no group)
+Touch touch_weights(const ep_vit_config &c, int32_t B, bool ranges, int32_t ranges_of)
 {
     const int64_t R = (int64_t)B * c.n_tokens, D = c.d_model, M = c.d_mlp;
     const size_t bytes = 2 * (size_t)(4 * D * D + 2 * D * M);       // of a layer
@@ -212,14 +227,27 @@ Touch touch_weights(const ep_vit_config &c, const Workspace &w, int32_t B)
     if (c.param_dtype != EP_BF16 || bytes > TOUCH_MOST_BYTES || rows_per_mb < TOUCH_ROWS_PER_MB) return TOUCH_NONE;
     if (!ep_bf16_attention_touches((int64_t)B * c.n_heads, c.n_tokens)) return TOUCH_NONE;
     if (D <= 768 || ep_bf16_ln_gemm_supported(R, 3 * D, D) || ep_bf16_ln_gemm_supported(R, M, D)) return D <= 768 || rows_per_mb >= TOUCH_ALL_ROWS_PER_MB ? TOUCH_ALL : TOUCH_LONG;
-    const bool group = w.ranges_of != 0;
-    const EpWeightWait fc2 = ep_bf16_gemm_weight_wait(R, D, M, EPI_BIAS_RESID, w.part ? fc2_splits(c, group ? w.ranges_of : B) : 1, group);
+    const bool group = ranges_of != 0;
+    const EpWeightWait fc2 = ep_bf16_gemm_weight_wait(R, D, M, EPI_BIAS_RESID, ranges ? fc2_splits(c, group ? ranges_of : B) : 1, group);
     if (fc2 == EP_WAITS_PERSISTENT || fc2 == EP_WAITS_HIGH) return TOUCH_NONE;
     if (fc2 == EP_WAITS_LARGE && bytes > TOUCH_LARGE_BYTES) return TOUCH_NONE;
     if (fc2 == EP_WAITS_RANGES && rows_per_mb < TOUCH_RANGES_ROWS_PER_MB) return TOUCH_NONE;
     if (fc2 != EP_WAITS_LARGE && ep_bf16_gemm_weight_wait(R, M, D, EPI_BIAS_GELU, 1, group) == EP_WAITS_PERSISTENT) return TOUCH_NONE;
     return rows_per_mb >= TOUCH_ALL_ROWS_PER_MB ? TOUCH_ALL : TOUCH_LONG;
 }
+
+// Where that range ends, in bytes from where the layer begins (it begins with the projection); `next`: a layer follows in the block
+size_t touch_end(const LayerLayout &l, Touch touch, bool next)
+{
+    switch (touch) {
+    case TOUCH_LONG: return l.off_w[3] + l.n_w[3] * 2;
+    case TOUCH_ALL: return next ? l.bytes + l.off_w[0] + l.n_w[0] * 2 : l.off_w[2] + l.n_w[2] * 2;
+    default: return l.off_w[1];
+    }
+}
+
+// What attention of a layer touches: `bytes` from its projection's weights on; before: the layer in front touched this one's first dense layer
+struct TouchHere { Touch what; uint32_t bytes; bool before; };
 
 // One layer on R = B*T rows.  `xin` is the residual stream read by this layer
 // (may be the caller's fp32 input), the layer leaves its result in `xout`.
@@ -228,11 +256,9 @@ Touch touch_weights(const ep_vit_config &c, const Workspace &w, int32_t B)
 // w.x, and *after says so with splits > 1); if null it finishes its output itself.
 // `xin16`: the stage's bf16 input in place of xin (which is w.x then and gets it as fp32).  `xout16`: where the layer
 // may leave its output as bf16 in place of xout; it says so in *narrowed.
-// `touch`: weights that attention touches, of this layer and, if there is one, of the `next` layer's first dense layer; `touched`: so it was
-// for this layer's first one.
 ep_status run_layer(ep_stage *st, const Workspace &w, const LayerDev &L, const float *xin, float *xout, int B,
                     hipStream_t s, const PendingSum *before, PendingSum *after, const uint16_t *xin16 = nullptr,
-                    uint16_t *xout16 = nullptr, bool *narrowed = nullptr, Touch touch = TOUCH_NONE, bool touched = false, const LayerDev *next = nullptr)
+                    uint16_t *xout16 = nullptr, bool *narrowed = nullptr, TouchHere touch = {TOUCH_NONE, 0, false})
 {
     const ep_vit_config &c = st->cfg;
     const int T = c.n_tokens, D = c.d_model, M = c.d_mlp, H = c.n_heads;
@@ -253,22 +279,17 @@ ep_status run_layer(ep_stage *st, const Workspace &w, const LayerDev &L, const f
             EP_TRACED(EP_K_LN1, fuse1 ? hipSuccess : ep_bf16_layernorm(xin, D, L.ln1_g, L.ln1_b, c.ln_eps, a, R, D, s));
         EP_TRACED_GEMM(EP_K_QKV, EP_K_QKV_MAIN,
                        fuse1 ? ep_bf16_ln_gemm(xin, L.ln1_g, L.ln1_b, c.ln_eps, (const uint16_t *)L.w_qkv, L.b_qkv, big, R,
-                                               3 * D, D, EPI_BIAS, touched, ts_.after_main(), s)
+                                               3 * D, D, EPI_BIAS, touch.before, ts_.after_main(), s)
                              : ep_bf16_gemm(a, (const uint16_t *)L.w_qkv, L.b_qkv, nullptr, big, R, 3 * D, D, EPI_BIAS,
                                             one_order, ts_.after_main(), s));
-        // in memory: projection, second MLP layer, first, the next layer's q|k|v
-        const char *touch_end = (const char *)L.w_o;
-        if (touch == TOUCH_LONG) touch_end = (const char *)L.w_fc2 + (size_t)D * M * 2;
-        if (touch == TOUCH_ALL) touch_end = next ? (const char *)next->w_qkv + (size_t)3 * D * D * 2 : (const char *)L.w_fc1 + (size_t)D * M * 2;
-        const EpTouch touched_here = {L.w_o, (uint32_t)(touch_end - (const char *)L.w_o)};
-        EP_TRACED(EP_K_ATTN, ep_bf16_attention(big, a, B, T, D, H, touched_here, s));
+        EP_TRACED(EP_K_ATTN, ep_bf16_attention(big, a, B, T, D, H, EpTouch{L.w_o, touch.bytes}, s));
         EP_TRACED_GEMM(EP_K_PROJ, EP_K_PROJ_MAIN,
                        ep_bf16_gemm(a, (const uint16_t *)L.w_o, L.b_o, xin, w.x, R, D, D, EPI_BIAS_RESID,
                                     one_order, ts_.after_main(), s));
         EP_TRACED(EP_K_LN2, fuse2 ? hipSuccess : ep_bf16_layernorm(w.x, D, L.ln2_g, L.ln2_b, c.ln_eps, a, R, D, s));
         EP_TRACED_GEMM(EP_K_FC1, EP_K_FC1_MAIN,
                        fuse2 ? ep_bf16_ln_gemm(w.x, L.ln2_g, L.ln2_b, c.ln_eps, (const uint16_t *)L.w_fc1, L.b_fc1, big, R, M, D,
-                                               EPI_BIAS_GELU, touch == TOUCH_ALL, ts_.after_main(), s)
+                                               EPI_BIAS_GELU, touch.what == TOUCH_ALL, ts_.after_main(), s)
                              : ep_bf16_gemm(a, (const uint16_t *)L.w_fc1, L.b_fc1, nullptr, big, R, M, D, EPI_BIAS_GELU,
                                             one_order, ts_.after_main(), s));
         int sp = w.part ? fc2_splits(c, w.ranges_of ? w.ranges_of : B) : 1;
@@ -394,15 +415,10 @@ extern "C" ep_status ep_stage_create(const ep_vit_config *cfg, int32_t layer_beg
         if (src != EP_OK) return fail(src);
     }
 
-    // ---- parameter block layout (per layer): dense weights, q|k|v, projection, second and first MLP layer (what attention touches, touch_weights,
-    // is one range), then fp32 vectors
-    const size_t n_w[4] = {(size_t)(3 * D * D), (size_t)(D * D), (size_t)(M * D), (size_t)(D * M)};
-    const size_t n_v[8] = {(size_t)D, (size_t)D, (size_t)(3 * D), (size_t)D,
-                           (size_t)D, (size_t)D, (size_t)M, (size_t)D};
-    size_t layer_bytes = 0;
-    size_t off_w[4], off_v[8];
-    for (int i : {0, 1, 3, 2}) { off_w[i] = layer_bytes; layer_bytes += align_up(n_w[i] * wsz, 256); }
-    for (int i = 0; i < 8; ++i) { off_v[i] = layer_bytes; layer_bytes += align_up(n_v[i] * 4, 256); }
+    const LayerLayout layout = layer_layout(*cfg);
+    const size_t layer_bytes = layout.bytes;
+    const auto &n_w = layout.n_w, &off_w = layout.off_w;
+    const auto &n_v = layout.n_v, &off_v = layout.off_v;
     st->params_bytes = layer_bytes * nl;
     e = hipMalloc((void **)&st->params, st->params_bytes);
     if (e != hipSuccess) {
@@ -504,13 +520,15 @@ ep_status forward_on(ep_stage *st, const Workspace &w, const void *x_in, int32_t
     uint16_t *out16 = c.out_dtype == EP_BF16 ? (uint16_t *)x_out : nullptr;
     bool narrowed = false;
     PendingSum pending = {1, nullptr};
-    const Touch touch = touch_weights(c, w, B);
+    const LayerLayout layout = layer_layout(c);
+    const Touch touch = touch_weights(c, B, w.part != nullptr, w.ranges_of);
     for (int l = 0; l < nl; ++l) {
         const bool last = l + 1 == nl;
         float *dst = (last && c.out_dtype == EP_F32) ? (float *)x_out : w.x;
         const PendingSum before = pending;
+        const TouchHere here = {touch, (uint32_t)(touch_end(layout, touch, !last) - layout.off_w[1]), touch == TOUCH_ALL && l > 0};
         ep_status rc = run_layer(st, w, st->layers[l], cur, dst, B, s, &before, last ? nullptr : &pending,
-                                 l == 0 ? in16 : nullptr, last ? out16 : nullptr, &narrowed, touch, touch == TOUCH_ALL && l > 0, !last ? &st->layers[l + 1] : nullptr);
+                                 l == 0 ? in16 : nullptr, last ? out16 : nullptr, &narrowed, here);
         if (rc != EP_OK) return rc;
         cur = dst;
     }
@@ -519,6 +537,17 @@ ep_status forward_on(ep_stage *st, const Workspace &w, const void *x_in, int32_t
 }
 
 }  // namespace
+
+extern "C" void ep_query_touch_plan(const ep_vit_config *cfg, int32_t batch, int32_t ranges_of, int32_t next, EpTouchPlan *out)
+{
+    const LayerLayout l = layer_layout(*cfg);
+    const Touch touch = touch_weights(*cfg, batch, true, ranges_of);
+    *out = {touch, (int64_t)l.off_w[1], (int64_t)touch_end(l, touch, next != 0), (int64_t)l.bytes, {}, {}};
+    for (int i = 0; i < 4; ++i) {
+        out->weights[i] = (int64_t)l.off_w[i];
+        out->weight_ends[i] = (int64_t)(l.off_w[i] + l.n_w[i] * (cfg->param_dtype == EP_BF16 ? 2 : 4));
+    }
+}
 
 extern "C" ep_status ep_stage_forward(ep_stage_t *st, const void *x_in, int32_t B, void *x_out, void *stream)
 {

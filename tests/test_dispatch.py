@@ -194,3 +194,62 @@ def test_heights_past_their_fit(rows, n, k, epi, shape):
 ])
 def test_one_round_of_wide_residual_tiles(rows, n, k, shape):
     assert str(dense_plan(rows, n, k, EPI_BIAS_RESID)) == shape
+
+
+class TouchPlan(C.Structure):
+    _fields_ = [("kind", C.c_int32), ("begin", C.c_int64), ("end", C.c_int64), ("layer_bytes", C.c_int64), ("weights", C.c_int64 * 4),
+                ("weight_ends", C.c_int64 * 4)]
+
+
+TOUCH_NONE, TOUCH_LONG, TOUCH_ALL = 0, 1, 2
+
+
+def touch_plan(d, heads, m, t, batch, ranges_of=0, next_layer=True, param_dtype=binding.EP_BF16):
+    """Which weights attention touches for the launches behind it, and where they lie from where the layer begins."""
+    cfg = binding.VitConfig(1, d, heads, m, t, 1e-6, param_dtype, param_dtype, binding.EP_F32).c_struct()
+    f, p = binding.lib().ep_query_touch_plan, TouchPlan()
+    f.argtypes, f.restype = [C.c_void_p, C.c_int32, C.c_int32, C.c_int32, C.POINTER(TouchPlan)], None
+    f(C.addressof(cfg), batch, ranges_of, next_layer, C.byref(p))
+    return p
+
+
+# either side of every line of the rule
+@pytest.mark.parametrize("d,heads,m,t,batch,kind", [
+    (768, 12, 3072, 382, 1, TOUCH_NONE), (768, 12, 3072, 383, 1, TOUCH_ALL),                # 27 rows to a MB of weights
+    (1024, 16, 4096, 283, 4, TOUCH_NONE), (1024, 16, 4096, 103, 11, TOUCH_LONG),            # 45 where the second MLP layer is cut into ranges
+    (1280, 16, 5120, 61, 29, TOUCH_NONE), (1280, 16, 5120, 59, 30, TOUCH_LONG), (1280, 16, 5120, 8, 200, TOUCH_LONG),       # uncut: 27 again
+    (1024, 16, 4096, 173, 16, TOUCH_LONG), (1024, 16, 4096, 213, 13, TOUCH_ALL),            # 110
+    (768, 12, 3072, 50, 16, TOUCH_ALL), (832, 13, 3328, 50, 16, TOUCH_LONG),                # up to 768 wide all of them
+    (768, 12, 42112, 100, 41, TOUCH_ALL), (768, 12, 42176, 100, 41, TOUCH_NONE),            # 128 MB
+    (1152, 18, 4608, 1000, 8, TOUCH_ALL), (1216, 19, 4864, 1000, 8, TOUCH_NONE),            # 256 x 192 tiles: 32 MB
+    (1024, 16, 4096, 8, 512, TOUCH_ALL), (1024, 16, 4096, 8, 513, TOUCH_NONE),              # a persistent first MLP layer
+    (1024, 16, 4096, 8, 1750, TOUCH_NONE),                                                  # a persistent second one
+    (128, 2, 256, 288, 140, TOUCH_ALL), (128, 2, 256, 320, 140, TOUCH_NONE), (1024, 16, 4096, 577, 6, TOUCH_NONE),          # ten query waves
+])
+def test_weights_that_attention_touches(d, heads, m, t, batch, kind):
+    assert touch_plan(d, heads, m, t, batch).kind == kind
+    assert touch_plan(d, heads, m, t, batch, param_dtype=binding.EP_F32).kind == TOUCH_NONE
+
+
+# a group of micro-batches uses the K ranges of each, so that other tiles run than for one batch of as many images
+@pytest.mark.parametrize("micro,count,group,alone", [(8, 6, TOUCH_NONE, TOUCH_ALL), (9, 3, TOUCH_ALL, TOUCH_NONE)])
+def test_weights_that_attention_touches_for_a_group(micro, count, group, alone):
+    assert touch_plan(1024, 16, 4096, 197, micro * count, ranges_of=micro).kind == group
+    assert touch_plan(1024, 16, 4096, 197, micro * count).kind == alone
+
+
+# the range holds the weights that it is for, and ends with them: inside the layer where no other follows
+@pytest.mark.parametrize("d,heads,m,t,batch", [(64, 1, 64, 15, 1), (192, 3, 768, 197, 4), (768, 12, 3072, 197, 8), (832, 13, 3328, 50, 16),
+                                               (1024, 16, 4096, 197, 8), (1024, 16, 4096, 197, 16), (1024, 16, 4096, 197, 1)])
+@pytest.mark.parametrize("next_layer", [False, True])
+def test_range_of_touched_weights(d, heads, m, t, batch, next_layer):
+    p = touch_plan(d, heads, m, t, batch, next_layer=next_layer)
+    qkv, proj, fc1, fc2 = zip(p.weights, p.weight_ends)
+    for (begin, end), size in zip((qkv, proj, fc1, fc2), (3 * d * d, d * d, d * m, d * m)):
+        assert 0 <= begin and end - begin == 2 * size and end <= p.layer_bytes
+    inside = {TOUCH_NONE: [], TOUCH_LONG: [proj, fc2], TOUCH_ALL: [proj, fc2, fc1]}[p.kind]
+    if p.kind == TOUCH_ALL and next_layer:
+        inside.append((p.layer_bytes + qkv[0], p.layer_bytes + qkv[1]))
+    assert p.begin == proj[0] and p.end == max([e for _, e in inside], default=p.begin)
+    assert all(p.begin <= b for b, _ in inside) and (next_layer or p.end <= p.layer_bytes)
+    assert (1 << 30) > p.end - p.begin                                   # offsets of touched lines are 32-bit
