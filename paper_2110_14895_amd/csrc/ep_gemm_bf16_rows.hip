@@ -351,11 +351,25 @@ hipError_t launch_k(const float *x, const float *g, const float *b, float eps, c
 //   K = 768    weights touched, N = 4 K: two launches 64.1 us and one 64.5 at 1773 rows, 68.1 and 65.5 at 1970, 77.2 and 74.9 at 2561; q|k|v 68.1 and 69.9 at 1970
 //              N = 4 K at 2626 rows 1.04 and at 10302 (129 panels of 80 rows: one group, half the chip) 0.97, 8 K 1.06 and 0.93, 12 K 1.03 and 0.89,
 //              8 K at 12625 1.00, 12 K at 11110 0.92, 16 K at 9595 0.98; two launches 139 us and one 147 at 25256 rows of 4 K
-//   K = 1024   N = 3.5 to 5 K at 1576 to 5122 rows, one launch against two: 0.94 to 1.06 with no line between them, 1.01 to 1.05 where attention has
-//              not touched the weights; N = 4 K at 5555 rows 0.97, at 6161 1.02; 5 K at 6363 0.96, 8 K 0.94, 12 K 0.89; two launches 85 us and one 106 at 9456 rows of 4 K
+//   K = 1024   N = 4 K at 5555 rows 0.97, at 6161 1.02; 5 K at 6363 0.96, 8 K 0.94, 12 K 0.89; two launches 85 us and one 106 at 9456 rows of 4 K
 // At 1024, layers past 2304 columns lose where tiles of 256 rows on their own are one nearly whole round: q|k|v at 6161 rows 0.99 and at 6565
 // 1.02, N = 2.75 K at 5757 0.97 and at 5959 1.01.
-bool one_launch_pays(int64_t M, int N, int K)
+// Below 5500 rows of 1024 the one launch takes 0.92 to 1.08 of the time of two with no line in rows, but for a first MLP layer whose weights
+// attention has touched and whose own launch would be one round of 256 x 256 tiles that fills more than three quarters and up to 13 sixteenths
+// of the units: 193 to 208 tiles (many others of so many run as 256 x 192 or 192 x 256).  A layer's time, one launch over two, N = 3.06 to 4.25 K,
+// 2885 to 4050 rows, weights resident and from memory: 0.963 to 0.988 at 28 points, 0.98 to 1.00 at another three, 3300 rows (ViT-Large on 16
+// images 107.5 -> 105.2 us and 111.3 -> 108.4).  210 to 225 tiles 0.975 to 1.007, from there on 0.98 to 1.03; tiles of 192 rows or columns 0.99
+// to 1.02.  Where attention has not touched the weights 1.01 to 1.05 (6 to 8 images of 577 tokens).
+bool tiles_leave_units(int64_t M, int N, int K)
+{
+    const int64_t cus = ep_bf16_gemm_persistent_workgroups(), tiles = (M + 255) / 256 * ((N + 255) / 256);
+    if (4 * tiles <= 3 * cus || 16 * tiles > 13 * cus) return false;
+    EpDensePlan p;
+    ep_query_dense_plan(M, N, K, EPI_BIAS_GELU, &p);
+    return !p.persistent && p.bm == 256 && p.bn == 256;
+}
+
+bool one_launch_pays(int64_t M, int N, int K, bool touched_mlp)
 {
     const double wide = (double)N / K;
     switch (K) {
@@ -363,7 +377,9 @@ bool one_launch_pays(int64_t M, int N, int K)
     case 320: case 384: return M >= 1024 || (M >= 500 && wide <= 16.0) || few_rows(M, N, K);
     case 512: return M <= 20000 && ((M >= 500 && wide <= 8.0) || (M >= 1000 && wide <= 16.0));
     case 768: return M >= (wide >= 4.0 ? 1900 : 2600) && M <= 20000 && (M <= 10240 ? wide <= 12.0 : wide <= 3.0 || (M > 10752 && wide <= 8.0));
-    case 1024: break;
+    case 1024:
+        if (touched_mlp && M < 5500 && wide > 3.0 && wide <= 4.25 && tiles_leave_units(M, N, K)) return true;
+        break;
     default: return false;
     }
     if (M < 5500 || M > 8192 || wide > 4.0 || (wide > 3.5 && M <= 5888)) return false;
@@ -377,24 +393,26 @@ bool one_launch_pays(int64_t M, int N, int K)
 
 }  // namespace
 
-bool ep_bf16_ln_gemm_supported(int64_t M, int N, int K)
+bool ep_bf16_ln_gemm_supported(int64_t M, int N, int K, bool touched_mlp)
 {
-    return one_launch_pays(M, N, K) && N % 16 == 0 && N < MAX_TILE_N && M * N < (1ll << 31) && (int64_t)N * K * 2 < 0x7FFFFFF0ll;
+    return one_launch_pays(M, N, K, touched_mlp) && N % 16 == 0 && N < MAX_TILE_N && M * N < (1ll << 31) && (int64_t)N * K * 2 < 0x7FFFFFF0ll;
 }
 
 extern "C" int32_t ep_query_ln_gemm_plan(int64_t M, int32_t N, int32_t K, int32_t epi, int32_t cus, int32_t *groups)
 {
-    if (M <= 0 || N <= 0 || !ep_bf16_ln_gemm_supported(M, N, K)) return 0;
+    if (M <= 0 || N <= 0 || !ep_bf16_ln_gemm_supported(M, N, K, false)) return 0;
     const RowsPlan p = plan_rows(M, N, K, epi == EPI_BIAS_GELU, cus);
     *groups = p.groups;
     return p.bm;
 }
 
+extern "C" int32_t ep_query_ln_gemm_touched_mlp(int64_t M, int32_t N, int32_t K) { return ep_bf16_ln_gemm_supported(M, N, K, true); }
+
 hipError_t ep_bf16_ln_gemm(const float *x, const float *g, const float *b, float eps, const uint16_t *W, const float *bias, void *C,
                            int64_t M, int N, int K, int epi, bool touched, hipEvent_t after_main, hipStream_t s)
 {
     if (M <= 0 || N <= 0) return hipSuccess;
-    if (!ep_bf16_ln_gemm_supported(M, N, K) || (epi != EPI_BIAS && epi != EPI_BIAS_GELU)) return hipErrorInvalidValue;
+    if (!ep_bf16_ln_gemm_supported(M, N, K, touched && epi == EPI_BIAS_GELU) || (epi != EPI_BIAS && epi != EPI_BIAS_GELU)) return hipErrorInvalidValue;
     int cus = 0;
     hipError_t e = ep_device_cu_count(&cus);
     if (e != hipSuccess) return e;

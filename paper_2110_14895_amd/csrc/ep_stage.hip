@@ -269,7 +269,7 @@ ep_status run_layer(ep_stage *st, const Workspace &w, const LayerDev &L, const f
         const bool one_order = w.ranges_of != 0;                // several micro-batches: each as it would be alone
         // a LayerNorm done inside the dense layer behind it leaves its own bracket empty
         const bool plain1 = !xin16 && !(before && before->splits > 1);
-        const bool fuse1 = plain1 && ep_bf16_ln_gemm_supported(R, 3 * D, D), fuse2 = ep_bf16_ln_gemm_supported(R, M, D);
+        const bool fuse1 = plain1 && ep_bf16_ln_gemm_supported(R, 3 * D, D), fuse2 = ep_bf16_ln_gemm_supported(R, M, D, touch.what == TOUCH_ALL);
         if (xin16)
             EP_TRACED(EP_K_LN1, ep_bf16_layernorm_widen(xin16, w.x, L.ln1_g, L.ln1_b, c.ln_eps, a, R, D, s));
         else if (!plain1)

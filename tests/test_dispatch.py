@@ -162,6 +162,25 @@ def test_layernorm_and_dense_layer_in_one_launch(rows, n, k, one):
     assert all((ln_plan(rows, n, k, epi)[0] > 0) == one for epi in (EPI_BIAS, EPI_BIAS_GELU))
 
 
+# A first MLP layer at 1024 wide whose weights attention has touched: in one launch with its LayerNorm where its own would be one round of
+# 256 x 256 tiles on 193 to 208 of 256 units; nothing else moves
+@pytest.mark.parametrize("rows,n,one", [
+    (3072, 4096, 0), (3073, 4096, 1), (3152, 4096, 1), (3328, 4096, 1), (3329, 4096, 0), (2880, 4352, 0), (2881, 4160, 1), (3072, 4352, 1), (3073, 4352, 0),
+    (2955, 4416, 0), (3840, 3136, 0), (3841, 3136, 1), (4096, 3136, 1), (4097, 3136, 0), (4000, 3072, 0), (3264, 3840, 0), (3265, 3840, 1), (3152, 3840, 0),
+    (4616, 4096, 0), (5888, 4096, 0), (5889, 4096, 1),
+])
+def test_layernorm_and_touched_first_mlp_layer(rows, n, one):
+    f = binding.lib().ep_query_ln_gemm_touched_mlp
+    f.argtypes, f.restype = [C.c_int64, C.c_int32, C.c_int32], C.c_int32
+    assert f(rows, n, 1024) == one
+    if rows < 5500:
+        assert ln_plan(rows, n, 1024, EPI_BIAS_GELU)[0] == 0
+        p = dense_plan(rows, n, 1024, EPI_BIAS_GELU)
+        assert not one or (p.m_main == rows and str(p) == "256x256")             # no rows that add up in another order
+    for k in (320, 512, 768):
+        assert f(rows, n, k) == (ln_plan(rows, n, k, EPI_BIAS_GELU)[0] > 0)
+
+
 # Narrow models of many rows: several column groups in two rounds where one round of 128-row panels leaves units without work
 @pytest.mark.parametrize("rows,n,k,epi,plan", [
     (16383, 1536, 384, EPI_BIAS_GELU, (64, 1)), (20037, 1536, 384, EPI_BIAS_GELU, (128, 3)), (21814, 2048, 256, EPI_BIAS_GELU, (64, 2)),

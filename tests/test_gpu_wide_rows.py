@@ -2,13 +2,15 @@
 few rows: every height of a panel, with a last panel that is rarely whole and column groups of less than a set of columns up to
 all of them.  Bit for bit against the two launches, with the height asked of the library, and against the oracle (the tolerance is the
 bf16 path's)."""
+import ctypes as C
+
 import numpy as np
 import pytest
 
 import oracle
-from paper_2110_14895_amd import synth
+from paper_2110_14895_amd import binding, synth
 from tests import harness as H
-from tests.test_dispatch import EPI_BIAS, EPI_BIAS_GELU, dense_plan, ln_plan
+from tests.test_dispatch import EPI_BIAS, EPI_BIAS_GELU, TOUCH_ALL, dense_plan, ln_plan, touch_plan
 
 pytestmark = pytest.mark.gpu
 
@@ -47,6 +49,25 @@ def test_bits_of_two_launches_with_gelu(T, D, Hh, M, few, B):
     st = H.make_stage(sh, p, 0, 1, B, bf16=True)
     one = H.run_stage(st, x)
     for i in range(0, B, few):
+        np.testing.assert_array_equal(H.run_stage(st, x[i:i + few]), one[i:i + few])
+
+
+# at 1024 wide below 5500 rows only where attention touches the weights
+@pytest.mark.parametrize("T,D,Hh,M,few,B", [(197, 1024, 16, 4096, 4, 16), (577, 1024, 16, 4352, 1, 5), (50, 1024, 16, 3136, 16, 77)])
+def test_bits_of_two_launches_behind_touching(T, D, Hh, M, few, B):
+    touched = binding.lib().ep_query_ln_gemm_touched_mlp
+    touched.argtypes, touched.restype = [C.c_int64, C.c_int32, C.c_int32], C.c_int32
+    assert touch_plan(D, Hh, M, T, B).kind == TOUCH_ALL and touched(T * B, M, D) and not touched(T * few, M, D)
+    assert dense_plan(T * few, M, D, EPI_BIAS_GELU).m_main == T * few
+    sh = synth.custom_shape(f"touched_{T}_{D}", 1, D, Hh, M, T)
+    p = synth.layer_params(sh, 0, bf16=True, randomize_affine=True, w_std=0.05)
+    # the second MLP layer passes hidden units on, one to a column: its sums are exact however K is cut
+    p["w_fc2"] = np.zeros_like(p["w_fc2"])
+    p["w_fc2"][np.arange(D), np.linspace(0, M - 1, D).astype(int)] = 1.0
+    x = synth.activations(sh, B, bf16=True)
+    st = H.make_stage(sh, [p], 0, 1, B, bf16=True)
+    one = H.run_stage(st, x)
+    for i in range(0, B - few + 1, few):
         np.testing.assert_array_equal(H.run_stage(st, x[i:i + few]), one[i:i + few])
 
 
