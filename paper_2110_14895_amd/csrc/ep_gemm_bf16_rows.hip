@@ -273,11 +273,13 @@ RowsPlan plan_many_narrow_rows(int64_t M, int N, int cus)
     return best;
 }
 
-// First MLP layers (N from 4 K on) of up to FEW_ROWS rows and models up to 384 wide in panels of 32, one round of workgroups.  A layer inside a stage, microseconds, in panels of 64 rows or
-// two launches and so: DeiT-Small on 1 image 30.2 and 28.2, 4 32.9 and 31.2, 8 37.4 and 36.3, 12 40.4 and 39.8; DeiT-Tiny on 1 image 22.4 and 21.8, 8 25.3 and 24.7, 12 26.3
-// and 25.9.  With q|k|v in them too (another 0.4 to 1.4 us of DeiT-Small on 4 and 8 images; it keeps its panels of 64 rows and its two launches) and past the line, 16 images 46.2 and
-// 46.5, 24 51.8 and 61.1, DeiT-Tiny on 16 level, 24 31.6 and 34.5; by outputs, 384 wide with an MLP of 8 K 3.0 million 35.4 and 34.6, 4.8 level, 7.3 43.9 and 46.0, of 16 K 3.6
-// 36.1 and 35.4, 6.1 41.4 and 42.0, 256 wide of 16 K 2.4 30.2 and 29.2, 4.0 31.5 and 31.8.  320 and 384 wide not past 16 K (384 of 32 K on 1 image 36.9 in two launches and 38.8).
+// First MLP layers (the ones with GELU, N from 4 K on) of up to FEW_ROWS rows and models up to 384 wide in panels of 32, one round of workgroups.
+// A layer inside a stage, microseconds, in panels of 64 rows or two launches and so: DeiT-Small on 1 image 30.2 and 28.2, 4 32.9 and 31.2, 8 37.4
+// and 36.3, 12 40.4 and 39.8; DeiT-Tiny on 1 image 22.4 and 21.8, 8 25.3 and 24.7, 12 26.3 and 25.9.  With q|k|v in them too another 0.4 to 1.4 us of
+// DeiT-Small on 4 and 8 images; it keeps its panels of 64 rows and its two launches.  Past the line, 16 images 46.2 and 46.5, 24 51.8 and 61.1,
+// DeiT-Tiny on 16 level, 24 31.6 and 34.5; by outputs, 384 wide with an MLP of 8 K 3.0 million 35.4 and 34.6, 4.8 level, 7.3 43.9 and 46.0, of 16 K
+// 3.6 36.1 and 35.4, 6.1 41.4 and 42.0, 256 wide of 16 K 2.4 30.2 and 29.2, 4.0 31.5 and 31.8.  320 and 384 wide not past 16 K (384 of 32 K on 1
+// image 36.9 in two launches and 38.8).  Narrower first layers keep what they had, though 1 to 3.5 K on 197 to 2364 rows would take 0.92 to 1.00 of it.
 constexpr int FEW_BM = 32, FEW_ROWS = 2560;
 constexpr int64_t FEW_OUTPUTS = 3800000;
 
@@ -288,7 +290,7 @@ bool few_rows(int64_t M, int N, int K)
 
 RowsPlan plan_rows(int64_t M, int N, int K, bool gelu, int cus)
 {
-    if (few_rows(M, N, K)) {
+    if (gelu && few_rows(M, N, K)) {
         const int64_t n = cus / ((M + FEW_BM - 1) / FEW_BM), units = N / 16;
         return {FEW_BM, (int)(n < 1 ? 1 : n < units ? n : units), 0.0};
     }
@@ -309,8 +311,8 @@ RowsPlan plan_rows(int64_t M, int N, int K, bool gelu, int cus)
     return best;
 }
 
-// Few rows of narrow models: panels of 32 rows, and 16 columns to a wave, so that a workgroup has at most a set or two of them, whose weights
-// are under way, all K of them, while the rows come in.
+// Few rows of narrow models: panels of 32 rows, and 16 columns to a wave, so that a wave has few sets of them (one or two of the named models, up
+// to five: 257 x 14784 x 256).  The weights of the first, all K of them, are under way while the rows come in.
 template <int KS, int EPI>
 hipError_t launch_few(const float *x, const float *g, const float *b, float eps, const uint16_t *W, const float *bias, void *C,
                       int M, int N, int groups, hipStream_t s)
@@ -325,7 +327,7 @@ hipError_t launch_k(const float *x, const float *g, const float *b, float eps, c
 {
     const RowsPlan p = plan_rows(M, N, K, EPI == EPI_BIAS_GELU, cus);
 #define EP_FEW(KS) if (K == KS * 32 && p.bm == FEW_BM) return launch_few<KS, EPI>(x, g, b, eps, W, bias, C, M, N, p.groups, s)
-    EP_FEW(2); EP_FEW(4); EP_FEW(6); EP_FEW(8); EP_FEW(10); EP_FEW(12);
+    if constexpr (EPI == EPI_BIAS_GELU) { EP_FEW(2); EP_FEW(4); EP_FEW(6); EP_FEW(8); EP_FEW(10); EP_FEW(12); }
 #undef EP_FEW
 #define EP_ROWS(KS, BM) \
     if (K == KS * 32 && p.bm == BM) return launch_rows<KS, BM, EPI>(x, g, b, eps, W, bias, C, M, N, p.groups, touched, s)
@@ -369,16 +371,16 @@ bool tiles_leave_units(int64_t M, int N, int K)
     return !p.persistent && p.bm == 256 && p.bn == 256;
 }
 
-bool one_launch_pays(int64_t M, int N, int K, bool touched_mlp)
+bool one_launch_pays(int64_t M, int N, int K, bool gelu, bool touched)
 {
     const double wide = (double)N / K;
     switch (K) {
     case 64: case 128: case 192: case 256: return true;
-    case 320: case 384: return M >= 1024 || (M >= 500 && wide <= 16.0) || few_rows(M, N, K);
+    case 320: case 384: return M >= 1024 || (M >= 500 && wide <= 16.0) || (gelu && few_rows(M, N, K));
     case 512: return M <= 20000 && ((M >= 500 && wide <= 8.0) || (M >= 1000 && wide <= 16.0));
     case 768: return M >= (wide >= 4.0 ? 1900 : 2600) && M <= 20000 && (M <= 10240 ? wide <= 12.0 : wide <= 3.0 || (M > 10752 && wide <= 8.0));
     case 1024:
-        if (touched_mlp && M < 5500 && wide > 3.0 && wide <= 4.25 && tiles_leave_units(M, N, K)) return true;
+        if (gelu && touched && M < 5500 && wide > 3.0 && wide <= 4.25 && tiles_leave_units(M, N, K)) return true;
         break;
     default: return false;
     }
@@ -393,26 +395,26 @@ bool one_launch_pays(int64_t M, int N, int K, bool touched_mlp)
 
 }  // namespace
 
-bool ep_bf16_ln_gemm_supported(int64_t M, int N, int K, bool touched_mlp)
+bool ep_bf16_ln_gemm_supported(int64_t M, int N, int K, int epi, bool touched)
 {
-    return one_launch_pays(M, N, K, touched_mlp) && N % 16 == 0 && N < MAX_TILE_N && M * N < (1ll << 31) && (int64_t)N * K * 2 < 0x7FFFFFF0ll;
+    return one_launch_pays(M, N, K, epi == EPI_BIAS_GELU, touched) && N % 16 == 0 && N < MAX_TILE_N && M * N < (1ll << 31) && (int64_t)N * K * 2 < 0x7FFFFFF0ll;
 }
 
 extern "C" int32_t ep_query_ln_gemm_plan(int64_t M, int32_t N, int32_t K, int32_t epi, int32_t cus, int32_t *groups)
 {
-    if (M <= 0 || N <= 0 || !ep_bf16_ln_gemm_supported(M, N, K, false)) return 0;
+    if (M <= 0 || N <= 0 || !ep_bf16_ln_gemm_supported(M, N, K, epi, false)) return 0;
     const RowsPlan p = plan_rows(M, N, K, epi == EPI_BIAS_GELU, cus);
     *groups = p.groups;
     return p.bm;
 }
 
-extern "C" int32_t ep_query_ln_gemm_touched_mlp(int64_t M, int32_t N, int32_t K) { return ep_bf16_ln_gemm_supported(M, N, K, true); }
+extern "C" int32_t ep_query_ln_gemm_touched_mlp(int64_t M, int32_t N, int32_t K) { return ep_bf16_ln_gemm_supported(M, N, K, EPI_BIAS_GELU, true); }
 
 hipError_t ep_bf16_ln_gemm(const float *x, const float *g, const float *b, float eps, const uint16_t *W, const float *bias, void *C,
                            int64_t M, int N, int K, int epi, bool touched, hipEvent_t after_main, hipStream_t s)
 {
     if (M <= 0 || N <= 0) return hipSuccess;
-    if (!ep_bf16_ln_gemm_supported(M, N, K, touched && epi == EPI_BIAS_GELU) || (epi != EPI_BIAS && epi != EPI_BIAS_GELU)) return hipErrorInvalidValue;
+    if (!ep_bf16_ln_gemm_supported(M, N, K, epi, touched) || (epi != EPI_BIAS && epi != EPI_BIAS_GELU)) return hipErrorInvalidValue;
     int cus = 0;
     hipError_t e = ep_device_cu_count(&cus);
     if (e != hipSuccess) return e;

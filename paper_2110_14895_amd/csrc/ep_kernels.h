@@ -104,9 +104,9 @@ extern "C" void ep_query_dense_plan_one_order(int64_t M, int32_t N, int32_t K, i
 
 // LayerNorm of x and the dense layer behind it (bias, or bias and GELU) in one launch, where that pays (ep_gemm_bf16_rows.hip):
 // the bits of ep_bf16_layernorm and ep_bf16_gemm.  touched: the weights have been brought into the memory-side cache, which at 1024 wide
-// decides for a first MLP layer (touched_mlp) on some counts of rows
-bool ep_bf16_ln_gemm_supported(int64_t M, int N, int K, bool touched_mlp = false);
-extern "C" int32_t ep_query_ln_gemm_touched_mlp(int64_t M, int32_t N, int32_t K);      // the same with touched_mlp, for tests
+// decides for a first MLP layer (with GELU) on some counts of rows
+bool ep_bf16_ln_gemm_supported(int64_t M, int N, int K, int epi, bool touched);
+extern "C" int32_t ep_query_ln_gemm_touched_mlp(int64_t M, int32_t N, int32_t K);      // for tests: with GELU, touched
 // rows of a panel and the column groups that share one, on `cus` compute units; 0: two launches.  For tests
 extern "C" int32_t ep_query_ln_gemm_plan(int64_t M, int32_t N, int32_t K, int32_t epi, int32_t cus, int32_t *groups);
 hipError_t ep_bf16_ln_gemm(const float *x, const float *g, const float *b, float eps, const uint16_t *W, const float *bias, void *C,

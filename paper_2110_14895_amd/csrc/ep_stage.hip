@@ -226,7 +226,7 @@ Touch touch_weights(const ep_vit_config &c, int32_t B, bool ranges, int32_t rang
     const double rows_per_mb = (double)R * 1e6 / (double)bytes;
     if (c.param_dtype != EP_BF16 || bytes > TOUCH_MOST_BYTES || rows_per_mb < TOUCH_ROWS_PER_MB) return TOUCH_NONE;
     if (!ep_bf16_attention_touches((int64_t)B * c.n_heads, c.n_tokens)) return TOUCH_NONE;
-    if (D <= 768 || ep_bf16_ln_gemm_supported(R, 3 * D, D) || ep_bf16_ln_gemm_supported(R, M, D)) return D <= 768 || rows_per_mb >= TOUCH_ALL_ROWS_PER_MB ? TOUCH_ALL : TOUCH_LONG;
+    if (D <= 768 || ep_bf16_ln_gemm_supported(R, 3 * D, D, EPI_BIAS, false) || ep_bf16_ln_gemm_supported(R, M, D, EPI_BIAS_GELU, false)) return D <= 768 || rows_per_mb >= TOUCH_ALL_ROWS_PER_MB ? TOUCH_ALL : TOUCH_LONG;
     const bool group = ranges_of != 0;
     const EpWeightWait fc2 = ep_bf16_gemm_weight_wait(R, D, M, EPI_BIAS_RESID, ranges ? fc2_splits(c, group ? ranges_of : B) : 1, group);
     if (fc2 == EP_WAITS_PERSISTENT || fc2 == EP_WAITS_HIGH) return TOUCH_NONE;
@@ -269,7 +269,7 @@ ep_status run_layer(ep_stage *st, const Workspace &w, const LayerDev &L, const f
         const bool one_order = w.ranges_of != 0;                // several micro-batches: each as it would be alone
         // a LayerNorm done inside the dense layer behind it leaves its own bracket empty
         const bool plain1 = !xin16 && !(before && before->splits > 1);
-        const bool fuse1 = plain1 && ep_bf16_ln_gemm_supported(R, 3 * D, D), fuse2 = ep_bf16_ln_gemm_supported(R, M, D, touch.what == TOUCH_ALL);
+        const bool fuse1 = plain1 && ep_bf16_ln_gemm_supported(R, 3 * D, D, EPI_BIAS, false), fuse2 = ep_bf16_ln_gemm_supported(R, M, D, EPI_BIAS_GELU, touch.what == TOUCH_ALL);
         if (xin16)
             EP_TRACED(EP_K_LN1, ep_bf16_layernorm_widen(xin16, w.x, L.ln1_g, L.ln1_b, c.ln_eps, a, R, D, s));
         else if (!plain1)
@@ -622,9 +622,9 @@ bool has_narrow_rows(const ep_vit_config &c, int32_t micro)
     // MLP layer, in one launch with LayerNorm between two numbers of rows only, which is not asked here: 33, 42 and 55 images of
     // ViT-Base are not grouped though neither launch has narrow tiles
     const bool narrow = D <= 384;
-    const bool qkv = !narrow || !ep_bf16_ln_gemm_supported(R, 3 * D, D) || c.in_dtype == EP_BF16 || sp > 1;
+    const bool qkv = !narrow || !ep_bf16_ln_gemm_supported(R, 3 * D, D, EPI_BIAS, false) || c.in_dtype == EP_BF16 || sp > 1;
     return (qkv && ep_bf16_gemm_narrow_rows(R, 3 * D, D, EPI_BIAS) > 0) || ep_bf16_gemm_narrow_rows(R, D, D, EPI_BIAS_RESID) > 0 ||
-           (!(narrow && ep_bf16_ln_gemm_supported(R, M, D)) && ep_bf16_gemm_narrow_rows(R, M, D, EPI_BIAS_GELU) > 0) ||
+           (!(narrow && ep_bf16_ln_gemm_supported(R, M, D, EPI_BIAS_GELU, false)) && ep_bf16_gemm_narrow_rows(R, M, D, EPI_BIAS_GELU) > 0) ||
            (sp == 1 && ep_bf16_gemm_narrow_rows(R, D, M, EPI_BIAS_RESID) > 0);
 }
 

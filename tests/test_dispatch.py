@@ -162,6 +162,17 @@ def test_layernorm_and_dense_layer_in_one_launch(rows, n, k, one):
     assert all((ln_plan(rows, n, k, epi)[0] > 0) == one for epi in (EPI_BIAS, EPI_BIAS_GELU))
 
 
+# Panels of 32 rows: first MLP layers (with GELU) of narrow models on few rows and no other layer
+@pytest.mark.parametrize("rows,n,k,few", [
+    (2560, 768, 192, 1), (2561, 768, 192, 0), (1, 256, 64, 1), (1, 240, 64, 0), (2473, 1536, 384, 1), (2474, 1536, 384, 0),     # 2560 rows, 4 K, 3.8 million outputs
+    (197, 6144, 384, 1), (197, 6160, 384, 0), (17, 5120, 320, 1), (17, 5136, 320, 0), (17, 16384, 256, 1),                      # 16 K past 256 wide
+    (197, 2048, 512, 0), (257, 14784, 256, 1), (257, 14800, 256, 0),
+])
+def test_panels_of_few_rows(rows, n, k, few):
+    assert (ln_plan(rows, n, k, EPI_BIAS_GELU)[0] == 32) == few
+    assert ln_plan(rows, n, k, EPI_BIAS)[0] != 32
+
+
 # A first MLP layer at 1024 wide whose weights attention has touched: in one launch with its LayerNorm where its own would be one round of
 # 256 x 256 tiles on 193 to 208 of 256 units; nothing else moves
 @pytest.mark.parametrize("rows,n,one", [

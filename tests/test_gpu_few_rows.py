@@ -7,7 +7,7 @@ import pytest
 import oracle
 from paper_2110_14895_amd import synth
 from tests import harness as H
-from tests.test_dispatch import EPI_BIAS, EPI_BIAS_GELU, ln_plan
+from tests.test_dispatch import EPI_BIAS_GELU, ln_plan
 
 pytestmark = pytest.mark.gpu
 
@@ -28,7 +28,6 @@ def panel_rows(rows, n, k):
 ])
 def test_the_same_bits_in_other_panels(T, D, Hh, M, few, B):
     assert panel_rows(T * few, M, D) == 32 < panel_rows(T * B, M, D)
-    assert ln_plan(T * few, M, D, EPI_BIAS)[0] == 32
     sh = synth.custom_shape(f"few_{T}_{D}", 1, D, Hh, M, T)
     p = synth.layer_params(sh, 0, bf16=True, randomize_affine=True, w_std=0.05)
     # out of the first MLP layer as it is: the second one passes hidden units on, one to a column, so that its sum is exact
