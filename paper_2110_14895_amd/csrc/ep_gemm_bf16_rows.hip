@@ -350,7 +350,10 @@ hipError_t launch_k(const float *x, const float *g, const float *b, float eps, c
 // (profiles/layernorm_dense_one_launch.md):
 //   K = 384    N = 12 K at 505 rows 1.03, 32 K 0.96, from 1010 rows on 1.00 and more
 //   K = 512    N = 4 K at 505 rows 0.99, at 2525 1.07; 12 K at 505 rows 0.97, at 1010 1.06; 16 K at 505 and 1010 0.95 and 1.01; 32 K at 8080 0.95
-//   K = 768    weights touched, N = 4 K: two launches 64.1 us and one 64.5 at 1773 rows, 68.1 and 65.5 at 1970, 77.2 and 74.9 at 2561; q|k|v 68.1 and 69.9 at 1970
+//   K = 768    weights touched, two launches and one, us: N = 4 K 58.0 and 57.1 at 1773 rows, 61.9 and 58.9 at 1970, 70.7 and 67.8 at 2561; 6 K 69.7
+//              and 67.6 at 1970, 83.5 and 81.8; 8 K 75.0 and 75.2 at 1773, 76.3 and 75.4, 97.3 and 92.1; 12 K 89.4 and 89.9 at 1773, 97.7 and 95.1,
+//              120.1 and 115.1.  Over 4 to 12 K, eight counts of rows from 1970 to 2561, weights resident and from memory, 0.94 to 0.99 (10 K at 1970
+//              1.005), 3.5 K 0.96 to 0.99 but not taken; q|k|v 68.1 and 69.9 at 1970
 //              N = 4 K at 2626 rows 1.04 and at 10302 (129 panels of 80 rows: one group, half the chip) 0.97, 8 K 1.06 and 0.93, 12 K 1.03 and 0.89,
 //              8 K at 12625 1.00, 12 K at 11110 0.92, 16 K at 9595 0.98; two launches 139 us and one 147 at 25256 rows of 4 K
 //   K = 1024   N = 4 K at 5555 rows 0.97, at 6161 1.02; 5 K at 6363 0.96, 8 K 0.94, 12 K 0.89; two launches 85 us and one 106 at 9456 rows of 4 K

@@ -151,6 +151,7 @@ def ln_plan(rows, n, k, epi):
 @pytest.mark.parametrize("rows,n,k,one", [
     (394, 1152, 384, 0), (500, 6144, 384, 1), (600, 12288, 384, 0), (1024, 12288, 384, 1), (17, 8192, 256, 1),
     (499, 1536, 512, 0), (500, 4096, 512, 1), (606, 6144, 512, 0), (1000, 8192, 512, 1), (8080, 16384, 512, 0), (20001, 2048, 512, 0),
+    (1899, 3072, 768, 0), (1900, 3072, 768, 1), (1899, 9216, 768, 0), (1900, 9216, 768, 1), (2599, 3056, 768, 0), (2600, 3056, 768, 1), (2000, 9232, 768, 0),
     (2599, 2304, 768, 0), (2600, 9216, 768, 1), (9595, 12288, 768, 0), (10240, 3072, 768, 1), (10241, 3072, 768, 0), (10302, 2304, 768, 1),
     (10752, 3072, 768, 0), (10753, 6144, 768, 1), (11110, 9216, 768, 0), (20001, 2304, 768, 0),
     (1750, 4096, 1024, 0), (3152, 4096, 1024, 0), (4616, 4096, 1024, 0), (4950, 4096, 1024, 0),       # up to 1.05 where weights are not touched

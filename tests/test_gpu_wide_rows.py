@@ -52,8 +52,9 @@ def test_bits_of_two_launches_with_gelu(T, D, Hh, M, few, B):
         np.testing.assert_array_equal(H.run_stage(st, x[i:i + few]), one[i:i + few])
 
 
-# at 1024 wide below 5500 rows only where attention touches the weights
-@pytest.mark.parametrize("T,D,Hh,M,few,B", [(197, 1024, 16, 4096, 4, 16), (577, 1024, 16, 4352, 1, 5), (50, 1024, 16, 3136, 16, 77)])
+# at 1024 wide below 5500 rows only where attention touches the weights; at 768 from 1900 rows on
+@pytest.mark.parametrize("T,D,Hh,M,few,B", [(197, 1024, 16, 4096, 4, 16), (577, 1024, 16, 4352, 1, 5), (50, 1024, 16, 3136, 16, 77), (197, 768, 12, 3072, 4, 10),
+                                              (577, 768, 12, 4608, 2, 4)])
 def test_bits_of_two_launches_behind_touching(T, D, Hh, M, few, B):
     touched = binding.lib().ep_query_ln_gemm_touched_mlp
     touched.argtypes, touched.restype = [C.c_int64, C.c_int32, C.c_int32], C.c_int32
