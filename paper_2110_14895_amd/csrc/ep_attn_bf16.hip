@@ -41,11 +41,12 @@
 // The last 32-component step of a head width that is not a multiple of 32 (80)
 // reads past the row into the next row (finite data) against zeros in Q.
 //
-// Weights touched.  The launches behind this one walk K in step with each other, every step's weights are new to all of them at once, and where they
-// come from memory each step waits a part of that trip (FC2 of ViT-Large on 16 images, 64 steps: 36 us, and 28 where its 8 MB
-// are in the memory-side cache; DeiT-Small on 32, 24 steps and 1.2 MB: 15.6 and 11.8).  This kernel is bound by its vector ALU, and memory idles
-// meanwhile, so a wave of each workgroup more brings the weights of the rest of the layer and of the next q|k|v projection into that cache (the stage
-// decides where that pays: touch_weights in ep_stage.hip).  The launch itself takes 2 to 3 us longer for 25 MB (64 components a head).
+// Weights touched.  The launches behind this one walk K in step with each other, every step's weights are new to all of them at once, and where
+// they come from memory each step waits a part of that trip (FC2 of ViT-Large on 16 images, 64 steps: 36 us, and 28 where its 8 MB are in the memory-side
+// cache; DeiT-Small on 32, 24 steps and 1.2 MB: 15.6 and 11.8).  This kernel is bound by its vector ALU, and memory idles meanwhile, so a
+// wave of each workgroup more brings weights into that cache: those of the rest of the layer and of the next q|k|v projection, those of the projection and
+// the second MLP layer, or none (the stage decides: touch_weights in ep_stage.hip).  The launch itself takes 2 to 3 us longer for 25 MB (64 components
+// a head).
 #include "ep_kernels.h"
 #include "ep_device.h"
 #include "ep_launch.h"

@@ -205,19 +205,37 @@ enum Touch { TOUCH_NONE, TOUCH_LONG, TOUCH_ALL };       // LONG: the projection 
 // in w.x still lacks ((part[0] + ... + part[splits-1]) + bias).
 struct PendingSum { int splits; const float *bias; };
 
-// Whether attention of a forward over R rows touches the weights of the launches behind it (why and how: ep_attn_bf16.hip).  A layer
-// of a stage whose weights come from memory, without and with, in us:
-//   It pays from some 27 rows to a MB of weights on, which the launch would otherwise be too short for (ViT-Large on 1 image 39.8 and 41.6; ViT-Huge on 1
-// 55.2 and 58.5; ViT-Base on 1 35.9 and 36.6, 2 41.4 and 40.8, 4 48.4 and 45.2, 8 64.6 and 60.4, 16 89.2 and 79.7), at any rows up to 768 wide (DeiT-Small on 8
-// images 39.7 and 36.9, 32 66.4 and 57.3, 128 160.8 and 151.1, DeiT-Tiny on 256 135.4 and 127.3, ViT-Base on 28 to 48 level, on 64 236 and 225), and past
-// that where LayerNorm goes with a dense layer or the second MLP layer waits for its weights: ViT-Large on 16 126.7 and 117.2, 48 288 and 279, 64 382 and 374,
-// ViT-Huge on 6 111.3 and 106.4, 8 130.1 and 125.8.  Cut into ranges of K that layer waits less, and ViT-Large on 5 images gains 3 % or loses 2, by the card; from 45 rows to
-// a MB on it gains (on 6 72.3 and 70.9, 8 82.3 and 79.3, 10 92.1 and 89.6).  Elsewhere attention only takes longer (ViT-Huge on 16 189.8 and 199.7, 64
-// 635 and 642; on 32, in 256 x 192 tiles, 354.5 and 350 on one card and 353 and 358 on another), and nearly so behind a persistent first MLP layer (ViT-Huge on 12 153.5 and 155.6).
-//   Past 768 wide below some 110 rows to a MB the projection and the second MLP layer are enough, 40 % of the bytes: ViT-Large on 8 images 79.3 for 80.2 with all, 10 89.5
-// for 91.4, 14 111.4 for 111.6, 16 118.6 for 117.2, ViT-Huge on 4 82.9 for 85.1, 6 106.4 for 107.2; ViT-Base on 4 images 46.4 for 45.2, 16 84.2 for 79.7.
-//   Dense layers that go with their LayerNorm touch their weights themselves otherwise, which takes them longer: ViT-Large on 28 images 180.7 and 178.6, 40 232.6
-// and 226.5, with its touching left out.
+// Whether attention of a forward over R rows touches the weights of the launches behind it (why and how: ep_attn_bf16.hip).  Whether a call's weights
+// come from memory or are still in the memory-side cache is not known here, so both count.  A layer's time over that with nothing touched,
+// resident / from memory (all of 160 shapes in profiles/weights_touched.md):
+//
+//   rows to a MB of weights             projection, second MLP layer     all of them
+//   ViT-Base   1 x 197    14            1.011 / 1.012                    1.026 / 1.010       nothing: attention is too short for it
+//              2 x 197    28            1.006 / 0.997                    1.021 / 0.976
+//              4 x 197    56            0.987 / 0.956                    1.000 / 0.923
+//              2 x 577    82            1.011 / 0.989                    1.020 / 0.974
+//             16 x 197   223            0.995 / 0.976                    0.999 / 0.906
+//   DeiT-Small 8 x 197   445            0.994 / 0.951                    0.993 / 0.906
+//             32 x 197  1781            0.999 / 0.948                    0.994 / 0.875
+//   512 wide   1 x 197    31            0.998 / 1.001                    1.017 / 1.012
+//              4 x 197   125            0.996 / 0.978                    0.990 / 0.947
+//   ViT-Large  5 x 197    39            1.007 / 1.005                    1.023 / 0.992       nothing: FC2 in ranges of K waits less
+//              6 x 197    47            0.991 / 0.972                    1.008 / 0.988
+//             14 x 197   110            0.995 / 0.976                    1.007 / 0.979
+//             16 x 197   125            0.994 / 0.944                    0.999 / 0.927
+//             32 x 197   250            1.005 / 1.008                    0.989 / 0.996       LayerNorm with dense layers
+//   ViT-Huge   8 x 197    40            1.003 / 0.933                    1.026 / 0.927
+//             12 x 257    78            1.004 / 1.002                    1.017 / 1.003       nothing: a persistent first MLP layer
+//             16 x 257   105            1.014 / 1.014                    1.025 / 1.039       nothing: higher tiles in FC2
+//             64 x 257   418            1.004 / 0.999                    1.014 / 1.004       nothing: a persistent FC2
+//
+//   Up to 768 wide therefore all from 27 rows to a MB on, which costs 1.4 to 2.1 % of a layer with resident weights below 41 rows to a MB and at 2 x
+// 577 and 4 x 257 of ViT-Base, and up to 1 % elsewhere (DeiT-Tiny, whose passes wait for the host, 1.9).  Past 768 wide only where LayerNorm goes with a dense layer or the second MLP layer waits for its
+// weights, and below 110 rows to a MB only that layer's and the projection's, 40 % of the bytes: at most 0.8 % with resident weights.  256 x 192
+// tiles of more than 32 MB of weights (ViT-Huge on 25 x 257 0.97 / 0.98, 32 x 197 1.00 / 1.00, 32 x 257 0.98 / 0.99) are left alone: on another card they
+// lost 1.5 %.  Images of 50 tokens gain more, and pay less, than as many rows of 197 to 577, so the line is not in tokens.
+//   Dense layers that go with their LayerNorm touch their weights themselves otherwise, which takes them longer: ViT-Base on 32 images 1.015, ViT-Large
+// on 28 180.7 us and 178.6, 40 232.6 and 226.5, with its touching left out.
 // ranges: whether the second MLP layer may be cut into ranges of K; ranges_of: of a group, the images of a micro-batch (0: no group)
 Touch touch_weights(const ep_vit_config &c, int32_t B, bool ranges, int32_t ranges_of)
 {
@@ -226,14 +244,15 @@ Touch touch_weights(const ep_vit_config &c, int32_t B, bool ranges, int32_t rang
     const double rows_per_mb = (double)R * 1e6 / (double)bytes;
     if (c.param_dtype != EP_BF16 || bytes > TOUCH_MOST_BYTES || rows_per_mb < TOUCH_ROWS_PER_MB) return TOUCH_NONE;
     if (!ep_bf16_attention_touches((int64_t)B * c.n_heads, c.n_tokens)) return TOUCH_NONE;
-    if (D <= 768 || ep_bf16_ln_gemm_supported(R, 3 * D, D, EPI_BIAS, false) || ep_bf16_ln_gemm_supported(R, M, D, EPI_BIAS_GELU, false)) return D <= 768 || rows_per_mb >= TOUCH_ALL_ROWS_PER_MB ? TOUCH_ALL : TOUCH_LONG;
+    const Touch most = D <= 768 || rows_per_mb >= TOUCH_ALL_ROWS_PER_MB ? TOUCH_ALL : TOUCH_LONG;
+    if (D <= 768 || ep_bf16_ln_gemm_supported(R, 3 * D, D, EPI_BIAS, false) || ep_bf16_ln_gemm_supported(R, M, D, EPI_BIAS_GELU, false)) return most;
     const bool group = ranges_of != 0;
     const EpWeightWait fc2 = ep_bf16_gemm_weight_wait(R, D, M, EPI_BIAS_RESID, ranges ? fc2_splits(c, group ? ranges_of : B) : 1, group);
     if (fc2 == EP_WAITS_PERSISTENT || fc2 == EP_WAITS_HIGH) return TOUCH_NONE;
     if (fc2 == EP_WAITS_LARGE && bytes > TOUCH_LARGE_BYTES) return TOUCH_NONE;
     if (fc2 == EP_WAITS_RANGES && rows_per_mb < TOUCH_RANGES_ROWS_PER_MB) return TOUCH_NONE;
     if (fc2 != EP_WAITS_LARGE && ep_bf16_gemm_weight_wait(R, M, D, EPI_BIAS_GELU, 1, group) == EP_WAITS_PERSISTENT) return TOUCH_NONE;
-    return rows_per_mb >= TOUCH_ALL_ROWS_PER_MB ? TOUCH_ALL : TOUCH_LONG;
+    return most;
 }
 
 // Where that range ends, in bytes from where the layer begins (it begins with the projection); `next`: a layer follows in the block
