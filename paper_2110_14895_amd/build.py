@@ -19,11 +19,12 @@ LIB = os.path.join(HERE, "libedgepipe.so")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 COMMON = ["-O3", "-std=c++17", "-fPIC", "-I", INCLUDE, "-I", CSRC, "-Wall", "-Wno-unused-function"]
-# Kernel arguments arrive in scalar registers as far as those reach (14 words), instead of by a load from memory with which every
-# launch would begin.  What a kernel needs first therefore comes first in its arguments, and grid and block sizes, which are not among them,
-# are passed as arguments or constants.  The flag: a layer of ViT-Large on 1 image 40.0 -> 38.1 us (seven launches), on 5 62.0 -> 60.2, of DeiT-Small on 1 28.2 -> 26.4,
-# on 32 57.5 -> 56.0, of DeiT-Tiny on 64 52.6 -> 51.5; then the order: 38.0 -> 36.7, 62.3 -> 61.5, 26.5 -> 25.4,
-# 59.0 -> 57.5, 52.0 -> 51.4.
+# Kernel arguments arrive in scalar registers as far as those reach (14 words), instead of by a load from memory with which every launch would
+# begin.  In LayerNorm, attention and the dense kernels of up to 256 x 256 tiles (bf16: streaming, one-tile, rows; fp32: direct, tile, rows) what is
+# needed first therefore comes first in the arguments, and grid and block sizes, which are not among them, are arguments or constants; the persistent
+# dense kernel and the embedding keep the order they had and read them.  The flag alone, builds in turn on one box: a layer of ViT-Large on 1 image
+# 40.0 -> 38.1 us (seven launches), on 5 62.0 -> 60.2, of DeiT-Small on 1 28.2 -> 26.4, on 32 57.5 -> 56.0, of DeiT-Tiny on 64 52.6 -> 51.5.  Then the
+# order, on another box: 38.0 -> 36.7, 62.3 -> 61.5, 26.5 -> 25.4, 59.0 -> 57.5, 52.0 -> 51.4.
 HIP_FLAGS = ["--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
              "-mllvm", "-amdgpu-kernarg-preload-count=16"]
 # Per-file additions.  The attention kernel takes maxima of matrix-pipe results; without the
