@@ -359,12 +359,12 @@ hipError_t launch_k(const float *x, const float *g, const float *b, float eps, c
 //   K = 1024   N = 4 K at 5555 rows 0.97, at 6161 1.02; 5 K at 6363 0.96, 8 K 0.94, 12 K 0.89; two launches 85 us and one 106 at 9456 rows of 4 K
 // At 1024, layers past 2304 columns lose where tiles of 256 rows on their own are one nearly whole round: q|k|v at 6161 rows 0.99 and at 6565
 // 1.02, N = 2.75 K at 5757 0.97 and at 5959 1.01.
-// Below 5500 rows of 1024 the one launch takes 0.92 to 1.08 of the time of two with no line in rows, but for a first MLP layer whose weights
+// Below 5500 rows of 1024 the one launch takes 0.93 to 1.08 of the time of two with no line in rows, but for a first MLP layer whose weights
 // attention has touched and whose own launch would be one round of 256 x 256 tiles that fills more than three quarters and up to 13 sixteenths
 // of the units: 193 to 208 tiles (many others of so many run as 256 x 192 or 192 x 256).  A layer's time, one launch over two, N = 3.06 to 4.25 K,
 // 2885 to 4050 rows, weights resident and from memory: 0.963 to 0.988 at 28 points, 0.98 to 1.00 at another three, 3300 rows (ViT-Large on 16
-// images 107.5 -> 105.2 us and 111.3 -> 108.4).  210 to 225 tiles 0.975 to 1.007, from there on 0.98 to 1.03; tiles of 192 rows or columns 0.99
-// to 1.02.  Where attention has not touched the weights 1.01 to 1.05 (6 to 8 images of 577 tokens).
+// images 107.5 -> 105.2 us and 111.3 -> 108.4).  210 to 225 tiles 0.975 to 1.01, more 0.93 to 1.04 without a line; tiles of 192 rows or
+// columns 0.97 to 1.02.  Where attention has not touched the weights 1.01 to 1.05 (6 to 8 images of 577 tokens).
 bool tiles_leave_units(int64_t M, int N, int K)
 {
     const int64_t cus = ep_bf16_gemm_persistent_workgroups(), tiles = (M + 255) / 256 * ((N + 255) / 256);
