@@ -3,9 +3,9 @@
 //
 //   C[M, N] = LN(x)[M, K] . W[N, K]^T + bias[N]   (+ erf GELU), bf16 out
 //
-// A workgroup brings 64 to 128 rows (32 where there are few: launch_few) of the fp32 residual stream in, normalises them (the arithmetic and the order of the
-// sums of ln_bf16_kernel, so the same bits) and keeps them in LDS as bf16, all K of them: 96 KB for 128 rows at K = 384,
-// 128 KB for 64 at K = 1024.  Behind that one barrier its eight waves have nothing to wait for: each takes 32 columns at a
+// A workgroup brings 64 to 128 rows (32 where there are few: launch_few) of the fp32 residual stream in, normalises them (the
+// arithmetic and the order of the sums of ln_bf16_kernel, so the same bits) and keeps them in LDS as bf16, all K of them: 96 KB
+// for 128 rows at K = 384, 128 KB for 64 at K = 1024.  Behind that one barrier its eight waves have nothing to wait for: each takes 32 columns at a
 // time, the weights straight into registers (fragment order, a ring of R slices that runs on from one set of columns to
 // the next), the rows from LDS, the result out through a staging area of its own.
 //
@@ -17,8 +17,8 @@
 // groups share a panel the workgroups of an XCD therefore touch all weights between them while their rows come in, a line to a lane
 // (weights from memory: 12608 x 2304 x 768 65.5 -> 51.1 us, 7880 x 3072 x 1024 63.9 -> 54.4; over 2500 launches 0.79 of the time at 768
 // wide in one group and at 1024 in two, 0.87, 0.92 and 0.97 at 768 in two, three and four, 1.00 at 384 in one, 0.98 and 1.03 at 512 in
-// one and two), unless attention in front has touched them (ep_attn_bf16.hip): then it only costs, 2 to 4 % of a ViT-Base layer on 20 to 96 images.  A K of two to twelve slices
-// is too short for a tile with a prologue and an epilogue of its own, and LayerNorm was a launch and two trips through
+// one and two), unless attention in front has touched them (ep_attn_bf16.hip): then it only costs, 2 to 4 % of a ViT-Base layer on
+// 20 to 96 images.  A K of two to twelve slices is too short for a tile with a prologue and an epilogue of its own, and LayerNorm was a launch and two trips through
 // memory.  LayerNorm and the dense layer, then this, in us, launches back to back with weights from memory: 6304 x 576 x 192 9.0 and 6.0,
 // 12672 x 768 x 192 with GELU 18.0 and 12.4, 6304 x 1536 x 384 with GELU 21.3 and 15.4 (17.3 inside a DeiT-Small stage), 4728 x 1152 x 384
 // 14.0 and 9.9, 50688 x 1152 x 384 72.6 and 67.3, 6344 x 1536 x 512 22.6 and 16.4, 3172 x 2304 x 768 21.4 and 18.8, 12608 x 3072 x 768

@@ -229,11 +229,12 @@ struct PendingSum { int splits; const float *bias; };
 //             16 x 257   105            1.014 / 1.014                    1.025 / 1.039       nothing: higher tiles in FC2
 //             64 x 257   418            1.004 / 0.999                    1.014 / 1.004       nothing: a persistent FC2
 //
-//   Up to 768 wide therefore all from 27 rows to a MB on, which costs 1.4 to 2.1 % of a layer with resident weights below 41 rows to a MB and at 2 x
-// 577 and 4 x 257 of ViT-Base, and up to 1 % elsewhere (DeiT-Tiny, whose passes wait for the host, 1.9).  Past 768 wide only where LayerNorm goes with a dense layer or the second MLP layer waits for its
-// weights, and below 110 rows to a MB only that layer's and the projection's, 40 % of the bytes: at most 0.8 % with resident weights.  256 x 192
-// tiles of more than 32 MB of weights (ViT-Huge on 25 x 257 0.97 / 0.98, 32 x 197 1.00 / 1.00, 32 x 257 0.98 / 0.99) are left alone: on another card they
-// lost 1.5 %.  Images of 50 tokens gain more, and pay less, than as many rows of 197 to 577, so the line is not in tokens.
+//   Up to 768 wide therefore all from 27 rows to a MB on, which costs 1.4 to 2.1 % of a layer with resident weights below 41 rows to a MB and at
+// 2 x 577 and 4 x 257 of ViT-Base, and up to 1 % elsewhere (DeiT-Tiny, whose passes wait for the host, 1.9).  Past 768 wide only where LayerNorm goes
+// with a dense layer or the second MLP layer waits for its weights, and below 110 rows to a MB only that layer's and the projection's, 40 % of the
+// bytes: at most 0.8 % with resident weights.  256 x 192 tiles of more than 32 MB of weights (ViT-Huge on 25 x 257 0.97 / 0.98, 32 x 197 1.00 / 1.00,
+// 32 x 257 0.98 / 0.99) are left alone: on another card they lost 1.5 %.  Images of 50 tokens gain more, and pay less, than as many rows of 197 to 577,
+// so the line is not in tokens.
 //   Dense layers that go with their LayerNorm touch their weights themselves otherwise, which takes them longer: ViT-Base on 32 images 1.015, ViT-Large
 // on 28 180.7 us and 178.6, 40 232.6 and 226.5, with its touching left out.
 // ranges: whether the second MLP layer may be cut into ranges of K; ranges_of: of a group, the images of a micro-batch (0: no group)
@@ -288,7 +289,8 @@ ep_status run_layer(ep_stage *st, const Workspace &w, const LayerDev &L, const f
         const bool one_order = w.ranges_of != 0;                // several micro-batches: each as it would be alone
         // a LayerNorm done inside the dense layer behind it leaves its own bracket empty
         const bool plain1 = !xin16 && !(before && before->splits > 1);
-        const bool fuse1 = plain1 && ep_bf16_ln_gemm_supported(R, 3 * D, D, EPI_BIAS, false), fuse2 = ep_bf16_ln_gemm_supported(R, M, D, EPI_BIAS_GELU, touch.what == TOUCH_ALL);
+        const bool fuse1 = plain1 && ep_bf16_ln_gemm_supported(R, 3 * D, D, EPI_BIAS, false);
+        const bool fuse2 = ep_bf16_ln_gemm_supported(R, M, D, EPI_BIAS_GELU, touch.what == TOUCH_ALL);
         if (xin16)
             EP_TRACED(EP_K_LN1, ep_bf16_layernorm_widen(xin16, w.x, L.ln1_g, L.ln1_b, c.ln_eps, a, R, D, s));
         else if (!plain1)
